@@ -205,9 +205,7 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
                                     hipMemcpyHostToDevice, hs));
             a.stencil = dst;
             // heavy tiles first within the item
-            if ((s = order_tiles(A, B, dst, a.nst, is_auto, geo[i].periodic != 0, &b->tiles[i],
-                                 b->ntiles[i], hs)) != CUTE_OK)
-                return s;
+            if ((s = order_tiles(a, &b->tiles[i], b->ntiles[i], hs)) != CUTE_OK) return s;
         }
         a.tiles = b->tiles[i];
         a.ntiles = b->ntiles[i];

@@ -80,7 +80,6 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
     S.a = sp0 + (size_t)wave * 3 * kSpanCap;
     S.b = S.a + kSpanCap;
     S.f = S.b + kSpanCap;
-    S.n = 0;
 
     uint32_t cur = 0xffffffffu;  // item whose counts the histogram holds
     for (;;) {
@@ -121,7 +120,7 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
             tl.end = uni(tp[4 * t + 1]);
             tl.row = uni(tp[4 * t + 2]);
             tl.c0c1 = uni(tp[4 * t + 3]);
-            do_tile<MODE, PREC, EST, true, false>(P, W, S, B1, B2, T1, T2, lane, tl);
+            do_tile<MODE, PREC, EST, true, false>(P, W, S, B1, B2, T1, T2, lane, tl, 0u, 0u);
         }
         // the re-test queue refers to this item's points: empty it now
         if constexpr (PREC == P_FP32E)

@@ -187,6 +187,21 @@ struct RadialSpec {
     double aperture;
 };
 
+// Parts per home tile (log2). A wave counts one task (a part of a tile) at a
+// time, so a count whose tiles hardly outnumber the wave slots ends with most
+// of the chip waiting for the last tiles: at 2 tiles per slot the r-mu count
+// of 250 000 points ran at 1200 Gpair/s, at 6 at 1550. The tiles are cut until
+// there are six tasks per slot, as long as a part keeps two chunks of
+// neighbours: below that the span generation of the part (a few thousand
+// cycles, as much as two chunks against a tile of 20 points) costs more than
+// the balance gives.
+int part_log(double ntiles, double neighbours, int ncu) {
+    const double slots = 16.0 * ncu, chunks = neighbours / 64.0;
+    int p = 0;
+    while (p < kMaxPartLog && ntiles * (double)(1 << p) < 6.0 * slots && chunks >= 4.0 * (double)(1 << p)) p++;
+    return p;
+}
+
 // One pair count; with max_tiles > 0 only an evenly spread sample of about
 // max_tiles home tiles is counted (the tuner's sample).
 // With fixed set, every device temporary is a slice of the caller's fixed
@@ -346,47 +361,34 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
         if (!fixed) dfree(tiles, hs);
         tiles = nullptr;
     };
-    if (fixed && A.n > 0 && B.n > 0) {
-        // slots without a host wait, compacted on the device (longest first
-        // when the neighbour rows are tabulated)
-        if ((s = build_tiles_nowait(A, geo.max_w, hs, &tiles, &ntiles, slot_overflow, &tmp)) !=
-            CUTE_OK)
-            return s;
-        dev_count = true;
-    } else if (A.n > 0 && B.n > 0) {
-        GridHost At = A;
-        // Too few tiles to give every wave slot of the chip two: cut them
-        // shorter (default tile size only; not below 16 points, where the
-        // per-tile neighbour walk starts to dominate).
-        int ncu = 0;
-        const bool may_shrink =
-            A.tile_auto && max_tiles == 0 &&
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess;
-        const uint64_t want = (uint64_t)ncu * 16u * 2u;
-        // Every tile holds at most tile_max points. When that many tiles
-        // already fill the chip and the host-side bound on their number is
-        // modest, build them into slots without waiting for their count; the
+    int plog = 0;
+    if (A.n > 0 && B.n > 0) {
+        // Tiles are built into slots without waiting for their count (the
         // longest-first reordering compacts them and leaves the count on the
-        // device.
-        const uint64_t min_tiles = ((uint64_t)A.n + At.tile_max - 1) / At.tile_max;
-        const uint64_t bound = tile_count_bound(At, geo.max_w);
-        if (max_tiles == 0 && dst != nullptr && a.nst > 0 && (!may_shrink || min_tiles >= want) &&
-            bound <= std::max<uint64_t>(65536, 4 * min_tiles)) {
-            if ((s = build_tiles_nowait(At, geo.max_w, hs, &tiles, &ntiles, slot_overflow)) !=
-                CUTE_OK)
+        // device) unless the bound on their number is far above the points'
+        // worth of tiles (very sparse grids: memory and time would go into
+        // empty slots) or the tuner wants to sample them on the host.
+        const uint64_t min_tiles = ((uint64_t)A.n + A.tile_max - 1) / A.tile_max;
+        const uint64_t bound = tile_count_bound(A, geo.max_w);
+        if (fixed || (max_tiles == 0 && bound <= std::max<uint64_t>(65536, 4 * min_tiles))) {
+            if ((s = build_tiles_nowait(A, geo.max_w, hs, &tiles, &ntiles, slot_overflow,
+                                        fixed ? &tmp : nullptr)) != CUTE_OK)
                 return s;
             dev_count = true;
-        } else {
-            if ((s = build_tiles(At, geo.max_w, hs, &tiles, &ntiles)) != CUTE_OK) return s;
-            while (may_shrink && ntiles < want && At.tile_max > 16) {
-                At.tile_max = std::max(16, At.tile_max / 2);
-                drop_tiles();
-                if ((s = build_tiles(At, geo.max_w, hs, &tiles, &ntiles)) != CUTE_OK) return s;
-            }
+        } else if ((s = build_tiles(A, geo.max_w, hs, &tiles, &ntiles)) != CUTE_OK) {
+            return s;
+        }
+        if (max_tiles == 0) {
+            int ncu = 0;
+            CUTE_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+            // the tiles lie between the two bounds when their number is not
+            // known yet: their geometric mean stands for it
+            const double nt = dev_count ? std::sqrt((double)min_tiles * (double)bound) : (double)ntiles;
+            plog = part_log(nt, geo.cost / (double)A.n, ncu);
         }
     }
-    if ((s = order_tiles(A, B, dst, a.nst, is_auto, geo.periodic != 0, &tiles, ntiles, hs,
-                         dev_count ? ntiles_dev : nullptr, fixed ? &tmp : nullptr)) != CUTE_OK) {
+    if ((s = order_tiles(a, &tiles, ntiles, hs, dev_count ? ntiles_dev : nullptr,
+                         fixed ? &tmp : nullptr)) != CUTE_OK) {
         drop_tiles();
         return s;
     }
@@ -414,6 +416,7 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     a.tiles = tiles;
     a.ntiles = ntiles;
     a.ntiles_dev = dev_count ? ntiles_dev : nullptr;
+    a.plog = plog;
     a.self = dargs;
     a.wA = A.wt;
     a.wB = B.wt;

@@ -1003,60 +1003,44 @@ __device__ __forceinline__ int imod(int a, int n) {
     return r < 0 ? r + n : r;
 }
 
-// Span list of one tile, built in LDS before any pair is evaluated, so that
-// the stencil's FP64 temporaries are dead while the hot loop runs.
+// Span list of one batch of stencil rows, in LDS.
 struct SpanBuf {
     uint32_t* a;   // first neighbour index
     uint32_t* b;   // one past the last
     uint32_t* f;   // image code (low 8 bits) | j > i test (bit 8)
-    uint32_t n;    // entries (wave-uniform)
 };
 
-__device__ __forceinline__ void push_span(SpanBuf& S, int lane, uint32_t a0, uint32_t a1,
-                                          uint32_t code, bool masked) {
-    if (a1 <= a0) return;
-    if (lane == 0) {
-        S.a[S.n] = a0;
-        S.b[S.n] = a1;
-        S.f[S.n] = code | (masked ? 0x100u : 0u);
-    }
-    S.n++;
-}
+// The stencil of one tile (Sec. 3.3: the rows of cells within r_max of it),
+// wave-uniform: how many rows to look at, and what the rows of each kind of
+// grid need.
+struct TileStencil {
+    uint32_t ts, te;
+    int c0, c1, cy, cz;
+    int nrows;
+    // SPHERE: first band, the phi range of every band, or the whole ring
+    int b0, x0, x1;
+    bool full;
+    // 3-D boxes without a row table: the rows' rectangle and the tile's box
+    int y0, z0, nyr;
+    double xlo, xhi, ylo, yhi, zlo, zhi;
+};
 
-// Neighbour spans of the cell range [pa, pb] of row rb in the B grid. In the
-// home row of an autocorrelation the range starting at the tile's first cell
-// is split into the tile itself (pairs j > i only) and the rest.
-__device__ __forceinline__ void push_cells(SpanBuf& S, int lane, const cu32p cs, uint32_t rb,
-                                           int pa, int pb, uint32_t code, bool home_start,
-                                           uint32_t ts, uint32_t te) {
-    const uint32_t j0 = uni(cs[rb + (uint32_t)pa]);
-    const uint32_t j1 = uni(cs[rb + (uint32_t)pb + 1u]);
-    if (home_start) {
-        // points of the first cell before the tile pair with it from their own tile
-        const uint32_t m1 = te < j1 ? te : j1;
-        push_span(S, lane, ts, m1, code, true);
-        push_span(S, lane, m1 > te ? m1 : te, j1, code, false);
-    } else {
-        push_span(S, lane, j0, j1, code, false);
-    }
-}
-
-// Fill the span buffer with the neighbour spans of rows [*row, ...) of the
-// tile's stencil (Sec. 3.3: the cells within r_max of the tile), stopping
-// before the buffer could overflow. Returns true when every row is done.
-__device__ bool gen_spans(const CountArgs& P, const Tile& tl, int lane, SpanBuf& S, int* row) {
-    const uint32_t ts = tl.start, te = tl.end;
-    const int c0 = (int)(tl.c0c1 & 0xffffu), c1 = (int)(tl.c0c1 >> 16);
+__device__ __forceinline__ TileStencil tile_stencil(const CountArgs& P, const Tile& tl) {
     const GridView& A = P.A;
     const GridView& B = P.B;
-    const int cy = (int)(tl.row % (uint32_t)A.ny), cz = (int)(tl.row / (uint32_t)A.ny);
-    const cu32p cs = (cu32p)(const void*)B.cstart;
-    S.n = 0;
-    const uint32_t room = kSpanCap - 3;
-
+    TileStencil t;
+    t.ts = tl.start;
+    t.te = tl.end;
+    t.c0 = (int)(tl.c0c1 & 0xffffu);
+    t.c1 = (int)(tl.c0c1 >> 16);
+    t.cy = (int)(tl.row % (uint32_t)A.ny);
+    t.cz = (int)(tl.row / (uint32_t)A.ny);
+    t.nrows = t.b0 = t.x0 = t.x1 = t.y0 = t.z0 = t.nyr = 0;
+    t.full = false;
+    t.xlo = t.xhi = t.ylo = t.yhi = t.zlo = t.zhi = 0.0;
     if (P.geom == CUTE_GEOM_SPHERE) {
         // tile pixel block: phi in [c0, c1+1) * ax, cos theta in one band
-        const double zlo = A.oy + cy * A.ay, zhi = zlo + A.ay;
+        const double zlo = A.oy + t.cy * A.ay, zhi = zlo + A.ay;
         const double zl = fmax(-1.0, fmin(1.0, zlo)), zh = fmax(-1.0, fmin(1.0, zhi));
         const double th_lo = acos(zh), th_hi = acos(zl);
         const double ths = P.th_s;
@@ -1065,187 +1049,225 @@ __device__ bool gen_spans(const CountArgs& P, const Tile& tl, int lane, SpanBuf&
         int b0 = (int)floor((zn_lo - B.oy) / B.ay) - 1, b1 = (int)floor((zn_hi - B.oy) / B.ay) + 1;
         b0 = clampi(b0, 0, B.ny - 1);
         b1 = clampi(b1, 0, B.ny - 1);
+        // an autocorrelation takes its own band and the ones after it
+        if (P.is_auto && b0 < t.cy) b0 = t.cy;
         // half-width in phi of a cap of radius th_s around any tile point:
         // asin(sin th_s / sin theta) at the tile colatitude nearest a pole
         const double zmax2 = fmax(zl * zl, zh * zh);
         const double smin = sqrt(fmax(0.0, 1.0 - zmax2));
         bool full = !(P.sin_th_s < smin * (1.0 - 1e-9)) || (P.th_s >= 0.5 * kPi);
         const double hw = full ? 0.0 : asin(P.sin_th_s / smin) * (1.0 + 1e-9) + 1e-12;
-        const double phlo = c0 * A.ax - hw, phhi = (c1 + 1) * A.ax + hw;
-        const int x0 = (int)floor(phlo / B.ax) - 1, x1 = (int)floor(phhi / B.ax) + 1;
-        if (x1 - x0 + 1 >= B.nx) full = true;
-        for (int by = b0 + *row; by <= b1; by++) {
-            if (S.n > room) {
-                *row = by - b0;
-                return false;
-            }
-            const int byu = unii(by);
-            const bool same = P.is_auto && byu == cy;
-            if (P.is_auto && byu < cy) continue;
-            const uint32_t rb = (uint32_t)byu * (uint32_t)B.nx;
-            if (same) {
-                // index rule inside the home band: partners with a larger
-                // index, i.e. cells >= c0 up to the right reach, plus the left
-                // reach that wraps past phi = 2 pi onto the band's last cells
-                int p0b = B.nx - 1, p1a = 0, p1b = -1;
-                if (!full) {
-                    const int r1 = x1 < B.nx - 1 ? x1 : B.nx - 1;
-                    const int s2 = x0 < 0 ? x0 + B.nx : B.nx;
-                    if (s2 > r1 + 1) {
-                        p0b = r1;
-                        p1a = s2;
-                        p1b = B.nx - 1;
-                    }
-                }
-                push_cells(S, lane, cs, rb, c0, p0b, kNoShift, true, ts, te);
-                if (p1b >= p1a) push_cells(S, lane, cs, rb, p1a, p1b, kNoShift, false, ts, te);
-            } else if (full) {
-                push_cells(S, lane, cs, rb, 0, B.nx - 1, kNoShift, false, ts, te);
-            } else {
-                // cyclic range [x0, x1] (length < nx) split at the phi wrap
-                const int a0 = imod(x0, B.nx);
-                const int len = x1 - x0 + 1;
-                if (a0 + len <= B.nx) {
-                    push_cells(S, lane, cs, rb, a0, a0 + len - 1, kNoShift, false, ts, te);
-                } else {
-                    push_cells(S, lane, cs, rb, a0, B.nx - 1, kNoShift, false, ts, te);
-                    push_cells(S, lane, cs, rb, 0, a0 + len - 1 - B.nx, kNoShift, false, ts, te);
-                }
-            }
+        const double phlo = t.c0 * A.ax - hw, phhi = (t.c1 + 1) * A.ax + hw;
+        t.x0 = unii((int)floor(phlo / B.ax) - 1);
+        t.x1 = unii((int)floor(phhi / B.ax) + 1);
+        t.full = unii((full || t.x1 - t.x0 + 1 >= B.nx) ? 1 : 0) != 0;
+        t.b0 = unii(b0);
+        t.nrows = unii(b1) - t.b0 + 1;
+    } else if (P.stencil != nullptr) {
+        t.nrows = P.nst;
+    } else {
+        // the tile box, grown by R, selects rows of neighbour cells
+        const double R = P.Rs;
+        t.xlo = A.ox + t.c0 * A.ax;
+        t.xhi = A.ox + (t.c1 + 1) * A.ax;
+        t.ylo = A.oy + t.cy * A.ay;
+        t.yhi = t.ylo + A.ay;
+        t.zlo = A.oz + t.cz * A.az;
+        t.zhi = t.zlo + A.az;
+        int y0 = (int)floor((t.ylo - R - B.oy) / B.ay), y1 = (int)floor((t.yhi + R - B.oy) / B.ay);
+        int z0 = (int)floor((t.zlo - R - B.oz) / B.az), z1 = (int)floor((t.zhi + R - B.oz) / B.az);
+        if (!P.periodic) {
+            y0 = clampi(y0, 0, B.ny - 1);
+            y1 = clampi(y1, 0, B.ny - 1);
+            z0 = clampi(z0, 0, B.nz - 1);
+            z1 = clampi(z1, 0, B.nz - 1);
         }
-        return true;
+        t.y0 = unii(y0);
+        t.z0 = unii(z0);
+        t.nyr = unii(y1) - t.y0 + 1;
+        t.nrows = t.nyr * (unii(z1) - t.z0 + 1);
     }
-
-    // 3-D boxes of one geometry: the rows are precomputed offsets
-    if (P.stencil != nullptr) {
-        const cu32p st = (cu32p)(const void*)P.stencil;
-        for (int e = *row; e < P.nst; e++) {
-            if (S.n > room) {
-                *row = e;
-                return false;
-            }
-            const int ody = (int)uni(st[4 * e]), odz = (int)uni(st[4 * e + 1]);
-            const int left = (int)uni(st[4 * e + 2]), right = (int)uni(st[4 * e + 3]);
-            const int byu = cy + ody, bzu = cz + odz;
-            const bool same = P.is_auto && ody == 0 && odz == 0;
-            const bool home = P.selfx && ody == 0 && odz == 0;
-            int x0 = same ? c0 : c0 - left, x1 = c1 + right;
-            int ry = byu, rz = bzu, ky = 0, kz = 0;
-            if (P.periodic) {
-                ky = floordiv(byu, B.ny);
-                kz = floordiv(bzu, B.nz);
-                ry = byu - ky * B.ny;
-                rz = bzu - kz * B.nz;
-                // never more than one full turn of the row
-                x1 = x1 < x0 + B.nx - 1 ? x1 : x0 + B.nx - 1;
-            } else {
-                if (byu < 0 || byu >= B.ny || bzu < 0 || bzu >= B.nz) continue;
-                x0 = x0 < 0 ? 0 : x0;
-                x1 = x1 > B.nx - 1 ? B.nx - 1 : x1;
-                if (x0 > x1) continue;
-            }
-            const uint32_t rb = (uint32_t)B.nx * ((uint32_t)ry + (uint32_t)B.ny * (uint32_t)rz);
-            int a0 = x0;
-            while (a0 <= x1) {
-                const int kx = P.periodic ? floordiv(a0, B.nx) : 0;
-                const int lim = P.periodic ? (kx + 1) * B.nx - 1 : x1;
-                const int a1 = x1 < lim ? x1 : lim;
-                const uint32_t code =
-                    (uint32_t)(kx + 1) | ((uint32_t)(ky + 1) << 2) | ((uint32_t)(kz + 1) << 4);
-                if (home && kx == 0 && a0 <= c0 && c1 <= a1) {
-                    // full stencil over one catalog: the tile's own cells are
-                    // split around the tile, whose points pair with all but
-                    // themselves (the j != i test)
-                    if (a0 < c0) push_cells(S, lane, cs, rb, a0, c0 - 1, code, false, ts, te);
-                    const uint32_t j0 = uni(cs[rb + (uint32_t)c0]);
-                    const uint32_t j1 = uni(cs[rb + (uint32_t)c1 + 1u]);
-                    push_span(S, lane, j0, ts, code, false);
-                    push_span(S, lane, ts, te, code, true);
-                    push_span(S, lane, te, j1, code, false);
-                    if (c1 < a1) push_cells(S, lane, cs, rb, c1 + 1, a1, code, false, ts, te);
-                } else {
-                    push_cells(S, lane, cs, rb, a0 - kx * B.nx, a1 - kx * B.nx, code,
-                               same && kx == 0 && a0 == c0, ts, te);
-                }
-                a0 = a1 + 1;
-            }
-        }
-        return true;
-    }
-
-    // 3-D boxes: the tile box, grown by R, selects rows of neighbour cells
-    const double R = P.Rs;
-    const double xlo = A.ox + c0 * A.ax, xhi = A.ox + (c1 + 1) * A.ax;
-    const double ylo = A.oy + cy * A.ay, yhi = ylo + A.ay;
-    const double zlo = A.oz + cz * A.az, zhi = zlo + A.az;
-    int y0 = (int)floor((ylo - R - B.oy) / B.ay), y1 = (int)floor((yhi + R - B.oy) / B.ay);
-    int z0 = (int)floor((zlo - R - B.oz) / B.az), z1 = (int)floor((zhi + R - B.oz) / B.az);
-    if (!P.periodic) {
-        y0 = clampi(y0, 0, B.ny - 1);
-        y1 = clampi(y1, 0, B.ny - 1);
-        z0 = clampi(z0, 0, B.nz - 1);
-        z1 = clampi(z1, 0, B.nz - 1);
-    }
-    const int nyr = y1 - y0 + 1;
-    const int nrows = nyr * (z1 - z0 + 1);
-    const double R2 = R * R;
-    for (int r = *row; r < nrows; r++) {
-        if (S.n > room) {
-            *row = r;
-            return false;
-        }
-        const int bzu = unii(z0 + r / nyr), byu = unii(y0 + r % nyr);
-        bool same = false;
-        if (P.is_auto) {
-            const int oz_ = bzu - cz, oy_ = byu - cy;
-            if (oz_ < 0 || (oz_ == 0 && oy_ < 0)) continue;
-            same = (oz_ == 0 && oy_ == 0);
-        }
-        // distance in y and z between the tile box and this row of cells
-        const double rylo = B.oy + byu * B.ay, ryhi = rylo + B.ay;
-        const double rzlo = B.oz + bzu * B.az, rzhi = rzlo + B.az;
-        const double dy = fmax(0.0, fmax(rylo - yhi, ylo - ryhi));
-        const double dz = fmax(0.0, fmax(rzlo - zhi, zlo - rzhi));
-        const double rem = R2 - dy * dy - dz * dz;
-        if (rem <= 0.0) continue;
-        const double w = sqrt(rem);
-        int x0 = (int)floor((xlo - w - B.ox) / B.ax), x1 = (int)floor((xhi + w - B.ox) / B.ax);
-        if (same && x0 < c0) x0 = c0;
-        int ry = byu, rz = bzu, ky = 0, kz = 0;
-        if (P.periodic) {
-            ky = floordiv(byu, B.ny);
-            kz = floordiv(bzu, B.nz);
-            ry = byu - ky * B.ny;
-            rz = bzu - kz * B.nz;
-        } else {
-            x0 = x0 < 0 ? 0 : x0;
-            x1 = x1 > B.nx - 1 ? B.nx - 1 : x1;
-            if (x0 > x1) continue;
-        }
-        const uint32_t rb = (uint32_t)B.nx * ((uint32_t)ry + (uint32_t)B.ny * (uint32_t)rz);
-        // split [x0, x1] at periodic wraps (at most two pieces)
-        int a0 = x0;
-        while (a0 <= x1) {
-            const int kx = P.periodic ? floordiv(a0, B.nx) : 0;
-            const int lim = P.periodic ? (kx + 1) * B.nx - 1 : x1;
-            const int a1 = x1 < lim ? x1 : lim;
-            const uint32_t code =
-                (uint32_t)(kx + 1) | ((uint32_t)(ky + 1) << 2) | ((uint32_t)(kz + 1) << 4);
-            push_cells(S, lane, cs, rb, a0 - kx * B.nx, a1 - kx * B.nx, code,
-                       same && kx == 0 && a0 == c0, ts, te);
-            a0 = a1 + 1;
-        }
-    }
-    return true;
+    return t;
 }
 
-// Count the pairs of one home tile: spans are generated into the LDS span
-// buffer, then fed chunk by chunk to the hot loop.
+// One stencil row (per lane): at most two pieces of its x-range (a periodic
+// or phi wrap cuts it once), as neighbour index ranges [a0, a1) and [b0, b1)
+// with their image codes. home: the tile's own row, whose part inside the
+// tile is a span of its own with the index test: m1 is the end of that span
+// [ts, m1) (0 = none), and [h0, h1) the rest of the row past the tile where
+// the pieces do not hold it (full stencils).
+struct RowSpans {
+    uint32_t a0, a1, b0, b1, ca, cb;
+    uint32_t m1, h0, h1;
+};
+
+// Row e of the tile's stencil, e < t.nrows (any lane value).
+__device__ __forceinline__ RowSpans row_spans(const CountArgs& P, const TileStencil& t, int e) {
+    const GridView& B = P.B;
+    RowSpans r;
+    r.a0 = r.a1 = r.b0 = r.b1 = 0u;
+    r.ca = r.cb = kNoShift;
+    r.m1 = r.h0 = r.h1 = 0u;
+    // the row's cells [pa, pb] and, past a wrap, [qa, qb]; empty when pb < pa
+    int pa = 0, pb = -1, qa = 0, qb = -1;
+    uint32_t rb = 0u;
+    bool same = false;   // the tile's own row of an autocorrelation
+    bool home = false;   // the tile's own row of a full stencil over one catalog
+    int kxa = 0, kxb = 0, ky = 0, kz = 0;
+    if (P.geom == CUTE_GEOM_SPHERE) {
+        const int by = t.b0 + e;
+        rb = (uint32_t)by * (uint32_t)B.nx;
+        same = P.is_auto && by == t.cy;
+        if (same) {
+            // index rule inside the home band: partners with a larger index,
+            // i.e. cells >= c0 up to the right reach, plus the left reach
+            // that wraps past phi = 2 pi onto the band's last cells
+            pa = t.c0;
+            pb = B.nx - 1;
+            if (!t.full) {
+                const int r1 = t.x1 < B.nx - 1 ? t.x1 : B.nx - 1;
+                const int s2 = t.x0 < 0 ? t.x0 + B.nx : B.nx;
+                if (s2 > r1 + 1) {
+                    pb = r1;
+                    qa = s2;
+                    qb = B.nx - 1;
+                }
+            }
+        } else if (t.full) {
+            pb = B.nx - 1;
+        } else {
+            // cyclic range [x0, x1] (length < nx) split at the phi wrap
+            pa = imod(t.x0, B.nx);
+            pb = pa + (t.x1 - t.x0);
+            if (pb > B.nx - 1) {
+                qb = pb - B.nx;
+                pb = B.nx - 1;
+            }
+        }
+    } else {
+        int by, bz, x0, x1;
+        bool ok = true;
+        if (P.stencil != nullptr) {
+            // 3-D boxes of one geometry: the rows are precomputed offsets
+            const int4 o = P.stencil[e];
+            by = t.cy + o.x;
+            bz = t.cz + o.y;
+            same = P.is_auto && o.x == 0 && o.y == 0;
+            home = P.selfx && o.x == 0 && o.y == 0;
+            x0 = same ? t.c0 : t.c0 - o.z;
+            x1 = t.c1 + o.w;
+            // never more than one full turn of the row
+            if (P.periodic) x1 = x1 < x0 + B.nx - 1 ? x1 : x0 + B.nx - 1;
+        } else {
+            bz = t.z0 + e / t.nyr;
+            by = t.y0 + e % t.nyr;
+            if (P.is_auto) {
+                const int oz_ = bz - t.cz, oy_ = by - t.cy;
+                if (oz_ < 0 || (oz_ == 0 && oy_ < 0)) ok = false;
+                same = (oz_ == 0 && oy_ == 0);
+            }
+            // distance in y and z between the tile box and this row of cells
+            const double R2 = P.Rs * P.Rs;
+            const double rylo = B.oy + by * B.ay, ryhi = rylo + B.ay;
+            const double rzlo = B.oz + bz * B.az, rzhi = rzlo + B.az;
+            const double dy = fmax(0.0, fmax(rylo - t.yhi, t.ylo - ryhi));
+            const double dz = fmax(0.0, fmax(rzlo - t.zhi, t.zlo - rzhi));
+            const double rem = R2 - dy * dy - dz * dz;
+            if (rem <= 0.0) ok = false;
+            const double w = sqrt(fmax(rem, 0.0));
+            x0 = (int)floor((t.xlo - w - B.ox) / B.ax);
+            x1 = (int)floor((t.xhi + w - B.ox) / B.ax);
+            if (same && x0 < t.c0) x0 = t.c0;
+        }
+        int ry = by, rz = bz;
+        if (P.periodic) {
+            ky = floordiv(by, B.ny);
+            kz = floordiv(bz, B.nz);
+            ry = by - ky * B.ny;
+            rz = bz - kz * B.nz;
+        } else {
+            if (by < 0 || by >= B.ny || bz < 0 || bz >= B.nz) ok = false;
+            x0 = x0 < 0 ? 0 : x0;
+            x1 = x1 > B.nx - 1 ? B.nx - 1 : x1;
+        }
+        if (!ok || x0 > x1) return r;
+        rb = (uint32_t)B.nx * ((uint32_t)ry + (uint32_t)B.ny * (uint32_t)rz);
+        // [x0, x1], cut at a periodic wrap (at most two pieces)
+        if (P.periodic) {
+            kxa = floordiv(x0, B.nx);
+            kxb = kxa + 1;
+            const int lim = kxb * B.nx - 1;
+            pa = x0 - kxa * B.nx;
+            pb = (x1 < lim ? x1 : lim) - kxa * B.nx;
+            qb = x1 - kxb * B.nx;
+        } else {
+            pa = x0;
+            pb = x1;
+        }
+    }
+    const uint32_t* cs = B.cstart;
+    if (pb >= pa) {
+        r.a0 = cs[rb + (uint32_t)pa];
+        r.a1 = cs[rb + (uint32_t)pb + 1u];
+    }
+    if (qb >= qa) {
+        r.b0 = cs[rb + (uint32_t)qa];
+        r.b1 = cs[rb + (uint32_t)qb + 1u];
+    }
+    r.ca = (uint32_t)(kxa + 1) | ((uint32_t)(ky + 1) << 2) | ((uint32_t)(kz + 1) << 4);
+    r.cb = (uint32_t)(kxb + 1) | ((uint32_t)(ky + 1) << 2) | ((uint32_t)(kz + 1) << 4);
+    if (P.geom == CUTE_GEOM_SPHERE) r.ca = r.cb = kNoShift;
+    if (same) {
+        // points of the first cell before the tile pair with it from their
+        // own tile; the tile's points pair among themselves (j > i) and with
+        // the rest of the row
+        r.m1 = t.te < r.a1 ? t.te : r.a1;
+        r.a0 = t.te;
+    } else if (home) {
+        // the tile's points pair with all of their row but themselves: the
+        // piece that holds the tile ends before it, the rest follows it
+        if (kxa == 0 && pa <= t.c0 && t.c1 <= pb) {
+            r.m1 = t.te;
+            r.h0 = t.te;
+            r.h1 = r.a1;
+            r.a1 = t.ts;
+        } else if (kxb == 0 && qa <= t.c0 && t.c1 <= qb) {
+            r.m1 = t.te;
+            r.h0 = t.te;
+            r.h1 = r.b1;
+            r.b1 = t.ts;
+        }
+    }
+    return r;
+}
+
+__device__ __forceinline__ uint32_t lane_u32(uint32_t v, int l) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+// number of lower lanes set in a mask
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = (uint32_t)__shfl_up((int)v, o);
+        v += lane >= o ? u : 0u;
+    }
+    return v;
+}
+
+// Count the pairs of one home tile, or one of its 2^plog parts. The stencil
+// rows are taken 64 at a time, one per lane (a serial walk of the rows spent
+// more time on dependent loads than the pairs of a small tile take); their
+// spans go to LDS in row order and are fed chunk by chunk to the hot loop. A
+// part is a run of whole chunks of the concatenated neighbours of each batch
+// of rows, so the parts of a tile share out its chunks evenly.
 template <int MODE, int PREC, int EST, bool PM, bool WT>
 __device__ void do_tile(const CountArgs& P, WaveState& W, SpanBuf& S, const float2* B1,
                         const float2* B2, const double* T1, const double* T2, int lane,
-                        const Tile& tl) {
-    W.tiles++;
+                        const Tile& tl, uint32_t part, uint32_t plog) {
+    if (part == 0u) W.tiles++;
     if (PM && P.mbA != nullptr) {
         // a tile whose home points are all masked out has no pair to count
         const uint32_t i = tl.start + (uint32_t)lane;
@@ -1259,15 +1281,97 @@ __device__ void do_tile(const CountArgs& P, WaveState& W, SpanBuf& S, const floa
     C.lj = 0;
     C.lcode = kNoShift;
     C.lmask = false;
-    int row = 0;
-    bool done = false;
-    while (!done) {
-        done = gen_spans(P, tl, lane, S, &row);
-        for (uint32_t k = 0; k < S.n; k++) {
-            const uint32_t a0 = uni(S.a[k]), a1 = uni(S.b[k]), f = uni(S.f[k]);
+    int nrows = 1;
+    for (int row0 = 0; row0 < nrows; row0 += 64) {
+        uint32_t nspan, k, skip, left;
+        {
+            // the stencil again for every batch of rows: its temporaries are
+            // dead while pairs are evaluated (the asm keeps the compiler from
+            // holding them across the loop)
+            Tile tb = tl;
+            asm volatile("" : "+s"(tb.row));
+            const TileStencil t = tile_stencil(P, tb);
+            nrows = t.nrows;
+            RowSpans r;
+            r.a0 = r.a1 = r.b0 = r.b1 = r.m1 = r.h0 = r.h1 = 0u;
+            r.ca = r.cb = kNoShift;
+            if (row0 + lane < t.nrows) r = row_spans(P, t, row0 + lane);
+            const uint32_t na = r.a1 > r.a0 ? r.a1 - r.a0 : 0u, nb = r.b1 > r.b0 ? r.b1 - r.b0 : 0u;
+            // the tile's own spans, from the lane that holds its row
+            const uint64_t mh = __builtin_amdgcn_ballot_w64(r.m1 != 0u);
+            uint32_t m1 = 0u, h0 = 0u, h1 = 0u;
+            if (mh != 0ull) {
+                const int l = __builtin_ctzll(mh);
+                m1 = lane_u32(r.m1, l);
+                h0 = lane_u32(r.h0, l);
+                h1 = lane_u32(r.h1, l);
+            }
+            const uint32_t nm = m1 > t.ts ? m1 - t.ts : 0u, nh = h1 > h0 ? h1 - h0 : 0u;
+            const uint32_t own = nm + nh, nown = (nm ? 1u : 0u) + (nh ? 1u : 0u);
+            const uint32_t end = own + wave_incl_scan(na + nb, lane);
+            const uint32_t total = lane_u32(end, 63);
+            // this part's chunks
+            const uint32_t nc = (total + 63u) >> 6;
+            const uint32_t c0 = (uint32_t)(((uint64_t)nc * part) >> plog);
+            const uint32_t c1 = (uint32_t)(((uint64_t)nc * (part + 1u)) >> plog);
+            if (c0 >= c1) continue;
+            const uint32_t v0 = c0 << 6, v1 = (c1 << 6) < total ? c1 << 6 : total;
+            left = v1 - v0;
+            const uint64_t ma = __builtin_amdgcn_ballot_w64(na != 0u);
+            const uint64_t mb = __builtin_amdgcn_ballot_w64(nb != 0u);
+            const uint32_t pos = nown + lanes_below(ma) + lanes_below(mb);
+            nspan = nown + (uint32_t)(__popcll(ma) + __popcll(mb));
+            if (lane == 0) {
+                if (nm) {
+                    S.a[0] = t.ts;
+                    S.b[0] = m1;
+                    S.f[0] = kNoShift | 0x100u;
+                }
+                if (nh) {
+                    S.a[nown - 1u] = h0;
+                    S.b[nown - 1u] = h1;
+                    S.f[nown - 1u] = kNoShift;
+                }
+            }
+            if (na) {
+                S.a[pos] = r.a0;
+                S.b[pos] = r.a1;
+                S.f[pos] = r.ca;
+            }
+            if (nb) {
+                const uint32_t q = pos + (na ? 1u : 0u);
+                S.a[q] = r.b0;
+                S.b[q] = r.b1;
+                S.f[q] = r.cb;
+            }
+            // the span that holds neighbour v0 of the concatenation
+            k = 0u;
+            skip = v0;
+            if (v0 >= own && v0 > 0u) {
+                const int l = (int)__popcll(__builtin_amdgcn_ballot_w64(end <= v0));
+                k = lane_u32(pos, l);
+                skip = v0 - (lane_u32(end, l) - lane_u32(na + nb, l));
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (; left > 0u && k < nspan; k++) {
+            uint32_t a0 = uni(S.a[k]), a1 = uni(S.b[k]);
+            const uint32_t f = uni(S.f[k]);
+            const uint32_t len = a1 - a0;
+            if (skip >= len) {
+                skip -= len;
+                continue;
+            }
+            a0 += skip;
+            skip = 0u;
+            if (a1 - a0 > left) a1 = a0 + left;
+            left -= a1 - a0;
             feed<MODE, PREC, EST, PM, WT>(P, W, B1, B2, T1, T2, lane, C, tl.start, tl.end, a0, a1,
                                   f & 0xffu, (f & 0x100u) != 0u);
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
     if (C.filled) run_chunk<MODE, PREC, EST, PM, WT>(P, W, B1, B2, T1, T2, lane, C, tl.start, tl.end);
 }

@@ -77,21 +77,27 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count(CountArgs
     S.a = sp0 + (size_t)wave * 3 * kSpanCap;
     S.b = S.a + kSpanCap;
     S.f = S.b + kSpanCap;
-    S.n = 0;
 
-    const uint32_t ntiles = P.ntiles_dev ? uni(*P.ntiles_dev) : P.ntiles;
-    for (;;) {
-        uint32_t t = 0;
-        if (lane == 0) t = atomicAdd(P.work_head, 1u);
-        t = uni(t);
-        if (t >= ntiles) break;
-        const cu32p tp = (cu32p)(const void*)P.tiles;
+    // tasks: the parts of the tiles. Every wave starts with the task of its
+    // own number, so that a launch of no more tasks than waves pops none; an
+    // empty tile slot is no tile.
+    const uint32_t plog = (uint32_t)P.plog;
+    const uint32_t ntasks = (P.ntiles_dev ? uni(*P.ntiles_dev) : P.ntiles) << plog;
+    const uint32_t nw = gridDim.x * (uint32_t)nwaves;
+    for (uint32_t t = blockIdx.x * (uint32_t)nwaves + (uint32_t)unii(wave); t < ntasks;) {
+        const cu32p tp = (cu32p)(const void*)P.tiles + 4 * (size_t)(t >> plog);
         Tile tl;
-        tl.start = uni(tp[4 * t]);
-        tl.end = uni(tp[4 * t + 1]);
-        tl.row = uni(tp[4 * t + 2]);
-        tl.c0c1 = uni(tp[4 * t + 3]);
-        do_tile<MODE, PREC, EST, false, WT>(P, W, S, B1, B2, T1, T2, lane, tl);
+        tl.start = uni(tp[0]);
+        tl.end = uni(tp[1]);
+        tl.row = uni(tp[2]);
+        tl.c0c1 = uni(tp[3]);
+        if (tl.end > tl.start)
+            do_tile<MODE, PREC, EST, false, WT>(P, W, S, B1, B2, T1, T2, lane, tl,
+                                                t & ((1u << plog) - 1u), plog);
+        if (ntasks <= nw) break;
+        uint32_t nx = 0;
+        if (lane == 0) nx = atomicAdd(P.work_head, 1u);
+        t = nw + uni(nx);
     }
     if constexpr (PREC == P_FP32E)
         W.tail = drain_queue<MODE, EST>(P.self, W.hist, W.qi, W.qj, W.qc, W.rstat, B1, B2, T1, T2, lane,
@@ -146,7 +152,7 @@ cute_status launch_one(const CountArgs& a, int wg_waves, size_t lds, hipStream_t
         cache[std::make_tuple(dev, wg_waves, lds, WT)] = std::make_pair(ncu, per_cu);
     }
     int64_t want = (int64_t)per_cu * ncu;
-    int64_t need = ((int64_t)a.ntiles + wg_waves - 1) / wg_waves;
+    int64_t need = (((int64_t)a.ntiles << a.plog) + wg_waves - 1) / wg_waves;
     int grid = (int)(want < need ? want : need);
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * wg_waves), lds, s, a);
@@ -375,19 +381,15 @@ namespace {
 
 // Estimated cost of each home tile for the longest-first order: candidate
 // pairs (home points times the neighbours its stencil rows hold) plus a
-// per-row and a per-tile overhead, in pair evaluations. Uses the precomputed
-// neighbour rows (grids of one geometry), so it is integer work.
+// per-row and a per-tile overhead, in pair evaluations.
 constexpr uint32_t kCostBuckets = 256;
 
 constexpr uint32_t kNoTile = 0xffffffffu;  // the key of an empty slot
 
 // One wave per tile slot, the lanes taking the stencil rows; writes the
 // tile's cost bucket to key[t] (kNoTile for an empty slot).
-__global__ __launch_bounds__(256) void k_tile_cost(const Tile* __restrict__ tiles, uint32_t ntiles,
-                                                   const uint32_t* __restrict__ cs, int any, int nx,
-                                                   int ny, int nz, const int4* __restrict__ st,
-                                                   int nst, int periodic, int is_auto,
-                                                   uint32_t* __restrict__ key) {
+__global__ __launch_bounds__(256) void k_tile_cost(CountArgs P, const Tile* __restrict__ tiles,
+                                                   uint32_t ntiles, uint32_t* __restrict__ key) {
     const int lane = (int)(threadIdx.x & 63u);
     const uint32_t t = uni((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     if (t >= ntiles) return;
@@ -401,56 +403,21 @@ __global__ __launch_bounds__(256) void k_tile_cost(const Tile* __restrict__ tile
         if (lane == 0) key[t] = kNoTile;
         return;
     }
-    const int c0 = (int)(tl.c0c1 & 0xffffu), c1 = (int)(tl.c0c1 >> 16);
-    const int cy = (int)(tl.row % (uint32_t)any), cz = (int)(tl.row / (uint32_t)any);
+    const TileStencil ts = tile_stencil(P, tl);
     uint64_t nb = 0;
-    uint32_t rows = 0;
-    for (int e = lane; e < nst; e += 64) {
-        const int4 o = st[e];
-        int by = cy + o.x, bz = cz + o.y;
-        const bool same = is_auto && o.x == 0 && o.y == 0;
-        int x0 = same ? c0 : c0 - o.z, x1 = c1 + o.w;
-        if (periodic) {
-            by -= floordiv(by, ny) * ny;
-            bz -= floordiv(bz, nz) * nz;
-            x1 = x1 < x0 + nx - 1 ? x1 : x0 + nx - 1;
-        } else {
-            if (by < 0 || by >= ny || bz < 0 || bz >= nz) continue;
-            x0 = x0 < 0 ? 0 : x0;
-            x1 = x1 > nx - 1 ? nx - 1 : x1;
-            if (x0 > x1) continue;
-        }
-        const uint32_t rb = (uint32_t)nx * ((uint32_t)by + (uint32_t)ny * (uint32_t)bz);
-        for (int a0 = x0; a0 <= x1;) {
-            const int kx = floordiv(a0, nx);
-            const int lim = (kx + 1) * nx - 1;
-            const int a1 = x1 < lim ? x1 : lim;
-            nb += cs[rb + (uint32_t)(a1 - kx * nx) + 1u] - cs[rb + (uint32_t)(a0 - kx * nx)];
-            a0 = a1 + 1;
-        }
-        rows++;
+    for (int e = lane; e < ts.nrows; e += 64) {
+        const RowSpans r = row_spans(P, ts, e);
+        nb += (r.a1 > r.a0 ? r.a1 - r.a0 : 0u) + (r.b1 > r.b0 ? r.b1 - r.b0 : 0u);
+        nb += (r.m1 > tl.start ? r.m1 - tl.start : 0u) + (r.h1 - r.h0);
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        nb += __shfl_xor(nb, off);
-        rows += __shfl_xor(rows, off);
-    }
+    for (int off = 32; off > 0; off >>= 1) nb += __shfl_xor(nb, off);
     if (lane == 0) {
         // bucket on a log scale, 8 per octave, largest cost first (bucket 0);
         // log2(c) is in [11, 64)
-        const uint64_t c = (uint64_t)(tl.end - tl.start) * nb + 128ull * rows + 2048ull;
+        const uint64_t c = (uint64_t)(tl.end - tl.start) * nb + 32ull * (uint32_t)ts.nrows + 2048ull;
         const float lc = (__builtin_amdgcn_logf((float)c) - 11.0f) * 8.0f;
         key[t] = kCostBuckets - 1u - (uint32_t)fminf(fmaxf(lc, 0.0f), (float)(kCostBuckets - 1));
     }
-}
-
-// Compaction without a cost estimate (grids without precomputed neighbour
-// rows): every tile gets bucket 0, an empty slot kNoTile.
-__global__ __launch_bounds__(256) void k_tile_live(const Tile* __restrict__ tiles, uint32_t ntiles,
-                                                   uint32_t* __restrict__ key) {
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ntiles) return;
-    const Tile tl = tiles[t];
-    key[t] = tl.end > tl.start ? 0u : kNoTile;
 }
 
 // Rank of each tile within its bucket: LDS atomics inside the block, then one
@@ -483,13 +450,19 @@ __global__ __launch_bounds__(256) void k_tile_scatter(const Tile* __restrict__ t
                                                       Tile* __restrict__ out,
                                                       uint32_t* __restrict__ total) {
     __shared__ uint32_t off[kCostBuckets];
-    if (threadIdx.x == 0) {
-        uint32_t acc = 0;
-        for (uint32_t b = 0; b < kCostBuckets; b++) {
-            off[b] = acc;
-            acc += hist[b];
-        }
-        if (blockIdx.x == 0 && total != nullptr) *total = acc;
+    __shared__ uint32_t wsum[kCostBuckets / 64];
+    {
+        // one bucket per thread: the waves scan 64 buckets each
+        static_assert(kCostBuckets == 256, "one bucket per thread");
+        const int lane = (int)(threadIdx.x & 63u);
+        const uint32_t v = hist[threadIdx.x];
+        const uint32_t incl = wave_incl_scan(v, lane);
+        if (lane == 63) wsum[threadIdx.x >> 6] = incl;
+        __syncthreads();
+        uint32_t base = 0;
+        for (uint32_t w = 0; w < (threadIdx.x >> 6); w++) base += wsum[w];
+        off[threadIdx.x] = base + incl - v;
+        if (blockIdx.x == 0 && threadIdx.x == 255 && total != nullptr) *total = base + incl;
     }
     __syncthreads();
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -502,15 +475,12 @@ __global__ __launch_bounds__(256) void k_tile_scatter(const Tile* __restrict__ t
 }  // namespace
 
 // Reorder tiles longest first (estimated cost, descending): the persistent
-// waves take the heavy tiles early and the light ones fill the tail. Without
-// neighbour rows the tiles keep their order, unless total is set: then the
-// empty slots are only dropped (tiles in no particular order).
-cute_status order_tiles(const GridHost& A, const GridHost& B, const int4* stencil, int nst,
-                        bool is_auto, bool periodic, Tile** tiles, uint32_t ntiles,
-                        hipStream_t s, uint32_t* total, DevArena* ar) {
-    const bool rows = stencil != nullptr && nst > 0;
+// waves take the heavy tiles early and the light ones fill the tail. With
+// total set, empty slots are dropped.
+cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, hipStream_t s,
+                        uint32_t* total, DevArena* ar) {
     if (total != nullptr && ntiles == 0) return fail(CUTE_E_INTERNAL, "tile compaction without tiles");
-    if (total == nullptr && (ntiles < 2 || !rows)) return CUTE_OK;
+    if (total == nullptr && ntiles < 2) return CUTE_OK;
     DevArena pool(s);
     DevArena& mem = ar != nullptr ? *ar : pool;
     uint32_t *key = nullptr, *rank = nullptr, *hist = nullptr;
@@ -528,13 +498,7 @@ cute_status order_tiles(const GridHost& A, const GridHost& B, const int4* stenci
         return st;
     }
     const unsigned nb = (ntiles + 255u) / 256u;
-    if (rows) {
-        hipLaunchKernelGGL(k_tile_cost, dim3((ntiles + 3u) / 4u), dim3(256), 0, s, *tiles, ntiles,
-                           B.cstart, A.ny, B.nx, B.ny, B.nz, stencil, nst, periodic ? 1 : 0,
-                           is_auto ? 1 : 0, key);
-    } else {
-        hipLaunchKernelGGL(k_tile_live, dim3(nb), dim3(256), 0, s, *tiles, ntiles, key);
-    }
+    hipLaunchKernelGGL(k_tile_cost, dim3((ntiles + 3u) / 4u), dim3(256), 0, s, a, *tiles, ntiles, key);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_tile_rank, dim3(nb), dim3(256), 0, s, key, ntiles, rank, hist);

@@ -20,7 +20,9 @@ struct alignas(32) P64 {
 
 // Sizes shared by the kernels and their launch planning.
 constexpr int kQCap = 128;        // FP64 re-test queue entries per wave
-constexpr int kSpanCap = 192;     // neighbour spans buffered per wave
+constexpr int kSpanCap = 132;     // neighbour spans buffered per wave: two per lane, two of the home row
+constexpr int kWaveLds = 3856;    // LDS bytes set aside per wave (queue, statistics, spans)
+constexpr int kMaxPartLog = 5;    // a home tile is counted in at most 2^5 parts
 constexpr int kWgWaves = 4;       // waves per count workgroup
 
 // Kinds of pair classification the kernels are specialised for.
@@ -77,7 +79,8 @@ struct CountArgs {
     uint32_t ntiles;
     const uint32_t* ntiles_dev;     // when set, the tile count in device memory (ntiles is
                                     // then only the capacity of tiles)
-    uint32_t* work_head;            // next tile to pop (global counter)
+    int plog;                       // every tile is counted in 2^plog parts (see do_tile)
+    uint32_t* work_head;            // tasks (tile parts) popped beyond the first of every wave
     unsigned long long* counts;     // nbins global uint64 counts
     unsigned long long* stats;      // [0] pair evals, [1] retests, [2] flips, [3] tiles
     int geom;                       // cute_geometry
@@ -210,12 +213,12 @@ struct GridHost {
     double ext;          // max |x - c| over points and axes (FP32 rounding scale)
     double rawmax;       // max |raw coordinate|
     double lmax;         // max |p| over points (for |p + q| bounds)
+    double phi_share;    // SPHERE: upper bound of the share of the ring the points span
     float4* p32;
     P64* p64;
     uint32_t* cstart;
     void* block;         // the one device allocation holding p64, p32 and cstart
     int tile_max;        // most points in a home tile (1..64)
-    bool tile_auto;      // tile_max is the default (counts may cut tiles shorter)
     // pixel maps: occupancy of each point in sorted order, and the non-empty
     // pixels (ids ascending) with their occupancies, all in one allocation
     uint32_t* wt;        // nullptr for plain catalogs
@@ -304,15 +307,13 @@ cute_status build_tiles_nowait(const GridHost& g, int max_w, hipStream_t s, Tile
 // upper bound of the number of tiles of g (no region labels)
 uint64_t tile_count_bound(const GridHost& g, int max_w);
 
-// reorder *tiles longest first by estimated cost (needs the precomputed
-// neighbour rows on the device; a no-op without them). With total set, empty
-// tiles are dropped and the number kept is written to *total (device
-// memory); without neighbour rows the kept tiles are then in no particular
-// order. With ar, the temporaries and the new list come from the arena and
+// reorder *tiles longest first by estimated cost (a: the count's arguments:
+// grids, stencil and symmetry; its tile list is not read). With total set,
+// empty tiles are dropped and the number kept is written to *total (device
+// memory). With ar, the temporaries and the new list come from the arena and
 // the old list is not freed; otherwise the old list is freed and replaced.
-cute_status order_tiles(const GridHost& A, const GridHost& B, const int4* stencil, int nst,
-                        bool is_auto, bool periodic, Tile** tiles, uint32_t ntiles,
-                        hipStream_t s, uint32_t* total = nullptr, DevArena* ar = nullptr);
+cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, hipStream_t s,
+                        uint32_t* total = nullptr, DevArena* ar = nullptr);
 
 // persistent count launch; *grid_used receives the number of workgroups
 // out[i] = in[input index of sorted point i] for the n points of g (in:

@@ -339,6 +339,22 @@ GridView GridHost::view() const {
 static constexpr int64_t kMaxCells = int64_t(1) << 26;
 static constexpr int kMaxAxis = 65535;
 
+// The share of the full circle in phi that the bounding rectangle of the
+// points in (x, y) subtends at the origin (1 when it holds the origin): an
+// upper bound of the share the points span.
+static double phi_share(const InStats& s) {
+    if (s.lo[0] <= 0.0 && s.hi[0] >= 0.0 && s.lo[1] <= 0.0 && s.hi[1] >= 0.0) return 1.0;
+    const double mx = 0.5 * (s.lo[0] + s.hi[0]), my = 0.5 * (s.lo[1] + s.hi[1]);
+    double lo = 0.0, hi = 0.0;
+    for (int k = 0; k < 4; k++) {
+        const double x = k & 1 ? s.hi[0] : s.lo[0], y = k & 2 ? s.hi[1] : s.lo[1];
+        const double d = std::atan2(mx * y - my * x, mx * x + my * y);  // from the centre's direction
+        lo = std::min(lo, d);
+        hi = std::max(hi, d);
+    }
+    return std::min(1.0, std::max((hi - lo) / kTwoPi, 1e-6));
+}
+
 // Choose the cells per axis and the cell geometry on the host.
 static cute_status plan_cells(GridHost& g, const cute_grid_params* p, const InStats& s) {
     const int64_t n = g.n;
@@ -429,6 +445,7 @@ static cute_status plan_cells(GridHost& g, const cute_grid_params* p, const InSt
         g.cx = g.cy = g.cz = 0.0;
         g.ext = 1.0 + 1e-6;
         g.L = 0.0;
+        g.phi_share = n ? phi_share(s) : 1.0;
     }
     double rawmax = 0.0;
     for (int d = 0; d < 3; d++)
@@ -475,7 +492,6 @@ extern "C" cute_status cute_build_grid(const double* x, const double* y, const d
     g.geom = p->geom;
     g.n = n;
     g.tile_max = p->tile_points > 0 ? p->tile_points : 64;
-    g.tile_auto = p->tile_points == 0;
 
     EventTimer timer(s);
     TempList tmp(s);

@@ -345,7 +345,7 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
     // estimated candidate pairs: nA nB times the stencil's share of B's domain
     double vol_b, vol_s;
     if (sphere) {
-        vol_b = std::max(B.nx * B.ax * B.ny * B.ay, 1e-300);  // phi range x cos(theta) range
+        vol_b = std::max(B.phi_share * B.nx * B.ax * B.ny * B.ay, 1e-300);  // phi x cos(theta)
         vol_s = kPiH * g->th_s * g->th_s;
     } else {
         vol_b = std::max(B.nx * B.ax * B.ny * B.ay * B.nz * B.az, 1e-300);
@@ -639,7 +639,9 @@ cute_status plan_lds(Plan& pl, size_t extra) {
     const int n1 = a.n1, n2 = a.n2, nbins = a.nbins;
     const size_t tables = 8 * (size_t)(n1 + 1) + 8 * (size_t)(n2 + 1) + 8 * (size_t)n1 +
                           8 * (size_t)std::max(n2, 1);
-    const size_t per_wave = 12 * (size_t)kQCap + 16 + 12 * (size_t)kSpanCap;
+    // (the bytes set aside per wave also bound the largest histogram)
+    const size_t per_wave = kWaveLds;
+    static_assert(12 * kQCap + 16 + 12 * kSpanCap <= kWaveLds, "per-wave LDS");
     // extra: the kernel's control words after the span buffers, plus the
     // budget word of a 32-bit histogram; a 32-bit histogram's bytes are
     // rounded up to 8
