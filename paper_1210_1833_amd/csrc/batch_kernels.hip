@@ -17,8 +17,6 @@ namespace cute {
 
 namespace {
 
-typedef const __attribute__((address_space(4))) CountArgs* cargp;
-
 // Sum the workgroup's histogram copies into counts (one atomic per non-empty
 // bin) and clear them (counters of 4 bytes when H32, else 8).
 template <bool H32>
@@ -41,45 +39,30 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int nwaves = blockDim.x >> 6;
-    const int n1 = BA.n1, n2 = BA.n2;
-    const int n2p = n2 > 0 ? n2 : 0;
-    double* T1 = reinterpret_cast<double*>(smem);
-    double* T2 = T1 + (n1 + 1);
-    float2* B1 = reinterpret_cast<float2*>(T2 + (n2p + 1));
-    float2* B2 = B1 + n1;
+    const int n1 = BA.n1;
+    const int n2p = BA.n2 > 0 ? BA.n2 : 0;
     constexpr bool H32 = kH32<MODE>;
-    // the histogram: hist_words counters of 4 (kH32) or 8 bytes, padded to 8
-    unsigned char* hist0 = reinterpret_cast<unsigned char*>(B2 + (n2p > 0 ? n2p : 1));
-    const size_t hbytes = ((size_t)BA.hist_words * (H32 ? 4 : 8) + 7) & ~(size_t)7;
-    uint32_t* q0 = reinterpret_cast<uint32_t*>(hist0 + hbytes);
-    unsigned long long* rs0 = reinterpret_cast<unsigned long long*>(q0 + (size_t)nwaves * 3 * kQCap);
-    uint32_t* sp0 = reinterpret_cast<uint32_t*>(rs0 + 2 * nwaves);
-    uint32_t* ctl = sp0 + (size_t)nwaves * 3 * kSpanCap;  // chunk id, item, next tile, end tile
-    uint32_t* budget = ctl + 4;                           // 32-bit histograms only
+    const WgLds L = wg_lds<H32, kMfma<MODE, PREC, EST>>(smem, nwaves, n1, BA.n2, BA.hist_words);
+    double *T1 = L.T1, *T2 = L.T2;
+    float2 *B1 = L.B1, *B2 = L.B2;
+    unsigned char* hist0 = L.hist;
+    uint32_t* ctl = L.ctl;        // chunk id, item, next tile, end tile
+    uint32_t* budget = ctl + 4;   // 32-bit histograms only
     for (int i = threadIdx.x; i <= n1; i += blockDim.x) T1[i] = BA.T1[i];
     for (int i = threadIdx.x; i <= n2p; i += blockDim.x) T2[i] = n2p ? BA.T2[i] : 0.0;
     if (PREC != P_FP64) {
-        for (int i = threadIdx.x; i < n1; i += blockDim.x) B1[i] = BA.band1[i];
-        for (int i = threadIdx.x; i < n2p; i += blockDim.x) B2[i] = BA.band2[i];
+        // (sigma-pi from the matrix cores: one entry past the last bin)
+        constexpr int more = kMfma<MODE, PREC, EST> && MODE == M_SIGMAPI ? 1 : 0;
+        for (int i = threadIdx.x; i < n1 + more; i += blockDim.x) B1[i] = BA.band1[i];
+        for (int i = threadIdx.x; i < n2p + more; i += blockDim.x) B2[i] = BA.band2[i];
     }
-    for (size_t i = threadIdx.x; i < hbytes / 4; i += blockDim.x) reinterpret_cast<uint32_t*>(hist0)[i] = 0u;
-    for (int i = threadIdx.x; i < 2 * nwaves; i += blockDim.x) rs0[i] = 0ull;
+    for (size_t i = threadIdx.x; i < L.hbytes / 4; i += blockDim.x) reinterpret_cast<uint32_t*>(hist0)[i] = 0u;
+    for (int i = threadIdx.x; i < 2 * nwaves; i += blockDim.x) L.rstat[i] = 0ull;
     if (H32 && threadIdx.x == 0) *budget = 0u;
 
-    WaveState W;
-    W.hist = hist0;
+    WaveState W = wave_state(L, wave);
     W.budget = budget;
-    W.pend = 0;
-    W.qi = q0 + (size_t)wave * 3 * kQCap;
-    W.qj = W.qi + kQCap;
-    W.qc = W.qj + kQCap;
-    W.rstat = rs0 + 2 * wave;
-    W.tail = 0;
-    W.evals = W.tiles = 0;
-    SpanBuf S;
-    S.a = sp0 + (size_t)wave * 3 * kSpanCap;
-    S.b = S.a + kSpanCap;
-    S.f = S.b + kSpanCap;
+    SpanBuf S = span_buf(L, wave);
 
     uint32_t cur = 0xffffffffu;  // item whose counts the histogram holds
     for (;;) {
@@ -101,14 +84,14 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
         const uint32_t tend = uni(ctl[3]);
         if (item != cur) {
             if (cur != 0xffffffffu) {
-                const CountArgs& Pc = *(const CountArgs*)(cargp)(const void*)(BA.items + cur);
+                const CountArgs& Pc = *(const CountArgs*)(cargp)(uintptr_t)(BA.items + cur);
                 flush_hist<H32>(hist0, BA.nbins, BA.copies, Pc.counts);
                 if (H32 && threadIdx.x == 0) *budget = 0u;
                 __syncthreads();
             }
             cur = item;
         }
-        const CountArgs& P = *(const CountArgs*)(cargp)(const void*)(BA.items + item);
+        const CountArgs& P = *(const CountArgs*)(cargp)(uintptr_t)(BA.items + item);
         for (;;) {
             uint32_t t = 0;
             if (lane == 0) t = atomicAdd(&ctl[2], 1u);
@@ -137,7 +120,7 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
         W.evals = W.tiles = 0;
     }
     if (cur != 0xffffffffu) {
-        const CountArgs& Pc = *(const CountArgs*)(cargp)(const void*)(BA.items + cur);
+        const CountArgs& Pc = *(const CountArgs*)(cargp)(uintptr_t)(BA.items + cur);
         flush_hist<H32>(hist0, BA.nbins, BA.copies, Pc.counts);
     }
 }
@@ -197,6 +180,10 @@ cute_status launch_b(const BatchArgs& ba, int grid, size_t lds, hipStream_t s) {
         if (m_ == M_RMU_Z && p_ == P_FP32E && est_muf(est)) {                                 \
             if (e_) return FN<1, 1, E_LOG | E_MUF>(__VA_ARGS__);                                \
             return FN<1, 1, E_MUF>(__VA_ARGS__);                                               \
+        }                                                                                     \
+        if (m_ == M_RMU_MID && p_ == P_FP32E && est_muf(est)) {                               \
+            if (e_) return FN<2, 1, E_LOG | E_MUF>(__VA_ARGS__);                                \
+            return FN<2, 1, E_MUF>(__VA_ARGS__);                                               \
         }                                                                                     \
         switch (m_ * 6 + p_ * 2 + e_) {                                                       \
             case 0: return FN<0, 0, 0>(__VA_ARGS__);                                          \

@@ -238,8 +238,9 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     Plan pl;
     plan_binning(bins, pl);
     ItemGeom geo;
-    if ((s = plan_item(A, B, is_auto, bins, pl, &geo)) != CUTE_OK) return s;
+    if ((s = plan_item(A, B, is_auto, bins, pl, (int)prec, &geo)) != CUTE_OK) return s;
     plan_bands(bins, geo.em, pl);
+    int kprec = served_prec((int)prec, geo, A, B, pl);
     if (rad) {
         // the aperture binning gave the geometry; the histogram is over the
         // redshift difference, compared with the unsquared edges
@@ -258,7 +259,7 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
         r.nbins = rad->n;
         r.n2p1 = 1;
     }
-    if ((s = plan_lds(pl, 0)) != CUTE_OK) return s;
+    if ((s = plan_lds(pl, 0, &kprec)) != CUTE_OK) return s;
     CountArgs a = pl.a;
     apply_item(geo, &a);
     const int nbins = a.nbins;
@@ -427,7 +428,7 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     int grid = 0;
     EventTimer timer(hs, fixed ? fixed->events : nullptr);
     if (ntiles > 0) {
-        s = launch_count(a, pl.mode, (int)prec, pl.est, kWgWaves, pl.lds, hs, &grid);
+        s = launch_count(a, pl.mode, kprec, pl.est, kWgWaves, pl.lds, hs, &grid);
         if (s != CUTE_OK) {
             drop_tiles();
             return s;
@@ -543,7 +544,7 @@ extern "C" cute_status cute_tune_grid(const double* x, const double* y, const do
         }
     } else {
         cand.push_back(0.0);  // the library's density rule
-        for (double f : {1.0 / 2, 1.0 / 3, 1.0 / 4, 1.0 / 5, 1.0 / 6}) cand.push_back(rmax * f);
+        for (double k : {2.0, 3.0, 4.0, 5.0, 6.0}) cand.push_back(rmax / k);
     }
     std::vector<int> tsz;
     if (n_tile > 0) {

@@ -21,6 +21,7 @@ typedef const __attribute__((address_space(4))) float* cfp;
 typedef const __attribute__((address_space(4))) double* cdp;
 typedef const __attribute__((address_space(4))) uint32_t* cu32p;
 typedef const __attribute__((address_space(4))) double* cf64p;
+typedef const __attribute__((address_space(4))) CountArgs* cargp;
 
 // x, y, z of the U consecutive points h .. h+U-1 from one base address with
 // constant offsets (the index is widened before the offsets are added, so the
@@ -53,6 +54,20 @@ __device__ __forceinline__ void load_points64(const P64* p, uint32_t h, double* 
 
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int unii(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+__device__ __forceinline__ uint32_t lane_u32(uint32_t v, int l) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+// base plus the number of lower lanes set in a mask
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m, uint32_t base = 0u) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
+}
+// A lane mask as a lane's own truth value.
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 __device__ __forceinline__ int floordiv(int a, int n) { return a >= 0 ? a / n : -((-a + n - 1) / n); }
 
@@ -230,8 +245,10 @@ struct C32 {
 // addresses of the band tables minus the bias times 8
 struct Tab32 {
     uint32_t vbias;      // VGPR copy of kBias
+    uint32_t vbias1;     // and of kBias + 1 (the float 2^23 + 1)
     uint32_t tb1, tb2;   // LDS byte address of B1 (B2) - (kBias << 3), modulo 2^32
-    float d0;            // VGPR copy of the constant term of the mu band (z line of sight)
+    float d0, d1;        // VGPR copies of the mu band's constant and linear terms
+    float mt;            // sigma-pi: the tile's t
 };
 
 typedef float __attribute__((ext_vector_type(2))) f2v;
@@ -245,7 +262,10 @@ template <int EST>
 __device__ __forceinline__ Tab32 make_tab32(const CountArgs& P, const float2* B1, const float2* B2) {
     Tab32 t;
     asm volatile("v_mov_b32 %0, %1" : "=v"(t.vbias) : "s"(kBias));
+    asm volatile("v_mov_b32 %0, %1" : "=v"(t.vbias1) : "s"(kBias + 1u));
     asm volatile("v_mov_b32 %0, %1" : "=v"(t.d0) : "s"(est_muf(EST) ? P.muB0 : P.dA0p));
+    asm volatile("v_mov_b32 %0, %1" : "=v"(t.d1) : "s"(P.muB1));
+    t.mt = 0.f;
     t.tb1 = lds_addr(B1) - (kBias << 3);
     t.tb2 = lds_addr(B2) - (kBias << 3);
     return t;
@@ -422,6 +442,9 @@ __device__ __forceinline__ C32 classify32(const CountArgs& P, const Tab32& T, fl
         float fsbot = fmaf(P.out_lo, ll, c2);       // out_lo holds -S2f[0] (or +BIG)
         float fpbot = fmaf(P.nlo2_first, ll, sl2);  // -P2f[0] (or +BIG)
         bool ok = (fsbot >= 0.0f) & (fstop < 0.0f) & (fpbot >= 0.0f) & (fptop < 0.0f);
+        // (top1 and top2 may be one past the last bin, see decide)
+        c.kb = min(c.kb, kBias + (uint32_t)(P.n1 - 1));
+        c.kmb = min(c.kmb, kBias + (uint32_t)(P.n2 - 1));
         *tent = ok ? c32_bin(P, c) : kNoBin;
         c.in = c.out = false;
         return c;
@@ -466,7 +489,14 @@ struct WaveState {
     unsigned char* hist; // the workgroup's shared histogram (hist_words counters, kH32)
     uint32_t* qi;        // re-test queue: home index
     uint32_t* qj;        // re-test queue: neighbour index
-    uint32_t* qc;        // re-test queue: neighbour image code
+    uint8_t* qc;         // re-test queue: neighbour image code
+    float4* stage;       // the tile's home points in its own frame (kMfma kernels)
+    uint16_t* list;      // ambiguous pairs of the chunk at hand: home offset << 6 | lane (kMfma)
+    uint32_t nlist;      // how many (wave-uniform)
+    float* alpha;        // per home point: |p|^2 - |P0|^2, P0 the origin (midpoint kinds)
+    float ox, oy, oz;    // that frame's origin in the grid's FP32 frame (wave-uniform)
+    float lx, ly, lz;    // midpoint kinds: L0 = 2 P0 from the observer (wave-uniform)
+    float mt, mb0, mb1;  // sigma-pi: the tile's t; mu: its band's constant and linear terms
     unsigned long long* rstat;  // [0] retests, [1] flips (LDS)
     uint32_t tail;       // queued entries (wave-uniform)
     uint64_t evals, tiles;
@@ -476,6 +506,44 @@ struct WaveState {
     uint32_t* budget;
     uint32_t pend;
 };
+
+// LDS of a count workgroup: [staged home points | tables | histogram |
+// re-test statistics | queues | spans | ambiguous pairs | queue and span
+// codes | control words]; stage and ambiguous pairs for kMfma kernels only.
+struct WgLds {
+    double *T1, *T2;
+    float2 *B1, *B2;
+    unsigned char* hist;
+    size_t hbytes;       // hist_words counters of 4 (kH32) or 8 bytes, padded to 8
+    unsigned long long* rstat;
+    uint32_t *queue, *spans, *ctl;
+    uint16_t* list;
+    uint8_t *qcodes, *scodes;
+    float4* stage;
+    float* alpha;
+};
+// (H32 are the midpoint kinds)
+template <bool H32, bool MFMA>
+__device__ __forceinline__ WgLds wg_lds(unsigned char* smem, int nwaves, int n1, int n2, int hist_words) {
+    const int n2p = n2 > 0 ? n2 : 0;
+    WgLds l;
+    l.stage = reinterpret_cast<float4*>(smem);
+    l.alpha = reinterpret_cast<float*>(smem + (MFMA ? (size_t)nwaves * kStage : 0));
+    l.T1 = reinterpret_cast<double*>(l.alpha + (MFMA && H32 ? (size_t)nwaves * (kStageMid / 4) : 0));
+    l.T2 = l.T1 + (n1 + 1);
+    l.B1 = reinterpret_cast<float2*>(l.T2 + (n2p + 1));
+    l.B2 = l.B1 + n1 + (MFMA ? 1 : 0);   // (sigma-pi: an entry past the last bin)
+    l.hist = reinterpret_cast<unsigned char*>(l.B2 + (n2p > 0 ? n2p : 1) + (MFMA ? 1 : 0));
+    l.hbytes = ((size_t)hist_words * (H32 ? 4 : 8) + 7) & ~(size_t)7;
+    l.rstat = reinterpret_cast<unsigned long long*>(l.hist + l.hbytes);
+    l.queue = reinterpret_cast<uint32_t*>(l.rstat + 2 * nwaves);
+    l.spans = l.queue + (size_t)nwaves * 2 * kQCap;
+    l.list = reinterpret_cast<uint16_t*>(l.spans + (size_t)nwaves * 2 * kSpanCap);
+    l.qcodes = reinterpret_cast<uint8_t*>(l.list + (MFMA ? (size_t)nwaves * kList : 0));
+    l.scodes = l.qcodes + (size_t)nwaves * kQCap;
+    l.ctl = reinterpret_cast<uint32_t*>(l.scodes + (size_t)nwaves * kSpanCap);
+    return l;
+}
 
 // The workgroup's histogram: several interleaved copies so that lanes
 // hitting the same bin use different banks, copies a power of two: counter =
@@ -501,6 +569,25 @@ __device__ __forceinline__ void lds_add(uint32_t byte_addr, uint64_t w) {
     else
         __hip_atomic_fetch_add((__attribute__((address_space(3))) unsigned long long*)(uintptr_t)byte_addr,
                                (unsigned long long)w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__device__ __forceinline__ WaveState wave_state(const WgLds& l, int wave) {
+    WaveState W;
+    W.hist = l.hist;
+    W.budget = nullptr;
+    W.pend = 0;
+    W.qi = l.queue + (size_t)wave * 2 * kQCap;
+    W.qj = W.qi + kQCap;
+    W.qc = l.qcodes + (size_t)wave * kQCap;
+    W.stage = l.stage + (size_t)wave * (kStage / 16);
+    W.list = l.list + (size_t)wave * kList;
+    W.nlist = 0;
+    W.alpha = l.alpha + (size_t)wave * (kStageMid / 4);
+    W.ox = W.oy = W.oz = W.lx = W.ly = W.lz = W.mt = W.mb0 = W.mb1 = 0.f;
+    W.rstat = l.rstat + 2 * wave;
+    W.tail = 0;
+    W.evals = W.tiles = 0;
+    return W;
 }
 
 // Move a 32-bit histogram to the global counts (one wave): every counter is
@@ -555,7 +642,7 @@ __device__ __forceinline__ uint64_t pair_weight2(const CountArgs& P, uint32_t i,
 // Returns the new queue length.
 template <int MODE, int EST>
 __device__ __forceinline__ uint32_t drain_queue(
-    const CountArgs* __restrict__ Pg, unsigned char* hist, uint32_t* qi, uint32_t* qj, uint32_t* qc,
+    const CountArgs* __restrict__ Pg, unsigned char* hist, uint32_t* qi, uint32_t* qj, uint8_t* qc,
     unsigned long long* rstat, const float2* B1, const float2* B2, const double* T1,
     const double* T2, int lane, uint32_t tail, bool all) {
     const CountArgs& P = *Pg;
@@ -592,7 +679,7 @@ __device__ __forceinline__ uint32_t drain_queue(
             const uint32_t a = qi[n + lane], b = qj[n + lane], c = qc[n + lane];
             qi[lane] = a;
             qj[lane] = b;
-            qc[lane] = c;
+            qc[lane] = (uint8_t)c;
         }
         tail = rest;
     }
@@ -608,7 +695,7 @@ __device__ __forceinline__ uint32_t drain_queue(
 // stack frame; inlined, the r-mu count takes 3 % less time, the others 1 %.
 template <int MODE, int EST>
 __device__ __forceinline__ uint32_t enqueue_chunk(
-    const CountArgs* __restrict__ Pg, unsigned char* hist, uint32_t* qi, uint32_t* qj, uint32_t* qc,
+    const CountArgs* __restrict__ Pg, unsigned char* hist, uint32_t* qi, uint32_t* qj, uint8_t* qc,
     unsigned long long* rstat, const float2* B1, const float2* B2, const double* T1,
     const double* T2, int lane, uint32_t tail, uint32_t ts, uint32_t lj, uint32_t lcode,
     uint64_t ambh, uint64_t hsum) {
@@ -625,7 +712,7 @@ __device__ __forceinline__ uint32_t enqueue_chunk(
             const uint32_t pos = tail + pre;
             qi[pos] = ts + o;
             qj[pos] = lj;
-            qc[pos] = lcode;
+            qc[pos] = (uint8_t)lcode;
         }
         tail += (uint32_t)__popcll(m);
         if (tail >= 64u)
@@ -758,6 +845,340 @@ __device__ __forceinline__ void step32(const CountArgs& P, WaveState& W, const T
     }
 }
 
+// ---------------------------------------------------------------------------
+// Separations from the matrix cores (FP32_EDGE). With the home points and the neighbours in the frame of the home
+// tile (a and b), |a - b|^2 = |b|^2 - 2 a.b + |a|^2 is one chain of four
+// v_mfma_f32_4x4x1 (sixteen blocks of 4 x 4 pairs, K = 1 each): the columns of
+// the blocks are the lanes' neighbours, the four rows of every block the same
+// four home points, so a lane receives its neighbour's values against four
+// home points in four registers, the layout of the VALU code that follows.
+// An instruction takes 10.4 cycles (measured; it shares the FP32 pipe, so it
+// does not overlap with VALU work) and does what four VALU fused
+// multiply-adds do in 17.8: the separations of four pairs take 41.4 cycles
+// instead of 107 for three subtractions and three multiply-adds per pair, and
+// dz 10.4 instead of 17.8. Each step is a fused multiply-add rounded once
+// (checked bit for bit against fmaf); the error of the expanded form is in
+// d2_bound. A point that is not there (past the tile's end, masked, or an
+// idle lane) has |a|^2 or |b|^2 = kFar and falls past the top edge.
+// ---------------------------------------------------------------------------
+typedef float __attribute__((ext_vector_type(4))) f4v;
+constexpr float kFar = 1e33f;
+template <int MODE>
+constexpr bool kMid = MODE == M_SIGMAPI || MODE == M_RMU_MID;
+
+// Origin of a tile's frame, in the grid's FP32 frame: the centre of its box
+// of cells (an axis of one cell: the grid's centre), on the sphere the point
+// in the middle of its run.
+template <bool SPH>
+__device__ __forceinline__ void tile_origin(const CountArgs& P, const Tile& tl, float* ox, float* oy,
+                                            float* oz) {
+    const GridView& A = P.A;
+    float x, y, z;
+    if constexpr (SPH) {
+        const float4 p = A.p32[tl.start + ((tl.end - tl.start) >> 1)];
+        x = p.x;
+        y = p.y;
+        z = p.z;
+    } else {
+        const int c0 = (int)(tl.c0c1 & 0xffffu), c1 = (int)(tl.c0c1 >> 16);
+        const int cy = (int)(tl.row % (uint32_t)A.ny), cz = (int)(tl.row / (uint32_t)A.ny);
+        x = A.nx == 1 ? 0.f : (float)(A.ox + 0.5 * (double)(c0 + c1 + 1) * A.ax - A.cx);
+        y = A.ny == 1 ? 0.f : (float)(A.oy + ((double)cy + 0.5) * A.ay - A.cy);
+        z = A.nz == 1 ? 0.f : (float)(A.oz + ((double)cz + 0.5) * A.az - A.cz);
+    }
+    *ox = __uint_as_float(uni(__float_as_uint(x)));
+    *oy = __uint_as_float(uni(__float_as_uint(y)));
+    *oz = __uint_as_float(uni(__float_as_uint(z)));
+}
+
+// The arguments' copy in device memory, out of the compiler's sight.
+__device__ __forceinline__ const CountArgs& args_again(const CountArgs& P) {
+    const uint64_t u = (uint64_t)(uintptr_t)P.self;
+    uint64_t v = (uint64_t)uni((uint32_t)u) | ((uint64_t)uni((uint32_t)(u >> 32)) << 32);
+    asm volatile("" : "+s"(v));
+    return *(const CountArgs*)(cargp)v;
+}
+
+__device__ __forceinline__ double dot64(float ax, float ay, float az, float bx, float by, float bz) {
+    return fma((double)az, (double)bz, fma((double)ay, (double)by, (double)ax * (double)bx));
+}
+__device__ __forceinline__ double sq64(float x, float y, float z) { return dot64(x, y, z, x, y, z); }
+__device__ __forceinline__ float unif(float v) { return __uint_as_float(uni(__float_as_uint(v))); }
+
+// Midpoint line of sight, l = p + q = L0 + a + b with L0 = 2 P0 (P0 the tile's
+// origin from the observer): s.l = |p|^2 - |q|^2 = alpha - beta with alpha =
+// L0.a + |a|^2 and beta = L0.b + |b|^2 (formed in FP64, rounded once), and
+// |l|^2 = |L0|^2 + 2 alpha + 2 beta - |s|^2. So sl and |l|^2 + v are two more
+// products of one step each and ll one subtraction, where the components took
+// twelve operations. Errors (u = 2^-24, M >= |a| + |b|, Lx = |L0| + M >= |l|):
+//   |sl32 - s.l| <= Esl + u |sl|,   Esl = u (Lx M + M^2)
+//   |ll32 - |l|^2| <= Ell = 1.01 u (3 Lx^2 + 2 Lx M + 9.1 M^2)
+// (u |alpha|, u |beta| <= u (|L0| |a| + a^2) each; 2 alpha, the rounding of 2
+// beta + |L0|^2, of the sum, of ll, and the error of v). In units of F (c2 or
+// sl^2, see midpoint_bands) they and the direction error of l are below
+//   t = K1 Lx + K0 + (T_max + R^2) Ell + 2 R Lx Esl + Esl^2
+// for every pair of the tile; mu: see midpoint_mu_band.
+template <int MODE>
+__device__ __forceinline__ void midpoint_tile(const CountArgs& P, WaveState& W) {
+    const float u = 0x1p-24f;
+    W.lx = unif((float)(2.0 * (P.A.cx + (double)W.ox)));
+    W.ly = unif((float)(2.0 * (P.A.cy + (double)W.oy)));
+    W.lz = unif((float)(2.0 * (P.A.cz + (double)W.oz)));
+    const float l0 = __builtin_sqrtf((float)sq64(W.lx, W.ly, W.lz));
+    const float M = P.mdM, Lx = fmaf(l0, 1.00001f, M);
+    const float esl = 1.001f * u * (Lx * M + M * M);
+    const float ell = 1.011f * u * (3.0f * Lx * Lx + 2.0f * Lx * M + 9.1f * M * M);
+    if constexpr (MODE == M_SIGMAPI) {
+        const float t = P.spK1 * Lx + P.spK0 + P.mdTR * ell + P.md2R * Lx * esl + esl * esl;
+        W.mt = unif(fmaxf(1.1f * t, P.mdTmin));
+    } else {
+        // |l| >= lmin; a tile too close to the observer decides nothing in
+        // FP32 (mt < 0) and is counted in FP64
+        const float lmin = l0 * 0.99999f - M;
+        const float i = 1.0f / lmin;
+        const float d0 = P.mdN * (2.0f * P.mdFe * i + 0.5f * ell * i * i), d1 = P.mdN * esl * i;
+        W.mt = unif(lmin > 0.05f * M && lmin > 16.0f * P.mdFe && d0 < 0.2f ? 1.0f : -1.0f);
+        W.mb0 = unif(P.muB0 - 1.001f * d0);
+        W.mb1 = unif(P.muB1 - 1.001f * d1);
+    }
+}
+
+// The tile's home points as the rows of the products: (-2 a, |a|^2), and alpha.
+template <int MODE, bool PM>
+__device__ __forceinline__ void stage_home(const CountArgs& Pk, WaveState& W, const Tile& tl, int lane) {
+    const CountArgs& P = args_again(Pk);   // see next_rows
+    tile_origin<kSphere<MODE>>(P, tl, &W.ox, &W.oy, &W.oz);
+    const uint32_t i = tl.start + (uint32_t)lane;
+    bool ok = i < tl.end;
+    if (PM && P.mbA != nullptr && ok) ok = ((P.mbA[i >> 5] >> (i & 31u)) & 1u) == 0u;
+    float4 s = make_float4(0.f, 0.f, 0.f, kFar);
+    float al = 0.f;
+    if constexpr (kMid<MODE>) midpoint_tile<MODE>(P, W);
+    if (ok) {
+        const float4 p = P.A.p32[i];
+        const float x = p.x - W.ox, y = p.y - W.oy, z = p.z - W.oz;
+        const double a2 = sq64(x, y, z);
+        s = make_float4(-2.0f * x, -2.0f * y, -2.0f * z, (float)a2);
+        if constexpr (kMid<MODE>) al = (float)(dot64(W.lx, W.ly, W.lz, x, y, z) + a2);
+    }
+    wave_lds_fence();
+    W.stage[lane] = s;
+    if constexpr (kMid<MODE>) W.alpha[lane] = al;
+    wave_lds_fence();
+}
+
+// A chunk's neighbour as a column: b, |b|^2 and -b_z in the four rows;
+// midpoint kinds: -beta and 2 beta + |L0|^2.
+struct Column {
+    float bx, by, bz;
+    f4v b2, nbz, nbeta, beta2;
+};
+
+// Decision of the lanes' pairs from v = |s|^2 and dz: the lanes whose pair is
+// certainly in the bin at LDS address *off (lt: the lanes whose pair is not
+// past the top edge). Lane masks throughout: the logic of a step is scalar
+// work then.
+// r-mu in bin units uses estimates biased by 2^23 + 1: x >= -1/2 then stays
+// at or above 2^23, where floats are whole, so the estimate needs no clamp (a
+// pair that is in has |x - k| < 1/2 and lies below the top edge, hence k is a
+// bin; the offset of any other pair is not used). NaN decides nothing.
+// d: dz, or sl for the midpoint kinds; ss: |l|^2 + v for those. Sigma-pi: the
+// tables hold one entry past the last bin, for the pairs certainly past the top
+// edge; *skip receives the lanes that are (not counted, not ambiguous).
+template <int MODE, int EST>
+__device__ __forceinline__ uint64_t decide(const CountArgs& P, const Tab32& T, float v, float d, float ss,
+                                           uint64_t lt, uint32_t lb, uint32_t* off, uint64_t* skip) {
+    if constexpr (MODE == M_SIGMAPI) {
+        const float ll = ss - v;
+        const float sl2 = d * d;
+        const float c2 = fmaf(v, ll, -sl2);
+        // (a c2 rounded below zero gives a NaN estimate, which the clamp puts
+        // past the last sigma bin, where its band test fails: re-tested)
+        const float rl = __builtin_amdgcn_rsqf(ll);
+        const uint32_t ks = est_bits(fmaf(__builtin_amdgcn_sqrtf(c2), rl, P.s1), P.e1a, T, P.top1);
+        const uint32_t kp = est_bits(fmaf(fabsf(d), rl, P.s2), P.e2a, T, P.top2);
+        const float2 bs = band_at(T.tb1, ks);
+        const float2 bp = band_at(T.tb2, kp);
+        const uint64_t in =
+            __builtin_amdgcn_ballot_w64(fabsf(fmaf(bs.x, ll, c2)) <= fmaf(bs.y, ll, -T.mt)) &
+            __builtin_amdgcn_ballot_w64(fabsf(fmaf(bp.x, ll, sl2)) <= fmaf(bp.y, ll, -T.mt)) & lt;
+        *off = __umul24(ks, (uint32_t)P.hs1) + (__umul24(kp, (uint32_t)P.hs2) + lb);
+        *skip = in & (__builtin_amdgcn_ballot_w64(ks == P.top1) | __builtin_amdgcn_ballot_w64(kp == P.top2));
+        return in & ~*skip;
+    }
+    float dz = d;
+    if constexpr (MODE == M_RMU_MID) dz = d * __builtin_amdgcn_rsqf(ss - v);   // |s.l| / |l|
+    if constexpr (MODE == M_MONO || MODE == M_THETA) {
+        float e;
+        if constexpr (MODE == M_THETA && est_log(EST)) {
+            // 2 log2(theta) = log2(v) + v / (12 ln 2) to the order of the
+            // table's guess: theta = c + c^3 / 24
+            const float t = fmaf(v, 0.12022458674074695f, P.s1 + P.s1);
+            e = fmaf(t + __builtin_amdgcn_logf(v), 0.5f * P.e1a, __uint_as_float(T.vbias));
+        } else {
+            float ts;
+            if constexpr (MODE == M_THETA) {
+                const float ch = __builtin_amdgcn_sqrtf(v);
+                ts = fmaf(ch * v, 1.0f / 24.0f, ch) + P.s1;  // 2 asin(c/2) to third order
+            } else if constexpr (est_log(EST)) {
+                ts = __builtin_amdgcn_logf(v) + P.s1;
+            } else {
+                ts = fmaf(v, __builtin_amdgcn_rsqf(v), P.s1);
+            }
+            e = fmaf(ts, P.e1a, __uint_as_float(T.vbias));
+        }
+        const uint32_t kb = med3u(__float_as_uint(e), T.vbias, P.top1);
+        *off = __umul24(kb, (uint32_t)P.hs1) + lb;
+        return __builtin_amdgcn_ballot_w64(in_band(v, band_at(T.tb1, kb)));
+    } else {
+        const float rinv = __builtin_amdgcn_rsqf(v);
+        const float ts = est_log(EST) ? __builtin_amdgcn_logf(v) + P.s1 : fmaf(v, rinv, P.s1);
+        const float ts2 = fmaf(fabsf(dz), rinv, P.s2);
+        if constexpr (est_muf(EST)) {
+            const float bias1 = __uint_as_float(T.vbias1);
+            const float em = fmaf(ts2, P.e2a, bias1);
+            const float half = fmaf(fmaf(P.muB2, rinv, T.d1), rinv, T.d0);
+            const uint64_t min_ = __builtin_amdgcn_ballot_w64(fabsf(fmaf(ts2, P.e2a, bias1 - em)) <= half);
+            const uint32_t om = __umul24(__float_as_uint(em), (uint32_t)P.hs2) + lb;
+            if constexpr (!est_log(EST)) {
+                const float er = fmaf(ts, P.e1a, bias1);
+                *off = __umul24(__float_as_uint(er), (uint32_t)P.hs1) + om;
+                return __builtin_amdgcn_ballot_w64(fabsf(fmaf(ts, P.e1a, bias1 - er)) <= P.rB0) & min_ & lt;
+            } else {
+                const uint32_t kr = est_bits(ts, P.e1a, T, P.top1);
+                *off = __umul24(kr, (uint32_t)P.hs1) + om;
+                return __builtin_amdgcn_ballot_w64(in_band(v, band_at(T.tb1, kr))) & min_ & lt;
+            }
+        } else {
+            const uint32_t kr = est_bits(ts, P.e1a, T, P.top1);
+            const uint32_t km = est_bits(ts2, P.e2a, T, P.top2);
+            *off = __umul24(kr, (uint32_t)P.hs1) + (__umul24(km, (uint32_t)P.hs2) + lb);
+            const float2 m = band_at(T.tb2, km);
+            const float dz2 = dz * dz;
+            const float delta = est_log(EST) ? fmaf(P.dA1, v * rinv, T.d0) : fmaf(P.dA1, ts, T.d0);
+            return __builtin_amdgcn_ballot_w64(fmaf(m.x, v, dz2) >= delta) &
+                   __builtin_amdgcn_ballot_w64(fmaf(m.y, v, dz2) <= -delta) &
+                   __builtin_amdgcn_ballot_w64(in_band(v, band_at(T.tb1, kr)));
+        }
+    }
+}
+
+// The histogram address of a decision's estimates starts at the lane's copy
+// minus the bias of each estimate that is one above the bin.
+template <int MODE, int EST>
+__device__ __forceinline__ uint32_t decide_base(const CountArgs& P, uint32_t lb) {
+    if constexpr (est_muf(EST))
+        return lb - (uint32_t)P.hs2 - (est_log(EST) ? 0u : (uint32_t)P.hs1);
+    return lb;
+}
+
+// |s|^2 of four home points against the chunk: the K-th four of the sixteen
+// whose rows are in a (in every group of 16 lanes; the instruction broadcasts
+// its K-th block to the group), or with K < 0 the four whose rows are in every
+// four lanes of a.
+template <int K>
+__device__ __forceinline__ f4v sep_mfma(const float4& a, const Column& q) {
+    constexpr int B = K < 0 ? 0 : 2, I = K < 0 ? 0 : K;
+    f4v v = __builtin_amdgcn_mfma_f32_4x4x1f32(a.x, q.bx, q.b2, B, I, 0);
+    v = __builtin_amdgcn_mfma_f32_4x4x1f32(a.y, q.by, v, B, I, 0);
+    v = __builtin_amdgcn_mfma_f32_4x4x1f32(a.z, q.bz, v, B, I, 0);
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a.w, 1.0f, v, B, I, 0);
+}
+
+// Four home points (the K-th of the rows a, home offsets o .. o + 3,
+// separations v) against the chunk. Ambiguous pairs go to the wave's list, which has room for all of
+// a step's.
+template <int MODE, int EST, bool WT, bool MASKED, int K>
+__device__ __forceinline__ void step_mfma(const CountArgs& P, WaveState& W, const Tab32& T, const float4& a,
+                                          float al, const f4v& v, const Column& q, bool lmask, uint32_t lj,
+                                          uint32_t lb, uint32_t lw, int lane, uint32_t ts,
+                                          uint32_t te, uint32_t o) {
+    // every pair past the top edge (the clean-out side of its rounding band):
+    // nothing to count or re-test
+    uint64_t lt[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) lt[u] = __builtin_amdgcn_ballot_w64(v[u] < P.skip32);
+    if ((lt[0] | lt[1] | lt[2] | lt[3]) == 0ull) return;
+    constexpr int B = K < 0 ? 0 : 2, I = K < 0 ? 0 : K;
+    f4v d = {0.f, 0.f, 0.f, 0.f}, ss = d;
+    if constexpr (kMid<MODE>) {
+        d = __builtin_amdgcn_mfma_f32_4x4x1f32(al, 1.0f, q.nbeta, B, I, 0);
+        ss = __builtin_amdgcn_mfma_f32_4x4x1f32(al, 2.0f, q.beta2, B, I, 0);
+    } else if constexpr (MODE == M_RMU_Z) {
+        d = __builtin_amdgcn_mfma_f32_4x4x1f32(a.z, -0.5f, q.nbz, B, I, 0);
+    }
+    uint32_t off[4];
+    uint64_t cnt[4], amb[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        uint64_t skip = 0;
+        cnt[u] = decide<MODE, EST>(P, T, v[u], d[u], ss[u], lt[u], lb, &off[u], &skip);
+        amb[u] = lt[u] & ~(cnt[u] | skip);
+        if constexpr (MASKED) {
+            const uint32_t h = ts + o + (uint32_t)u;
+            const uint64_t act = __builtin_amdgcn_ballot_w64(!lmask | (lj > h) | ((P.selfx != 0) & (lj < h)));
+            cnt[u] &= act;
+            amb[u] &= act;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        uint64_t w = lw;
+        if constexpr (WT) {
+            // (rows past the tile's end are never counted)
+            const cu32p wa = (cu32p)(const void*)P.wA;
+            const uint32_t i = ts + o + (uint32_t)u;
+            w *= wa[i < te ? i : te - 1u];
+        }
+        if (in_mask(cnt[u])) lds_add<kH32<MODE>>(off[u], w);
+    }
+    if ((amb[0] | amb[1] | amb[2] | amb[3]) != 0ull) {
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            // pairs below the first edge are clean (out_lo < 0 without one)
+            if (amb[u] == 0ull) continue;
+            uint64_t m = amb[u];
+            if constexpr (MODE != M_SIGMAPI) {
+                m &= ~__builtin_amdgcn_ballot_w64(v[u] < P.out_lo);
+            } else if (P.sp_low) {
+                const float ll = ss[u] - v[u], sl2 = d[u] * d[u], c2 = fmaf(v[u], ll, -sl2);
+                m &= ~(__builtin_amdgcn_ballot_w64(fmaf(P.sp_wsbot, ll, c2) <= -T.mt) |
+                       __builtin_amdgcn_ballot_w64(fmaf(P.sp_wpbot, ll, sl2) <= -T.mt));
+            }
+            const uint32_t pos = lanes_below(m, W.nlist);
+            if (in_mask(m)) W.list[pos] = (uint16_t)(((o + (uint32_t)u) << 6) | (uint32_t)lane);
+            W.nlist += (uint32_t)__popcll(m);
+        }
+    }
+}
+
+// Move the listed pairs of the chunk at hand (neighbour lj, image lcode in
+// each lane) to the re-test queue, draining it whenever 64 are waiting.
+template <int MODE, int EST>
+__device__ __forceinline__ void queue_list(const CountArgs& P, WaveState& W, const float2* B1,
+                                           const float2* B2, const double* T1, const double* T2,
+                                           int lane, uint32_t ts, uint32_t lj, uint32_t lcode) {
+    wave_lds_fence();
+    for (uint32_t i = 0; i < W.nlist; i += 64u) {
+        const uint32_t n = W.nlist - i < 64u ? W.nlist - i : 64u;
+        const uint32_t e = (uint32_t)lane < n ? (uint32_t)W.list[i + (uint32_t)lane] : 0u;
+        const uint32_t j = (uint32_t)__shfl((int)lj, (int)(e & 63u));
+        const uint32_t c = (uint32_t)__shfl((int)lcode, (int)(e & 63u));
+        if ((uint32_t)lane < n) {
+            const uint32_t pos = W.tail + (uint32_t)lane;
+            W.qi[pos] = ts + (e >> 6);
+            W.qj[pos] = j;
+            W.qc[pos] = (uint8_t)c;
+        }
+        W.tail += n;
+        wave_lds_fence();
+        if (W.tail >= 64u)
+            W.tail = drain_queue<MODE, EST>(P.self, W.hist, W.qi, W.qj, W.qc, W.rstat, B1, B2, T1, T2,
+                                            lane, W.tail, false);
+    }
+    W.nlist = 0;
+}
+
 // Radial pairs (Sec. 2.1, radial 2PCF; Sec. 3.4): inside the aperture when
 // the chord^2 of the unit vectors is below ap2, then binned by the redshift
 // difference |r_i - r_j| against the unsquared edges T1 (half-open).
@@ -871,9 +1292,107 @@ struct Chunk {
     bool lmask;        // per lane: j > i test applies
 };
 
+// A chunk against the tile's staged home points. q: the lanes' neighbours in
+// FP32, loaded a chunk ahead. The separations of a step are formed while the
+// step before it is decided, so that their chain of dependent instructions
+// does not wait in the open.
+template <int MODE, int EST, bool PM, bool WT>
+__device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W, const Tab32& T,
+                                               const float2* B1, const float2* B2, const double* T1,
+                                               const double* T2, int lane, const Chunk& C,
+                                               const float4& p, uint32_t ts, uint32_t te) {
+    if constexpr (kH32<MODE>) {
+        // every pair of the chunk adds at most the largest region weight
+        const uint32_t wmax = P.regs == nullptr ? 1u : (P.wsame > P.wdiff ? P.wsame : P.wdiff);
+        h32_account(P, W, lane, C.filled * (te - ts) * wmax);
+    }
+    bool ok = (uint32_t)lane < C.filled;
+    // a neighbour excluded by the point mask leaves its lane idle
+    if (PM && P.mbB != nullptr && ok) ok = ((P.mbB[C.lj >> 5] >> (C.lj & 31u)) & 1u) == 0u;
+    uint32_t lw = 1u;
+    if constexpr (WT) lw = ok ? P.wB[C.lj] : 1u;
+    else if (P.regs != nullptr) lw = ok ? pair_weight(P, C.lj) : 1u;
+    // the neighbour in the home grid's FP32 frame (q - (cA - cB) for two open
+    // grids, or its periodic image q + k L: only one of the two is ever
+    // non-zero), then in the tile's
+    float kx = P.offx, ky = P.offy, kz = P.offz;
+    if (C.shifted) {
+        const float Lf = (float)P.L;
+        kx -= shift32(C.lcode, 0, Lf);
+        ky -= shift32(C.lcode, 1, Lf);
+        kz -= shift32(C.lcode, 2, Lf);
+    }
+    Column q;
+    q.bx = ok ? (p.x - kx) - W.ox : 0.f;
+    q.by = ok ? (p.y - ky) - W.oy : 0.f;
+    q.bz = ok ? (p.z - kz) - W.oz : 0.f;
+    const double b2d = sq64(q.bx, q.by, q.bz);
+    const float b2 = ok ? (float)b2d : kFar;
+    q.b2 = f4v{b2, b2, b2, b2};
+    if constexpr (kMid<MODE>) {
+        const double beta = dot64(W.lx, W.ly, W.lz, q.bx, q.by, q.bz) + b2d;
+        const float nb = (float)-beta, be = (float)fma(2.0, beta, sq64(W.lx, W.ly, W.lz));
+        q.nbeta = f4v{nb, nb, nb, nb};
+        q.beta2 = f4v{be, be, be, be};
+    } else {
+        q.nbz = f4v{-q.bz, -q.bz, -q.bz, -q.bz};
+    }
+    // this lane's histogram copy
+    const uint32_t lb = decide_base<MODE, EST>(
+        P, lds_addr(W.hist) + ((uint32_t)lane & (uint32_t)(P.copies - 1)) * (kH32<MODE> ? 4u : 8u));
+    const uint32_t n = te - ts;
+    uint32_t o = 0;
+#define CUTE_STEP(K)                                                                               \
+    {                                                                                              \
+        const f4v w = sep_mfma<(K + 1) & 3>(K == 3 ? an : a, q);                                   \
+        step_mfma<MODE, EST, WT, false, K>(P, W, T, a, al, v, q, false, 0u, lb, lw, lane, ts, te, o); \
+        v = w;                                                                                     \
+        o += 4u;                                                                                   \
+        if (o >= n || W.nlist > kList - 256u) break;                                               \
+    }
+    while (o < n) {
+        if (!C.masked && (o & 15u) == 0u) {
+            // Sixteen home points per read of the stage: the wait for a read
+            // is also one for the histogram adds before it (one counter, in
+            // order), and with a read per step it stood open in every step.
+            const float4* row = W.stage + (lane & 15);
+            const float* arow = W.alpha + (lane & 15);
+            float4 a = row[o];
+            float al = kMid<MODE> ? arow[o] : 0.f;
+            f4v v = sep_mfma<0>(a, q);
+            for (;;) {
+                const float4 an = row[(o + 16u) & 48u];
+                const float aln = kMid<MODE> ? arow[(o + 16u) & 48u] : 0.f;
+                CUTE_STEP(0)
+                CUTE_STEP(1)
+                CUTE_STEP(2)
+                CUTE_STEP(3)
+                a = an;
+                al = aln;
+            }
+        } else {
+            // chunks with the index test, and what is left of sixteen home
+            // points after the list was moved
+            const float4* row = W.stage + (lane & 3);
+            do {
+                const float4 a = row[o];
+                const float al = kMid<MODE> ? W.alpha[o + (uint32_t)(lane & 3)] : 0.f;
+                step_mfma<MODE, EST, WT, true, -1>(P, W, T, a, al, sep_mfma<-1>(a, q), q, C.lmask,
+                                                   C.lj, lb, lw, lane, ts, te, o);
+                o += 4u;
+            } while (o < n && W.nlist <= kList - 256u && (C.masked || (o & 15u) != 0u));
+        }
+        // a step adds at most 256 pairs to the list: it is moved to the queue
+        // when it could not take another step's, and at the chunk's end
+        if (W.nlist > kList - 256u || (o >= n && W.nlist != 0u))
+            queue_list<MODE, EST>(P, W, B1, B2, T1, T2, lane, ts, C.lj, C.lcode);
+    }
+#undef CUTE_STEP
+}
+
 template <int MODE, int PREC, int EST, bool PM, bool WT>
 __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, const float2* B2,
-                          const double* T1, const double* T2, int lane, Chunk& C, uint32_t ts,
+                          const double* T1, const double* T2, int lane, const Chunk& C, uint32_t ts,
                           uint32_t te) {
     constexpr uint32_t U = 4;
     if constexpr (kH32<MODE>) {
@@ -932,6 +1451,11 @@ __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, co
             qly = qy + P.lcy;
             qlz = qz + P.lcz;
         }
+        // ambiguous pairs of this chunk: per lane, bit (home - ts); per wave,
+        // the home offsets with any (queued once the home loop is done)
+        uint64_t ambh = 0, hsum = 0;
+        // bins starting at zero separation have no low-side clean "out"
+        const bool low = MODE == M_SIGMAPI ? P.sp_low != 0 : !(P.out_lo < 0.0f);
 #define CUTE_RUN32(MSK, LOW)                                                                     \
     {                                                                                              \
         uint32_t h = ts;                                                                           \
@@ -944,11 +1468,6 @@ __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, co
                                                      C.lmask, C.lj, C.lcode, qx, qy, qz, qlx, qly, \
                                                      qlz, lb, lw, ts, ambh, hsum, h);              \
     }
-        // ambiguous pairs of this chunk: per lane, bit (home - ts); per wave,
-        // the home offsets with any (queued once the home loop is done)
-        uint64_t ambh = 0, hsum = 0;
-        // bins starting at zero separation have no low-side clean "out"
-        const bool low = MODE == M_SIGMAPI ? P.sp_low != 0 : !(P.out_lo < 0.0f);
         if (C.masked) {
             if (low) CUTE_RUN32(true, true) else CUTE_RUN32(true, false)
         } else {
@@ -959,42 +1478,6 @@ __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, co
                                               T2, lane, W.tail, ts, C.lj, C.lcode, ambh, hsum);
 #undef CUTE_RUN32
     }
-    C.filled = 0;
-    C.masked = false;
-    C.shifted = false;
-}
-
-// Append the neighbour span [a0, a1) (image code, j > i test) to the chunk,
-// running every chunk that fills up.
-template <int MODE, int PREC, int EST, bool PM, bool WT>
-__device__ void feed(const CountArgs& P, WaveState& W, const float2* B1, const float2* B2,
-                     const double* T1, const double* T2, int lane, Chunk& C, uint32_t ts,
-                     uint32_t te, uint32_t a0, uint32_t a1, uint32_t code, bool masked) {
-    if (masked && a1 > a0 && P.selfx) {
-        // the tile against itself: every pair but the point with itself
-        W.evals += (uint64_t)(te - ts) * (a1 - a0) - (a1 - a0);
-    } else if (masked && a1 > a0) {
-        // lanes with neighbour j pair with the home points h < j: sum of (j - ts)
-        const uint64_t lo_ = a0 - ts, hi_ = a1 - 1u - ts;
-        W.evals += (lo_ + hi_) * (hi_ - lo_ + 1u) / 2u;
-    } else if (a1 > a0) {
-        W.evals += (uint64_t)(te - ts) * (a1 - a0);
-    }
-    while (a0 < a1) {
-        const uint32_t room = 64u - C.filled;
-        const uint32_t take = (a1 - a0) < room ? (a1 - a0) : room;
-        const uint32_t l = (uint32_t)lane;
-        if (l >= C.filled && l < C.filled + take) {
-            C.lj = a0 + (l - C.filled);
-            C.lcode = code;
-            C.lmask = masked;
-        }
-        C.filled += take;
-        C.masked = C.masked | masked;
-        C.shifted = C.shifted | (code != kNoShift);
-        a0 += take;
-        if (C.filled == 64u) run_chunk<MODE, PREC, EST, PM, WT>(P, W, B1, B2, T1, T2, lane, C, ts, te);
-    }
 }
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
@@ -1003,12 +1486,27 @@ __device__ __forceinline__ int imod(int a, int n) {
     return r < 0 ? r + n : r;
 }
 
-// Span list of one batch of stencil rows, in LDS.
+// Span list of one batch of stencil rows (in LDS) and where the walk over a
+// tile's neighbours stands (wave-uniform).
 struct SpanBuf {
     uint32_t* a;   // first neighbour index
     uint32_t* b;   // one past the last
-    uint32_t* f;   // image code (low 8 bits) | j > i test (bit 8)
+    uint8_t* f;    // image code | kSelfSpan
+    int nrows, row0;            // rows of the stencil, first row not taken yet
+    uint32_t n, k, skip, left;  // spans of the batch, next one, points to pass over, to take
+    uint32_t p0, p1, pf;        // the span at hand: its points not taken yet, its code
 };
+constexpr uint32_t kSelfSpan = 0x80u;   // the j > i test applies
+
+__device__ __forceinline__ SpanBuf span_buf(const WgLds& l, int wave) {
+    SpanBuf S;
+    S.a = l.spans + (size_t)wave * 2 * kSpanCap;
+    S.b = S.a + kSpanCap;
+    S.f = l.scodes + (size_t)wave * kSpanCap;
+    S.nrows = S.row0 = 0;
+    S.n = S.k = S.skip = S.left = S.p0 = S.p1 = S.pf = 0u;
+    return S;
+}
 
 // The stencil of one tile (Sec. 3.3: the rows of cells within r_max of it),
 // wave-uniform: how many rows to look at, and what the rows of each kind of
@@ -1025,6 +1523,9 @@ struct TileStencil {
     double xlo, xhi, ylo, yhi, zlo, zhi;
 };
 
+// SPH: spherical grids (their kernels hold no code of the boxes, and the
+// other way round: the trigonometry alone set the registers of every kernel)
+template <bool SPH>
 __device__ __forceinline__ TileStencil tile_stencil(const CountArgs& P, const Tile& tl) {
     const GridView& A = P.A;
     const GridView& B = P.B;
@@ -1038,31 +1539,20 @@ __device__ __forceinline__ TileStencil tile_stencil(const CountArgs& P, const Ti
     t.nrows = t.b0 = t.x0 = t.x1 = t.y0 = t.z0 = t.nyr = 0;
     t.full = false;
     t.xlo = t.xhi = t.ylo = t.yhi = t.zlo = t.zhi = 0.0;
-    if (P.geom == CUTE_GEOM_SPHERE) {
-        // tile pixel block: phi in [c0, c1+1) * ax, cos theta in one band
-        const double zlo = A.oy + t.cy * A.ay, zhi = zlo + A.ay;
-        const double zl = fmax(-1.0, fmin(1.0, zlo)), zh = fmax(-1.0, fmin(1.0, zhi));
-        const double th_lo = acos(zh), th_hi = acos(zl);
-        const double ths = P.th_s;
-        const double zn_hi = (th_lo - ths <= 0.0) ? 1.0 : cos(th_lo - ths);
-        const double zn_lo = (th_hi + ths >= kPi) ? -1.0 : cos(th_hi + ths);
-        int b0 = (int)floor((zn_lo - B.oy) / B.ay) - 1, b1 = (int)floor((zn_hi - B.oy) / B.ay) + 1;
-        b0 = clampi(b0, 0, B.ny - 1);
-        b1 = clampi(b1, 0, B.ny - 1);
+    if constexpr (SPH) {
+        // tile pixel block: phi in [c0, c1+1) * ax, cos theta in one band; the
+        // band's reach (first and last band, half-width in phi, negative for
+        // whole rings) comes from the host's table
+        const cu32p st = (cu32p)(const void*)P.stencil + 4 * (size_t)t.cy;
+        const int b0 = (int)uni(st[0]), b1 = (int)uni(st[1]);
+        const double hw = __hiloint2double((int)uni(st[3]), (int)uni(st[2]));
         // an autocorrelation takes its own band and the ones after it
-        if (P.is_auto && b0 < t.cy) b0 = t.cy;
-        // half-width in phi of a cap of radius th_s around any tile point:
-        // asin(sin th_s / sin theta) at the tile colatitude nearest a pole
-        const double zmax2 = fmax(zl * zl, zh * zh);
-        const double smin = sqrt(fmax(0.0, 1.0 - zmax2));
-        bool full = !(P.sin_th_s < smin * (1.0 - 1e-9)) || (P.th_s >= 0.5 * kPi);
-        const double hw = full ? 0.0 : asin(P.sin_th_s / smin) * (1.0 + 1e-9) + 1e-12;
+        t.b0 = P.is_auto && b0 < t.cy ? t.cy : b0;
         const double phlo = t.c0 * A.ax - hw, phhi = (t.c1 + 1) * A.ax + hw;
         t.x0 = unii((int)floor(phlo / B.ax) - 1);
         t.x1 = unii((int)floor(phhi / B.ax) + 1);
-        t.full = unii((full || t.x1 - t.x0 + 1 >= B.nx) ? 1 : 0) != 0;
-        t.b0 = unii(b0);
-        t.nrows = unii(b1) - t.b0 + 1;
+        t.full = unii((hw < 0.0 || t.x1 - t.x0 + 1 >= B.nx) ? 1 : 0) != 0;
+        t.nrows = b1 - t.b0 + 1;
     } else if (P.stencil != nullptr) {
         t.nrows = P.nst;
     } else {
@@ -1102,6 +1592,7 @@ struct RowSpans {
 };
 
 // Row e of the tile's stencil, e < t.nrows (any lane value).
+template <bool SPH>
 __device__ __forceinline__ RowSpans row_spans(const CountArgs& P, const TileStencil& t, int e) {
     const GridView& B = P.B;
     RowSpans r;
@@ -1114,7 +1605,7 @@ __device__ __forceinline__ RowSpans row_spans(const CountArgs& P, const TileSten
     bool same = false;   // the tile's own row of an autocorrelation
     bool home = false;   // the tile's own row of a full stencil over one catalog
     int kxa = 0, kxb = 0, ky = 0, kz = 0;
-    if (P.geom == CUTE_GEOM_SPHERE) {
+    if constexpr (SPH) {
         const int by = t.b0 + e;
         rb = (uint32_t)by * (uint32_t)B.nx;
         same = P.is_auto && by == t.cy;
@@ -1214,9 +1705,9 @@ __device__ __forceinline__ RowSpans row_spans(const CountArgs& P, const TileSten
         r.b0 = cs[rb + (uint32_t)qa];
         r.b1 = cs[rb + (uint32_t)qb + 1u];
     }
+    // (no images on the sphere: kx, ky and kz are 0)
     r.ca = (uint32_t)(kxa + 1) | ((uint32_t)(ky + 1) << 2) | ((uint32_t)(kz + 1) << 4);
     r.cb = (uint32_t)(kxb + 1) | ((uint32_t)(ky + 1) << 2) | ((uint32_t)(kz + 1) << 4);
-    if (P.geom == CUTE_GEOM_SPHERE) r.ca = r.cb = kNoShift;
     if (same) {
         // points of the first cell before the tile pair with it from their
         // own tile; the tile's points pair among themselves (j > i) and with
@@ -1241,13 +1732,6 @@ __device__ __forceinline__ RowSpans row_spans(const CountArgs& P, const TileSten
     return r;
 }
 
-__device__ __forceinline__ uint32_t lane_u32(uint32_t v, int l) {
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
-}
-// number of lower lanes set in a mask
-__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane) {
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -1257,12 +1741,147 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane) {
     return v;
 }
 
-// Count the pairs of one home tile, or one of its 2^plog parts. The stencil
-// rows are taken 64 at a time, one per lane (a serial walk of the rows spent
-// more time on dependent loads than the pairs of a small tile take); their
-// spans go to LDS in row order and are fed chunk by chunk to the hot loop. A
-// part is a run of whole chunks of the concatenated neighbours of each batch
-// of rows, so the parts of a tile share out its chunks evenly.
+// The spans of the next kRowBatch stencil rows of a tile, one row per lane (a serial
+// walk of the rows spent more time on dependent loads than the pairs of a
+// small tile take), compacted to LDS in row order. Of their concatenated
+// neighbours a part takes a run of whole chunks, so that the parts of a tile
+// share out its chunks evenly.
+template <bool SPH>
+__device__ __forceinline__ void next_rows(const CountArgs& Pk, SpanBuf& S, const Tile& tl, int lane,
+                                          uint32_t part, uint32_t plog) {
+    // the stencil again for every batch of rows, from the arguments' copy in
+    // memory: nothing of it is live while pairs are evaluated (the asm keeps
+    // the compiler from loading or deriving it ahead of the walk, where it
+    // would fill the registers of the pair loop)
+    const CountArgs& P = args_again(Pk);
+    Tile tb = tl;
+    tb.row = uni(tb.row);
+    asm volatile("" : "+s"(tb.row));
+    const TileStencil t = tile_stencil<SPH>(P, tb);
+    S.nrows = t.nrows;
+    RowSpans r;
+    r.a0 = r.a1 = r.b0 = r.b1 = r.m1 = r.h0 = r.h1 = 0u;
+    r.ca = r.cb = kNoShift;
+    if (lane < kRowBatch && S.row0 + lane < t.nrows) r = row_spans<SPH>(P, t, S.row0 + lane);
+    S.row0 += kRowBatch;
+    S.left = 0u;
+    const uint32_t na = r.a1 > r.a0 ? r.a1 - r.a0 : 0u, nb = r.b1 > r.b0 ? r.b1 - r.b0 : 0u;
+    // the tile's own spans, from the lane that holds its row
+    const uint64_t mh = __builtin_amdgcn_ballot_w64(r.m1 != 0u);
+    uint32_t m1 = 0u, h0 = 0u, h1 = 0u;
+    if (mh != 0ull) {
+        const int l = __builtin_ctzll(mh);
+        m1 = lane_u32(r.m1, l);
+        h0 = lane_u32(r.h0, l);
+        h1 = lane_u32(r.h1, l);
+    }
+    const uint32_t nm = m1 > t.ts ? m1 - t.ts : 0u, nh = h1 > h0 ? h1 - h0 : 0u;
+    const uint32_t own = nm + nh, nown = (nm ? 1u : 0u) + (nh ? 1u : 0u);
+    const uint32_t end = own + wave_incl_scan(na + nb, lane);
+    const uint32_t total = lane_u32(end, 63);
+    // this part's chunks
+    const uint32_t nc = (total + 63u) >> 6;
+    const uint32_t c0 = (uint32_t)(((uint64_t)nc * part) >> plog);
+    const uint32_t c1 = (uint32_t)(((uint64_t)nc * (part + 1u)) >> plog);
+    if (c0 >= c1) return;
+    const uint32_t v0 = c0 << 6, v1 = (c1 << 6) < total ? c1 << 6 : total;
+    S.left = v1 - v0;
+    const uint64_t ma = __builtin_amdgcn_ballot_w64(na != 0u);
+    const uint64_t mb = __builtin_amdgcn_ballot_w64(nb != 0u);
+    const uint32_t pos = nown + lanes_below(ma) + lanes_below(mb);
+    S.n = nown + (uint32_t)(__popcll(ma) + __popcll(mb));
+    wave_lds_fence();
+    if (lane == 0) {
+        if (nm) {
+            S.a[0] = t.ts;
+            S.b[0] = m1;
+            S.f[0] = (uint8_t)(kNoShift | kSelfSpan);
+        }
+        if (nh) {
+            S.a[nown - 1u] = h0;
+            S.b[nown - 1u] = h1;
+            S.f[nown - 1u] = (uint8_t)kNoShift;
+        }
+    }
+    if (na) {
+        S.a[pos] = r.a0;
+        S.b[pos] = r.a1;
+        S.f[pos] = (uint8_t)r.ca;
+    }
+    if (nb) {
+        const uint32_t q = pos + (na ? 1u : 0u);
+        S.a[q] = r.b0;
+        S.b[q] = r.b1;
+        S.f[q] = (uint8_t)r.cb;
+    }
+    // the span that holds neighbour v0 of the concatenation
+    S.k = 0u;
+    S.skip = v0;
+    if (v0 >= own && v0 > 0u) {
+        const int l = (int)__popcll(__builtin_amdgcn_ballot_w64(end <= v0));
+        S.k = lane_u32(pos, l);
+        S.skip = v0 - (lane_u32(end, l) - lane_u32(na + nb, l));
+    }
+    wave_lds_fence();
+}
+
+// Assemble the next chunk of the walk over a tile's neighbours (filled = 0 at
+// its end), and account its pair evaluations.
+template <bool SPH>
+__device__ __forceinline__ void next_chunk(const CountArgs& P, WaveState& W, SpanBuf& S, Chunk& C,
+                                           const Tile& tl, int lane, uint32_t part, uint32_t plog) {
+    const uint32_t ts = tl.start, te = tl.end, l = (uint32_t)lane;
+    C.filled = 0;
+    C.masked = false;
+    C.shifted = false;
+    while (C.filled < 64u) {
+        if (S.p0 < S.p1) {
+            const uint32_t room = 64u - C.filled;
+            const uint32_t take = S.p1 - S.p0 < room ? S.p1 - S.p0 : room;
+            const bool masked = (S.pf & kSelfSpan) != 0u;
+            const uint32_t code = S.pf & 0x3fu;
+            if (masked && P.selfx) {
+                // the tile against itself: every pair but the point with itself
+                W.evals += (uint64_t)(te - ts) * take - take;
+            } else if (masked) {
+                // lanes with neighbour j pair with the home points h < j: sum of (j - ts)
+                const uint64_t lo_ = S.p0 - ts, hi_ = S.p0 + take - 1u - ts;
+                W.evals += (lo_ + hi_) * (hi_ - lo_ + 1u) / 2u;
+            } else {
+                W.evals += (uint64_t)(te - ts) * take;
+            }
+            if (l >= C.filled) {   // (the lanes past the span are set again, or not used)
+                C.lj = S.p0 + (l - C.filled);
+                C.lcode = code;
+                C.lmask = masked;
+            }
+            C.filled += take;
+            C.masked = C.masked | masked;
+            C.shifted = C.shifted | (code != kNoShift);
+            S.p0 += take;
+        } else if (S.left > 0u && S.k < S.n) {
+            uint32_t a0 = uni(S.a[S.k]), a1 = uni(S.b[S.k]);
+            S.pf = uni((uint32_t)S.f[S.k]);
+            S.k++;
+            if (S.skip >= a1 - a0) {
+                S.skip -= a1 - a0;
+                continue;
+            }
+            a0 += S.skip;
+            S.skip = 0u;
+            if (a1 - a0 > S.left) a1 = a0 + S.left;
+            S.left -= a1 - a0;
+            S.p0 = a0;
+            S.p1 = a1;
+        } else if (S.row0 < S.nrows) {
+            next_rows<SPH>(P, S, tl, lane, part, plog);
+        } else {
+            break;
+        }
+    }
+}
+
+// Count the pairs of one home tile, or one of its 2^plog parts.
 template <int MODE, int PREC, int EST, bool PM, bool WT>
 __device__ void do_tile(const CountArgs& P, WaveState& W, SpanBuf& S, const float2* B1,
                         const float2* B2, const double* T1, const double* T2, int lane,
@@ -1274,106 +1893,44 @@ __device__ void do_tile(const CountArgs& P, WaveState& W, SpanBuf& S, const floa
         const bool live = i < tl.end && ((P.mbA[i >> 5] >> (i & 31u)) & 1u) == 0u;
         if (__builtin_amdgcn_ballot_w64(live) == 0ull) return;
     }
+    S.row0 = 0;
+    S.nrows = 1;
+    S.n = S.k = S.skip = S.left = S.p0 = S.p1 = 0u;
     Chunk C;
-    C.filled = 0;
-    C.masked = false;
-    C.shifted = false;
     C.lj = 0;
     C.lcode = kNoShift;
     C.lmask = false;
-    int nrows = 1;
-    for (int row0 = 0; row0 < nrows; row0 += 64) {
-        uint32_t nspan, k, skip, left;
-        {
-            // the stencil again for every batch of rows: its temporaries are
-            // dead while pairs are evaluated (the asm keeps the compiler from
-            // holding them across the loop)
-            Tile tb = tl;
-            asm volatile("" : "+s"(tb.row));
-            const TileStencil t = tile_stencil(P, tb);
-            nrows = t.nrows;
-            RowSpans r;
-            r.a0 = r.a1 = r.b0 = r.b1 = r.m1 = r.h0 = r.h1 = 0u;
-            r.ca = r.cb = kNoShift;
-            if (row0 + lane < t.nrows) r = row_spans(P, t, row0 + lane);
-            const uint32_t na = r.a1 > r.a0 ? r.a1 - r.a0 : 0u, nb = r.b1 > r.b0 ? r.b1 - r.b0 : 0u;
-            // the tile's own spans, from the lane that holds its row
-            const uint64_t mh = __builtin_amdgcn_ballot_w64(r.m1 != 0u);
-            uint32_t m1 = 0u, h0 = 0u, h1 = 0u;
-            if (mh != 0ull) {
-                const int l = __builtin_ctzll(mh);
-                m1 = lane_u32(r.m1, l);
-                h0 = lane_u32(r.h0, l);
-                h1 = lane_u32(r.h1, l);
-            }
-            const uint32_t nm = m1 > t.ts ? m1 - t.ts : 0u, nh = h1 > h0 ? h1 - h0 : 0u;
-            const uint32_t own = nm + nh, nown = (nm ? 1u : 0u) + (nh ? 1u : 0u);
-            const uint32_t end = own + wave_incl_scan(na + nb, lane);
-            const uint32_t total = lane_u32(end, 63);
-            // this part's chunks
-            const uint32_t nc = (total + 63u) >> 6;
-            const uint32_t c0 = (uint32_t)(((uint64_t)nc * part) >> plog);
-            const uint32_t c1 = (uint32_t)(((uint64_t)nc * (part + 1u)) >> plog);
-            if (c0 >= c1) continue;
-            const uint32_t v0 = c0 << 6, v1 = (c1 << 6) < total ? c1 << 6 : total;
-            left = v1 - v0;
-            const uint64_t ma = __builtin_amdgcn_ballot_w64(na != 0u);
-            const uint64_t mb = __builtin_amdgcn_ballot_w64(nb != 0u);
-            const uint32_t pos = nown + lanes_below(ma) + lanes_below(mb);
-            nspan = nown + (uint32_t)(__popcll(ma) + __popcll(mb));
-            if (lane == 0) {
-                if (nm) {
-                    S.a[0] = t.ts;
-                    S.b[0] = m1;
-                    S.f[0] = kNoShift | 0x100u;
-                }
-                if (nh) {
-                    S.a[nown - 1u] = h0;
-                    S.b[nown - 1u] = h1;
-                    S.f[nown - 1u] = kNoShift;
-                }
-            }
-            if (na) {
-                S.a[pos] = r.a0;
-                S.b[pos] = r.a1;
-                S.f[pos] = r.ca;
-            }
-            if (nb) {
-                const uint32_t q = pos + (na ? 1u : 0u);
-                S.a[q] = r.b0;
-                S.b[q] = r.b1;
-                S.f[q] = r.cb;
-            }
-            // the span that holds neighbour v0 of the concatenation
-            k = 0u;
-            skip = v0;
-            if (v0 >= own && v0 > 0u) {
-                const int l = (int)__popcll(__builtin_amdgcn_ballot_w64(end <= v0));
-                k = lane_u32(pos, l);
-                skip = v0 - (lane_u32(end, l) - lane_u32(na + nb, l));
-            }
+    if constexpr (kMfma<MODE, PREC, EST>) {
+        stage_home<MODE, PM>(P, W, tl, lane);
+        Tab32 tab = make_tab32<EST>(P, B1, B2);
+        if constexpr (MODE == M_SIGMAPI) tab.mt = W.mt;
+        if constexpr (MODE == M_RMU_MID) {
+            tab.d0 = W.mb0;
+            tab.d1 = W.mb1;
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (; left > 0u && k < nspan; k++) {
-            uint32_t a0 = uni(S.a[k]), a1 = uni(S.b[k]);
-            const uint32_t f = uni(S.f[k]);
-            const uint32_t len = a1 - a0;
-            if (skip >= len) {
-                skip -= len;
-                continue;
-            }
-            a0 += skip;
-            skip = 0u;
-            if (a1 - a0 > left) a1 = a0 + left;
-            left -= a1 - a0;
-            feed<MODE, PREC, EST, PM, WT>(P, W, B1, B2, T1, T2, lane, C, tl.start, tl.end, a0, a1,
-                                  f & 0xffu, (f & 0x100u) != 0u);
+        // the neighbours of a chunk are loaded while the one before it is
+        // counted
+        Chunk N = C;
+        N.filled = 0u;
+        float4 pn = make_float4(0.f, 0.f, 0.f, 0.f);
+        do {
+            C = N;
+            const float4 p = pn;
+            next_chunk<kSphere<MODE>>(P, W, S, N, tl, lane, part, plog);
+            if ((uint32_t)lane < N.filled) pn = P.B.p32[N.lj];
+            if (C.filled == 0u) continue;
+            if (MODE == M_RMU_MID && W.mt < 0.f)
+                run_chunk<MODE, P_FP64, EST & E_LOG, PM, WT>(P, W, B1, B2, T1, T2, lane, C, tl.start, tl.end);
+            else
+                run_chunk_mfma<MODE, EST, PM, WT>(P, W, tab, B1, B2, T1, T2, lane, C, p, tl.start, tl.end);
+        } while (N.filled != 0u);
+    } else {
+        for (;;) {
+            next_chunk<kSphere<MODE>>(P, W, S, C, tl, lane, part, plog);
+            if (C.filled == 0u) break;
+            run_chunk<MODE, PREC, EST, PM, WT>(P, W, B1, B2, T1, T2, lane, C, tl.start, tl.end);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
     }
-    if (C.filled) run_chunk<MODE, PREC, EST, PM, WT>(P, W, B1, B2, T1, T2, lane, C, tl.start, tl.end);
 }
 
 

@@ -38,45 +38,29 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count(CountArgs
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int nwaves = blockDim.x >> 6;
-    const int n1 = P.n1, n2 = P.n2;
-    const int n2p = n2 > 0 ? n2 : 0;
-    double* T1 = reinterpret_cast<double*>(smem);
-    double* T2 = T1 + (n1 + 1);
-    float2* B1 = reinterpret_cast<float2*>(T2 + (n2p + 1));
-    float2* B2 = B1 + n1;
+    const int n1 = P.n1;
+    const int n2p = P.n2 > 0 ? P.n2 : 0;
     constexpr bool H32 = kH32<MODE>;
-    // the histogram: hist_words counters of 4 (kH32) or 8 bytes, padded to 8
-    unsigned char* hist0 = reinterpret_cast<unsigned char*>(B2 + (n2p > 0 ? n2p : 1));
-    const size_t hbytes = ((size_t)P.hist_words * (H32 ? 4 : 8) + 7) & ~(size_t)7;
-    uint32_t* q0 = reinterpret_cast<uint32_t*>(hist0 + hbytes);
-    unsigned long long* rs0 = reinterpret_cast<unsigned long long*>(q0 + (size_t)nwaves * 3 * kQCap);
-    uint32_t* sp0 = reinterpret_cast<uint32_t*>(rs0 + 2 * nwaves);
-    uint32_t* budget = sp0 + (size_t)nwaves * 3 * kSpanCap;  // 32-bit histograms only
+    const WgLds L = wg_lds<H32, kMfma<MODE, PREC, EST>>(smem, nwaves, n1, P.n2, P.hist_words);
+    double *T1 = L.T1, *T2 = L.T2;
+    float2 *B1 = L.B1, *B2 = L.B2;
+    unsigned char* hist0 = L.hist;
     for (int i = threadIdx.x; i <= n1; i += blockDim.x) T1[i] = P.T1[i];
     for (int i = threadIdx.x; i <= n2p; i += blockDim.x) T2[i] = n2p ? P.T2[i] : 0.0;
     if (PREC != P_FP64) {
-        for (int i = threadIdx.x; i < n1; i += blockDim.x) B1[i] = P.band1[i];
-        for (int i = threadIdx.x; i < n2p; i += blockDim.x) B2[i] = P.band2[i];
+        // (sigma-pi from the matrix cores: one entry past the last bin)
+        constexpr int more = kMfma<MODE, PREC, EST> && MODE == M_SIGMAPI ? 1 : 0;
+        for (int i = threadIdx.x; i < n1 + more; i += blockDim.x) B1[i] = P.band1[i];
+        for (int i = threadIdx.x; i < n2p + more; i += blockDim.x) B2[i] = P.band2[i];
     }
-    for (size_t i = threadIdx.x; i < hbytes / 4; i += blockDim.x) reinterpret_cast<uint32_t*>(hist0)[i] = 0u;
-    for (int i = threadIdx.x; i < 2 * nwaves; i += blockDim.x) rs0[i] = 0ull;
-    if (H32 && threadIdx.x == 0) *budget = 0u;
+    for (size_t i = threadIdx.x; i < L.hbytes / 4; i += blockDim.x) reinterpret_cast<uint32_t*>(hist0)[i] = 0u;
+    for (int i = threadIdx.x; i < 2 * nwaves; i += blockDim.x) L.rstat[i] = 0ull;
+    if (H32 && threadIdx.x == 0) L.ctl[0] = 0u;
     __syncthreads();
 
-    WaveState W;
-    W.hist = hist0;
-    W.budget = budget;
-    W.pend = 0;
-    W.qi = q0 + (size_t)wave * 3 * kQCap;
-    W.qj = W.qi + kQCap;
-    W.qc = W.qj + kQCap;
-    W.rstat = rs0 + 2 * wave;
-    W.tail = 0;
-    W.evals = W.tiles = 0;
-    SpanBuf S;
-    S.a = sp0 + (size_t)wave * 3 * kSpanCap;
-    S.b = S.a + kSpanCap;
-    S.f = S.b + kSpanCap;
+    WaveState W = wave_state(L, wave);
+    W.budget = L.ctl;   // 32-bit histograms only
+    SpanBuf S = span_buf(L, wave);
 
     // tasks: the parts of the tiles. Every wave starts with the task of its
     // own number, so that a launch of no more tasks than waves pops none; an
@@ -173,7 +157,7 @@ cute_status launch_est(const CountArgs& a, int est, int wg_waves, size_t lds, hi
             return fail(CUTE_E_UNSUPPORTED, "weighted pairs need a THETA binning");
         }
     }
-    if constexpr (MODE == M_RMU_Z && PREC == P_FP32E) {
+    if constexpr ((MODE == M_RMU_Z || MODE == M_RMU_MID) && PREC == P_FP32E) {
         // the mu decision in mu space (FP32_EDGE only)
         if (est == (E_LOG | E_MUF)) return launch_one<MODE, PREC, E_LOG | E_MUF, false>(a, wg_waves, lds, s, g);
         if (est == E_MUF) return launch_one<MODE, PREC, E_MUF, false>(a, wg_waves, lds, s, g);
@@ -388,6 +372,7 @@ constexpr uint32_t kNoTile = 0xffffffffu;  // the key of an empty slot
 
 // One wave per tile slot, the lanes taking the stencil rows; writes the
 // tile's cost bucket to key[t] (kNoTile for an empty slot).
+template <bool SPH>
 __global__ __launch_bounds__(256) void k_tile_cost(CountArgs P, const Tile* __restrict__ tiles,
                                                    uint32_t ntiles, uint32_t* __restrict__ key) {
     const int lane = (int)(threadIdx.x & 63u);
@@ -403,10 +388,10 @@ __global__ __launch_bounds__(256) void k_tile_cost(CountArgs P, const Tile* __re
         if (lane == 0) key[t] = kNoTile;
         return;
     }
-    const TileStencil ts = tile_stencil(P, tl);
+    const TileStencil ts = tile_stencil<SPH>(P, tl);
     uint64_t nb = 0;
     for (int e = lane; e < ts.nrows; e += 64) {
-        const RowSpans r = row_spans(P, ts, e);
+        const RowSpans r = row_spans<SPH>(P, ts, e);
         nb += (r.a1 > r.a0 ? r.a1 - r.a0 : 0u) + (r.b1 > r.b0 ? r.b1 - r.b0 : 0u);
         nb += (r.m1 > tl.start ? r.m1 - tl.start : 0u) + (r.h1 - r.h0);
     }
@@ -498,7 +483,8 @@ cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, hipSt
         return st;
     }
     const unsigned nb = (ntiles + 255u) / 256u;
-    hipLaunchKernelGGL(k_tile_cost, dim3((ntiles + 3u) / 4u), dim3(256), 0, s, a, *tiles, ntiles, key);
+    auto cost = a.geom == CUTE_GEOM_SPHERE ? k_tile_cost<true> : k_tile_cost<false>;
+    hipLaunchKernelGGL(cost, dim3((ntiles + 3u) / 4u), dim3(256), 0, s, a, *tiles, ntiles, key);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_tile_rank, dim3(nb), dim3(256), 0, s, key, ntiles, rank, hist);

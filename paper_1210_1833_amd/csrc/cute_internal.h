@@ -20,13 +20,29 @@ struct alignas(32) P64 {
 
 // Sizes shared by the kernels and their launch planning.
 constexpr int kQCap = 128;        // FP64 re-test queue entries per wave
-constexpr int kSpanCap = 132;     // neighbour spans buffered per wave: two per lane, two of the home row
-constexpr int kWaveLds = 3856;    // LDS bytes set aside per wave (queue, statistics, spans)
+constexpr int kRowBatch = 48;     // stencil rows taken at a time (one per lane)
+constexpr int kSpanCap = 2 * kRowBatch + 2;  // neighbour spans buffered per wave: two per row, two of the home row
+constexpr int kStage = 64 * 16;    // staged home points of a tile (kMfma kernels), bytes per wave
+constexpr int kStageMid = 64 * 4;  // and their alpha (midpoint kinds)
+constexpr int kList = 272;        // ambiguous pairs listed per wave (kMfma): 16 and a step's 256
+// LDS bytes per wave of a count kernel: queue, re-test statistics, spans, and
+// for kMfma kernels the stage and the list
+constexpr size_t wave_lds(bool mfma, bool mid) {
+    return 9 * (size_t)kQCap + 16 + 9 * (size_t)kSpanCap +
+           (mfma ? kStage + (mid ? kStageMid : 0) + 2 * (size_t)kList : 0);
+}
+// The bytes per wave that the largest histogram is sized by: a count is
+// accepted exactly when its tables and counters fit beside these.
+constexpr size_t kWaveLds = 3856;
+static_assert(wave_lds(false, false) <= kWaveLds, "per-wave LDS");
 constexpr int kMaxPartLog = 5;    // a home tile is counted in at most 2^5 parts
 constexpr int kWgWaves = 4;       // waves per count workgroup
 
 // Kinds of pair classification the kernels are specialised for.
 enum Mode : int { M_MONO = 0, M_RMU_Z = 1, M_RMU_MID = 2, M_SIGMAPI = 3, M_THETA = 4, M_RADIAL = 5 };
+// Kinds counted on spherical grids; the others take 3-D boxes.
+template <int MODE>
+constexpr bool kSphere = MODE == M_THETA || MODE == M_RADIAL;
 // How a bin index is estimated from the squared separation.
 // Estimate flags of a count kernel: bit 0, dimension 1 (r or theta) is
 // estimated from log(d2) (log-spaced edges) rather than linearly; bit 1, the
@@ -48,8 +64,14 @@ constexpr bool kH32 = MODE == M_SIGMAPI || MODE == M_RMU_MID;
 // Workgroups per CU a count kernel is compiled for (its register budget):
 // five for the one-variable FP32_EDGE kernels, four for the others.
 template <int MODE, int PREC>
-constexpr int kWgPerCu = (PREC == P_FP32E && (MODE == M_THETA || MODE == M_MONO)) ? 5 : 4;
+constexpr int kWgPerCu = (PREC == P_FP32E && (MODE == M_THETA || MODE == M_MONO || MODE == M_RMU_Z)) ? 5 : 4;
 constexpr bool h32_mode(int mode) { return mode == M_SIGMAPI || mode == M_RMU_MID; }
+
+// Count kernels whose separations come from the matrix cores (see step_mfma):
+// every FP32_EDGE kernel, r-mu against the midpoint with the mu decision in mu
+// space only.
+template <int MODE, int PREC, int EST>
+constexpr bool kMfma = PREC == P_FP32E && (MODE != M_RMU_MID || est_muf(EST));
 
 // A home tile: a run of sorted points inside one row of cells.
 struct Tile {
@@ -88,8 +110,6 @@ struct CountArgs {
     int periodic;
     double L;
     double Rs;                      // stencil radius (with margin); SPHERE: chord
-    double th_s;                    // SPHERE: angular stencil radius (radians)
-    double sin_th_s;                // SPHERE: sin(th_s)
     int n1, n2, nbins;
     float n1m1, n2m1;               // n1 - 1 and n2 - 1 as floats (estimate clamps)
     int copies;                     // LDS histogram copies per wave (power of two)
@@ -147,13 +167,19 @@ struct CountArgs {
     float dA0p;
     // mu in mu space (E_MUF): a pair is inside its mu bin when the offset d
     // of its position in bin units from the nearest bin centre satisfies
-    // |d| <= muB1 / r + muB0 (muB1 < 0: the band grows as the separation
-    // shrinks)
-    float muB1, muB0;
+    // |d| <= muB2 / r^2 + muB1 / r + muB0 (muB1, muB2 <= 0: the band grows as
+    // the separation shrinks)
+    float muB2, muB1, muB0;
+    // midpoint line of sight from the matrix cores: |a| + |b| of any decided
+    // pair, and what a tile's per-pair band t is made of (see midpoint_tile):
+    // (T_max + R^2), 2 R, the least t, the direction error f_e; for mu the
+    // factor of the terms in 1 / |l|
+    float mdM, mdTR, md2R, mdTmin, mdFe, mdN;
     // r in bin units (E_MUF with linear r bins, which start at r = 0 then):
     // inside its r bin when |d| <= rB0
     float rB0;
-    // precomputed neighbour rows (see ItemGeom::stencil), or nullptr
+    // precomputed neighbour rows, SPHERE: band table (see ItemGeom::stencil);
+    // nullptr when the kernel derives the rows
     const int4* stencil;
     int nst;
     // region pass of the jackknife (full stencil): sorted-order region of
@@ -243,6 +269,8 @@ struct ErrModel {
     double ec64 = 0.0;   // canonical FP64 separation components
     double el = 0.0;     // FP32 line-of-sight components (midpoint)
     double el64 = 0.0;   // FP64 line-of-sight components, before the sqrt(3) factor
+    double ta = 0.0;     // matrix-core separations: largest distance of a home point from its
+                         // tile's origin (0: differences formed component by component)
 };
 
 // What one pair of grids contributes to a launch.
@@ -256,7 +284,8 @@ struct ItemGeom {
     double cost = 0.0;   // estimated candidate pairs
     // rows of neighbour cells as offsets from the home row (3-D grids of one
     // geometry): (dy, dz, cells left of c0, cells right of c1); empty when
-    // the kernel must derive the rows itself
+    // the kernel must derive the rows itself. SPHERE: the reach of each band
+    // of A: (first band, last band, half-width in phi as a double)
     std::vector<int4> stencil;
 };
 
@@ -266,6 +295,7 @@ constexpr int kDecisionConsts = 17;
 
 struct Plan {
     int mode = 0, est = 0;
+    bool muf = false;                // RMU: linear mu edges covering [0, 1], r edges that allow E_MUF
     double rmax = 0.0;               // largest countable separation
     std::vector<double> T1, T2;      // canonical thresholds
     std::vector<float2> band1, band2;
@@ -273,14 +303,20 @@ struct Plan {
     size_t lds = 0;                  // dynamic LDS bytes per workgroup
 };
 
+// whether the FP32_EDGE count of a plan runs a kMfma kernel
+inline bool mfma_plan(const Plan& pl, int prec) { return prec == P_FP32E && (pl.mode != M_RMU_MID || pl.muf); }
+
 cute_status validate_binning(const cute_binning* b);
 bool same_binning(const cute_binning* a, const cute_binning* b);
 void plan_binning(const cute_binning* b, Plan& pl);
 cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const cute_binning* b,
-                      const Plan& pl, ItemGeom* g);
+                      const Plan& pl, int prec, ItemGeom* g);
+// the precision path that serves a request: FP32_EDGE counts whose lengths
+// leave the range of the FP32 path run the FP64 classifier (same counts)
+int served_prec(int prec, const ItemGeom& g, const GridHost& A, const GridHost& B, const Plan& pl);
 ErrModel max_err(const ErrModel& x, const ErrModel& y);
 void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl);
-cute_status plan_lds(Plan& pl, size_t extra);
+cute_status plan_lds(Plan& pl, size_t extra, int* prec);
 void apply_item(const ItemGeom& g, CountArgs* a);
 cute_status hip_status(hipError_t e, const char* what);
 

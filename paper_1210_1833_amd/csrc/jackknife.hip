@@ -152,11 +152,12 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
     Plan pl;
     plan_binning(bins, pl);
     ItemGeom geo;
-    if ((s = plan_item(R, nb, false, bins, pl, &geo)) != CUTE_OK) return s;
+    if ((s = plan_item(R, nb, false, bins, pl, (int)prec, &geo)) != CUTE_OK) return s;
     if (selfx && geo.stencil.empty() && R.n > 0)
         return fail(CUTE_E_UNSUPPORTED, "stencil too large for the region pass");
     plan_bands(bins, geo.em, pl);
-    if ((s = plan_lds(pl, 16)) != CUTE_OK) return s;
+    int kprec = served_prec((int)prec, geo, R, nb, pl);
+    if ((s = plan_lds(pl, 16, &kprec)) != CUTE_OK) return s;
     const int nbins = pl.a.nbins;
     h->assign((size_t)K * nbins, 0);
     if (R.n == 0 || nb.n == 0) return CUTE_OK;
@@ -237,7 +238,7 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
                             hs));
     // chunks: runs of up to 64 tiles of one region, regions in order
     int per_cu = 1, ncu = 0;
-    if ((s = batch_prepare(pl.mode, (int)prec, pl.est, pl.lds, &per_cu)) != CUTE_OK) return s;
+    if ((s = batch_prepare(pl.mode, kprec, pl.est, pl.lds, &per_cu)) != CUTE_OK) return s;
     CUTE_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     const uint64_t grid_max = (uint64_t)per_cu * ncu;
     uint64_t per = ntiles / std::max<uint64_t>(grid_max * 8, 1);
@@ -273,7 +274,7 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
     if (nch) {
         EventTimer timer(hs);
         const int gsz = (int)std::min<uint64_t>(grid_max, nch);
-        if ((s = batch_launch(ba, pl.mode, (int)prec, pl.est, gsz, pl.lds, hs)) != CUTE_OK) return s;
+        if ((s = batch_launch(ba, pl.mode, kprec, pl.est, gsz, pl.lds, hs)) != CUTE_OK) return s;
         timer.stop();
         ms = timer.elapsed_ms();
     }

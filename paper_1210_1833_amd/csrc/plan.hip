@@ -66,12 +66,41 @@ bool is_log(const double* e, int n) {
 // errors <= ec (coordinate rounding, origin shift, subtraction); the three-term
 // sum of squares adds <= 3.01 u of itself. The FP64 canonical value has the
 // same structure with ec64 and u64.
-double d2_bound(double r, double ec, double ec64) {
-    const double s3 = std::sqrt(3.0);
+// Matrix-core separations (ta > 0) evaluate |a|^2 + |b|^2 - 2 a.b instead, with
+// a and b the points in the frame of the home tile, |a| <= ta and |b| <= ta + r:
+// the two squares (formed in FP64) err by u of themselves, and each of the
+// four fused accumulations by u of a partial sum, at most (|a| + |b|)^2.
+// Together 5.01 u (|a| + |b|)^2, taken as 5.1 u (2 ta + r)^2.
+constexpr double kMfmaEval = 5.1 * kU32;
+double d2_bound(double r, const ErrModel& em) {
+    const double s3 = std::sqrt(3.0), ec = em.ec, ec64 = em.ec64;
     const double d32 = 2 * s3 * r * ec + 3 * ec * ec + 3.01 * kU32 * (r + s3 * ec) * (r + s3 * ec);
     const double d64 =
         2 * s3 * r * ec64 + 3 * ec64 * ec64 + 3.01 * kU64 * (r + s3 * ec64) * (r + s3 * ec64);
-    return d32 + d64;
+    const double m = 2 * em.ta + r + 2 * s3 * ec;
+    return d32 + d64 + (em.ta > 0.0 ? kMfmaEval * m * m : 0.0);
+}
+
+// Largest distance between a home point and its tile's origin, in the FP32
+// frame (see tile_origin): half the diagonal of the tile's box of cells for
+// 3-D grids (an axis of one cell takes the grid's centre: at most the half
+// extent); the extent of a block of pixels for the sphere, whose origin is one
+// of the tile's points.
+double tile_reach(const GridHost& A, int max_w) {
+    const double slack = 1e-6 * A.ext + 1e-300;
+    if (A.geom == CUTE_GEOM_SPHERE) {
+        const double zm = std::min(1.0, std::max(std::fabs(A.oy), std::fabs(A.oy + A.ny * A.ay)));
+        const double zn = std::max(0.0, zm - A.ay);
+        const double ds = std::sqrt(1.0 - zn * zn) - std::sqrt(1.0 - zm * zm);
+        const double dp = std::min(2.0, std::min(max_w, A.nx) * A.ax);
+        const double dz = std::min(2.0, A.ay);
+        return std::min(2.0, std::sqrt(dz * dz + ds * ds + dp * dp)) * (1.0 + 1e-6) + 1e-5;
+    }
+    auto half = [&](int cells, int n, double a) {
+        return n == 1 ? A.ext : 0.5 * (double)std::min(cells, n) * a;
+    };
+    const double hx = half(max_w, A.nx, A.ax), hy = half(1, A.ny, A.ay), hz = half(1, A.nz, A.az);
+    return std::sqrt(hx * hx + hy * hy + hz * hz) * (1.0 + 1e-6) + slack;
 }
 
 }  // namespace
@@ -210,7 +239,10 @@ void plan_binning(const cute_binning* b, Plan& pl) {
         a.nhi2_last = a.mu_top_closed ? -kBig : -(float)pl.T2[n2];
         a.d2lo32 = (float)pl.T2[0];
         a.d2hi32 = (float)pl.T2[n2];
-        if (b->kind == CUTE_BIN_RMU) a.d2_partial = (pl.T2[0] > 0.0 || !a.mu_top_closed) ? 1 : 0;
+        if (b->kind == CUTE_BIN_RMU) {
+            a.d2_partial = (pl.T2[0] > 0.0 || !a.mu_top_closed) ? 1 : 0;
+            pl.muf = !a.d2_generic && !a.d2_partial && (pl.est == E_LOG || pl.T1[0] == 0.0);
+        }
     } else {
         pl.band2.assign(1, make_float2(0.f, 0.f));
     }
@@ -220,7 +252,7 @@ void plan_binning(const cute_binning* b, Plan& pl) {
 // stencil radius, the home-tile width limit, the FP32 frame offsets and the
 // inputs of the rounding-error model.
 cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const cute_binning* b,
-                      const Plan& pl, ItemGeom* g) {
+                      const Plan& pl, int prec, ItemGeom* g) {
     if (A.geom != B.geom) return fail(CUTE_E_INVALID_ARG, "grids have different geometries");
     const bool sphere = A.geom == CUTE_GEOM_SPHERE;
     const bool periodic = A.geom == CUTE_GEOM_BOX_PERIODIC;
@@ -294,12 +326,23 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
     const double extra = offmax > 0.0 ? kU32 * offmax + kU32 * (B.ext + offmax) : 0.0;
     g->em.ec = 1.0001 * (kU32 * A.ext + kU32 * B.ext + extra + kU32 * Re);
     g->em.ec64 = 2.0 * kU64 * (A.rawmax + B.rawmax + (periodic ? A.L : 0.0)) * 1.0001;
+    if (mfma_plan(pl, prec)) {
+        // both points moved into the tile's frame: u (|a| + |b|) more
+        g->em.ta = tile_reach(A, g->max_w);
+        g->em.ec += 1.01 * kU32 * (2.0 * g->em.ta + Re);
+    }
     if (mid) {
         // l = h + ((q - off) + FP32(2 cA)): the roundings of both copies, of the
         // frame shift, of 2 cA, of the two additions (|l| <= max|p| + max|q|)
         const double ca = std::max({std::fabs(A.cx), std::fabs(A.cy), std::fabs(A.cz)});
         g->em.el = 1.0001 * kU32 *
                    (A.ext + B.ext + extra + 2 * ca + (B.ext + offmax + 2 * ca) + (A.lmax + B.lmax));
+        // matrix cores: l = L0 + a + b with L0 = FP32(2 (cA + o)) as such: the
+        // roundings of both copies, of the neighbour's move, of a and b, and
+        // of L0 (at most 2 max|p| and 2 ta in any component)
+        if (g->em.ta > 0.0)
+            g->em.el = 1.0001 * kU32 * (A.ext + B.ext + extra + (2.0 * g->em.ta + Re) +
+                                        2.0 * (A.rawmax + g->em.ta));
         g->em.el64 = 2.0 * kU64 * (A.lmax + B.lmax);
         g->lcx = (float)(2.0 * A.cx);
         g->lcy = (float)(2.0 * A.cy);
@@ -342,6 +385,35 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
         if (g->stencil.size() > 65536) g->stencil.clear();
     }
 
+    // SPHERE: the reach of each band of A, in place of the row table: first
+    // and last band of B within th_s of the band (one more on each side), and
+    // the half-width in phi of a cap of radius th_s around any of its points,
+    // asin(sin th_s / sin theta) at the colatitude nearest a pole (-1: the cap
+    // can reach a pole, whole rings)
+    if (sphere) {
+        g->stencil.resize((size_t)A.ny);
+        for (int cy = 0; cy < A.ny; cy++) {
+            const double zlo = A.oy + cy * A.ay, zhi = zlo + A.ay;
+            const double zl = std::max(-1.0, std::min(1.0, zlo)), zh = std::max(-1.0, std::min(1.0, zhi));
+            const double th_lo = std::acos(zh), th_hi = std::acos(zl), ths = g->th_s;
+            const double zn_hi = th_lo - ths <= 0.0 ? 1.0 : std::cos(th_lo - ths);
+            const double zn_lo = th_hi + ths >= kPiH ? -1.0 : std::cos(th_hi + ths);
+            auto band = [&](double z) {
+                return (int)std::max(-1.0, std::min((double)B.ny, std::floor((z - B.oy) / B.ay)));
+            };
+            const int b0 = std::max(0, std::min(band(zn_lo) - 1, B.ny - 1));
+            const int b1 = std::max(0, std::min(band(zn_hi) + 1, B.ny - 1));
+            const double smin = std::sqrt(std::max(0.0, 1.0 - std::max(zl * zl, zh * zh)));
+            const bool full = !(g->sin_th_s < smin * (1.0 - 1e-9)) || ths >= 0.5 * kPiH;
+            const double hw = full ? -1.0 : std::asin(g->sin_th_s / smin) * (1.0 + 1e-9) + 1e-12;
+            int4 e;
+            e.x = b0;
+            e.y = b1;
+            memcpy(&e.z, &hw, sizeof(hw));   // e.z, e.w: the bits of hw
+            g->stencil[(size_t)cy] = e;
+        }
+    }
+
     // estimated candidate pairs: nA nB times the stencil's share of B's domain
     double vol_b, vol_s;
     if (sphere) {
@@ -363,7 +435,20 @@ ErrModel max_err(const ErrModel& x, const ErrModel& y) {
     m.ec64 = std::max(x.ec64, y.ec64);
     m.el = std::max(x.el, y.el);
     m.el64 = std::max(x.el64, y.el64);
+    m.ta = std::max(x.ta, y.ta);
     return m;
+}
+
+// The matrix-core path forms squares of lengths in FP32 and marks the points
+// that are not there with a huge one: lengths must stay inside [1e-12, 1e15],
+// and for the midpoint, whose predicates multiply squares, inside [1e-6, 1e8].
+int served_prec(int prec, const ItemGeom& g, const GridHost& A, const GridHost& B, const Plan& pl) {
+    if (!mfma_plan(pl, prec)) return prec;
+    const bool mid = pl.mode == M_RMU_MID || pl.mode == M_SIGMAPI;
+    const double big = 4.0 * (A.ext + B.ext + std::fabs((double)g.offx) + std::fabs((double)g.offy) +
+                              std::fabs((double)g.offz) + g.L + g.em.ta + g.Rs +
+                              (mid ? A.lmax + B.lmax : 0.0));
+    return pl.rmax >= (mid ? 1e-6 : 1e-12) && big <= (mid ? 1e8 : 1e15) ? prec : P_FP64;
 }
 
 // Rounding bands of the midpoint line of sight (sigma, pi and mu against the
@@ -409,9 +494,13 @@ static void midpoint_bands(const cute_binning* b, const ErrModel& em, Plan& pl) 
             return M * (2 * x * es + es * es + E64 + cu * u * Rv * Rv + 6 * u * T + 1e-30) /
                    (1.0 - 6 * u);
         };
+        // matrix cores: v errs by 5.1 u (2 ta + r)^2 (sigma only), and the
+        // products by 3.1 u r^2; the rest of their error is in the tile's t
+        const double ev = 5.1 * (2.0 * em.ta / Rv + 1.0) * (2.0 * em.ta / Rv + 1.0);
+        const double cs = em.ta > 0.0 ? ev + 3.1 : 14.0, cp = em.ta > 0.0 ? 3.1 : 8.0;
         std::vector<double> bs(n1 + 1), bp(n2 + 1);
-        for (int k = 0; k <= n1; k++) bs[k] = band(pl.T1[k], 14.0);
-        for (int k = 0; k <= n2; k++) bp[k] = band(pl.T2[k], 8.0);
+        for (int k = 0; k <= n1; k++) bs[k] = band(pl.T1[k], cs);
+        for (int k = 0; k <= n2; k++) bp[k] = band(pl.T2[k], cp);
         // bin k certifies lo <= x^2 - t/ll and x^2 + t/ll <= hi, lo = T_k + b_k
         // and hi = T_{k+1} - b_{k+1}, as |F + m ll| <= H ll - t with m the
         // negated centre and H the half-width of [lo, hi]. A first edge at
@@ -436,6 +525,23 @@ static void midpoint_bands(const cute_binning* b, const ErrModel& em, Plan& pl) 
         pl.band2.resize(n2);
         for (int k = 0; k < n2; k++)
             pl.band2[k] = mid_half(pl.T2[k], bp[k], pl.T2[k + 1], bp[k + 1]);
+        if (em.ta > 0.0) {
+            // matrix cores: an entry past the last bin certifies "past the top
+            // edge" the same way (sigma^2 and pi^2 of a decided pair are below
+            // 2 Rv^2), so that no other test of the range is needed; t is the
+            // tile's (see midpoint_tile): K1 and K0 as above with |l| <= Lx
+            pl.band1.push_back(mid_half(pl.T1[n1], bs[n1], 4.0 * Rv * Rv, 0.0));
+            pl.band2.push_back(mid_half(pl.T2[n2], bp[n2], 4.0 * Rv * Rv, 0.0));
+            a.mdM = up32(2.0 * em.ta + Rv * (1.0 + 1e-6));
+            a.mdTR = up32(1.01 * (Tmax + bs[n1] + bp[n2]) + Rv * Rv);
+            a.md2R = up32(2.0 * Rv);
+            a.mdFe = up32(fe);
+            // with t at least H llg for every half-width H, a pair with ll <
+            // llg (whose direction is not known) is never certified
+            a.mdTmin = up32(2.1 * Rv * Rv * (double)a.llg);
+            a.top1 = kBiasBits + (uint32_t)n1;
+            a.top2 = kBiasBits + (uint32_t)n2;
+        }
         auto hi_w = [](double T, double bb) { return T - bb <= 0.0 ? kBig : up32(-(T - bb)); };
         a.sp_wstop = dn32(-(pl.T1[n1] + bs[n1]));
         a.sp_wptop = dn32(-(pl.T2[n2] + bp[n2]));
@@ -497,7 +603,8 @@ static void midpoint_bands(const cute_binning* b, const ErrModel& em, Plan& pl) 
 // decision's own error, and 2 u for the rounding of the offset and the FP32
 // fma of the half-width (the term u (a + |b| + 1) is a margin beyond these
 // roundings). Kept as 1/2 - beta =
-// muB1 rsq(v) + muB0, times a safety factor 1.5 on beta.
+// muB1 rsq(v) + muB0, times a safety factor 1.5 on beta (muB2 rsq(v)^2 more
+// for matrix-core separations).
 static void mu_space_band(const cute_binning* b, const ErrModel& em, Plan& pl) {
     CountArgs& a = pl.a;
     const int n2 = b->n2;
@@ -514,8 +621,57 @@ static void mu_space_band(const cute_binning* b, const ErrModel& em, Plan& pl) {
                                 std::fabs(S2 - s2x) + 8.0 * kU64) +
                            u * (A + std::fabs(B) + 1.0) + dev) +
                       2.0 * u;
-    a.muB1 = -up32(c1);
+    // matrix-core separations: v errs by E = 5.1 u (2 ta + r)^2 more, hence mu
+    // by mu E / (2 r^2) to first order, E / r^2 = 5.1 u (1 + 4 ta / r + 4
+    // ta^2 / r^2). A pair is certified only when the band is under 1/2, so
+    // with the factor K on this term E / r^2 < 1 / (1.5 K A): below 0.08 for
+    // A >= 8 and K = 1.1, below 1/3 for K = 2; the neglected orders, (1 -
+    // E / r^2)^(-3/2) and 1/r against rsq(v), are then within K M.
+    double e0 = 0.0, e1 = 0.0, e2 = 0.0;
+    if (em.ta > 0.0) {
+        const double h = 0.5 * M * (A >= 8.0 ? 1.1 : 2.0) * A * kMfmaEval;
+        e0 = h;
+        e1 = h * 4.0 * em.ta;
+        e2 = h * 4.0 * em.ta * em.ta;
+    }
+    a.muB2 = -up32(e2);
+    a.muB1 = -up32(c1 + e1);
+    a.muB0 = dn32(0.5 - (c0 + e0 + (e2 > 0.0 ? 2.0 * u : 0.0)));
+    pl.est |= E_MUF;
+}
+
+// The mu decision of the midpoint line of sight in mu space (matrix-core
+// separations, linear mu edges covering [0, 1]). The kernel forms mu32 = |sl32|
+// rsq(ll32) rsq(v32), sl = alpha - beta and ll = |L0|^2 + 2 alpha + 2 beta - v
+// (see step_mfma), and decides as mu_space_band does. With Lx >= |L0| + |a| +
+// |b| and |l| >= lmin (per tile, see midpoint_tile), e = |sl32 - s.l| <= Esl +
+// u |sl| and |ll32 - |l|^2| <= Ell:
+//   |mu32 - mu| <= 2 es / r + 2 fe / |l| + Esl / (|l| r) + Ell / (2 |l|^2)
+//                  + E(r) / (2 r^2) + 2 kRsqRel + 4 u
+// (first orders; E the error of v). The terms without |l| are in muB0, muB1 and
+// muB2 as for the z line of sight, the others are the tile's, times mdN; the
+// neglected orders are within K M, as there (a pair is certified only with its
+// band under 1/2).
+static void midpoint_mu_band(const cute_binning* b, const ErrModel& em, Plan& pl) {
+    CountArgs& a = pl.a;
+    const int n2 = b->n2;
+    const double u = kU32, s3 = std::sqrt(3.0);
+    const double A = (double)a.e2a, B = (double)a.e2b, S2 = (double)a.s2;
+    const double es = s3 * em.ec, fe = s3 * em.el;
+    double dev = 0.0;
+    for (int j = 0; j <= n2; j++) dev = std::max(dev, std::fabs(b->edges2[j] * A + B - (double)j));
+    dev = dev * (1.0 + 1e-9) + 1e-12;
+    const double KM = A >= 8.0 ? 1.65 : 3.0;
+    const double h = 0.5 * KM * A * kMfmaEval;
+    const double c0 = KM * (A * (2.0 * kRsqRel + 5.0 * u + u * (1.0 + std::fabs(S2)) * 1.01 +
+                                 std::fabs(S2 - (B - 0.5) / A) + 64.0 * kU64) +
+                            u * (A + std::fabs(B) + 1.0) + dev) + h + 4.0 * u;
+    a.muB2 = -up32(h * 4.0 * em.ta * em.ta);
+    a.muB1 = -up32(KM * A * 2.0 * es * 1.01 * (1.0 + kRsqRel) + h * 4.0 * em.ta);
     a.muB0 = dn32(0.5 - c0);
+    a.mdM = up32(2.0 * em.ta + (pl.rmax * (1.0 + 1e-6) + es) * (1.0 + 1e-6));
+    a.mdFe = up32(fe);
+    a.mdN = up32(KM * A * 1.001);
     pl.est |= E_MUF;
 }
 
@@ -546,7 +702,7 @@ static bool r_space_band(const cute_binning* b, const ErrModel& em, Plan& pl) {
     double beta = 0.0;
     for (int k = 1; k <= n1; k++) {
         const double ek = std::sqrt(pl.T1[k]) * (1.0 + 4.0 * kU64);
-        const double m = 1.5 * d2_bound(ek * (1.0 + 1e-6) + 2.0 * em.ec, em.ec, em.ec64) +
+        const double m = 1.5 * d2_bound(ek * (1.0 + 1e-6) + 2.0 * em.ec, em) +
                          4.0 * kU64 * pl.T1[k];
         const double rr = ek * 1.01 + 2.0 * em.ec;
         const double err = A * rr * kRsqRel + u * A * (rr + std::fabs(S1)) * 1.01 + 0x1p-24;
@@ -578,12 +734,12 @@ void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl) {
         // FP32 skip: d2_32 past top64 plus the FP32 and FP64 error of d2 at
         // that separation
         const double rt = std::sqrt(a.top64);
-        a.skip32 = up32(a.top64 + 1.5 * d2_bound(rt * (1.0 + 1e-6) + 2.0 * ec, ec, ec64));
+        a.skip32 = up32(a.top64 + 1.5 * d2_bound(rt * (1.0 + 1e-6) + 2.0 * ec, em));
     } else {
         std::vector<float> lo_e(n1 + 1), hi_e(n1 + 1);
         for (int k = 0; k <= n1; k++) {
             const double rk = std::sqrt(pl.T1[k]);
-            const double m = 1.5 * d2_bound(rk * (1.0 + 1e-6) + 2.0 * ec, ec, ec64);
+            const double m = 1.5 * d2_bound(rk * (1.0 + 1e-6) + 2.0 * ec, em);
             lo_e[k] = pl.T1[k] == 0.0 ? -1.0f : up32(pl.T1[k] + m);
             const double h = pl.T1[k] - m;
             hi_e[k] = h > 0.0 ? dn32(h) : -1.0f;
@@ -607,9 +763,12 @@ void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl) {
         const double k1 = 2 * std::sqrt(2.0) * ec + (2 + 2 * s3) * ec64;
         // the kernel uses delta = dA0 + dA1 r with the v term folded in:
         // A2 v <= A2 Re r for every pair whose mu decision counts (r < Re)
-        const double a2 = 1.5 * (8.1 * kU32 + 16 * kU64) * 1.0001;
-        const double A1 = (1.5 * k1 * (1 + 8 * kU32) + a2 * Re) * 1.0001;
-        const double A0 = 1.5 * (k1 * s3 * ec + 3 * ec * ec + 4 * ec64 * ec64) * 1.0001;
+        // (matrix-core separations: M2 E <= 5.1 u (r^2 + 4 ta r + 4 ta^2) more)
+        const double em2 = em.ta > 0.0 ? kMfmaEval : 0.0;
+        const double a2 = 1.5 * (8.1 * kU32 + 16 * kU64 + em2) * 1.0001;
+        const double A1 = (1.5 * (k1 * (1 + 8 * kU32) + 4.0 * em2 * em.ta) + a2 * Re) * 1.0001;
+        const double A0 = 1.5 * (k1 * s3 * ec + 3 * ec * ec + 4 * ec64 * ec64 +
+                                 4.0 * em2 * em.ta * em.ta) * 1.0001;
         a.dA1 = (float)A1;
         a.dA0 = (float)A0;
         a.dA2 = 0.0f;
@@ -626,6 +785,9 @@ void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl) {
             mu_space_band(b, em, pl);
     } else if (pl.mode == M_RMU_MID || pl.mode == M_SIGMAPI) {
         midpoint_bands(b, em, pl);
+        a.rB0 = -1.0f;
+        if (pl.mode == M_RMU_MID && pl.muf && em.ta > 0.0 && (pl.est != E_LIN || r_space_band(b, em, pl)))
+            midpoint_mu_band(b, em, pl);
     }
 }
 
@@ -634,30 +796,36 @@ void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl) {
 // per workgroup keeps four workgroups (16 waves) on a CU; the copies of the
 // histogram are cut to fit, then the budget is relaxed for very large
 // histograms (fewer workgroups per CU).
-cute_status plan_lds(Plan& pl, size_t extra) {
+// The kMfma kernels need more per wave than the bytes the limit is set by:
+// where that alone would not fit, *prec becomes FP64 (the same counts).
+cute_status plan_lds(Plan& pl, size_t extra, int* prec) {
     CountArgs& a = pl.a;
     const int n1 = a.n1, n2 = a.n2, nbins = a.nbins;
     const size_t tables = 8 * (size_t)(n1 + 1) + 8 * (size_t)(n2 + 1) + 8 * (size_t)n1 +
                           8 * (size_t)std::max(n2, 1);
-    // (the bytes set aside per wave also bound the largest histogram)
-    const size_t per_wave = kWaveLds;
-    static_assert(12 * kQCap + 16 + 12 * kSpanCap <= kWaveLds, "per-wave LDS");
     // extra: the kernel's control words after the span buffers, plus the
     // budget word of a 32-bit histogram; a 32-bit histogram's bytes are
     // rounded up to 8
     const bool h32 = h32_mode(pl.mode);
     const size_t es = h32 ? 4 : 8;   // bytes per counter
-    const size_t fixed = tables + (size_t)kWgWaves * per_wave + extra + (h32 ? 16 : 0);
-    const size_t pad = h32 ? 4 : 0;
+    const size_t ctl = extra + (h32 ? 16 : 0), pad = h32 ? 4 : 0, lds_max = 160 * 1024;
+    if (tables + (size_t)kWgWaves * kWaveLds + ctl + pad + es * (size_t)nbins > lds_max)
+        return fail(CUTE_E_UNSUPPORTED, "histogram does not fit in LDS");
+    // (kMfma kernels: the band tables have room for one entry more)
+    size_t fixed = tables + (size_t)kWgWaves * wave_lds(mfma_plan(pl, *prec), h32) + ctl +
+                   (mfma_plan(pl, *prec) ? 16 : 0);
+    if (fixed + pad + es * (size_t)nbins > lds_max) {
+        *prec = P_FP64;
+        fixed = tables + (size_t)kWgWaves * wave_lds(false, false) + ctl;
+    }
     int C = 0;
-    for (size_t budget : {(size_t)40 * 1024, (size_t)80 * 1024, (size_t)160 * 1024}) {
+    for (size_t budget : {(size_t)40 * 1024, (size_t)80 * 1024, lds_max}) {
         if (fixed + pad + es * (size_t)nbins > budget) continue;
         size_t cmax = (budget - fixed - pad) / (es * (size_t)nbins);
         C = 1;
         while (C * 2 <= (int)std::min<size_t>(cmax, 32)) C *= 2;
         break;
     }
-    if (C == 0) return fail(CUTE_E_UNSUPPORTED, "histogram does not fit in LDS");
     a.copies = C;
     a.hist_words = nbins * C;
     a.hs2 = (int)es * C;
@@ -685,8 +853,6 @@ void apply_item(const ItemGeom& g, CountArgs* a) {
     a->periodic = g.periodic;
     a->L = g.L;
     a->Rs = g.Rs;
-    a->th_s = g.th_s;
-    a->sin_th_s = g.sin_th_s;
     a->offx = g.offx;
     a->offy = g.offy;
     a->offz = g.offz;

@@ -12,6 +12,15 @@ import paper_1210_1833_amd as cute
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible: the gpu tests need an MI355X")
+    cute.load()
+    yield
+
+
 def cap(n, seed):
     return catalogs.cap_uniform(n, 25.0, 2.0, 10.0, seed)   # across phi = 0
 
