@@ -262,7 +262,9 @@ cute_status cute_count_pairs_noalloc(const cute_grid* a, const cute_grid* b,
  *   differences; a pair with dz = |r_i - r_j| (one FP64 subtraction) is
  *   counted in bin k when edges[k] <= dz < edges[k + 1].
  * counts: n_bins uint64, OVERWRITTEN (a device pointer if counts_on_device).
- * FP64 throughout: few pairs fall inside an aperture, so no FP32 path.
+ * Counts are those of FP64 throughout. With linear edges FP32 decides the
+ * pairs that lie farther than a proven rounding bound from the aperture and
+ * from every edge, and the rest are re-tested in FP64 (st->retests).
  * Errors: CUTE_E_INVALID_ARG for NULL pointers, bad edges or aperture,
  * non-SPHERE grids or non-finite redshifts; CUTE_E_UNSUPPORTED for pixel
  * maps; those of cute_count_pairs otherwise. */

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
     const int n1 = BA.n1;
     const int n2p = BA.n2 > 0 ? BA.n2 : 0;
     constexpr bool H32 = kH32<MODE>;
-    const WgLds L = wg_lds<H32, kMfma<MODE, PREC, EST>>(smem, nwaves, n1, BA.n2, BA.hist_words);
+    const WgLds L = wg_lds<H32, kMfma<MODE, PREC, EST>, kAlpha<MODE>>(smem, nwaves, n1, BA.n2, BA.hist_words);
     double *T1 = L.T1, *T2 = L.T2;
     float2 *B1 = L.B1, *B2 = L.B2;
     unsigned char* hist0 = L.hist;

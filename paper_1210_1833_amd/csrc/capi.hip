@@ -244,20 +244,7 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     if (rad) {
         // the aperture binning gave the geometry; the histogram is over the
         // redshift difference, compared with the unsquared edges
-        CountArgs& r = pl.a;
-        const double c = 2.0 * std::sin(0.5 * rad->aperture);
-        r.ap2 = c * c;
-        r.top64 = r.ap2;
-        pl.mode = M_RADIAL;
-        pl.est = E_LIN;
-        pl.T1.assign(rad->edges, rad->edges + rad->n + 1);
-        pl.T2.assign(1, 0.0);
-        pl.band1.assign(rad->n, make_float2(0.f, 0.f));
-        pl.band2.assign(1, make_float2(0.f, 0.f));
-        r.n1 = rad->n;
-        r.n2 = 0;
-        r.nbins = rad->n;
-        r.n2p1 = 1;
+        plan_radial(rad->edges, rad->n, pl, &kprec);
     }
     if ((s = plan_lds(pl, 0, &kprec)) != CUTE_OK) return s;
     CountArgs a = pl.a;
@@ -515,8 +502,8 @@ extern "C" cute_status cute_count_radial(const cute_grid* a, const double* ra, c
     ab.n1 = 1;
     ab.edges1 = ae;
     RadialSpec rs{ra, is_auto ? ra : rb, r_on_device, n_bins, edges, aperture};
-    return count_impl(a, b, &ab, CUTE_PREC_FP64, counts, counts_on_device, st, stream, 0, nullptr,
-                      &rs);
+    return count_impl(a, b, &ab, radial_prec(edges, n_bins) == P_FP32E ? CUTE_PREC_FP32_EDGE : CUTE_PREC_FP64,
+                      counts, counts_on_device, st, stream, 0, nullptr, &rs);
 }
 
 extern "C" cute_status cute_tune_grid(const double* x, const double* y, const double* z,

@@ -493,10 +493,12 @@ struct WaveState {
     float4* stage;       // the tile's home points in its own frame (kMfma kernels)
     uint16_t* list;      // ambiguous pairs of the chunk at hand: home offset << 6 | lane (kMfma)
     uint32_t nlist;      // how many (wave-uniform)
-    float* alpha;        // per home point: |p|^2 - |P0|^2, P0 the origin (midpoint kinds)
+    float* alpha;        // per home point: |p|^2 - |P0|^2, P0 the origin (midpoint kinds); its
+                         // redshift in bins (radial)
     float ox, oy, oz;    // that frame's origin in the grid's FP32 frame (wave-uniform)
     float lx, ly, lz;    // midpoint kinds: L0 = 2 P0 from the observer (wave-uniform)
-    float mt, mb0, mb1;  // sigma-pi: the tile's t; mu: its band's constant and linear terms
+    float mt, mb0, mb1;  // sigma-pi: the tile's t; mu: its band's constant and linear terms;
+                         // radial: mt the largest alpha in size
     unsigned long long* rstat;  // [0] retests, [1] flips (LDS)
     uint32_t tail;       // queued entries (wave-uniform)
     uint64_t evals, tiles;
@@ -522,14 +524,13 @@ struct WgLds {
     float4* stage;
     float* alpha;
 };
-// (H32 are the midpoint kinds)
-template <bool H32, bool MFMA>
+template <bool H32, bool MFMA, bool ALPHA>
 __device__ __forceinline__ WgLds wg_lds(unsigned char* smem, int nwaves, int n1, int n2, int hist_words) {
     const int n2p = n2 > 0 ? n2 : 0;
     WgLds l;
     l.stage = reinterpret_cast<float4*>(smem);
     l.alpha = reinterpret_cast<float*>(smem + (MFMA ? (size_t)nwaves * kStage : 0));
-    l.T1 = reinterpret_cast<double*>(l.alpha + (MFMA && H32 ? (size_t)nwaves * (kStageMid / 4) : 0));
+    l.T1 = reinterpret_cast<double*>(l.alpha + (MFMA && ALPHA ? (size_t)nwaves * (kStageMid / 4) : 0));
     l.T2 = l.T1 + (n1 + 1);
     l.B1 = reinterpret_cast<float2*>(l.T2 + (n2p + 1));
     l.B2 = l.B1 + n1 + (MFMA ? 1 : 0);   // (sigma-pi: an entry past the last bin)
@@ -637,6 +638,22 @@ __device__ __forceinline__ uint64_t pair_weight2(const CountArgs& P, uint32_t i,
     return pair_weight(P, j);
 }
 
+// Radial pairs (Sec. 2.1, radial 2PCF; Sec. 3.4): inside the aperture when
+// the chord^2 of the unit vectors is below ap2, then binned by the redshift
+// difference |r_i - r_j| against the unsquared edges T1 (half-open).
+__device__ __forceinline__ uint32_t classify_radial(const CountArgs& P, const double* T1, double d2,
+                                                    double dr) {
+    if (!(d2 < P.ap2)) return kNoBin;
+    const int n = P.n1;
+    if (!(T1[0] <= dr && dr < T1[n])) return kNoBin;
+    int lo = 0, hi = n;  // T1[lo] <= dr < T1[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (T1[mid] <= dr) lo = mid; else hi = mid;
+    }
+    return (uint32_t)lo;
+}
+
 // Re-test up to 64 queued pairs per pass, one per lane, through the canonical
 // FP64 predicates; count the pairs whose FP32-only decision differs (flips).
 // Returns the new queue length.
@@ -655,19 +672,27 @@ __device__ __forceinline__ uint32_t drain_queue(
             const uint32_t i = qi[lane], j = qj[lane], code = qc[lane];
             const P64 p = P.A.p64[i];
             const P64 q = P.B.p64[j];
-            k = classify_pair64<MODE, EST>(P, T1, T2, p, q);
+            if constexpr (MODE == M_RADIAL) {
+                const double dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
+                k = classify_radial(P, T1, fma(dz, dz, fma(dy, dy, dx * dx)), fabs(P.rA[i] - P.rB[j]));
+                t = k;   // (no FP32-only decision to differ from)
+            } else {
+                k = classify_pair64<MODE, EST>(P, T1, T2, p, q);
+            }
             if (k != kNoBin) hist_add<kH32<MODE>>(hist, k, P.copies, lane, pair_weight2(P, i, j));
-            // the FP32-only decision of the same pair, as the main loop made it
-            const float4 a = P.A.p32[i];
-            const float4 b = P.B.p32[j];
-            const float Lf = (float)P.L;
-            const float qx = b.x - (P.offx - shift32(code, 0, Lf));
-            const float qy = b.y - (P.offy - shift32(code, 1, Lf));
-            const float qz = b.z - (P.offz - shift32(code, 2, Lf));
-            const Tab32 tab = make_tab32<EST>(P, B1, B2);
-            (void)classify32<MODE, EST, true>(P, tab, a.x - qx, a.y - qy, a.z - qz,
-                                              a.x + (qx + P.lcx), a.y + (qy + P.lcy),
-                                              a.z + (qz + P.lcz), &t);
+            if constexpr (MODE != M_RADIAL) {
+                // the FP32-only decision of the same pair, as the main loop made it
+                const float4 a = P.A.p32[i];
+                const float4 b = P.B.p32[j];
+                const float Lf = (float)P.L;
+                const float qx = b.x - (P.offx - shift32(code, 0, Lf));
+                const float qy = b.y - (P.offy - shift32(code, 1, Lf));
+                const float qz = b.z - (P.offz - shift32(code, 2, Lf));
+                const Tab32 tab = make_tab32<EST>(P, B1, B2);
+                (void)classify32<MODE, EST, true>(P, tab, a.x - qx, a.y - qy, a.z - qz,
+                                                  a.x + (qx + P.lcx), a.y + (qy + P.lcy),
+                                                  a.z + (qz + P.lcz), &t);
+            }
         }
         const uint64_t fl = __builtin_amdgcn_ballot_w64(act && k != t);
         if (lane == 0) {
@@ -865,6 +890,8 @@ typedef float __attribute__((ext_vector_type(4))) f4v;
 constexpr float kFar = 1e33f;
 template <int MODE>
 constexpr bool kMid = MODE == M_SIGMAPI || MODE == M_RMU_MID;
+template <int MODE>
+constexpr bool kAlpha = alpha_mode(MODE);
 
 // Origin of a tile's frame, in the grid's FP32 frame: the centre of its box
 // of cells (an axis of one cell: the grid's centre), on the sphere the point
@@ -960,15 +987,22 @@ __device__ __forceinline__ void stage_home(const CountArgs& Pk, WaveState& W, co
         const double a2 = sq64(x, y, z);
         s = make_float4(-2.0f * x, -2.0f * y, -2.0f * z, (float)a2);
         if constexpr (kMid<MODE>) al = (float)(dot64(W.lx, W.ly, W.lz, x, y, z) + a2);
+        if constexpr (MODE == M_RADIAL) al = (float)(P.rA[i] * P.rdA);
+    }
+    if constexpr (MODE == M_RADIAL) {
+        float m = fabsf(al);
+        for (int k = 32; k > 0; k >>= 1) m = fmaxf(m, __shfl_xor(m, k));
+        W.mt = unif(m);
     }
     wave_lds_fence();
     W.stage[lane] = s;
-    if constexpr (kMid<MODE>) W.alpha[lane] = al;
+    if constexpr (kAlpha<MODE>) W.alpha[lane] = al;
     wave_lds_fence();
 }
 
 // A chunk's neighbour as a column: b, |b|^2 and -b_z in the four rows;
-// midpoint kinds: -beta and 2 beta + |L0|^2.
+// midpoint kinds: -beta and 2 beta + |L0|^2; radial: nbeta its negated redshift
+// in bins, beta2 the half-width of the band.
 struct Column {
     float bx, by, bz;
     f4v b2, nbz, nbeta, beta2;
@@ -985,6 +1019,8 @@ struct Column {
 // d: dz, or sl for the midpoint kinds; ss: |l|^2 + v for those. Sigma-pi: the
 // tables hold one entry past the last bin, for the pairs certainly past the top
 // edge; *skip receives the lanes that are (not counted, not ambiguous).
+// Radial: d the redshift difference in bins, ss the half-width; the bin counts
+// from 2^23 + 1 as for r-mu, *skip receives the lanes certainly outside the bins.
 template <int MODE, int EST>
 __device__ __forceinline__ uint64_t decide(const CountArgs& P, const Tab32& T, float v, float d, float ss,
                                            uint64_t lt, uint32_t lb, uint32_t* off, uint64_t* skip) {
@@ -1005,6 +1041,17 @@ __device__ __forceinline__ uint64_t decide(const CountArgs& P, const Tab32& T, f
         *off = __umul24(ks, (uint32_t)P.hs1) + (__umul24(kp, (uint32_t)P.hs2) + lb);
         *skip = in & (__builtin_amdgcn_ballot_w64(ks == P.top1) | __builtin_amdgcn_ballot_w64(kp == P.top2));
         return in & ~*skip;
+    }
+    if constexpr (MODE == M_RADIAL) {
+        const float bias1 = __uint_as_float(T.vbias1);
+        const float ts = fabsf(d) + P.s1;
+        const float e = ts + bias1;
+        const uint64_t sure = __builtin_amdgcn_ballot_w64(fabsf(ts + (bias1 - e)) <= ss) & lt;
+        uint64_t bin = __builtin_amdgcn_ballot_w64(__float_as_uint(e) < P.top1);
+        if (P.rdLow) bin &= __builtin_amdgcn_ballot_w64(__float_as_uint(e) > kBias);
+        *off = __umul24(__float_as_uint(e), (uint32_t)P.hs1) + lb;
+        *skip = sure & ~bin;
+        return sure & bin & __builtin_amdgcn_ballot_w64(v <= P.rdIn);
     }
     float dz = d;
     if constexpr (MODE == M_RMU_MID) dz = d * __builtin_amdgcn_rsqf(ss - v);   // |s.l| / |l|
@@ -1067,6 +1114,7 @@ __device__ __forceinline__ uint64_t decide(const CountArgs& P, const Tab32& T, f
 // minus the bias of each estimate that is one above the bin.
 template <int MODE, int EST>
 __device__ __forceinline__ uint32_t decide_base(const CountArgs& P, uint32_t lb) {
+    if constexpr (MODE == M_RADIAL) return lb - (uint32_t)P.hs1;
     if constexpr (est_muf(EST))
         return lb - (uint32_t)P.hs2 - (est_log(EST) ? 0u : (uint32_t)P.hs1);
     return lb;
@@ -1104,6 +1152,9 @@ __device__ __forceinline__ void step_mfma(const CountArgs& P, WaveState& W, cons
     if constexpr (kMid<MODE>) {
         d = __builtin_amdgcn_mfma_f32_4x4x1f32(al, 1.0f, q.nbeta, B, I, 0);
         ss = __builtin_amdgcn_mfma_f32_4x4x1f32(al, 2.0f, q.beta2, B, I, 0);
+    } else if constexpr (MODE == M_RADIAL) {
+        d = __builtin_amdgcn_mfma_f32_4x4x1f32(al, 1.0f, q.nbeta, B, I, 0);
+        ss = q.beta2;
     } else if constexpr (MODE == M_RMU_Z) {
         d = __builtin_amdgcn_mfma_f32_4x4x1f32(a.z, -0.5f, q.nbz, B, I, 0);
     }
@@ -1177,22 +1228,6 @@ __device__ __forceinline__ void queue_list(const CountArgs& P, WaveState& W, con
                                             lane, W.tail, false);
     }
     W.nlist = 0;
-}
-
-// Radial pairs (Sec. 2.1, radial 2PCF; Sec. 3.4): inside the aperture when
-// the chord^2 of the unit vectors is below ap2, then binned by the redshift
-// difference |r_i - r_j| against the unsquared edges T1 (half-open).
-__device__ __forceinline__ uint32_t classify_radial(const CountArgs& P, const double* T1, double d2,
-                                                    double dr) {
-    if (!(d2 < P.ap2)) return kNoBin;
-    const int n = P.n1;
-    if (!(T1[0] <= dr && dr < T1[n])) return kNoBin;
-    int lo = 0, hi = n;  // T1[lo] <= dr < T1[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (T1[mid] <= dr) lo = mid; else hi = mid;
-    }
-    return (uint32_t)lo;
 }
 
 template <int MODE, int EST, bool PM, bool WT, bool MASKED, bool SHIFTED, uint32_t U>
@@ -1293,14 +1328,14 @@ struct Chunk {
 };
 
 // A chunk against the tile's staged home points. q: the lanes' neighbours in
-// FP32, loaded a chunk ahead. The separations of a step are formed while the
+// FP32 (and redshifts, radial), loaded a chunk ahead. The separations of a step are formed while the
 // step before it is decided, so that their chain of dependent instructions
 // does not wait in the open.
 template <int MODE, int EST, bool PM, bool WT>
 __device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W, const Tab32& T,
                                                const float2* B1, const float2* B2, const double* T1,
                                                const double* T2, int lane, const Chunk& C,
-                                               const float4& p, uint32_t ts, uint32_t te) {
+                                               const float4& p, double pr, uint32_t ts, uint32_t te) {
     if constexpr (kH32<MODE>) {
         // every pair of the chunk adds at most the largest region weight
         const uint32_t wmax = P.regs == nullptr ? 1u : (P.wsame > P.wdiff ? P.wsame : P.wdiff);
@@ -1334,6 +1369,11 @@ __device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W,
         const float nb = (float)-beta, be = (float)fma(2.0, beta, sq64(W.lx, W.ly, W.lz));
         q.nbeta = f4v{nb, nb, nb, nb};
         q.beta2 = f4v{be, be, be, be};
+    } else if constexpr (MODE == M_RADIAL) {
+        const float w = ok ? (float)(pr * P.rdA) : 0.f;
+        const float half = fmaf(-3.5f * 0x1p-24f, W.mt + fabsf(w), P.rB0);
+        q.nbeta = f4v{-w, -w, -w, -w};
+        q.beta2 = f4v{half, half, half, half};
     } else {
         q.nbz = f4v{-q.bz, -q.bz, -q.bz, -q.bz};
     }
@@ -1358,11 +1398,11 @@ __device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W,
             const float4* row = W.stage + (lane & 15);
             const float* arow = W.alpha + (lane & 15);
             float4 a = row[o];
-            float al = kMid<MODE> ? arow[o] : 0.f;
+            float al = kAlpha<MODE> ? arow[o] : 0.f;
             f4v v = sep_mfma<0>(a, q);
             for (;;) {
                 const float4 an = row[(o + 16u) & 48u];
-                const float aln = kMid<MODE> ? arow[(o + 16u) & 48u] : 0.f;
+                const float aln = kAlpha<MODE> ? arow[(o + 16u) & 48u] : 0.f;
                 CUTE_STEP(0)
                 CUTE_STEP(1)
                 CUTE_STEP(2)
@@ -1376,7 +1416,7 @@ __device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W,
             const float4* row = W.stage + (lane & 3);
             do {
                 const float4 a = row[o];
-                const float al = kMid<MODE> ? W.alpha[o + (uint32_t)(lane & 3)] : 0.f;
+                const float al = kAlpha<MODE> ? W.alpha[o + (uint32_t)(lane & 3)] : 0.f;
                 step_mfma<MODE, EST, WT, true, -1>(P, W, T, a, al, sep_mfma<-1>(a, q), q, C.lmask,
                                                    C.lj, lb, lw, lane, ts, te, o);
                 o += 4u;
@@ -1913,16 +1953,21 @@ __device__ void do_tile(const CountArgs& P, WaveState& W, SpanBuf& S, const floa
         Chunk N = C;
         N.filled = 0u;
         float4 pn = make_float4(0.f, 0.f, 0.f, 0.f);
+        double rn = 0.0;
         do {
             C = N;
             const float4 p = pn;
+            const double pr = rn;
             next_chunk<kSphere<MODE>>(P, W, S, N, tl, lane, part, plog);
-            if ((uint32_t)lane < N.filled) pn = P.B.p32[N.lj];
+            if ((uint32_t)lane < N.filled) {
+                pn = P.B.p32[N.lj];
+                if constexpr (MODE == M_RADIAL) rn = P.rB[N.lj];
+            }
             if (C.filled == 0u) continue;
             if (MODE == M_RMU_MID && W.mt < 0.f)
                 run_chunk<MODE, P_FP64, EST & E_LOG, PM, WT>(P, W, B1, B2, T1, T2, lane, C, tl.start, tl.end);
             else
-                run_chunk_mfma<MODE, EST, PM, WT>(P, W, tab, B1, B2, T1, T2, lane, C, p, tl.start, tl.end);
+                run_chunk_mfma<MODE, EST, PM, WT>(P, W, tab, B1, B2, T1, T2, lane, C, p, pr, tl.start, tl.end);
         } while (N.filled != 0u);
     } else {
         for (;;) {

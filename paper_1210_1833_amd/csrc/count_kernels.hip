@@ -41,7 +41,7 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count(CountArgs
     const int n1 = P.n1;
     const int n2p = P.n2 > 0 ? P.n2 : 0;
     constexpr bool H32 = kH32<MODE>;
-    const WgLds L = wg_lds<H32, kMfma<MODE, PREC, EST>>(smem, nwaves, n1, P.n2, P.hist_words);
+    const WgLds L = wg_lds<H32, kMfma<MODE, PREC, EST>, kAlpha<MODE>>(smem, nwaves, n1, P.n2, P.hist_words);
     double *T1 = L.T1, *T2 = L.T2;
     float2 *B1 = L.B1, *B2 = L.B2;
     unsigned char* hist0 = L.hist;
@@ -187,9 +187,10 @@ cute_status launch_count(const CountArgs& args, int mode, int prec, int est, int
         case M_SIGMAPI: return launch_prec<M_SIGMAPI>(args, prec, est, wg_waves, lds_bytes, stream, grid_used);
         case M_THETA: return launch_prec<M_THETA>(args, prec, est, wg_waves, lds_bytes, stream, grid_used);
         case M_RADIAL:
-            // few pairs fall inside an aperture: FP64 only
-            if (prec != P_FP64 || args.wA != nullptr)
-                return fail(CUTE_E_UNSUPPORTED, "radial counts are FP64 and unweighted");
+            if (prec == P_FP32O || args.wA != nullptr)
+                return fail(CUTE_E_UNSUPPORTED, "radial counts are exact and unweighted");
+            if (prec == P_FP32E)
+                return launch_one<M_RADIAL, P_FP32E, E_LIN, false>(args, wg_waves, lds_bytes, stream, grid_used);
             return launch_one<M_RADIAL, P_FP64, E_LIN, false>(args, wg_waves, lds_bytes, stream, grid_used);
         default: return fail(CUTE_E_INTERNAL, "unknown mode");
     }

@@ -23,13 +23,13 @@ constexpr int kQCap = 128;        // FP64 re-test queue entries per wave
 constexpr int kRowBatch = 48;     // stencil rows taken at a time (one per lane)
 constexpr int kSpanCap = 2 * kRowBatch + 2;  // neighbour spans buffered per wave: two per row, two of the home row
 constexpr int kStage = 64 * 16;    // staged home points of a tile (kMfma kernels), bytes per wave
-constexpr int kStageMid = 64 * 4;  // and their alpha (midpoint kinds)
+constexpr int kStageMid = 64 * 4;  // and their alpha (midpoint kinds) or redshifts (radial)
 constexpr int kList = 272;        // ambiguous pairs listed per wave (kMfma): 16 and a step's 256
 // LDS bytes per wave of a count kernel: queue, re-test statistics, spans, and
-// for kMfma kernels the stage and the list
-constexpr size_t wave_lds(bool mfma, bool mid) {
+// for kMfma kernels the stage (with alpha: kAlpha kinds) and the list
+constexpr size_t wave_lds(bool mfma, bool alpha) {
     return 9 * (size_t)kQCap + 16 + 9 * (size_t)kSpanCap +
-           (mfma ? kStage + (mid ? kStageMid : 0) + 2 * (size_t)kList : 0);
+           (mfma ? kStage + (alpha ? kStageMid : 0) + 2 * (size_t)kList : 0);
 }
 // The bytes per wave that the largest histogram is sized by: a count is
 // accepted exactly when its tables and counters fit beside these.
@@ -62,10 +62,13 @@ template <int MODE>
 constexpr bool kH32 = MODE == M_SIGMAPI || MODE == M_RMU_MID;
 
 // Workgroups per CU a count kernel is compiled for (its register budget):
-// five for the one-variable FP32_EDGE kernels, four for the others.
+// five for the FP32_EDGE kernels without a pair line of sight, four for the
+// others.
 template <int MODE, int PREC>
-constexpr int kWgPerCu = (PREC == P_FP32E && (MODE == M_THETA || MODE == M_MONO || MODE == M_RMU_Z)) ? 5 : 4;
+constexpr int kWgPerCu = PREC == P_FP32E && !kH32<MODE> ? 5 : 4;
 constexpr bool h32_mode(int mode) { return mode == M_SIGMAPI || mode == M_RMU_MID; }
+// Kinds whose matrix-core kernels stage one more value per home point.
+constexpr bool alpha_mode(int mode) { return h32_mode(mode) || mode == M_RADIAL; }
 
 // Count kernels whose separations come from the matrix cores (see step_mfma):
 // every FP32_EDGE kernel, r-mu against the midpoint with the mu decision in mu
@@ -200,10 +203,15 @@ struct CountArgs {
     const uint32_t* wA;
     const uint32_t* wB;
     // radial pairs (M_RADIAL): redshifts in sorted order and the chord^2 of
-    // the aperture; T1 then holds the unsquared redshift-difference edges
+    // the aperture; T1 then holds the unsquared redshift-difference edges.
+    // FP32_EDGE (linear edges): bins per unit of redshift, and the largest FP32
+    // chord^2 certainly inside the aperture (see radial_band)
     const double* rA;
     const double* rB;
     double ap2;
+    double rdA;
+    float rdIn;
+    int rdLow;                      // the first edge is above zero
     // the FP64 top threshold: a pair with d2 >= top64 is never counted
     // (T1[n1] for MONO, RMU and THETA; ap2 for radial pairs; for SIGMAPI
     // (sigma_max^2 + pi_max^2)(1 + 1e-12), rounded up)
@@ -314,6 +322,10 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
 // the precision path that serves a request: FP32_EDGE counts whose lengths
 // leave the range of the FP32 path run the FP64 classifier (same counts)
 int served_prec(int prec, const ItemGeom& g, const GridHost& A, const GridHost& B, const Plan& pl);
+// the precision path of a radial count over these edges, and the plan of its
+// aperture (a THETA binning) made into the radial one
+int radial_prec(const double* edges, int n);
+void plan_radial(const double* edges, int n, Plan& pl, int* prec);
 ErrModel max_err(const ErrModel& x, const ErrModel& y);
 void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl);
 cute_status plan_lds(Plan& pl, size_t extra, int* prec);
