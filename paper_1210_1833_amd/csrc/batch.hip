@@ -1,5 +1,5 @@
 // Host side of the batched counts: planning of the items, launch groups (one
-// per distinct binning), work chunks ordered by estimated cost, sorted-order
+// per distinct binning), the workgroups' shares by estimated cost, sorted-order
 // mask bits, the device counts, and the HIP graph that replays the launches.
 #include <string.h>
 
@@ -24,7 +24,7 @@ struct Group {
     std::vector<int> items;          // item indices, largest estimated cost first
     double *dT1 = nullptr, *dT2 = nullptr;
     float2 *dB1 = nullptr, *dB2 = nullptr;
-    uint32_t* dchunks = nullptr;
+    uint32_t *dlist = nullptr, *dfirst = nullptr;   // items, first item of each workgroup
 };
 
 }  // namespace
@@ -38,9 +38,10 @@ struct cute_batch {
     std::vector<int64_t> offset;     // offset of each item's counts
     std::vector<uint32_t> ntiles;    // home tiles per item
     int64_t total_words = 0;
-    unsigned long long* work = nullptr;   // counts | stats (4 per item) | chunk heads
+    unsigned long long* work = nullptr;   // counts | stats (4 per item) | heads (1 per item) | done (1 per group)
     size_t work_words = 0;
     CountArgs* dargs = nullptr;      // one per item
+    uint32_t* dntiles = nullptr;     // home tiles per item
     std::vector<void*> owned;        // device allocations (hipMalloc)
     std::vector<Tile*> tiles;        // per item (stream-ordered allocations)
     hipStream_t cap = nullptr;       // private stream used for capture
@@ -75,13 +76,13 @@ void release(cute_batch* b) {
     delete b;
 }
 
-// Enqueue one run: clear counts, statistics and chunk heads, then one
+// Enqueue one run: clear counts, statistics and task heads, then one
 // persistent launch per group. No allocation, memset or synchronisation.
 cute_status enqueue_run(cute_batch* b, hipStream_t s) {
     cute_status st = zero_u64(b->work, b->work_words, s);
     if (st != CUTE_OK) return st;
     for (const Group& g : b->groups) {
-        if (g.ba.nchunks == 0) continue;
+        if (g.ba.nlist == 0) continue;
         st = batch_launch(g.ba, g.pl.mode, g.prec, g.pl.est, g.grid, g.pl.lds, s);
         if (st != CUTE_OK) return st;
     }
@@ -161,9 +162,10 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
                          [&](int x, int y) { return geo[x].cost > geo[y].cost; });
     }
     // ---- device memory -------------------------------------------------------
-    b->work_words = (size_t)b->total_words + 4 * (size_t)n_items + b->groups.size();
+    b->work_words = (size_t)b->total_words + 5 * (size_t)n_items + b->groups.size();
     if ((s = owned_alloc(b, &b->work, b->work_words)) != CUTE_OK) return s;
     if ((s = owned_alloc(b, &b->dargs, (size_t)n_items)) != CUTE_OK) return s;
+    if ((s = owned_alloc(b, &b->dntiles, (size_t)n_items)) != CUTE_OK) return s;
     for (Group& G : b->groups) {
         if ((s = owned_alloc(b, &G.dT1, G.pl.T1.size())) != CUTE_OK) return s;
         if ((s = owned_alloc(b, &G.dT2, G.pl.T2.size())) != CUTE_OK) return s;
@@ -246,36 +248,44 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
     }
     CUTE_HIP(hipMemcpyAsync(b->dargs, args.data(), sizeof(CountArgs) * (size_t)n_items,
                             hipMemcpyHostToDevice, hs));
-    // ---- chunks: runs of home tiles of one item, largest items first --------
-    size_t head_slot = (size_t)b->total_words + 4 * (size_t)n_items;
-    std::vector<std::vector<uint32_t>> chunk_lists(b->groups.size());  // alive until the sync
+    CUTE_HIP(hipMemcpyAsync(b->dntiles, b->ntiles.data(), sizeof(uint32_t) * (size_t)n_items,
+                            hipMemcpyHostToDevice, hs));
+    // ---- the groups' item lists, largest first, and first items --------------
+    unsigned long long* heads = b->work + b->total_words + 4 * (size_t)n_items;
+    std::vector<std::vector<uint32_t>> lists(2 * b->groups.size());  // alive until the sync
     for (size_t gi = 0; gi < b->groups.size(); gi++) {
         Group& G = b->groups[gi];
-        uint64_t total = 0;
-        for (int i : G.items) total += b->ntiles[i];
-        // about 8 chunks per workgroup, 4 to 64 tiles each
-        uint64_t per = total / ((uint64_t)std::max(G.grid, 1) * 8);
-        per = std::max<uint64_t>(4, std::min<uint64_t>(64, per));
-        std::vector<uint32_t>& ch = chunk_lists[gi];
-        for (int i : G.items)
-            for (uint64_t t0 = 0; t0 < b->ntiles[i]; t0 += per) {
-                const uint64_t t1 = std::min<uint64_t>(t0 + per, b->ntiles[i]);
-                ch.push_back((uint32_t)i);
-                ch.push_back((uint32_t)t0);
-                ch.push_back((uint32_t)t1);
-                ch.push_back(0u);
-            }
-        const uint32_t nch = (uint32_t)(ch.size() / 4);
-        if ((s = owned_alloc(b, &G.dchunks, std::max<size_t>(ch.size(), 4))) != CUTE_OK) return s;
-        if (nch)
-            CUTE_HIP(hipMemcpyAsync(G.dchunks, ch.data(), ch.size() * 4, hipMemcpyHostToDevice, hs));
-        G.grid = (int)std::min<uint64_t>((uint64_t)G.grid, std::max<uint32_t>(nch, 1u));
+        std::vector<uint32_t>&list = lists[2 * gi], &first = lists[2 * gi + 1];
+        std::vector<double> cost;
+        double tiles = 0.0, homes = 0.0, total = 0.0;
+        for (int i : G.items) {
+            if (b->ntiles[i] == 0) continue;
+            list.push_back((uint32_t)i);
+            cost.push_back(std::max(geo[i].cost, 1.0));
+            tiles += (double)b->ntiles[i];
+            homes += (double)items[i].a->h.n;
+            total += cost.back();
+        }
+        const int plog = homes > 0.0 ? part_log(tiles, total / homes, ncu) : 0;
+        const double tasks = tiles * (double)(1 << plog);
+        G.grid = (int)std::max(1.0, std::min((double)G.grid, std::ceil(tasks / kWgWaves)));
+        if (!list.empty()) {
+            first = batch_first(cost, G.grid);
+            if ((s = owned_alloc(b, &G.dlist, list.size())) != CUTE_OK) return s;
+            if ((s = owned_alloc(b, &G.dfirst, first.size())) != CUTE_OK) return s;
+            CUTE_HIP(hipMemcpyAsync(G.dlist, list.data(), list.size() * 4, hipMemcpyHostToDevice, hs));
+            CUTE_HIP(hipMemcpyAsync(G.dfirst, first.data(), first.size() * 4, hipMemcpyHostToDevice, hs));
+        }
         BatchArgs& ba = G.ba;
         memset(&ba, 0, sizeof(ba));
         ba.items = b->dargs;
-        ba.chunks = G.dchunks;
-        ba.nchunks = nch;
-        ba.head = reinterpret_cast<uint32_t*>(b->work + head_slot++);
+        ba.list = G.dlist;
+        ba.nlist = (uint32_t)list.size();
+        ba.first = G.dfirst;
+        ba.ntiles = b->dntiles;
+        ba.plog = (uint32_t)plog;
+        ba.heads = heads;
+        ba.done = heads + n_items + gi;
         ba.n1 = G.pl.a.n1;
         ba.n2 = G.pl.a.n2;
         ba.nbins = G.pl.a.nbins;

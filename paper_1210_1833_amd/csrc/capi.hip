@@ -187,21 +187,6 @@ struct RadialSpec {
     double aperture;
 };
 
-// Parts per home tile (log2). A wave counts one task (a part of a tile) at a
-// time, so a count whose tiles hardly outnumber the wave slots ends with most
-// of the chip waiting for the last tiles: at 2 tiles per slot the r-mu count
-// of 250 000 points ran at 1200 Gpair/s, at 6 at 1550. The tiles are cut until
-// there are six tasks per slot, as long as a part keeps two chunks of
-// neighbours: below that the span generation of the part (a few thousand
-// cycles, as much as two chunks against a tile of 20 points) costs more than
-// the balance gives.
-int part_log(double ntiles, double neighbours, int ncu) {
-    const double slots = 16.0 * ncu, chunks = neighbours / 64.0;
-    int p = 0;
-    while (p < kMaxPartLog && ntiles * (double)(1 << p) < 6.0 * slots && chunks >= 4.0 * (double)(1 << p)) p++;
-    return p;
-}
-
 // One pair count; with max_tiles > 0 only an evenly spread sample of about
 // max_tiles home tiles is counted (the tuner's sample).
 // With fixed set, every device temporary is a slice of the caller's fixed

@@ -475,6 +475,8 @@ __device__ __forceinline__ C32 classify32(const CountArgs& P, const Tab32& T, fl
 // Periodic image of a neighbour point: (kx+1) | (ky+1) << 2 | (kz+1) << 4,
 // k in {-1, 0, 1}; the image lies at q + k L in the home point's frame.
 constexpr uint32_t kNoShift = 0x15u;
+// Beside it in a chunk's codes: the j > i test applies.
+constexpr uint32_t kSelfSpan = 0x80u;
 
 __device__ __forceinline__ float shift32(uint32_t code, int axis, float Lf) {
     return (float)((int)((code >> (2 * axis)) & 3u) - 1) * Lf;
@@ -1008,6 +1010,42 @@ struct Column {
     f4v b2, nbz, nbeta, beta2;
 };
 
+// The arguments that every step reads, in registers. The batched kernels read
+// their arguments through a pointer, and the compiler took these up again from
+// memory in every step (six loads, each a wait): PIN keeps it from doing so.
+struct Hot {
+    float s1, e1a, s2, e2a, skip32, muB2, rB0, dA1, out_lo, rdIn;
+    uint32_t top1, top2, hs1, hs2, rdLow;
+};
+template <bool PIN>
+__device__ __forceinline__ Hot hot_args(const CountArgs& P) {
+    Hot h;
+    auto f = [](float x) {
+        if constexpr (PIN) asm volatile("" : "+s"(x));
+        return x;
+    };
+    auto u = [](uint32_t x) {
+        if constexpr (PIN) asm volatile("" : "+s"(x));
+        return x;
+    };
+    h.s1 = f(P.s1);
+    h.e1a = f(P.e1a);
+    h.s2 = f(P.s2);
+    h.e2a = f(P.e2a);
+    h.skip32 = f(P.skip32);
+    h.muB2 = f(P.muB2);
+    h.rB0 = f(P.rB0);
+    h.dA1 = f(P.dA1);
+    h.out_lo = f(P.out_lo);
+    h.rdIn = P.rdIn;
+    h.top1 = u(P.top1);
+    h.top2 = u(P.top2);
+    h.hs1 = u((uint32_t)P.hs1);
+    h.hs2 = u((uint32_t)P.hs2);
+    h.rdLow = (uint32_t)P.rdLow;
+    return h;
+}
+
 // Decision of the lanes' pairs from v = |s|^2 and dz: the lanes whose pair is
 // certainly in the bin at LDS address *off (lt: the lanes whose pair is not
 // past the top edge). Lane masks throughout: the logic of a step is scalar
@@ -1022,7 +1060,7 @@ struct Column {
 // Radial: d the redshift difference in bins, ss the half-width; the bin counts
 // from 2^23 + 1 as for r-mu, *skip receives the lanes certainly outside the bins.
 template <int MODE, int EST>
-__device__ __forceinline__ uint64_t decide(const CountArgs& P, const Tab32& T, float v, float d, float ss,
+__device__ __forceinline__ uint64_t decide(const Hot& P, const Tab32& T, float v, float d, float ss,
                                            uint64_t lt, uint32_t lb, uint32_t* off, uint64_t* skip) {
     if constexpr (MODE == M_SIGMAPI) {
         const float ll = ss - v;
@@ -1137,7 +1175,7 @@ __device__ __forceinline__ f4v sep_mfma(const float4& a, const Column& q) {
 // separations v) against the chunk. Ambiguous pairs go to the wave's list, which has room for all of
 // a step's.
 template <int MODE, int EST, bool WT, bool MASKED, int K>
-__device__ __forceinline__ void step_mfma(const CountArgs& P, WaveState& W, const Tab32& T, const float4& a,
+__device__ __forceinline__ void step_mfma(const CountArgs& P, const Hot& H, WaveState& W, const Tab32& T, const float4& a,
                                           float al, const f4v& v, const Column& q, bool lmask, uint32_t lj,
                                           uint32_t lb, uint32_t lw, int lane, uint32_t ts,
                                           uint32_t te, uint32_t o) {
@@ -1145,7 +1183,7 @@ __device__ __forceinline__ void step_mfma(const CountArgs& P, WaveState& W, cons
     // nothing to count or re-test
     uint64_t lt[4];
 #pragma unroll
-    for (int u = 0; u < 4; u++) lt[u] = __builtin_amdgcn_ballot_w64(v[u] < P.skip32);
+    for (int u = 0; u < 4; u++) lt[u] = __builtin_amdgcn_ballot_w64(v[u] < H.skip32);
     if ((lt[0] | lt[1] | lt[2] | lt[3]) == 0ull) return;
     constexpr int B = K < 0 ? 0 : 2, I = K < 0 ? 0 : K;
     f4v d = {0.f, 0.f, 0.f, 0.f}, ss = d;
@@ -1163,7 +1201,7 @@ __device__ __forceinline__ void step_mfma(const CountArgs& P, WaveState& W, cons
 #pragma unroll
     for (int u = 0; u < 4; u++) {
         uint64_t skip = 0;
-        cnt[u] = decide<MODE, EST>(P, T, v[u], d[u], ss[u], lt[u], lb, &off[u], &skip);
+        cnt[u] = decide<MODE, EST>(H, T, v[u], d[u], ss[u], lt[u], lb, &off[u], &skip);
         amb[u] = lt[u] & ~(cnt[u] | skip);
         if constexpr (MASKED) {
             const uint32_t h = ts + o + (uint32_t)u;
@@ -1190,7 +1228,7 @@ __device__ __forceinline__ void step_mfma(const CountArgs& P, WaveState& W, cons
             if (amb[u] == 0ull) continue;
             uint64_t m = amb[u];
             if constexpr (MODE != M_SIGMAPI) {
-                m &= ~__builtin_amdgcn_ballot_w64(v[u] < P.out_lo);
+                m &= ~__builtin_amdgcn_ballot_w64(v[u] < H.out_lo);
             } else if (P.sp_low) {
                 const float ll = ss[u] - v[u], sl2 = d[u] * d[u], c2 = fmaf(v[u], ll, -sl2);
                 m &= ~(__builtin_amdgcn_ballot_w64(fmaf(P.sp_wsbot, ll, c2) <= -T.mt) |
@@ -1323,30 +1361,48 @@ struct Chunk {
     bool masked;       // some lane needs the j > i test
     bool shifted;      // some lane holds a periodic image
     uint32_t lj;       // per lane: neighbour index
-    uint32_t lcode;    // per lane: image code
-    bool lmask;        // per lane: j > i test applies
+    uint32_t lcode;    // per lane: image code | kSelfSpan
 };
 
-// A chunk against the tile's staged home points. q: the lanes' neighbours in
-// FP32 (and redshifts, radial), loaded a chunk ahead. The separations of a step are formed while the
+// What a chunk's lanes load of their neighbours, a chunk ahead: the FP32 point,
+// the redshift (radial), the point weight (pixel maps) or region (region
+// passes), the word of the point mask. (Loaded where they are used, the
+// regions alone cost the region pass the whole latency of every chunk's loads:
+// loads return in order.)
+struct Near {
+    float4 p;
+    double r;
+    uint32_t w, mask;
+};
+template <int MODE, bool PM, bool WT>
+__device__ __forceinline__ void load_near(const CountArgs& P, Near& n, uint32_t j) {
+    n.p = P.B.p32[j];
+    if constexpr (MODE == M_RADIAL) n.r = P.rB[j];
+    if constexpr (WT) n.w = P.wB[j];
+    else if (PM && P.regs != nullptr) n.w = P.regs[j];
+    if (PM && P.mbB != nullptr) n.mask = P.mbB[j >> 5];
+}
+
+// A chunk against the tile's staged home points. p: the lanes' neighbours. The separations of a step are formed while the
 // step before it is decided, so that their chain of dependent instructions
 // does not wait in the open.
 template <int MODE, int EST, bool PM, bool WT>
-__device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W, const Tab32& T,
+__device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, const Hot& H, WaveState& W, const Tab32& T,
                                                const float2* B1, const float2* B2, const double* T1,
                                                const double* T2, int lane, const Chunk& C,
-                                               const float4& p, double pr, uint32_t ts, uint32_t te) {
+                                               const Near& p, uint32_t ts, uint32_t te) {
     if constexpr (kH32<MODE>) {
         // every pair of the chunk adds at most the largest region weight
-        const uint32_t wmax = P.regs == nullptr ? 1u : (P.wsame > P.wdiff ? P.wsame : P.wdiff);
+        const uint32_t wmax = !PM || P.regs == nullptr ? 1u : (P.wsame > P.wdiff ? P.wsame : P.wdiff);
         h32_account(P, W, lane, C.filled * (te - ts) * wmax);
     }
     bool ok = (uint32_t)lane < C.filled;
     // a neighbour excluded by the point mask leaves its lane idle
-    if (PM && P.mbB != nullptr && ok) ok = ((P.mbB[C.lj >> 5] >> (C.lj & 31u)) & 1u) == 0u;
+    if (PM && P.mbB != nullptr) ok = ok && ((p.mask >> (C.lj & 31u)) & 1u) == 0u;
     uint32_t lw = 1u;
-    if constexpr (WT) lw = ok ? P.wB[C.lj] : 1u;
-    else if (P.regs != nullptr) lw = ok ? pair_weight(P, C.lj) : 1u;
+    if constexpr (WT) lw = p.w;
+    else if (PM && P.regs != nullptr) lw = p.w == (uint32_t)P.region ? P.wsame : P.wdiff;
+    const bool self = (C.lcode & kSelfSpan) != 0u;
     // the neighbour in the home grid's FP32 frame (q - (cA - cB) for two open
     // grids, or its periodic image q + k L: only one of the two is ever
     // non-zero), then in the tile's
@@ -1358,9 +1414,9 @@ __device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W,
         kz -= shift32(C.lcode, 2, Lf);
     }
     Column q;
-    q.bx = ok ? (p.x - kx) - W.ox : 0.f;
-    q.by = ok ? (p.y - ky) - W.oy : 0.f;
-    q.bz = ok ? (p.z - kz) - W.oz : 0.f;
+    q.bx = ok ? (p.p.x - kx) - W.ox : 0.f;
+    q.by = ok ? (p.p.y - ky) - W.oy : 0.f;
+    q.bz = ok ? (p.p.z - kz) - W.oz : 0.f;
     const double b2d = sq64(q.bx, q.by, q.bz);
     const float b2 = ok ? (float)b2d : kFar;
     q.b2 = f4v{b2, b2, b2, b2};
@@ -1370,7 +1426,7 @@ __device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W,
         q.nbeta = f4v{nb, nb, nb, nb};
         q.beta2 = f4v{be, be, be, be};
     } else if constexpr (MODE == M_RADIAL) {
-        const float w = ok ? (float)(pr * P.rdA) : 0.f;
+        const float w = ok ? (float)(p.r * P.rdA) : 0.f;
         const float half = fmaf(-3.5f * 0x1p-24f, W.mt + fabsf(w), P.rB0);
         q.nbeta = f4v{-w, -w, -w, -w};
         q.beta2 = f4v{half, half, half, half};
@@ -1385,7 +1441,7 @@ __device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W,
 #define CUTE_STEP(K)                                                                               \
     {                                                                                              \
         const f4v w = sep_mfma<(K + 1) & 3>(K == 3 ? an : a, q);                                   \
-        step_mfma<MODE, EST, WT, false, K>(P, W, T, a, al, v, q, false, 0u, lb, lw, lane, ts, te, o); \
+        step_mfma<MODE, EST, WT, false, K>(P, H, W, T, a, al, v, q, false, 0u, lb, lw, lane, ts, te, o); \
         v = w;                                                                                     \
         o += 4u;                                                                                   \
         if (o >= n || W.nlist > kList - 256u) break;                                               \
@@ -1417,7 +1473,7 @@ __device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, WaveState& W,
             do {
                 const float4 a = row[o];
                 const float al = kAlpha<MODE> ? W.alpha[o + (uint32_t)(lane & 3)] : 0.f;
-                step_mfma<MODE, EST, WT, true, -1>(P, W, T, a, al, sep_mfma<-1>(a, q), q, C.lmask,
+                step_mfma<MODE, EST, WT, true, -1>(P, H, W, T, a, al, sep_mfma<-1>(a, q), q, self,
                                                    C.lj, lb, lw, lane, ts, te, o);
                 o += 4u;
             } while (o < n && W.nlist <= kList - 256u && (C.masked || (o & 15u) != 0u));
@@ -1437,13 +1493,14 @@ __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, co
     constexpr uint32_t U = 4;
     if constexpr (kH32<MODE>) {
         // every pair of the chunk adds at most the largest region weight
-        const uint32_t wmax = P.regs == nullptr ? 1u : (P.wsame > P.wdiff ? P.wsame : P.wdiff);
+        const uint32_t wmax = !PM || P.regs == nullptr ? 1u : (P.wsame > P.wdiff ? P.wsame : P.wdiff);
         h32_account(P, W, lane, C.filled * (te - ts) * wmax);
     }
     bool lvalid = (uint32_t)lane < C.filled;
     // a neighbour excluded by the point mask leaves its lane idle
     if (PM && P.mbB != nullptr && lvalid) lvalid = ((P.mbB[C.lj >> 5] >> (C.lj & 31u)) & 1u) == 0u;
-    const uint32_t lw = lvalid ? (WT ? P.wB[C.lj] : pair_weight(P, C.lj)) : 1u;
+    const uint32_t lw = lvalid ? (WT ? P.wB[C.lj] : PM ? pair_weight(P, C.lj) : 1u) : 1u;
+    const bool self = (C.lcode & kSelfSpan) != 0u;
     if constexpr (PREC == P_FP64) {
         double qx = 0.0, qy = 0.0, qz = 0.0, sx = 0.0, sy = 0.0, sz = 0.0, qr = 0.0;
         if (MODE == M_RADIAL && lvalid) qr = P.rB[C.lj];
@@ -1460,10 +1517,10 @@ __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, co
     {                                                                                           \
         uint32_t h = ts;                                                                        \
         for (; h + U <= te; h += U)                                                             \
-            step64<MODE, EST, PM, WT, MSK, SH, U>(P, W, T1, T2, lane, lvalid, C.lmask, C.lj, qx, qy, qz, \
+            step64<MODE, EST, PM, WT, MSK, SH, U>(P, W, T1, T2, lane, lvalid, self, C.lj, qx, qy, qz, \
                                           sx, sy, sz, lw, h, qr);                               \
         for (; h < te; h++)                                                                     \
-            step64<MODE, EST, PM, WT, MSK, SH, 1>(P, W, T1, T2, lane, lvalid, C.lmask, C.lj, qx, qy, qz, \
+            step64<MODE, EST, PM, WT, MSK, SH, 1>(P, W, T1, T2, lane, lvalid, self, C.lj, qx, qy, qz, \
                                           sx, sy, sz, lw, h, qr);                               \
     }
         if (C.masked) {
@@ -1501,11 +1558,11 @@ __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, co
         uint32_t h = ts;                                                                           \
         for (; h + U <= te; h += U)                                                                \
             step32<MODE, PREC, EST, PM, WT, MSK, LOW, U>(P, W, tab, B1, B2, T1, T2, lane, lvalid,  \
-                                                     C.lmask, C.lj, C.lcode, qx, qy, qz, qlx, qly, \
+                                                     self, C.lj, C.lcode, qx, qy, qz, qlx, qly, \
                                                      qlz, lb, lw, ts, ambh, hsum, h);              \
         for (; h < te; h++)                                                                        \
             step32<MODE, PREC, EST, PM, WT, MSK, LOW, 1>(P, W, tab, B1, B2, T1, T2, lane, lvalid,  \
-                                                     C.lmask, C.lj, C.lcode, qx, qy, qz, qlx, qly, \
+                                                     self, C.lj, C.lcode, qx, qy, qz, qlx, qly, \
                                                      qlz, lb, lw, ts, ambh, hsum, h);              \
     }
         if (C.masked) {
@@ -1529,22 +1586,20 @@ __device__ __forceinline__ int imod(int a, int n) {
 // Span list of one batch of stencil rows (in LDS) and where the walk over a
 // tile's neighbours stands (wave-uniform).
 struct SpanBuf {
-    uint32_t* a;   // first neighbour index
-    uint32_t* b;   // one past the last
+    uint2* e;      // position of the span's first neighbour in the concatenation of the
+                   // batch's spans, and that neighbour's index minus this position
     uint8_t* f;    // image code | kSelfSpan
-    int nrows, row0;            // rows of the stencil, first row not taken yet
-    uint32_t n, k, skip, left;  // spans of the batch, next one, points to pass over, to take
-    uint32_t p0, p1, pf;        // the span at hand: its points not taken yet, its code
+    int nrows, row0;   // rows of the stencil, first row not taken yet
+    uint32_t n, k;     // spans of the batch, the one at hand
+    uint32_t pos, end; // positions not taken yet
+    uint32_t own;      // the j > i test applies to positions below it
 };
-constexpr uint32_t kSelfSpan = 0x80u;   // the j > i test applies
-
 __device__ __forceinline__ SpanBuf span_buf(const WgLds& l, int wave) {
     SpanBuf S;
-    S.a = l.spans + (size_t)wave * 2 * kSpanCap;
-    S.b = S.a + kSpanCap;
+    S.e = reinterpret_cast<uint2*>(l.spans + (size_t)wave * 2 * kSpanCap);
     S.f = l.scodes + (size_t)wave * kSpanCap;
     S.nrows = S.row0 = 0;
-    S.n = S.k = S.skip = S.left = S.p0 = S.p1 = S.pf = 0u;
+    S.n = S.k = S.pos = S.end = S.own = 0u;
     return S;
 }
 
@@ -1787,8 +1842,8 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane) {
 // neighbours a part takes a run of whole chunks, so that the parts of a tile
 // share out its chunks evenly.
 template <bool SPH>
-__device__ __forceinline__ void next_rows(const CountArgs& Pk, SpanBuf& S, const Tile& tl, int lane,
-                                          uint32_t part, uint32_t plog) {
+__device__ __forceinline__ void next_rows(const CountArgs& Pk, WaveState& W, SpanBuf& S, const Tile& tl,
+                                          int lane, uint32_t part, uint32_t plog) {
     // the stencil again for every batch of rows, from the arguments' copy in
     // memory: nothing of it is live while pairs are evaluated (the asm keeps
     // the compiler from loading or deriving it ahead of the walk, where it
@@ -1804,7 +1859,7 @@ __device__ __forceinline__ void next_rows(const CountArgs& Pk, SpanBuf& S, const
     r.ca = r.cb = kNoShift;
     if (lane < kRowBatch && S.row0 + lane < t.nrows) r = row_spans<SPH>(P, t, S.row0 + lane);
     S.row0 += kRowBatch;
-    S.left = 0u;
+    S.pos = S.end = S.own = 0u;
     const uint32_t na = r.a1 > r.a0 ? r.a1 - r.a0 : 0u, nb = r.b1 > r.b0 ? r.b1 - r.b0 : 0u;
     // the tile's own spans, from the lane that holds its row
     const uint64_t mh = __builtin_amdgcn_ballot_w64(r.m1 != 0u);
@@ -1825,100 +1880,82 @@ __device__ __forceinline__ void next_rows(const CountArgs& Pk, SpanBuf& S, const
     const uint32_t c1 = (uint32_t)(((uint64_t)nc * (part + 1u)) >> plog);
     if (c0 >= c1) return;
     const uint32_t v0 = c0 << 6, v1 = (c1 << 6) < total ? c1 << 6 : total;
-    S.left = v1 - v0;
+    S.pos = v0;
+    S.end = v1;
+    S.own = nm;
+    // the pairs of these neighbours: with the tile's own points j > i (or j !=
+    // i), so neighbour ts + p pairs with p home points
+    const uint32_t q = v1 < nm ? v1 : nm, nq = q > v0 ? q - v0 : 0u, nhome = t.te - t.ts;
+    W.evals += (uint64_t)nhome * (v1 - v0 - nq);
+    W.evals += P.selfx ? (uint64_t)(nhome - 1u) * nq : (uint64_t)(v0 + q - 1u) * nq / 2u;
     const uint64_t ma = __builtin_amdgcn_ballot_w64(na != 0u);
     const uint64_t mb = __builtin_amdgcn_ballot_w64(nb != 0u);
     const uint32_t pos = nown + lanes_below(ma) + lanes_below(mb);
     S.n = nown + (uint32_t)(__popcll(ma) + __popcll(mb));
+    // (starts clipped to v0, so that no lane below it takes a span)
+    auto put = [&](uint32_t k, uint32_t start, uint32_t first, uint32_t code) {
+        S.e[k] = make_uint2(start > v0 ? start : v0, first - start);
+        S.f[k] = (uint8_t)code;
+    };
     wave_lds_fence();
     if (lane == 0) {
-        if (nm) {
-            S.a[0] = t.ts;
-            S.b[0] = m1;
-            S.f[0] = (uint8_t)(kNoShift | kSelfSpan);
-        }
-        if (nh) {
-            S.a[nown - 1u] = h0;
-            S.b[nown - 1u] = h1;
-            S.f[nown - 1u] = (uint8_t)kNoShift;
-        }
+        if (nm) put(0u, 0u, t.ts, kNoShift | kSelfSpan);
+        if (nh) put(nown - 1u, nm, h0, kNoShift);
     }
-    if (na) {
-        S.a[pos] = r.a0;
-        S.b[pos] = r.a1;
-        S.f[pos] = (uint8_t)r.ca;
-    }
-    if (nb) {
-        const uint32_t q = pos + (na ? 1u : 0u);
-        S.a[q] = r.b0;
-        S.b[q] = r.b1;
-        S.f[q] = (uint8_t)r.cb;
-    }
-    // the span that holds neighbour v0 of the concatenation
+    const uint32_t sa = end - na - nb;
+    if (na) put(pos, sa, r.a0, r.ca);
+    if (nb) put(pos + (na ? 1u : 0u), sa + na, r.b0, r.cb);
+    // the span that holds position v0, or the one before it in its row
     S.k = 0u;
-    S.skip = v0;
-    if (v0 >= own && v0 > 0u) {
-        const int l = (int)__popcll(__builtin_amdgcn_ballot_w64(end <= v0));
-        S.k = lane_u32(pos, l);
-        S.skip = v0 - (lane_u32(end, l) - lane_u32(na + nb, l));
-    }
+    if (v0 >= own) S.k = lane_u32(pos, (int)__popcll(__builtin_amdgcn_ballot_w64(end <= v0)));
     wave_lds_fence();
 }
 
 // Assemble the next chunk of the walk over a tile's neighbours (filled = 0 at
-// its end), and account its pair evaluations.
+// its end): every lane takes the last span that starts at or before its
+// position. A span costs four VALU instructions and no scalar bookkeeping but
+// its number. (Copying span by span took about 100 scalar instructions each and
+// as much time as the pairs of a tile of 16 points: the r-mu count of 1e6
+// points takes 2.60 ms with this, 2.73 with that; of 2.5e5, 1.28 and 1.42.)
 template <bool SPH>
 __device__ __forceinline__ void next_chunk(const CountArgs& P, WaveState& W, SpanBuf& S, Chunk& C,
                                            const Tile& tl, int lane, uint32_t part, uint32_t plog) {
-    const uint32_t ts = tl.start, te = tl.end, l = (uint32_t)lane;
     C.filled = 0;
     C.masked = false;
     C.shifted = false;
-    while (C.filled < 64u) {
-        if (S.p0 < S.p1) {
-            const uint32_t room = 64u - C.filled;
-            const uint32_t take = S.p1 - S.p0 < room ? S.p1 - S.p0 : room;
-            const bool masked = (S.pf & kSelfSpan) != 0u;
-            const uint32_t code = S.pf & 0x3fu;
-            if (masked && P.selfx) {
-                // the tile against itself: every pair but the point with itself
-                W.evals += (uint64_t)(te - ts) * take - take;
-            } else if (masked) {
-                // lanes with neighbour j pair with the home points h < j: sum of (j - ts)
-                const uint64_t lo_ = S.p0 - ts, hi_ = S.p0 + take - 1u - ts;
-                W.evals += (lo_ + hi_) * (hi_ - lo_ + 1u) / 2u;
-            } else {
-                W.evals += (uint64_t)(te - ts) * take;
+    for (;;) {
+        if (S.pos < S.end) {
+            // (lanes filled from the batch before have positions below S.pos,
+            // perhaps negative ones; positions stay below 2^31)
+            const int v = (int)(S.pos - C.filled) + lane;
+            uint2 e = S.e[S.k];
+            uint32_t f = S.f[S.k];
+            for (;;) {
+                const uint32_t kn = S.k + 1u < S.n ? S.k + 1u : S.k;
+                const uint2 en = S.e[kn];
+                const uint32_t fn = S.f[kn];
+                const bool in = v >= (int)e.x;
+                C.lj = in ? (uint32_t)v + e.y : C.lj;
+                C.lcode = in ? f : C.lcode;
+                if (kn == S.k || __builtin_amdgcn_ballot_w64(v >= (int)en.x) == 0ull) break;
+                S.k = kn;
+                e = en;
+                f = fn;
             }
-            if (l >= C.filled) {   // (the lanes past the span are set again, or not used)
-                C.lj = S.p0 + (l - C.filled);
-                C.lcode = code;
-                C.lmask = masked;
-            }
+            const uint32_t room = 64u - C.filled, left = S.end - S.pos;
+            const uint32_t take = left < room ? left : room;
+            C.masked = C.masked | (S.pos < S.own);
             C.filled += take;
-            C.masked = C.masked | masked;
-            C.shifted = C.shifted | (code != kNoShift);
-            S.p0 += take;
-        } else if (S.left > 0u && S.k < S.n) {
-            uint32_t a0 = uni(S.a[S.k]), a1 = uni(S.b[S.k]);
-            S.pf = uni((uint32_t)S.f[S.k]);
-            S.k++;
-            if (S.skip >= a1 - a0) {
-                S.skip -= a1 - a0;
-                continue;
-            }
-            a0 += S.skip;
-            S.skip = 0u;
-            if (a1 - a0 > S.left) a1 = a0 + S.left;
-            S.left -= a1 - a0;
-            S.p0 = a0;
-            S.p1 = a1;
+            S.pos += take;
+            if (C.filled == 64u) break;
         } else if (S.row0 < S.nrows) {
-            next_rows<SPH>(P, S, tl, lane, part, plog);
+            next_rows<SPH>(P, W, S, tl, lane, part, plog);
         } else {
             break;
         }
     }
+    if (!SPH && P.periodic)
+        C.shifted = __builtin_amdgcn_ballot_w64((uint32_t)lane < C.filled && (C.lcode & ~kSelfSpan) != kNoShift) != 0ull;
 }
 
 // Count the pairs of one home tile, or one of its 2^plog parts.
@@ -1935,14 +1972,14 @@ __device__ void do_tile(const CountArgs& P, WaveState& W, SpanBuf& S, const floa
     }
     S.row0 = 0;
     S.nrows = 1;
-    S.n = S.k = S.skip = S.left = S.p0 = S.p1 = 0u;
+    S.n = S.k = S.pos = S.end = S.own = 0u;
     Chunk C;
     C.lj = 0;
     C.lcode = kNoShift;
-    C.lmask = false;
     if constexpr (kMfma<MODE, PREC, EST>) {
         stage_home<MODE, PM>(P, W, tl, lane);
         Tab32 tab = make_tab32<EST>(P, B1, B2);
+        const Hot hot = hot_args<PM>(P);
         if constexpr (MODE == M_SIGMAPI) tab.mt = W.mt;
         if constexpr (MODE == M_RMU_MID) {
             tab.d0 = W.mb0;
@@ -1952,22 +1989,21 @@ __device__ void do_tile(const CountArgs& P, WaveState& W, SpanBuf& S, const floa
         // counted
         Chunk N = C;
         N.filled = 0u;
-        float4 pn = make_float4(0.f, 0.f, 0.f, 0.f);
-        double rn = 0.0;
+        Near pn;
+        pn.p = make_float4(0.f, 0.f, 0.f, 0.f);
+        pn.r = 0.0;
+        pn.w = 1u;
+        pn.mask = 0u;
         do {
             C = N;
-            const float4 p = pn;
-            const double pr = rn;
+            const Near p = pn;
             next_chunk<kSphere<MODE>>(P, W, S, N, tl, lane, part, plog);
-            if ((uint32_t)lane < N.filled) {
-                pn = P.B.p32[N.lj];
-                if constexpr (MODE == M_RADIAL) rn = P.rB[N.lj];
-            }
+            if ((uint32_t)lane < N.filled) load_near<MODE, PM, WT>(P, pn, N.lj);
             if (C.filled == 0u) continue;
             if (MODE == M_RMU_MID && W.mt < 0.f)
                 run_chunk<MODE, P_FP64, EST & E_LOG, PM, WT>(P, W, B1, B2, T1, T2, lane, C, tl.start, tl.end);
             else
-                run_chunk_mfma<MODE, EST, PM, WT>(P, W, tab, B1, B2, T1, T2, lane, C, p, pr, tl.start, tl.end);
+                run_chunk_mfma<MODE, EST, PM, WT>(P, hot, W, tab, B1, B2, T1, T2, lane, C, p, tl.start, tl.end);
         } while (N.filled != 0u);
     } else {
         for (;;) {

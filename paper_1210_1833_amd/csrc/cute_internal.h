@@ -225,9 +225,13 @@ struct CountArgs {
 // the binning whose tables are given here.
 struct BatchArgs {
     const CountArgs* items;
-    const uint32_t* chunks;         // per chunk: item, first tile, end tile, 0
-    uint32_t nchunks;
-    uint32_t* head;                 // next chunk to pop (global counter)
+    const uint32_t* list;           // items of the launch
+    uint32_t nlist;
+    const uint32_t* first;          // per workgroup: the entry of list it starts with
+    const uint32_t* ntiles;         // home tiles of each item (indexed by item)
+    uint32_t plog;                  // every tile is counted in 2^plog parts
+    unsigned long long* heads;      // per item: its next task (a tile's part)
+    unsigned long long* done;       // entries of the list whose tasks are all taken
     int n1, n2, nbins, copies, hist_words;
     const double* T1;
     const double* T2;
@@ -324,6 +328,10 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
 int served_prec(int prec, const ItemGeom& g, const GridHost& A, const GridHost& B, const Plan& pl);
 // the precision path of a radial count over these edges, and the plan of its
 // aperture (a THETA binning) made into the radial one
+// parts per home tile (log2) of a count with about ntiles tiles, each against
+// that many neighbours
+int part_log(double ntiles, double neighbours, int ncu);
+std::vector<uint32_t> batch_first(const std::vector<double>& cost, int grid);
 int radial_prec(const double* edges, int n);
 void plan_radial(const double* edges, int n, Plan& pl, int* prec);
 ErrModel max_err(const ErrModel& x, const ErrModel& y);

@@ -185,13 +185,13 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
         std::vector<uint32_t> at(off.begin(), off.end() - 1);
         for (const Tile& t : ht) grouped[at[hreg[t.start]]++] = t;
     }
-    // device buffers of the launch: tables, stencil, tiles, items, chunks, histograms
+    // device buffers of the launch: tables, stencil, tiles, items, histograms
     Tile* dtiles;
     double *dT1, *dT2;
     float2 *dB1, *dB2;
     int4* dst;
     CountArgs* dargs;
-    unsigned long long* work;  // K * nbins histograms, 4 stats per item, chunk head
+    unsigned long long* work;  // K * nbins histograms, 4 stats and a head per item, done
     if ((s = tmp.alloc(&dtiles, std::max<size_t>(ntiles, 1))) != CUTE_OK) return s;
     if ((s = tmp.alloc(&dT1, pl.T1.size())) != CUTE_OK) return s;
     if ((s = tmp.alloc(&dT2, pl.T2.size())) != CUTE_OK) return s;
@@ -199,7 +199,7 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
     if ((s = tmp.alloc(&dB2, pl.band2.size())) != CUTE_OK) return s;
     if ((s = tmp.alloc(&dst, std::max<size_t>(geo.stencil.size(), 1))) != CUTE_OK) return s;
     if ((s = tmp.alloc(&dargs, (size_t)K)) != CUTE_OK) return s;
-    const size_t wwords = (size_t)K * nbins + 4 * (size_t)K + 1;
+    const size_t wwords = (size_t)K * nbins + 5 * (size_t)K + 1;
     if ((s = tmp.alloc(&work, wwords)) != CUTE_OK) return s;
     if (ntiles)
         CUTE_HIP(hipMemcpyAsync(dtiles, grouped.data(), ntiles * sizeof(Tile), hipMemcpyHostToDevice,
@@ -236,31 +236,39 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
     }
     CUTE_HIP(hipMemcpyAsync(dargs, args.data(), sizeof(CountArgs) * (size_t)K, hipMemcpyHostToDevice,
                             hs));
-    // chunks: runs of up to 64 tiles of one region, regions in order
+    // the regions that have tiles, the workgroups shared out by their tiles
     int per_cu = 1, ncu = 0;
     if ((s = batch_prepare(pl.mode, kprec, pl.est, pl.lds, &per_cu)) != CUTE_OK) return s;
     CUTE_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    const uint64_t grid_max = (uint64_t)per_cu * ncu;
-    uint64_t per = ntiles / std::max<uint64_t>(grid_max * 8, 1);
-    per = std::max<uint64_t>(4, std::min<uint64_t>(64, per));
-    std::vector<uint32_t> ch;
-    for (int k = 0; k < K; k++)
-        for (uint32_t t0 = 0; t0 < off[k + 1] - off[k]; t0 += (uint32_t)per) {
-            ch.push_back((uint32_t)k);
-            ch.push_back(t0);
-            ch.push_back(std::min<uint32_t>(t0 + (uint32_t)per, off[k + 1] - off[k]));
-            ch.push_back(0u);
-        }
-    const uint32_t nch = (uint32_t)(ch.size() / 4);
-    uint32_t* dch = nullptr;
-    if ((s = tmp.alloc(&dch, std::max<size_t>(ch.size(), 4))) != CUTE_OK) return s;
-    if (nch) CUTE_HIP(hipMemcpyAsync(dch, ch.data(), ch.size() * 4, hipMemcpyHostToDevice, hs));
+    const int plog = part_log((double)ntiles, geo.cost / (double)R.n, ncu);
+    const int gsz = (int)std::min<uint64_t>((uint64_t)per_cu * ncu,
+                                            (((uint64_t)ntiles << plog) + kWgWaves - 1) / kWgWaves);
+    std::vector<uint32_t> lst, first, nt((size_t)K);
+    std::vector<double> share;
+    for (int k = 0; k < K; k++) {
+        nt[k] = off[k + 1] - off[k];
+        if (nt[k] == 0) continue;
+        lst.push_back((uint32_t)k);
+        share.push_back((double)nt[k]);
+    }
+    if (!lst.empty()) first = batch_first(share, gsz);
+    // [ntiles per region | list | first]
+    std::vector<uint32_t> tab(nt);
+    tab.insert(tab.end(), lst.begin(), lst.end());
+    tab.insert(tab.end(), first.begin(), first.end());
+    uint32_t* dtab = nullptr;
+    if ((s = tmp.alloc(&dtab, tab.size())) != CUTE_OK) return s;
+    CUTE_HIP(hipMemcpyAsync(dtab, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, hs));
     BatchArgs ba;
     memset(&ba, 0, sizeof(ba));
     ba.items = dargs;
-    ba.chunks = dch;
-    ba.nchunks = nch;
-    ba.head = reinterpret_cast<uint32_t*>(work + (size_t)K * nbins + 4 * (size_t)K);
+    ba.list = dtab + K;
+    ba.nlist = (uint32_t)lst.size();
+    ba.first = dtab + K + lst.size();
+    ba.ntiles = dtab;
+    ba.plog = (uint32_t)plog;
+    ba.heads = work + (size_t)K * nbins + 4 * (size_t)K;
+    ba.done = ba.heads + K;
     ba.n1 = pl.a.n1;
     ba.n2 = pl.a.n2;
     ba.nbins = nbins;
@@ -271,9 +279,8 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
     ba.band1 = dB1;
     ba.band2 = dB2;
     double ms = 0.0;
-    if (nch) {
+    if (ntiles) {
         EventTimer timer(hs);
-        const int gsz = (int)std::min<uint64_t>(grid_max, nch);
         if ((s = batch_launch(ba, pl.mode, kprec, pl.est, gsz, pl.lds, hs)) != CUTE_OK) return s;
         timer.stop();
         ms = timer.elapsed_ms();

@@ -451,6 +451,36 @@ int served_prec(int prec, const ItemGeom& g, const GridHost& A, const GridHost& 
     return pl.rmax >= (mid ? 1e-6 : 1e-12) && big <= (mid ? 1e8 : 1e15) ? prec : P_FP64;
 }
 
+// Parts per home tile (log2). A wave counts one task (a part of a tile) at a
+// time, so a count whose tiles hardly outnumber the wave slots ends with most
+// of the chip waiting for the last tiles: at 2 tiles per slot the r-mu count
+// of 250 000 points ran at 1200 Gpair/s, at 6 at 1550. The tiles are cut until
+// there are six tasks per slot, as long as a part keeps two chunks of
+// neighbours: below that the span generation of the part (a few thousand
+// cycles, as much as two chunks against a tile of 20 points) costs more than
+// the balance gives.
+int part_log(double ntiles, double neighbours, int ncu) {
+    const double slots = 16.0 * ncu, chunks = neighbours / 64.0;
+    int p = 0;
+    while (p < kMaxPartLog && ntiles * (double)(1 << p) < 6.0 * slots && chunks >= 4.0 * (double)(1 << p)) p++;
+    return p;
+}
+
+// The item each workgroup of a batched launch starts with: the workgroups are
+// shared out by the items' estimated costs, in the order of the list.
+std::vector<uint32_t> batch_first(const std::vector<double>& cost, int grid) {
+    double total = 0.0;
+    for (double c : cost) total += c;
+    std::vector<uint32_t> f((size_t)grid);
+    double cum = cost[0];
+    size_t k = 0;
+    for (int g = 0; g < grid; g++) {
+        while (k + 1 < cost.size() && cum <= total * (g + 0.5) / grid) cum += cost[++k];
+        f[(size_t)g] = (uint32_t)k;
+    }
+    return f;
+}
+
 // Rounding bands of the midpoint line of sight (sigma, pi and mu against the
 // pair midpoint, Sec. 2.1 with l = p + q). Every constant below is a term of
 // the bound derived in the design notes; the FP32 operation order it assumes
@@ -844,7 +874,8 @@ void plan_radial(const double* edges, int n, Plan& pl, int* prec) {
 
 // LDS of a count workgroup of kWgWaves waves: tables, the shared 64-bit
 // histogram, per-wave queues and span buffers (plus extra bytes). About 40 KB
-// per workgroup keeps four workgroups (16 waves) on a CU; the copies of the
+// per workgroup keeps four workgroups (16 waves) on a CU, 32000 bytes five
+// where the kernel's registers allow them; the copies of the
 // histogram are cut to fit, then the budget is relaxed for very large
 // histograms (fewer workgroups per CU).
 // The kMfma kernels need more per wave than the bytes the limit is set by:
@@ -870,7 +901,10 @@ cute_status plan_lds(Plan& pl, size_t extra, int* prec) {
         fixed = tables + (size_t)kWgWaves * wave_lds(false, false) + ctl;
     }
     int C = 0;
-    for (size_t budget : {(size_t)40 * 1024, (size_t)80 * 1024, lds_max}) {
+    // (the kernels of five workgroups per CU: 32000 bytes each; 1500 bins run
+    // 4 % faster with one copy and five than with two copies and four)
+    const size_t best = mfma_plan(pl, *prec) && !h32 ? 32000 : 40 * 1024;
+    for (size_t budget : {best, (size_t)40 * 1024, (size_t)80 * 1024, lds_max}) {
         if (fixed + pad + es * (size_t)nbins > budget) continue;
         size_t cmax = (budget - fixed - pad) / (es * (size_t)nbins);
         C = 1;
