@@ -1268,11 +1268,60 @@ __device__ __forceinline__ void queue_list(const CountArgs& P, WaveState& W, con
     W.nlist = 0;
 }
 
+// The canonical FP64 bin of a pair when a guess from FP32 holds: the edges
+// around the guessed bin are compared once, without a search. False when the
+// guess is off by a bin, at zero separation and in the closed last mu edge: the
+// pair then goes through classify64, so that a search costs a step nothing
+// unless one of its pairs needs it. (The predicates are those of classify64:
+// the products with the squared mu edges grow with the edge, so a pair between
+// two of them has no larger edge below it.) With the search in every step, the
+// 1.8e9 candidate pairs of an r-mu count of 4e5 points cost 50 VALU instructions
+// each and 2.9 ms; they cost 24 and 1.6 ms. VALU bound (78 % busy), beside LDS
+// reads of the edges (57 %).
+struct EdgePair {
+    double lo, hi;
+};
+__device__ __forceinline__ EdgePair edges_at(uint32_t base, uint32_t kb) {
+    typedef const __attribute__((address_space(3))) double* lds_dp;
+    const lds_dp p = (lds_dp)(uintptr_t)((kb << 3) + base);
+    EdgePair e;
+    e.lo = p[0];
+    e.hi = p[1];
+    return e;
+}
+template <int MODE, int EST>
+__device__ __forceinline__ bool guessed64(const CountArgs& P, const Tab32& T, double dz, double d2, uint32_t* bin) {
+    const float v = (float)d2;
+    const float rinv = __builtin_amdgcn_rsqf(v);
+    float ts;
+    if constexpr (MODE == M_THETA) {
+        const float c = v * rinv;
+        const float th = fmaf(c * v, 1.0f / 24.0f, c);  // 2 asin(c/2) to third order
+        ts = (est_log(EST) ? __builtin_amdgcn_logf(th) : th) + P.s1;
+    } else {
+        ts = est_log(EST) ? __builtin_amdgcn_logf(v) + P.s1 : fmaf(v, rinv, P.s1);
+    }
+    const uint32_t k1 = est_bits(ts, P.e1a, T, kBias + (uint32_t)(P.n1 - 1));
+    const EdgePair e = edges_at(T.tb1, k1);
+    bool ok = (e.lo <= d2) & (d2 < e.hi);
+    if constexpr (MODE == M_RMU_Z) {
+        const uint32_t k2 = est_bits(fmaf(fabsf((float)dz), rinv, P.s2), P.e2a, T, kBias + (uint32_t)(P.n2 - 1));
+        const EdgePair m = edges_at(T.tb2, k2);
+        const double num = dz * dz;
+        ok = ok & (num >= m.lo * d2) & (num < m.hi * d2);
+        *bin = __umul24(k1, (uint32_t)P.hs1) + __umul24(k2, (uint32_t)P.hs2);
+    } else {
+        *bin = __umul24(k1, (uint32_t)P.hs1);
+    }
+    return ok;
+}
+
 template <int MODE, int EST, bool PM, bool WT, bool MASKED, bool SHIFTED, uint32_t U>
 __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const double* T1,
                                        const double* T2, int lane, bool lvalid, bool lmask,
                                        uint32_t lj, double qx, double qy, double qz, double sx, double sy,
-                                       double sz, uint32_t lw, uint32_t h, double qr) {
+                                       double sz, uint32_t lw, uint32_t h, double qr,
+                                       const Tab32& T, uint32_t lb) {
     double hx[U], hy[U], hz[U];
     load_points64<U>(P.A.p64, h, hx, hy, hz);
     bool hv[U];
@@ -1294,6 +1343,62 @@ __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const d
             dmin = u == 0 ? d2 : fmin(dmin, d2);
         }
         if (__builtin_amdgcn_ballot_w64(dmin < P.top64) == 0ull) return;
+    }
+    if constexpr (MODE == M_MONO || MODE == M_THETA || MODE == M_RMU_Z) {
+        uint32_t off[U];
+        bool cnt[U], amb[U], any = false;
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+            double dx = hx[u] - qx, dy = hy[u] - qy, dz = hz[u] - qz;
+            if (SHIFTED) {
+                dx = dx - sx;
+                dy = dy - sy;
+                dz = dz - sz;
+            }
+            const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
+            bool act = lvalid & hv[u] & (d2 < P.top64);
+            if constexpr (MASKED) act = act & (!lmask | (lj > h + u) | ((P.selfx != 0) & (lj < h + u)));
+            const bool ok = guessed64<MODE, EST>(P, T, dz, d2, &off[u]);
+            cnt[u] = act & ok;
+            amb[u] = act & !ok;
+            any = any | amb[u];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++)
+            if (cnt[u]) lds_add<kH32<MODE>>(off[u] + lb, WT ? (uint64_t)lw * hw[u] : (uint64_t)lw);
+        if (__builtin_amdgcn_ballot_w64(any) == 0ull) return;
+#pragma unroll 1
+        for (uint32_t u = 0; u < U; u++) {
+            bool a = false;
+            double x = 0.0, y = 0.0, z = 0.0;
+            uint32_t w = 1u;
+#pragma unroll
+            for (uint32_t t = 0; t < U; t++)
+                if (t == u) {
+                    a = amb[t];
+                    x = hx[t];
+                    y = hy[t];
+                    z = hz[t];
+                    w = hw[t];
+                }
+            if (!a) continue;
+            double dx = x - qx, dy = y - qy, dz = z - qz;
+            if (SHIFTED) {
+                dx = dx - sx;
+                dy = dy - sy;
+                dz = dz - sz;
+            }
+            const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
+            const float v = (float)d2;
+            const int k1 = guess1<MODE == M_THETA ? M_THETA : M_MONO, EST>(P, v);
+            int k2 = 0;
+            if constexpr (MODE == M_RMU_Z)
+                k2 = guess_lin(fabsf((float)dz) * __builtin_amdgcn_rsqf(v), P.e2a, P.e2b, P.n2m1);
+            const uint32_t bin = classify64<MODE>(P, T1, T2, dx, dy, dz, 0.0, 0.0, 0.0, k1, k2);
+            if (bin != kNoBin)
+                hist_add<kH32<MODE>>(W.hist, bin, P.copies, lane, WT ? (uint64_t)lw * w : (uint64_t)lw);
+        }
+        return;
     }
     double hr[U];
     if constexpr (MODE == M_RADIAL) {
@@ -1329,12 +1434,7 @@ __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const d
             continue;
         }
         const float v = (float)d2;
-        if (MODE == M_MONO || MODE == M_THETA) {
-            k1 = guess1<MODE, EST>(P, v);
-        } else if (MODE == M_RMU_Z) {
-            k1 = guess1<M_MONO, EST>(P, v);
-            k2 = guess_lin(fabsf((float)dz) * __builtin_amdgcn_rsqf(v), P.e2a, P.e2b, P.n2m1);
-        } else if (MODE == M_RMU_MID) {
+        if (MODE == M_RMU_MID) {
             k1 = guess1<M_MONO, EST>(P, v);
             const float sl = (float)fma(dz, lz, fma(dy, ly, dx * lx));
             const float ll = (float)fma(lz, lz, fma(ly, ly, lx * lx));
@@ -1503,6 +1603,12 @@ __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, co
     const bool self = (C.lcode & kSelfSpan) != 0u;
     if constexpr (PREC == P_FP64) {
         double qx = 0.0, qy = 0.0, qz = 0.0, sx = 0.0, sy = 0.0, sz = 0.0, qr = 0.0;
+        // the tables here are the canonical edges, and this lane's histogram copy
+        Tab32 tab = make_tab32<EST>(P, B1, B2);
+        tab.tb1 = lds_addr(T1) - (kBias << 3);
+        tab.tb2 = lds_addr(T2) - (kBias << 3);
+        const uint32_t lb = lds_addr(W.hist) +
+                            ((uint32_t)lane & (uint32_t)(P.copies - 1)) * (kH32<MODE> ? 4u : 8u);
         if (MODE == M_RADIAL && lvalid) qr = P.rB[C.lj];
         if (lvalid) {
             const P64 q = P.B.p64[C.lj];
@@ -1518,10 +1624,10 @@ __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, co
         uint32_t h = ts;                                                                        \
         for (; h + U <= te; h += U)                                                             \
             step64<MODE, EST, PM, WT, MSK, SH, U>(P, W, T1, T2, lane, lvalid, self, C.lj, qx, qy, qz, \
-                                          sx, sy, sz, lw, h, qr);                               \
+                                          sx, sy, sz, lw, h, qr, tab, lb);                               \
         for (; h < te; h++)                                                                     \
             step64<MODE, EST, PM, WT, MSK, SH, 1>(P, W, T1, T2, lane, lvalid, self, C.lj, qx, qy, qz, \
-                                          sx, sy, sz, lw, h, qr);                               \
+                                          sx, sy, sz, lw, h, qr, tab, lb);                               \
     }
         if (C.masked) {
             if (C.shifted) CUTE_RUN64(true, true) else CUTE_RUN64(true, false)
