@@ -20,18 +20,23 @@ namespace cute {
 namespace {
 
 // Sum the workgroup's histogram copies into counts (one atomic per non-empty
-// bin) and clear them (counters of 4 bytes when H32, else 8).
+// bin) and clear them (counters of 4 bytes when H32, else 8; with hi set, the
+// high halves go there).
 template <bool H32>
-__device__ void flush_hist(unsigned char* hist0, int nbins, int copies, unsigned long long* counts) {
+__device__ void flush_hist(unsigned char* hist0, int nbins, int copies, unsigned long long* counts,
+                           unsigned long long* hi) {
     typedef typename std::conditional<H32, uint32_t, unsigned long long>::type word;
     for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
-        uint64_t s = 0;
+        uint64_t s = 0, t = 0;
         word* hh = reinterpret_cast<word*>(hist0) + (size_t)b * copies;
         for (int c = 0; c < copies; c++) {
-            s += hh[c];
+            const uint64_t w = hh[c];
+            s += H32 || hi == nullptr ? w : (uint64_t)(uint32_t)w;
+            if (!H32 && hi != nullptr) t += w >> 32;
             hh[c] = 0;
         }
         if (s) atomicAdd(&counts[b], (unsigned long long)s);
+        if (t) atomicAdd(&hi[b], (unsigned long long)t);
     }
 }
 
@@ -73,7 +78,7 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
     float2 *B1 = L.B1, *B2 = L.B2;
     unsigned char* hist0 = L.hist;
     uint32_t* ctl = L.ctl;        // [0] the next entry of the list
-    uint32_t* budget = ctl + 4;   // 32-bit histograms only
+    uint32_t* budget = H32 ? ctl + 4 : ctl + 1;   // 32-bit counters and pairs of them
     for (int i = threadIdx.x; i <= n1; i += blockDim.x) T1[i] = BA.T1[i];
     for (int i = threadIdx.x; i <= n2p; i += blockDim.x) T2[i] = n2p ? BA.T2[i] : 0.0;
     if (PREC != P_FP64) {
@@ -84,7 +89,7 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
     }
     for (size_t i = threadIdx.x; i < L.hbytes / 4; i += blockDim.x) reinterpret_cast<uint32_t*>(hist0)[i] = 0u;
     for (int i = threadIdx.x; i < 2 * nwaves; i += blockDim.x) L.rstat[i] = 0ull;
-    if (H32 && threadIdx.x == 0) *budget = 0u;
+    if (threadIdx.x == 0) *budget = 0u;
 
     WaveState W = wave_state(L, wave);
     W.budget = budget;
@@ -136,8 +141,8 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
         }
         // every wave is done with the item
         if (__syncthreads_or(any ? 1 : 0)) {
-            flush_hist<H32>(hist0, BA.nbins, BA.copies, P.counts);
-            if (H32 && threadIdx.x == 0) *budget = 0u;
+            flush_hist<H32>(hist0, BA.nbins, BA.copies, P.counts, P.counts_hi);
+            if (threadIdx.x == 0) *budget = 0u;
         }
         if (wave == 0) {
             const uint32_t nx = next_item(BA, pos, lane);

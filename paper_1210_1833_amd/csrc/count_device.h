@@ -606,12 +606,26 @@ __device__ __attribute__((noinline)) void h32_flush(uint32_t* hist, int words, i
     }
 }
 
+// The same for 64-bit counters that hold two 32-bit ones (region passes: pairs
+// with a neighbour in the home region in the low half, others in the high).
+__device__ __attribute__((noinline)) void h64_flush(unsigned long long* hist, int words, int copies,
+                                                    unsigned long long* lo, unsigned long long* hi, int lane) {
+    const uint32_t lc = (uint32_t)__builtin_ctz((unsigned)copies);
+    for (int w = lane; w < words; w += 64) {
+        const unsigned long long v = atomicExch(&hist[w], 0ull);
+        if ((uint32_t)v) atomicAdd(&lo[(uint32_t)w >> lc], v & 0xffffffffull);
+        if (v >> 32) atomicAdd(&hi[(uint32_t)w >> lc], v >> 32);
+    }
+}
+
 // Account the pair evaluations of a chunk to the workgroup's budget of a
-// 32-bit histogram (every pair adds at most wmax to one counter). A wave
+// 32-bit histogram (every pair adds at most wmax to one counter; PAIR: one of
+// two halves, at most 1). A wave
 // reports its evaluations every h32_report of them; the wave that finds the
 // budget at h32_flush or more resets it and moves the histogram. A counter
 // then holds at most h32_flush plus what the waves have not reported or were
 // adding during the move (a few h32_report), far below 2^32.
+template <bool PAIR = false>
 __device__ __forceinline__ void h32_account(const CountArgs& P, WaveState& W, int lane,
                                             uint32_t evals) {
     W.pend += evals;
@@ -623,12 +637,16 @@ __device__ __forceinline__ void h32_account(const CountArgs& P, WaveState& W, in
     W.pend = 0;
     if (now < P.h32_flush) return;
     if (lane == 0) atomicExch(W.budget, 0u);
-    h32_flush(reinterpret_cast<uint32_t*>(W.hist), P.hist_words, P.copies, P.counts, lane);
+    if constexpr (PAIR)
+        h64_flush(reinterpret_cast<unsigned long long*>(W.hist), P.hist_words, P.copies, P.counts,
+                  P.counts_hi, lane);
+    else
+        h32_flush(reinterpret_cast<uint32_t*>(W.hist), P.hist_words, P.copies, P.counts, lane);
 }
 
 // Weight of a pair in a region pass: wsame if the neighbour lies in the home
 // region, wdiff otherwise (1 outside region passes).
-__device__ __forceinline__ uint32_t pair_weight(const CountArgs& P, uint32_t j) {
+__device__ __forceinline__ uint64_t pair_weight(const CountArgs& P, uint32_t j) {
     if (P.regs == nullptr) return 1u;
     return P.regs[j] == (uint16_t)P.region ? P.wsame : P.wdiff;
 }
@@ -799,7 +817,7 @@ __device__ __forceinline__ void step32(const CountArgs& P, WaveState& W, const T
                                        const float2* B1, const float2* B2, const double* T1,
                                        const double* T2, int lane, bool lvalid, bool lmask,
                                        uint32_t lj, uint32_t lcode, float qx, float qy, float qz,
-                                       float qlx, float qly, float qlz, uint32_t lb, uint32_t lw,
+                                       float qlx, float qly, float qlz, uint32_t lb, uint64_t lw,
                                        uint32_t ts, uint64_t& ambh, uint64_t& hsum, uint32_t h) {
     float hx[U], hy[U], hz[U];
     load_points32<U>(P.A.p32, h, hx, hy, hz);
@@ -859,7 +877,7 @@ __device__ __forceinline__ void step32(const CountArgs& P, WaveState& W, const T
     }
 #pragma unroll
     for (uint32_t u = 0; u < U; u++)
-        if (cnt[u]) lds_add<kH32<MODE>>(off[u], WT ? (uint64_t)lw * hw[u] : (uint64_t)lw);
+        if (cnt[u]) lds_add<kH32<MODE>>(off[u], WT ? lw * hw[u] : lw);
     if (PREC == P_FP32E && any_amb) {
         // remember the pair for the end of the chunk: bit (home - ts) of this
         // lane's mask, and the home offset in the wave's mask
@@ -1177,7 +1195,7 @@ __device__ __forceinline__ f4v sep_mfma(const float4& a, const Column& q) {
 template <int MODE, int EST, bool WT, bool MASKED, int K>
 __device__ __forceinline__ void step_mfma(const CountArgs& P, const Hot& H, WaveState& W, const Tab32& T, const float4& a,
                                           float al, const f4v& v, const Column& q, bool lmask, uint32_t lj,
-                                          uint32_t lb, uint32_t lw, int lane, uint32_t ts,
+                                          uint32_t lb, uint64_t lw, int lane, uint32_t ts,
                                           uint32_t te, uint32_t o) {
     // every pair past the top edge (the clean-out side of its rounding band):
     // nothing to count or re-test
@@ -1320,7 +1338,7 @@ template <int MODE, int EST, bool PM, bool WT, bool MASKED, bool SHIFTED, uint32
 __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const double* T1,
                                        const double* T2, int lane, bool lvalid, bool lmask,
                                        uint32_t lj, double qx, double qy, double qz, double sx, double sy,
-                                       double sz, uint32_t lw, uint32_t h, double qr,
+                                       double sz, uint64_t lw, uint32_t h, double qr,
                                        const Tab32& T, uint32_t lb) {
     double hx[U], hy[U], hz[U];
     load_points64<U>(P.A.p64, h, hx, hy, hz);
@@ -1365,7 +1383,7 @@ __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const d
         }
 #pragma unroll
         for (uint32_t u = 0; u < U; u++)
-            if (cnt[u]) lds_add<kH32<MODE>>(off[u] + lb, WT ? (uint64_t)lw * hw[u] : (uint64_t)lw);
+            if (cnt[u]) lds_add<kH32<MODE>>(off[u] + lb, WT ? lw * hw[u] : lw);
         if (__builtin_amdgcn_ballot_w64(any) == 0ull) return;
 #pragma unroll 1
         for (uint32_t u = 0; u < U; u++) {
@@ -1396,7 +1414,7 @@ __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const d
                 k2 = guess_lin(fabsf((float)dz) * __builtin_amdgcn_rsqf(v), P.e2a, P.e2b, P.n2m1);
             const uint32_t bin = classify64<MODE>(P, T1, T2, dx, dy, dz, 0.0, 0.0, 0.0, k1, k2);
             if (bin != kNoBin)
-                hist_add<kH32<MODE>>(W.hist, bin, P.copies, lane, WT ? (uint64_t)lw * w : (uint64_t)lw);
+                hist_add<kH32<MODE>>(W.hist, bin, P.copies, lane, WT ? lw * w : lw);
         }
         return;
     }
@@ -1451,7 +1469,7 @@ __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const d
     }
 #pragma unroll
     for (uint32_t u = 0; u < U; u++)
-        if (cnt[u]) hist_add<kH32<MODE>>(W.hist, bin[u], P.copies, lane, WT ? (uint64_t)lw * hw[u] : (uint64_t)lw);
+        if (cnt[u]) hist_add<kH32<MODE>>(W.hist, bin[u], P.copies, lane, WT ? lw * hw[u] : lw);
 }
 
 // The chunk being assembled from neighbour spans (per-lane fields in VGPRs,
@@ -1493,13 +1511,15 @@ __device__ __forceinline__ void run_chunk_mfma(const CountArgs& P, const Hot& H,
                                                const Near& p, uint32_t ts, uint32_t te) {
     if constexpr (kH32<MODE>) {
         // every pair of the chunk adds at most the largest region weight
-        const uint32_t wmax = !PM || P.regs == nullptr ? 1u : (P.wsame > P.wdiff ? P.wsame : P.wdiff);
+        const uint32_t wmax = !PM || P.regs == nullptr ? 1u : (uint32_t)(P.wsame > P.wdiff ? P.wsame : P.wdiff);
         h32_account(P, W, lane, C.filled * (te - ts) * wmax);
+    } else if (PM && P.counts_hi != nullptr) {
+        h32_account<true>(P, W, lane, C.filled * (te - ts));
     }
     bool ok = (uint32_t)lane < C.filled;
     // a neighbour excluded by the point mask leaves its lane idle
     if (PM && P.mbB != nullptr) ok = ok && ((p.mask >> (C.lj & 31u)) & 1u) == 0u;
-    uint32_t lw = 1u;
+    uint64_t lw = 1u;
     if constexpr (WT) lw = p.w;
     else if (PM && P.regs != nullptr) lw = p.w == (uint32_t)P.region ? P.wsame : P.wdiff;
     const bool self = (C.lcode & kSelfSpan) != 0u;
@@ -1593,13 +1613,15 @@ __device__ void run_chunk(const CountArgs& P, WaveState& W, const float2* B1, co
     constexpr uint32_t U = 4;
     if constexpr (kH32<MODE>) {
         // every pair of the chunk adds at most the largest region weight
-        const uint32_t wmax = !PM || P.regs == nullptr ? 1u : (P.wsame > P.wdiff ? P.wsame : P.wdiff);
+        const uint32_t wmax = !PM || P.regs == nullptr ? 1u : (uint32_t)(P.wsame > P.wdiff ? P.wsame : P.wdiff);
         h32_account(P, W, lane, C.filled * (te - ts) * wmax);
+    } else if (PM && P.counts_hi != nullptr) {
+        h32_account<true>(P, W, lane, C.filled * (te - ts));
     }
     bool lvalid = (uint32_t)lane < C.filled;
     // a neighbour excluded by the point mask leaves its lane idle
     if (PM && P.mbB != nullptr && lvalid) lvalid = ((P.mbB[C.lj >> 5] >> (C.lj & 31u)) & 1u) == 0u;
-    const uint32_t lw = lvalid ? (WT ? P.wB[C.lj] : PM ? pair_weight(P, C.lj) : 1u) : 1u;
+    const uint64_t lw = lvalid ? (WT ? P.wB[C.lj] : PM ? pair_weight(P, C.lj) : 1u) : 1u;
     const bool self = (C.lcode & kSelfSpan) != 0u;
     if constexpr (PREC == P_FP64) {
         double qx = 0.0, qy = 0.0, qz = 0.0, sx = 0.0, sy = 0.0, sz = 0.0, qr = 0.0;

@@ -107,6 +107,8 @@ struct CountArgs {
     int plog;                       // every tile is counted in 2^plog parts (see do_tile)
     uint32_t* work_head;            // tasks (tile parts) popped beyond the first of every wave
     unsigned long long* counts;     // nbins global uint64 counts
+    unsigned long long* counts_hi;  // when set, 64-bit LDS counters hold two of 32 bits: the low
+                                    // halves are summed into counts, the high ones into this
     unsigned long long* stats;      // [0] pair evals, [1] retests, [2] flips, [3] tiles
     int geom;                       // cute_geometry
     int is_auto;
@@ -192,7 +194,7 @@ struct CountArgs {
     // neighbours are one catalog; regs == nullptr otherwise (weight 1)
     const uint16_t* regs;
     int region;
-    uint32_t wsame, wdiff;
+    uint64_t wsame, wdiff;
     int selfx;
     // point masks (batched counts): bit i of word i / 32 set = sorted point i
     // excluded; nullptr = no mask
@@ -349,9 +351,15 @@ cute_status exclusive_scan(const uint32_t* in, uint32_t* out, size_t n, hipStrea
 
 // home tiles of grid g (runs of <= 64 points in one row, x-extent <= max_w
 // cells); *tiles is a stream-ordered allocation owned by the caller
-// (reg: optional sorted-order region per point; tiles then never mix regions)
-cute_status build_tiles(const GridHost& g, int max_w, hipStream_t s, Tile** tiles,
-                        uint32_t* ntiles, const uint16_t* reg = nullptr);
+cute_status build_tiles(const GridHost& g, int max_w, hipStream_t s, Tile** tiles, uint32_t* ntiles);
+
+// The home tiles of g, a grid whose points are sorted by region inside each
+// cell, cut where the region changes and grouped by region: rc holds each
+// point's (region << 16 | cell along x). off (device, K + 1 words) receives the
+// offset of each region's tiles; with out == nullptr only that (the tiles are
+// then written by a second call with fill, K words of scratch).
+cute_status region_tiles(const GridHost& g, int max_w, const uint32_t* rc, uint32_t K, uint32_t* off,
+                         uint32_t* fill, Tile* out, hipStream_t s);
 
 // The same tiles without a wait for their count (no region labels): *tiles
 // holds *cap = tile_count_bound slots, rows in order, with empty tiles
