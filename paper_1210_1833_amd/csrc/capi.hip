@@ -242,7 +242,8 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
 
     // ---- device buffers: one block, filled by one copy ------------------------
     // [T1 | T2 | B1 | B2 | stencil | args | counts, stats[4], head, tile count,
-    //  tile-slot overflow]
+    //  tile-slot overflow | bucket counts of the tile order]; copied with its
+    // zeroes, so that nothing is cleared by a launch of its own
     auto up16 = [](size_t v) { return (v + 15) & ~(size_t)15; };
     const size_t oT1 = 0;
     const size_t oT2 = oT1 + up16(pl.T1.size() * 8);
@@ -251,13 +252,14 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     const size_t oST = oB2 + up16(pl.band2.size() * 8);
     const size_t oAR = oST + up16(geo.stencil.size() * sizeof(int4));
     const size_t oWK = oAR + up16(sizeof(CountArgs));
-    const size_t total = oWK + ((size_t)nbins + 7) * 8;
+    const size_t oBK = oWK + ((size_t)nbins + 7) * 8;
+    const size_t total = oBK + kTileBuckets * sizeof(uint32_t);
     if (fixed != nullptr) {
         if (rad != nullptr || max_tiles > 0)
             return fail(CUTE_E_INTERNAL, "fixed scratch serves plain counts only");
         // every temporary of the count, with the slot bound of its tiles
         const uint64_t bound = A.n > 0 && B.n > 0 ? tile_count_bound(A, geo.max_w) : 0;
-        const size_t need = DevArena::cost<unsigned char>(total) +
+        const size_t need = DevArena::cost<unsigned char>(oBK) +
                             2 * DevArena::cost<Tile>((size_t)bound) +
                             2 * DevArena::cost<uint32_t>((size_t)bound) +
                             DevArena::cost<uint32_t>(256);
@@ -271,14 +273,14 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     DevArena& tmp = fixed ? mem_fixed : mem_pool;
     unsigned char* blob = nullptr;
     if ((s = tmp.get(&blob, total)) != CUTE_OK) return s;
-    // pinned staging: [blob image | argument block | read-back of counts and
-    // statistics]; the lease outlives every copy below (declared after tmp,
-    // released first, which records its event after the copies)
-    const size_t hArgs = up16(total), hBack = hArgs + up16(sizeof(CountArgs));
+    // pinned staging: [blob image | read-back of counts and statistics]; the
+    // lease outlives every copy below (declared after tmp, released first,
+    // which records its event after the copies)
+    const size_t hBack = up16(total);
     HostStage stage(hs);
     std::vector<unsigned char> pageable;
     unsigned char* hb = nullptr;
-    const size_t hbytes = hBack + ((size_t)nbins + 7) * 8;
+    const size_t hbytes = hBack + (oBK - oWK);
     if (fixed) {
         // pageable host memory: no pinned allocation (the copies then wait)
         pageable.resize(hbytes);
@@ -286,7 +288,7 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     } else if ((s = stage.get(hbytes, &hb)) != CUTE_OK) {
         return s;
     }
-    // tables and zeroed counts in one copy (the argument block follows later)
+    // tables, arguments and zeroed counts (one copy, below)
     memset(hb, 0, total);
     memcpy(hb + oT1, pl.T1.data(), pl.T1.size() * 8);
     memcpy(hb + oT2, pl.T2.data(), pl.T2.size() * 8);
@@ -294,7 +296,6 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     memcpy(hb + oB2, pl.band2.data(), pl.band2.size() * 8);
     if (!geo.stencil.empty())
         memcpy(hb + oST, geo.stencil.data(), geo.stencil.size() * sizeof(int4));
-    CUTE_HIP(hipMemcpyAsync(blob, hb, total, hipMemcpyHostToDevice, hs));
     unsigned long long* work = reinterpret_cast<unsigned long long*>(blob + oWK);
     // the tile count and the slot-overflow flag, when the tiles are built
     // without a wait
@@ -326,75 +327,102 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     a.stats = work + nbins;
     a.work_head = reinterpret_cast<uint32_t*>(work + nbins + 4);
 
-    Tile* tiles = nullptr;
-    uint32_t ntiles = 0;   // the count, or with dev_count the capacity of tiles
-    bool dev_count = false;
-    // tiles from the fixed area are never freed
-    auto drop_tiles = [&]() {
-        if (!fixed) dfree(tiles, hs);
-        tiles = nullptr;
-    };
-    int plog = 0;
-    if (A.n > 0 && B.n > 0) {
-        // Tiles are built into slots without waiting for their count (the
-        // longest-first reordering compacts them and leaves the count on the
-        // device) unless the bound on their number is far above the points'
-        // worth of tiles (very sparse grids: memory and time would go into
-        // empty slots) or the tuner wants to sample them on the host.
-        const uint64_t min_tiles = ((uint64_t)A.n + A.tile_max - 1) / A.tile_max;
-        const uint64_t bound = tile_count_bound(A, geo.max_w);
-        if (fixed || (max_tiles == 0 && bound <= std::max<uint64_t>(65536, 4 * min_tiles))) {
-            if ((s = build_tiles_nowait(A, geo.max_w, hs, &tiles, &ntiles, slot_overflow,
-                                        fixed ? &tmp : nullptr)) != CUTE_OK)
-                return s;
-            dev_count = true;
-        } else if ((s = build_tiles(A, geo.max_w, hs, &tiles, &ntiles)) != CUTE_OK) {
-            return s;
-        }
-        if (max_tiles == 0) {
-            int ncu = 0;
-            CUTE_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-            // the tiles lie between the two bounds when their number is not
-            // known yet: their geometric mean stands for it
-            const double nt = dev_count ? std::sqrt((double)min_tiles * (double)bound) : (double)ntiles;
-            plog = part_log(nt, geo.cost / (double)A.n, ncu);
-        }
-    }
-    if ((s = order_tiles(a, &tiles, ntiles, hs, dev_count ? ntiles_dev : nullptr,
-                         fixed ? &tmp : nullptr)) != CUTE_OK) {
-        drop_tiles();
-        return s;
-    }
-    const uint32_t tile_stride = max_tiles > 0 ? (ntiles + max_tiles - 1) / max_tiles : 1;
-    if (tile_stride > 1 && ntiles > 0) {
-        // keep every tile_stride-th tile (in place: a stream-ordered round trip)
-        std::vector<Tile> h(ntiles);
-        hipError_t e = hipMemcpyAsync(h.data(), tiles, ntiles * sizeof(Tile), hipMemcpyDeviceToHost, hs);
-        if (e == hipSuccess) e = hipStreamSynchronize(hs);
-        if (e != hipSuccess) {
-            drop_tiles();
-            return hip_status(e, "tile sample");
-        }
-        uint32_t k = 0;
-        for (uint32_t t = 0; t < ntiles; t += tile_stride) h[k++] = h[t];
-        if (sampled_share) *sampled_share = (double)k / (double)ntiles;
-        ntiles = k;
-        e = hipMemcpyAsync(tiles, h.data(), ntiles * sizeof(Tile), hipMemcpyHostToDevice, hs);
-        if (e == hipSuccess) e = hipStreamSynchronize(hs);
-        if (e != hipSuccess) {
-            drop_tiles();
-            return hip_status(e, "tile sample");
-        }
-    }
-    a.tiles = tiles;
-    a.ntiles = ntiles;
-    a.ntiles_dev = dev_count ? ntiles_dev : nullptr;
-    a.plog = plog;
     a.self = dargs;
     a.wA = A.wt;
     a.wB = B.wt;
-    memcpy(hb + hArgs, &a, sizeof(a));
-    CUTE_HIP(hipMemcpyAsync(dargs, hb + hArgs, sizeof(a), hipMemcpyHostToDevice, hs));
+    // Tiles are built into slots without waiting for their count unless the
+    // bound on their number is far above the points' worth of tiles (very
+    // sparse grids: memory and time would go into empty slots) or the tuner
+    // wants to sample them on the host. The longest-first order compacts the
+    // slots and leaves the count on the device; when every task is some
+    // wave's first, no order is needed and the waves look at the slots as
+    // they are (an empty one costs its wave a read): with the one copy for
+    // tables and arguments, 116 -> 66 us for a kept grid of 2000 points. Two
+    // tasks per wave slot is where the order starts to pay for its kernels.
+    Tile *slots = nullptr, *owned = nullptr;
+    const Tile* tiles = nullptr;
+    uint32_t ntiles = 0;   // tiles, or slots (slotted)
+    bool slotted = false, ordered = true;
+    // slots from the fixed area or the arena are never freed here
+    auto drop_tiles = [&]() {
+        dfree(owned, hs);
+        owned = nullptr;
+    };
+    const uint64_t min_tiles = ((uint64_t)A.n + A.tile_max - 1) / A.tile_max;
+    const uint64_t bound = A.n > 0 && B.n > 0 ? tile_count_bound(A, geo.max_w) : 0;
+    int ncu = 0;
+    CUTE_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    if (bound > 0 && (fixed || (max_tiles == 0 && bound <= std::max<uint64_t>(65536, 4 * min_tiles)))) {
+        if (bound >= (uint64_t(1) << 31)) return fail(CUTE_E_INTERNAL, "tile bound too large");
+        slotted = true;
+        ntiles = (uint32_t)bound;
+        // the tiles lie between the two bounds: their geometric mean stands
+        // for their number
+        a.plog = part_log(std::sqrt((double)min_tiles * (double)bound), geo.near, ncu);
+        ordered = (bound << a.plog) > 32 * (uint64_t)ncu;
+        if ((s = tmp.get(&slots, (size_t)bound)) != CUTE_OK) return s;
+        tiles = slots;
+        uint32_t *key = nullptr, *rank = nullptr;
+        Tile* out = nullptr;
+        if (ordered) {
+            if ((s = tmp.get(&key, (size_t)bound)) != CUTE_OK) return s;
+            if ((s = tmp.get(&rank, (size_t)bound)) != CUTE_OK) return s;
+            if ((s = tmp.get(&out, (size_t)bound)) != CUTE_OK) return s;
+            tiles = out;
+            a.ntiles_dev = ntiles_dev;
+        }
+        a.tiles = tiles;
+        a.ntiles = ntiles;
+        memcpy(hb + oAR, &a, sizeof(a));
+        CUTE_HIP(hipMemcpyAsync(blob, hb, total, hipMemcpyHostToDevice, hs));
+        if ((s = tiles_to_slots(A, geo.max_w, ntiles, slots, slot_overflow, ordered ? nullptr : ntiles_dev, hs)) !=
+            CUTE_OK)
+            return s;
+        if (ordered && (s = order_tiles_to(a, slots, ntiles, key, rank, reinterpret_cast<uint32_t*>(blob + oBK),
+                                           out, ntiles_dev, hs)) != CUTE_OK)
+            return s;
+    } else {
+        // (the stencil's rows are read by the tile order: they go first)
+        CUTE_HIP(hipMemcpyAsync(blob, hb, total, hipMemcpyHostToDevice, hs));
+        if (bound > 0) {
+            if ((s = build_tiles(A, geo.max_w, hs, &owned, &ntiles)) != CUTE_OK) return s;
+            if (max_tiles == 0) a.plog = part_log((double)ntiles, geo.near, ncu);
+        }
+        if ((s = order_tiles(a, &owned, ntiles, hs)) != CUTE_OK) {
+            drop_tiles();
+            return s;
+        }
+        const uint32_t tile_stride = max_tiles > 0 ? (ntiles + max_tiles - 1) / max_tiles : 1;
+        if (tile_stride > 1 && ntiles > 0) {
+            // keep every tile_stride-th tile (in place: a stream-ordered round trip)
+            std::vector<Tile> h(ntiles);
+            hipError_t e = hipMemcpyAsync(h.data(), owned, ntiles * sizeof(Tile), hipMemcpyDeviceToHost, hs);
+            if (e == hipSuccess) e = hipStreamSynchronize(hs);
+            if (e != hipSuccess) {
+                drop_tiles();
+                return hip_status(e, "tile sample");
+            }
+            uint32_t k = 0;
+            for (uint32_t t = 0; t < ntiles; t += tile_stride) h[k++] = h[t];
+            if (sampled_share) *sampled_share = (double)k / (double)ntiles;
+            ntiles = k;
+            e = hipMemcpyAsync(owned, h.data(), ntiles * sizeof(Tile), hipMemcpyHostToDevice, hs);
+            if (e == hipSuccess) e = hipStreamSynchronize(hs);
+            if (e != hipSuccess) {
+                drop_tiles();
+                return hip_status(e, "tile sample");
+            }
+        }
+        tiles = owned;
+        a.tiles = tiles;
+        a.ntiles = ntiles;
+        memcpy(hb + oAR, &a, sizeof(a));
+        const hipError_t e = hipMemcpyAsync(dargs, hb + oAR, sizeof(a), hipMemcpyHostToDevice, hs);
+        if (e != hipSuccess) {
+            drop_tiles();
+            return hip_status(e, "arguments");
+        }
+    }
 
     // launch, then the copies, then one wait (the end event is read after it)
     int grid = 0;
@@ -438,8 +466,8 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
         for (int k = 0; k < nbins; k++) tot += (uint64_t)hw[k];
         st->pairs_in_range = tot;
     }
-    if (dev_count && hst[6] != 0) return fail(CUTE_E_INTERNAL, "tile slots overflowed");
-    const uint64_t want_tiles = dev_count ? (uint64_t)hst[5] : (uint64_t)ntiles;
+    if (slotted && hst[6] != 0) return fail(CUTE_E_INTERNAL, "tile slots overflowed");
+    const uint64_t want_tiles = slotted ? (uint64_t)hst[5] : (uint64_t)ntiles;
     if (hst[3] != want_tiles) return fail(CUTE_E_INTERNAL, "not every tile was processed");
     return CUTE_OK;
 }

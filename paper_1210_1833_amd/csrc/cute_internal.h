@@ -296,6 +296,7 @@ struct ItemGeom {
     int max_w = 1;       // home-tile width limit in cells
     ErrModel em;
     double cost = 0.0;   // estimated candidate pairs
+    double near = 0.0;   // estimated neighbours of a home tile
     // rows of neighbour cells as offsets from the home row (3-D grids of one
     // geometry): (dy, dz, cells left of c0, cells right of c1); empty when
     // the kernel must derive the rows itself. SPHERE: the reach of each band
@@ -361,23 +362,25 @@ cute_status build_tiles(const GridHost& g, int max_w, hipStream_t s, Tile** tile
 cute_status region_tiles(const GridHost& g, int max_w, const uint32_t* rc, uint32_t K, uint32_t* off,
                          uint32_t* fill, Tile* out, hipStream_t s);
 
-// The same tiles without a wait for their count (no region labels): *tiles
-// holds *cap = tile_count_bound slots, rows in order, with empty tiles
-// (start == end) in the unused slots, for order_tiles to drop. *overflow
-// (device memory) is raised if a row had more tiles than its slots.
-class DevArena;
-cute_status build_tiles_nowait(const GridHost& g, int max_w, hipStream_t s, Tile** tiles,
-                               uint32_t* cap, uint32_t* overflow, DevArena* ar = nullptr);
-// upper bound of the number of tiles of g (no region labels)
+// The same tiles without a wait for their count: t has bound =
+// tile_count_bound slots and receives the rows in order, with empty tiles
+// (start == end) in the unused slots. *overflow (device memory) is raised if a
+// row had more tiles than its slots; with total set, the number of tiles is
+// added to it.
+cute_status tiles_to_slots(const GridHost& g, int max_w, uint32_t bound, Tile* t, uint32_t* overflow,
+                           uint32_t* total, hipStream_t s);
+// upper bound of the number of tiles of g
 uint64_t tile_count_bound(const GridHost& g, int max_w);
 
-// reorder *tiles longest first by estimated cost (a: the count's arguments:
-// grids, stencil and symmetry; its tile list is not read). With total set,
-// empty tiles are dropped and the number kept is written to *total (device
-// memory). With ar, the temporaries and the new list come from the arena and
-// the old list is not freed; otherwise the old list is freed and replaced.
-cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, hipStream_t s,
-                        uint32_t* total = nullptr, DevArena* ar = nullptr);
+// out: the tiles of in (ntiles slots) longest first by estimated cost (a: the
+// count's arguments: grids, stencil and symmetry; its tile list is not read);
+// empty slots are dropped, and the number kept is written to *total when set.
+// key, rank: ntiles words each; hist: kTileBuckets words, zero.
+constexpr uint32_t kTileBuckets = 256;
+cute_status order_tiles_to(const CountArgs& a, const Tile* in, uint32_t ntiles, uint32_t* key, uint32_t* rank,
+                           uint32_t* hist, Tile* out, uint32_t* total, hipStream_t s);
+// The same in place: *tiles, a stream-ordered allocation, is replaced.
+cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, hipStream_t s);
 
 // persistent count launch; *grid_used receives the number of workgroups
 // out[i] = in[input index of sorted point i] for the n points of g (in:

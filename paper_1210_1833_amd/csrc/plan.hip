@@ -423,6 +423,19 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
         vol_b = std::max(B.nx * B.ax * B.ny * B.ay * B.nz * B.az, 1e-300);
         vol_s = 4.0 / 3.0 * kPiH * g->Rs * g->Rs * g->Rs;
     }
+    // neighbours of a tile of one cell: the cells of its stencil rows, or the
+    // tile's box grown by the reach (whose corners hold no rows)
+    if (!g->stencil.empty() && !sphere) {
+        double cells = 0.0;
+        for (const int4& e : g->stencil) cells += std::min<double>(e.z + e.w + 1, B.nx);
+        g->near = (double)B.n * cells / ((double)B.nx * B.ny * B.nz);
+    } else if (sphere) {
+        g->near = (double)B.n * std::min(1.0, (A.ay + 2.0 * g->th_s) * (A.ax + 2.0 * g->th_s) / vol_b);
+    } else {
+        g->near = (double)B.n * std::min(1.0, 0.7 * (A.ax + 2.0 * g->Rs) * (A.ay + 2.0 * g->Rs) *
+                                                  (A.az + 2.0 * g->Rs) / vol_b);
+    }
+    if (is_auto && g->stencil.empty()) g->near *= 0.5;
     g->cost = (double)A.n * (double)B.n * std::min(1.0, 1.5 * vol_s / vol_b) * (is_auto ? 0.5 : 1.0);
     return CUTE_OK;
 }
@@ -455,14 +468,20 @@ int served_prec(int prec, const ItemGeom& g, const GridHost& A, const GridHost& 
 // time, so a count whose tiles hardly outnumber the wave slots ends with most
 // of the chip waiting for the last tiles: at 2 tiles per slot the r-mu count
 // of 250 000 points ran at 1200 Gpair/s, at 6 at 1550. The tiles are cut until
-// there are six tasks per slot, as long as a part keeps two chunks of
-// neighbours: below that the span generation of the part (a few thousand
-// cycles, as much as two chunks against a tile of 20 points) costs more than
-// the balance gives.
+// there are six tasks per slot, as long as a part keeps eight chunks of
+// neighbours (its spans cost about as much as two), or, while every task is
+// some wave's first (no task is popped then: 4 ns each, one after the other),
+// two chunks.
 int part_log(double ntiles, double neighbours, int ncu) {
     const double slots = 16.0 * ncu, chunks = neighbours / 64.0;
     int p = 0;
-    while (p < kMaxPartLog && ntiles * (double)(1 << p) < 6.0 * slots && chunks >= 4.0 * (double)(1 << p)) p++;
+    while (p < kMaxPartLog) {
+        const double n = ntiles * (double)(1 << p);
+        const bool first = 2.0 * n <= slots && chunks >= 4.0 * (double)(1 << p);
+        const bool more = n < 6.0 * slots && chunks >= 16.0 * (double)(1 << p);
+        if (!first && !more) break;
+        p++;
+    }
     return p;
 }
 
