@@ -22,9 +22,6 @@ struct Group {
     int grid = 0;                    // workgroups
     BatchArgs ba;                    // device pointers filled at creation
     std::vector<int> items;          // item indices, largest estimated cost first
-    double *dT1 = nullptr, *dT2 = nullptr;
-    float2 *dB1 = nullptr, *dB2 = nullptr;
-    uint32_t *dlist = nullptr, *dfirst = nullptr;   // items, first item of each workgroup
 };
 
 }  // namespace
@@ -36,14 +33,12 @@ struct cute_batch {
     std::vector<Group> groups;
     std::vector<int64_t> words;      // count words per item
     std::vector<int64_t> offset;     // offset of each item's counts
-    std::vector<uint32_t> ntiles;    // home tiles per item
     int64_t total_words = 0;
     unsigned long long* work = nullptr;   // counts | stats (4 per item) | heads (1 per item) | done (1 per group)
     size_t work_words = 0;
     CountArgs* dargs = nullptr;      // one per item
     uint32_t* dntiles = nullptr;     // home tiles per item
-    std::vector<void*> owned;        // device allocations (hipMalloc)
-    std::vector<Tile*> tiles;        // per item (stream-ordered allocations)
+    std::vector<void*> owned;        // device allocations (stream-ordered)
     hipStream_t cap = nullptr;       // private stream used for capture
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -52,15 +47,10 @@ struct cute_batch {
 namespace {
 
 template <typename T>
-cute_status owned_alloc(cute_batch* b, T** p, size_t count) {
-    *p = nullptr;
-    if (count == 0) count = 1;
-    if (inject_alloc_failure())
-        return fail(CUTE_E_OUT_OF_MEMORY, "device allocation refused (CUTE_TEST_FAIL_ALLOC)");
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
-    if (e != hipSuccess) return hip_status(e, "hipMalloc");
-    b->owned.push_back(*p);
-    return CUTE_OK;
+cute_status owned_alloc(cute_batch* b, T** p, size_t count, hipStream_t s) {
+    cute_status st = dalloc(p, count, s);
+    if (st == CUTE_OK) b->owned.push_back(*p);
+    return st;
 }
 
 void release(cute_batch* b) {
@@ -69,10 +59,7 @@ void release(cute_batch* b) {
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->cap) (void)hipStreamDestroy(b->cap);
-    for (Tile* t : b->tiles)
-        if (t) (void)hipFreeAsync(t, nullptr);  // stream-ordered allocations
-    (void)hipStreamSynchronize(nullptr);
-    for (void* p : b->owned) (void)hipFree(p);
+    for (void* p : b->owned) dfree(p, nullptr);
     delete b;
 }
 
@@ -89,8 +76,10 @@ cute_status enqueue_run(cute_batch* b, hipStream_t s) {
     return CUTE_OK;
 }
 
+// graph: capture a run for CUTE_BATCH_GRAPH (a batch that runs once is not
+// worth its capture).
 cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision prec,
-                   hipStream_t hs, cute_batch* b) {
+                   hipStream_t hs, bool graph, cute_batch* b) {
     cute_status s;
     if (prec != CUTE_PREC_FP64 && prec != CUTE_PREC_FP32_EDGE && prec != CUTE_PREC_FP32_ONLY)
         return fail(CUTE_E_INVALID_ARG, "unknown precision");
@@ -161,63 +150,42 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
         std::stable_sort(G.items.begin(), G.items.end(),
                          [&](int x, int y) { return geo[x].cost > geo[y].cost; });
     }
-    // ---- device memory -------------------------------------------------------
-    b->work_words = (size_t)b->total_words + 5 * (size_t)n_items + b->groups.size();
-    if ((s = owned_alloc(b, &b->work, b->work_words)) != CUTE_OK) return s;
-    if ((s = owned_alloc(b, &b->dargs, (size_t)n_items)) != CUTE_OK) return s;
-    if ((s = owned_alloc(b, &b->dntiles, (size_t)n_items)) != CUTE_OK) return s;
-    for (Group& G : b->groups) {
-        if ((s = owned_alloc(b, &G.dT1, G.pl.T1.size())) != CUTE_OK) return s;
-        if ((s = owned_alloc(b, &G.dT2, G.pl.T2.size())) != CUTE_OK) return s;
-        if ((s = owned_alloc(b, &G.dB1, G.pl.band1.size())) != CUTE_OK) return s;
-        if ((s = owned_alloc(b, &G.dB2, G.pl.band2.size())) != CUTE_OK) return s;
-        CUTE_HIP(hipMemcpyAsync(G.dT1, G.pl.T1.data(), G.pl.T1.size() * 8, hipMemcpyHostToDevice, hs));
-        CUTE_HIP(hipMemcpyAsync(G.dT2, G.pl.T2.data(), G.pl.T2.size() * 8, hipMemcpyHostToDevice, hs));
-        CUTE_HIP(hipMemcpyAsync(G.dB1, G.pl.band1.data(), G.pl.band1.size() * 8,
-                                hipMemcpyHostToDevice, hs));
-        CUTE_HIP(hipMemcpyAsync(G.dB2, G.pl.band2.data(), G.pl.band2.size() * 8,
-                                hipMemcpyHostToDevice, hs));
-    }
-    // ---- per item: tiles, mask bits, arguments --------------------------------
-    b->tiles.assign(n_items, nullptr);
-    b->ntiles.assign(n_items, 0);
+    // ---- per item: slots of its tiles, mask bits -------------------------------
+    // Tiles are built into slots without a wait for their count, as a single
+    // count does; only for very sparse grids they are counted first.
+    struct ItemTiles {
+        Tile *built = nullptr, *out = nullptr;   // counted tiles (sparse grids), the ordered list
+        uint32_t n = 0;                          // slots
+        double est = 0.0;                        // estimated tiles
+    };
+    std::vector<ItemTiles> it_tiles(n_items);
     std::vector<CountArgs> args(n_items);
+    TempList tmp(hs);
+    size_t max_slots = 1;
     for (int i = 0; i < n_items; i++) {
         const cute_batch_item& it = items[i];
         const bool is_auto = it.b == nullptr || it.b == it.a;
         const GridHost& A = it.a->h;
         const GridHost& B = is_auto ? it.a->h : it.b->h;
-        const Group& G = b->groups[gid[i]];
-        CountArgs& a = args[i];
-        a = G.pl.a;
-        apply_item(geo[i], &a);
-        a.T1 = G.dT1;
-        a.T2 = G.dT2;
-        a.band1 = G.dB1;
-        a.band2 = G.dB2;
-        a.self = b->dargs + i;
-        a.counts = b->work + b->offset[i];
-        a.stats = b->work + b->total_words + 4 * (size_t)i;
+        ItemTiles& t = it_tiles[i];
         if (A.n > 0 && B.n > 0) {
-            Tile* t = nullptr;
-            uint32_t nt = 0;
-            if ((s = build_tiles(A, geo[i].max_w, hs, &t, &nt)) != CUTE_OK) return s;
-            b->tiles[i] = t;
-            b->ntiles[i] = nt;
+            const uint64_t min_tiles = ((uint64_t)A.n + A.tile_max - 1) / A.tile_max;
+            const uint64_t bound = tile_count_bound(A, geo[i].max_w);
+            if (bound <= std::max<uint64_t>(65536, 4 * min_tiles)) {
+                t.n = (uint32_t)bound;
+                t.est = std::sqrt((double)min_tiles * (double)bound);
+                max_slots = std::max<size_t>(max_slots, t.n);
+            } else {
+                if ((s = build_tiles(A, geo[i].max_w, hs, &t.built, &t.n)) != CUTE_OK) return s;
+                tmp.ptrs.push_back(t.built);
+                t.est = (double)t.n;
+                max_slots = std::max<size_t>(max_slots, t.n);
+            }
+            if ((s = owned_alloc(b, &t.out, (size_t)t.n, hs)) != CUTE_OK) return s;
         }
-        a.stencil = nullptr;
-        a.nst = (int)geo[i].stencil.size();
-        if (a.nst > 0) {
-            int4* dst = nullptr;
-            if ((s = owned_alloc(b, &dst, geo[i].stencil.size())) != CUTE_OK) return s;
-            CUTE_HIP(hipMemcpyAsync(dst, geo[i].stencil.data(), geo[i].stencil.size() * sizeof(int4),
-                                    hipMemcpyHostToDevice, hs));
-            a.stencil = dst;
-            // heavy tiles first within the item
-            if ((s = order_tiles(a, &b->tiles[i], b->ntiles[i], hs)) != CUTE_OK) return s;
-        }
-        a.tiles = b->tiles[i];
-        a.ntiles = b->ntiles[i];
+        CountArgs& a = args[i];
+        a = b->groups[gid[i]].pl.a;
+        apply_item(geo[i], &a);
         // masks -> sorted-order bits
         const uint8_t* masks[2] = {it.mask_a, is_auto ? nullptr : it.mask_b};
         const GridHost* gh[2] = {&A, &B};
@@ -226,77 +194,140 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
             if (!masks[side] || gh[side]->n == 0) continue;
             const size_t n = (size_t)gh[side]->n;
             uint32_t* mb = nullptr;
-            if ((s = owned_alloc(b, &mb, (n + 31) / 32)) != CUTE_OK) return s;
+            if ((s = owned_alloc(b, &mb, (n + 31) / 32, hs)) != CUTE_OK) return s;
             const uint8_t* src = masks[side];
-            uint8_t* tmp = nullptr;
+            uint8_t* dm = nullptr;
             if (!it.masks_on_device) {
-                if ((s = dalloc(&tmp, n, hs)) != CUTE_OK) return s;
-                const hipError_t e = hipMemcpyAsync(tmp, src, n, hipMemcpyHostToDevice, hs);
+                if ((s = dalloc(&dm, n, hs)) != CUTE_OK) return s;
+                const hipError_t e = hipMemcpyAsync(dm, src, n, hipMemcpyHostToDevice, hs);
                 if (e != hipSuccess) {
-                    dfree(tmp, hs);
+                    dfree(dm, hs);
                     return hip_status(e, "mask copy");
                 }
-                src = tmp;
+                src = dm;
             }
             s = mask_bits(src, *gh[side], mb, hs);
-            if (tmp) dfree(tmp, hs);
+            if (dm) dfree(dm, hs);
             if (s != CUTE_OK) return s;
             bits[side] = mb;
         }
         a.mbA = bits[0];
         a.mbB = is_auto ? bits[0] : bits[1];
     }
-    CUTE_HIP(hipMemcpyAsync(b->dargs, args.data(), sizeof(CountArgs) * (size_t)n_items,
-                            hipMemcpyHostToDevice, hs));
-    CUTE_HIP(hipMemcpyAsync(b->dntiles, b->ntiles.data(), sizeof(uint32_t) * (size_t)n_items,
-                            hipMemcpyHostToDevice, hs));
-    // ---- the groups' item lists, largest first, and first items --------------
-    unsigned long long* heads = b->work + b->total_words + 4 * (size_t)n_items;
-    std::vector<std::vector<uint32_t>> lists(2 * b->groups.size());  // alive until the sync
+    // ---- one device block, filled by one copy ----------------------------------
+    // [per group: T1 | T2 | B1 | B2 | items, largest first | first item of each
+    //  workgroup] [per item: stencil] [arguments] [tiles per item, overflow flag,
+    //  bucket counts of the tile orders: zero]
+    std::vector<unsigned char> img;
+    auto put = [&](const void* p, size_t bytes) {
+        const size_t o = img.size();
+        img.resize(o + ((bytes + 15) & ~(size_t)15));
+        if (bytes) memcpy(img.data() + o, p, bytes);
+        return o;
+    };
+    struct GroupOff {
+        size_t t1, t2, b1, b2, list, first;
+    };
+    std::vector<GroupOff> go(b->groups.size());
     for (size_t gi = 0; gi < b->groups.size(); gi++) {
         Group& G = b->groups[gi];
-        std::vector<uint32_t>&list = lists[2 * gi], &first = lists[2 * gi + 1];
+        std::vector<uint32_t> list, first;
         std::vector<double> cost;
-        double tiles = 0.0, homes = 0.0, total = 0.0;
+        double tiles = 0.0, slots = 0.0, homes = 0.0, near = 0.0;
         for (int i : G.items) {
-            if (b->ntiles[i] == 0) continue;
+            if (it_tiles[i].n == 0) continue;
             list.push_back((uint32_t)i);
             cost.push_back(std::max(geo[i].cost, 1.0));
-            tiles += (double)b->ntiles[i];
+            tiles += it_tiles[i].est;
+            slots += (double)it_tiles[i].n;
             homes += (double)items[i].a->h.n;
-            total += cost.back();
+            near += geo[i].near * (double)items[i].a->h.n;
         }
-        const int plog = homes > 0.0 ? part_log(tiles, total / homes, ncu) : 0;
-        const double tasks = tiles * (double)(1 << plog);
+        const int plog = homes > 0.0 ? part_log(tiles, near / homes, ncu) : 0;
+        const double tasks = slots * (double)(1 << plog);
         G.grid = (int)std::max(1.0, std::min((double)G.grid, std::ceil(tasks / kWgWaves)));
-        if (!list.empty()) {
-            first = batch_first(cost, G.grid);
-            if ((s = owned_alloc(b, &G.dlist, list.size())) != CUTE_OK) return s;
-            if ((s = owned_alloc(b, &G.dfirst, first.size())) != CUTE_OK) return s;
-            CUTE_HIP(hipMemcpyAsync(G.dlist, list.data(), list.size() * 4, hipMemcpyHostToDevice, hs));
-            CUTE_HIP(hipMemcpyAsync(G.dfirst, first.data(), first.size() * 4, hipMemcpyHostToDevice, hs));
-        }
+        if (!list.empty()) first = batch_first(cost, G.grid);
+        go[gi].t1 = put(G.pl.T1.data(), G.pl.T1.size() * 8);
+        go[gi].t2 = put(G.pl.T2.data(), G.pl.T2.size() * 8);
+        go[gi].b1 = put(G.pl.band1.data(), G.pl.band1.size() * 8);
+        go[gi].b2 = put(G.pl.band2.data(), G.pl.band2.size() * 8);
+        go[gi].list = put(list.data(), list.size() * 4);
+        go[gi].first = put(first.data(), first.size() * 4);
+        memset(&G.ba, 0, sizeof(G.ba));
+        G.ba.nlist = (uint32_t)list.size();
+        G.ba.plog = (uint32_t)plog;
+    }
+    std::vector<size_t> so(n_items);
+    for (int i = 0; i < n_items; i++) so[i] = put(geo[i].stencil.data(), geo[i].stencil.size() * sizeof(int4));
+    const size_t oAR = img.size();
+    const size_t oNT = oAR + ((sizeof(CountArgs) * (size_t)n_items + 15) & ~(size_t)15);
+    const size_t oHI = oNT + (((size_t)n_items + 1) * 4 + 15) / 16 * 16;
+    const size_t total = oHI + (size_t)n_items * kTileBuckets * 4;
+    img.resize(total, 0);
+    unsigned char* blob = nullptr;
+    b->work_words = (size_t)b->total_words + 5 * (size_t)n_items + b->groups.size();
+    if ((s = owned_alloc(b, &blob, total, hs)) != CUTE_OK) return s;
+    if ((s = owned_alloc(b, &b->work, b->work_words, hs)) != CUTE_OK) return s;
+    b->dargs = reinterpret_cast<CountArgs*>(blob + oAR);
+    b->dntiles = reinterpret_cast<uint32_t*>(blob + oNT);
+    for (int i = 0; i < n_items; i++) {
+        const GroupOff& g = go[gid[i]];
+        CountArgs& a = args[i];
+        a.T1 = reinterpret_cast<const double*>(blob + g.t1);
+        a.T2 = reinterpret_cast<const double*>(blob + g.t2);
+        a.band1 = reinterpret_cast<const float2*>(blob + g.b1);
+        a.band2 = reinterpret_cast<const float2*>(blob + g.b2);
+        a.self = b->dargs + i;
+        a.counts = b->work + b->offset[i];
+        a.stats = b->work + b->total_words + 4 * (size_t)i;
+        a.nst = (int)geo[i].stencil.size();
+        a.stencil = a.nst > 0 ? reinterpret_cast<const int4*>(blob + so[i]) : nullptr;
+        a.tiles = it_tiles[i].out;
+        a.ntiles = it_tiles[i].n;
+        memcpy(img.data() + oAR + sizeof(CountArgs) * (size_t)i, &a, sizeof(a));
+    }
+    for (size_t gi = 0; gi < b->groups.size(); gi++) {
+        Group& G = b->groups[gi];
         BatchArgs& ba = G.ba;
-        memset(&ba, 0, sizeof(ba));
         ba.items = b->dargs;
-        ba.list = G.dlist;
-        ba.nlist = (uint32_t)list.size();
-        ba.first = G.dfirst;
+        ba.list = reinterpret_cast<const uint32_t*>(blob + go[gi].list);
+        ba.first = reinterpret_cast<const uint32_t*>(blob + go[gi].first);
         ba.ntiles = b->dntiles;
-        ba.plog = (uint32_t)plog;
-        ba.heads = heads;
-        ba.done = heads + n_items + gi;
+        ba.heads = b->work + b->total_words + 4 * (size_t)n_items;
+        ba.done = ba.heads + n_items + gi;
         ba.n1 = G.pl.a.n1;
         ba.n2 = G.pl.a.n2;
         ba.nbins = G.pl.a.nbins;
         ba.copies = G.pl.a.copies;
         ba.hist_words = G.pl.a.hist_words;
-        ba.T1 = G.dT1;
-        ba.T2 = G.dT2;
-        ba.band1 = G.dB1;
-        ba.band2 = G.dB2;
+        ba.T1 = reinterpret_cast<const double*>(blob + go[gi].t1);
+        ba.T2 = reinterpret_cast<const double*>(blob + go[gi].t2);
+        ba.band1 = reinterpret_cast<const float2*>(blob + go[gi].b1);
+        ba.band2 = reinterpret_cast<const float2*>(blob + go[gi].b2);
     }
+    CUTE_HIP(hipMemcpyAsync(blob, img.data(), total, hipMemcpyHostToDevice, hs));
+    // ---- the tiles, heavy ones first within each item ---------------------------
+    // (one set of slots, keys and ranks for all items: the stream orders them)
+    Tile* slots = nullptr;
+    uint32_t* keys = nullptr;
+    if ((s = tmp.alloc(&slots, max_slots)) != CUTE_OK) return s;
+    if ((s = tmp.alloc(&keys, 2 * max_slots)) != CUTE_OK) return s;
+    uint32_t* overflow = b->dntiles + n_items;
+    for (int i = 0; i < n_items; i++) {
+        const ItemTiles& t = it_tiles[i];
+        if (t.n == 0) continue;
+        if (!t.built && (s = tiles_to_slots(items[i].a->h, geo[i].max_w, t.n, slots, overflow, nullptr, hs)) != CUTE_OK)
+            return s;
+        if ((s = order_tiles_to(args[i], t.built ? t.built : slots, t.n, keys, keys + max_slots,
+                                reinterpret_cast<uint32_t*>(blob + oHI) + (size_t)i * kTileBuckets, t.out,
+                                b->dntiles + i, hs)) != CUTE_OK)
+            return s;
+    }
+    uint32_t over = 0;
+    CUTE_HIP(hipMemcpyAsync(&over, overflow, sizeof(over), hipMemcpyDeviceToHost, hs));
     CUTE_HIP(hipStreamSynchronize(hs));
+    if (over) return fail(CUTE_E_INTERNAL, "tile slots overflowed");
+    if (!graph) return CUTE_OK;
     // ---- capture one run in a graph ----------------------------------------------
     CUTE_HIP(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
     CUTE_HIP(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
@@ -315,13 +346,12 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
 
 }  // namespace
 
-extern "C" cute_status cute_batch_create(const cute_batch_item* items, int32_t n_items,
-                                         cute_precision prec, void* stream, cute_batch** out) {
-    if (!out) return fail(CUTE_E_INVALID_ARG, "out is NULL");
+static cute_status batch_create(const cute_batch_item* items, int32_t n_items, cute_precision prec,
+                                void* stream, bool graph, cute_batch** out) {
     *out = nullptr;
     if (!items || n_items < 1) return fail(CUTE_E_INVALID_ARG, "no items");
     cute_batch* b = new cute_batch();
-    cute_status s = create(items, n_items, prec, (hipStream_t)stream, b);
+    cute_status s = create(items, n_items, prec, (hipStream_t)stream, graph, b);
     if (s != CUTE_OK) {
         (void)hipStreamSynchronize((hipStream_t)stream);
         release(b);
@@ -329,6 +359,12 @@ extern "C" cute_status cute_batch_create(const cute_batch_item* items, int32_t n
     }
     *out = b;
     return CUTE_OK;
+}
+
+extern "C" cute_status cute_batch_create(const cute_batch_item* items, int32_t n_items,
+                                         cute_precision prec, void* stream, cute_batch** out) {
+    if (!out) return fail(CUTE_E_INVALID_ARG, "out is NULL");
+    return batch_create(items, n_items, prec, stream, true, out);
 }
 
 extern "C" cute_status cute_batch_run(cute_batch* b, int32_t flags, void* stream) {
@@ -362,28 +398,37 @@ extern "C" cute_status cute_batch_counts(const cute_batch* b, int32_t item, uint
     return CUTE_OK;
 }
 
+// Statistics of an item (or all) from the work area and the tile counts on the
+// host.
+static cute_status batch_stats(const cute_batch* b, int32_t item, const unsigned long long* h,
+                               const uint32_t* ntiles, cute_count_stats* st) {
+    memset(st, 0, sizeof(*st));
+    bool complete = true;
+    for (int i = 0; i < b->n_items; i++) {
+        if (item >= 0 && i != item) continue;
+        const unsigned long long* sv = h + b->total_words + 4 * (size_t)i;
+        st->pair_evals += sv[0];
+        st->retests += sv[1];
+        st->flips += sv[2];
+        st->tiles += sv[3];
+        for (int64_t k = 0; k < b->words[i]; k++) st->pairs_in_range += h[b->offset[i] + k];
+        complete = complete && sv[3] == ntiles[i];
+    }
+    if (!complete) return fail(CUTE_E_INTERNAL, "not every tile was processed");
+    return CUTE_OK;
+}
+
 extern "C" cute_status cute_batch_stats(const cute_batch* b, int32_t item, cute_count_stats* st,
                                         void* stream) {
     if (!b || !st) return fail(CUTE_E_INVALID_ARG, "NULL argument");
     if (item < -1 || item >= b->n_items) return fail(CUTE_E_INVALID_ARG, "item out of range");
     hipStream_t hs = (hipStream_t)stream;
     std::vector<unsigned long long> h(b->work_words);
+    std::vector<uint32_t> nt((size_t)b->n_items);
     CUTE_HIP(hipMemcpyAsync(h.data(), b->work, b->work_words * 8, hipMemcpyDeviceToHost, hs));
+    CUTE_HIP(hipMemcpyAsync(nt.data(), b->dntiles, nt.size() * 4, hipMemcpyDeviceToHost, hs));
     CUTE_HIP(hipStreamSynchronize(hs));
-    memset(st, 0, sizeof(*st));
-    bool complete = true;
-    for (int i = 0; i < b->n_items; i++) {
-        if (item >= 0 && i != item) continue;
-        const unsigned long long* sv = h.data() + b->total_words + 4 * (size_t)i;
-        st->pair_evals += sv[0];
-        st->retests += sv[1];
-        st->flips += sv[2];
-        st->tiles += sv[3];
-        for (int64_t k = 0; k < b->words[i]; k++) st->pairs_in_range += h[b->offset[i] + k];
-        complete = complete && sv[3] == b->ntiles[i];
-    }
-    if (!complete) return fail(CUTE_E_INTERNAL, "not every tile was processed");
-    return CUTE_OK;
+    return batch_stats(b, item, h.data(), nt.data(), st);
 }
 
 extern "C" void cute_batch_free(cute_batch* b) { release(b); }
@@ -396,28 +441,42 @@ extern "C" cute_status cute_count_pairs_batched(const cute_batch_item* items, in
     for (int i = 0; i < n_items; i++)
         if (!counts[i]) return fail(CUTE_E_INVALID_ARG, "counts[" + std::to_string(i) + "] is NULL");
     cute_batch* b = nullptr;
-    cute_status s = cute_batch_create(items, n_items, prec, stream, &b);
+    cute_status s = batch_create(items, n_items, prec, stream, false, &b);
     if (s != CUTE_OK) return s;
     hipStream_t hs = (hipStream_t)stream;
-    double ms = 0.0;
-    {
+    auto run = [&]() -> cute_status {
+        cute_status r;
         EventTimer timer(hs);
-        s = cute_batch_run(b, CUTE_BATCH_GRAPH, stream);
-        if (s == CUTE_OK) ms = timer.stop_ms();
-    }
-    for (int i = 0; s == CUTE_OK && i < n_items; i++)
-        s = cute_batch_counts(b, i, counts[i], counts_on_device, stream);
-    if (s == CUTE_OK && st) {
-        s = cute_batch_stats(b, -1, st, stream);
-        st->ms_count = ms;
-    } else if (s == CUTE_OK) {
-        cute_count_stats tmp;
-        s = cute_batch_stats(b, -1, &tmp, stream);
-    }
-    if (s == CUTE_OK) {
-        hipError_t e = hipStreamSynchronize(hs);
-        if (e != hipSuccess) s = hip_status(e, "hipStreamSynchronize");
-    }
+        if ((r = enqueue_run(b, hs)) != CUTE_OK) return r;
+        timer.stop();
+        if (counts_on_device)
+            for (int i = 0; i < n_items; i++)
+                if ((r = cute_batch_counts(b, i, counts[i], 1, stream)) != CUTE_OK) return r;
+        // counts, statistics and tile counts in one wait, through pinned memory
+        // unless they are large
+        const size_t wb = b->work_words * 8, bytes = wb + (size_t)n_items * 4;
+        HostStage stage(hs);
+        std::vector<unsigned char> pageable;
+        unsigned char* hb = nullptr;
+        if (bytes > ((size_t)64 << 20)) {
+            pageable.resize(bytes);
+            hb = pageable.data();
+        } else if ((r = stage.get(bytes, &hb)) != CUTE_OK) {
+            return r;
+        }
+        CUTE_HIP(hipMemcpyAsync(hb, b->work, wb, hipMemcpyDeviceToHost, hs));
+        CUTE_HIP(hipMemcpyAsync(hb + wb, b->dntiles, (size_t)n_items * 4, hipMemcpyDeviceToHost, hs));
+        CUTE_HIP(hipStreamSynchronize(hs));
+        const unsigned long long* h = reinterpret_cast<const unsigned long long*>(hb);
+        if (!counts_on_device)
+            for (int i = 0; i < n_items; i++) memcpy(counts[i], h + b->offset[i], (size_t)b->words[i] * 8);
+        cute_count_stats all;
+        r = batch_stats(b, -1, h, reinterpret_cast<const uint32_t*>(hb + wb), &all);
+        all.ms_count = timer.elapsed_ms();
+        if (st) *st = all;
+        return r;
+    };
+    s = run();
     cute_batch_free(b);
     return s;
 }
