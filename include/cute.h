@@ -372,17 +372,18 @@ cute_status cute_count_pairs_batched(const cute_batch_item* items, int32_t n_ite
 /* ---- Jackknife by region decomposition ---------------------------------------
  * Jackknife error bars need the autocorrelation of the catalog with one
  * region left out, for each of K regions (the pair counts of Sec. 2.2 on K
- * sub-catalogs). Here all of them come from two passes over the grid,
- * whatever K: the total, and
- * one full-stencil pass that finds for each region k the pairs with at least
- * one point in it (T_k); then jack_k = total - T_k. The counts equal those of
+ * sub-catalogs). Here all of them come from one full-stencil pass over the
+ * grid, whatever K, that finds for each region k the pairs with both points in
+ * it and those with one: they give T_k, the pairs with at least one point in
+ * it, and the total (which the midpoint kinds and FP32_ONLY count separately);
+ * then jack_k = total - T_k. The counts equal those of
  * cute_count_pairs on each catalog without region k (bit-exact for FP64 and
  * FP32_EDGE).
  * g: a 3-D grid (BOX_OPEN or BOX_PERIODIC). region: g's n labels in its input
  * order, each in [0, K) (device pointer if regions_on_device). K: 1..65535.
  * total: n1 * max(n2, 1) uint64 (host), the autocorrelation of g.
  * jack: K * n1 * max(n2, 1) uint64 (host), row k = catalog without region k.
- * st (nullable): both passes together.
+ * st (nullable): all passes together.
  * Errors: CUTE_E_INVALID_ARG for NULL pointers, K out of range or a label
  * outside [0, K); CUTE_E_UNSUPPORTED for a SPHERE grid or a stencil too large
  * to tabulate; the errors of cute_count_pairs. */
@@ -393,9 +394,10 @@ cute_status cute_count_jackknife(const cute_grid* g, const int32_t* region, int3
 
 /* The same for a cross-correlation (DR of the Landy-Szalay estimator, Sec.
  * 2.2): jack_k counts the pairs between a without its region-k points and b
- * without its region-k points. Three passes whatever K: the total, the pairs
- * whose a point lies in region k (a's points as home), and the pairs whose b
- * point lies in region k and whose a point does not (b's points as home);
+ * without its region-k points. Two passes whatever K: the pairs whose a point
+ * lies in region k (a's points as home; over all regions, the total, which
+ * FP32_ONLY counts separately), and the pairs whose b point lies in region k
+ * and whose a point does not (b's points as home);
  * T_k is their sum and jack_k = total - T_k. Bit-exact like
  * cute_count_pairs on each pair of catalogs.
  * a, b: two different 3-D grids of one geometry kind; region_a, region_b:
