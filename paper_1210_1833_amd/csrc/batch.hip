@@ -458,7 +458,7 @@ extern "C" cute_status cute_count_pairs_batched(const cute_batch_item* items, in
         HostStage stage(hs);
         std::vector<unsigned char> pageable;
         unsigned char* hb = nullptr;
-        if (bytes > ((size_t)64 << 20)) {
+        if (bytes > ((size_t)8 << 20)) {
             pageable.resize(bytes);
             hb = pageable.data();
         } else if ((r = stage.get(bytes, &hb)) != CUTE_OK) {

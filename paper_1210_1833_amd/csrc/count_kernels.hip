@@ -3,9 +3,10 @@
 // One wavefront owns one home tile at a time (a run of up to 64 sorted points
 // inside one row of cells) and walks the neighbour cells of Sec. 3.3 as
 // contiguous spans of the other catalog. The spans are cut into chunks of 64
-// neighbour points, one per lane in VGPRs; the home points are wave-uniform
-// and arrive four at a time through scalar loads, so that each lane evaluates
-// four independent pairs per step. Counts go to one 64-bit LDS histogram per
+// neighbour points, one per lane in VGPRs. A step evaluates four home points
+// against them, four independent pairs per lane: in FP32_EDGE the separations
+// are matrix products whose rows are home points staged in LDS, in the other
+// paths the home points are wave-uniform and arrive through scalar loads. Counts go to one 64-bit LDS histogram per
 // workgroup (several interleaved copies, so that lanes hitting the same bin
 // use different banks), summed into uint64 global counts at the end.
 //
@@ -28,9 +29,9 @@ namespace cute {
 namespace {
 
 // Four 4-wave workgroups per CU: the register budget stays at 128 VGPRs.
-// The one-variable FP32_EDGE kernels (MONO, THETA) run five (96 VGPRs),
-// which hides more latency: the angular count takes 10 % less time; the r-mu
-// and sigma-pi ones gain nothing.
+// The FP32_EDGE kernels without a pair line of sight run five (96 VGPRs),
+// which hides more latency: the angular count took 10 % less time, the region
+// pass of 1500 bins 4 %; the midpoint kinds would spill.
 // WT: pixel maps, each pair weighted by the product of the point weights.
 template <int MODE, int PREC, int EST, bool WT>
 __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count(CountArgs P) {

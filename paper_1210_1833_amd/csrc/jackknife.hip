@@ -293,7 +293,7 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
     HostStage stage(hs);
     std::vector<unsigned char> pageable;
     unsigned char* hb = nullptr;
-    if (wwords * 8 > ((size_t)64 << 20)) {
+    if (wwords * 8 > ((size_t)8 << 20)) {
         pageable.resize(wwords * 8);
         hb = pageable.data();
     } else if ((s = stage.get(wwords * 8, &hb)) != CUTE_OK) {
