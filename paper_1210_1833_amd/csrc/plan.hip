@@ -803,7 +803,12 @@ void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl) {
                                   : make_float2(INFINITY, INFINITY);
         }
         a.out_hi = lo_e[n1];
-        a.out_lo = hi_e[0];
+        // A pair with v < out_lo is certainly below the first edge. Where that
+        // edge certifies nothing (zero, or inside its own band) no v is: not
+        // even a negative one, since the expanded form of a close pair's
+        // separation can be as low as minus its error, which in small length
+        // units is far below any constant.
+        a.out_lo = hi_e[0] > 0.0f ? hi_e[0] : -INFINITY;
         a.skip32 = a.out_hi;
     }
     if (pl.mode == M_RMU_Z) {
