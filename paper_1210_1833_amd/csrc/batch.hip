@@ -37,7 +37,7 @@ struct cute_batch {
     unsigned long long* work = nullptr;   // counts | stats (4 per item) | heads (1 per item) | done (1 per group)
     size_t work_words = 0;
     CountArgs* dargs = nullptr;      // one per item
-    uint32_t* dntiles = nullptr;     // home tiles per item
+    uint32_t* dntiles = nullptr;     // per item: home tiles, log2 of their parts
     std::vector<void*> owned;        // device allocations (stream-ordered)
     hipStream_t cap = nullptr;       // private stream used for capture
     hipGraph_t graph = nullptr;
@@ -157,6 +157,7 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
         Tile *built = nullptr, *out = nullptr;   // counted tiles (sparse grids), the ordered list
         uint32_t n = 0;                          // slots
         double est = 0.0;                        // estimated tiles
+        PartCost pc{1u, 0.f, 0.f, 0.f};          // the item's share of its launch's waves
     };
     std::vector<ItemTiles> it_tiles(n_items);
     std::vector<CountArgs> args(n_items);
@@ -216,7 +217,7 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
     }
     // ---- one device block, filled by one copy ----------------------------------
     // [per group: T1 | T2 | B1 | B2 | items, largest first | first item of each
-    //  workgroup] [per item: stencil] [arguments] [tiles per item, overflow flag,
+    //  workgroup] [per item: stencil] [arguments] [tiles and parts per item, overflow flag,
     //  bucket counts of the tile orders: zero]
     std::vector<unsigned char> img;
     auto put = [&](const void* p, size_t bytes) {
@@ -243,13 +244,17 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
             homes += (double)items[i].a->h.n;
             near += geo[i].near * (double)items[i].a->h.n;
         }
-        // (twice the tiles: three tasks per slot do, since the items' workgroups
-        // balance each other; at six the 12-mock batch's kernels took 3.1 ms, so
-        // 2.85)
+        // (an estimate of the parts for the size of the launch; the cut itself is
+        // made on the device, by the tiles' costs)
         const int plog = homes > 0.0 ? part_log(2.0 * tiles, near / homes, ncu) : 0;
         const double tasks = slots * (double)(1 << plog);
         G.grid = (int)std::max(1.0, std::min((double)G.grid, std::ceil(tasks / kWgWaves)));
         if (!list.empty()) first = batch_first(cost, G.grid);
+        double all = 0.0;
+        for (double c : cost) all += c;
+        for (size_t k = 0; k < list.size(); k++)
+            it_tiles[list[k]].pc =
+                part_cost(G.pl, G.prec, (uint32_t)std::ceil((double)(G.grid * kWgWaves) * cost[k] / all));
         go[gi].t1 = put(G.pl.T1.data(), G.pl.T1.size() * 8);
         go[gi].t2 = put(G.pl.T2.data(), G.pl.T2.size() * 8);
         go[gi].b1 = put(G.pl.band1.data(), G.pl.band1.size() * 8);
@@ -258,13 +263,12 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
         go[gi].first = put(first.data(), first.size() * 4);
         memset(&G.ba, 0, sizeof(G.ba));
         G.ba.nlist = (uint32_t)list.size();
-        G.ba.plog = (uint32_t)plog;
     }
     std::vector<size_t> so(n_items);
     for (int i = 0; i < n_items; i++) so[i] = put(geo[i].stencil.data(), geo[i].stencil.size() * sizeof(int4));
     const size_t oAR = img.size();
     const size_t oNT = oAR + ((sizeof(CountArgs) * (size_t)n_items + 15) & ~(size_t)15);
-    const size_t oHI = oNT + (((size_t)n_items + 1) * 4 + 15) / 16 * 16;
+    const size_t oHI = oNT + ((2 * (size_t)n_items + 1) * 4 + 15) / 16 * 16;
     const size_t total = oHI + (size_t)n_items * kTileBuckets * 4;
     img.resize(total, 0);
     unsigned char* blob = nullptr;
@@ -315,15 +319,15 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
     uint32_t* keys = nullptr;
     if ((s = tmp.alloc(&slots, max_slots)) != CUTE_OK) return s;
     if ((s = tmp.alloc(&keys, 2 * max_slots)) != CUTE_OK) return s;
-    uint32_t* overflow = b->dntiles + n_items;
+    uint32_t* overflow = b->dntiles + 2 * (size_t)n_items;
     for (int i = 0; i < n_items; i++) {
         const ItemTiles& t = it_tiles[i];
         if (t.n == 0) continue;
         if (!t.built && (s = tiles_to_slots(items[i].a->h, geo[i].max_w, t.n, slots, overflow, nullptr, hs)) != CUTE_OK)
             return s;
-        if ((s = order_tiles_to(args[i], t.built ? t.built : slots, t.n, keys, keys + max_slots,
+        if ((s = order_tiles_to(args[i], t.built ? t.built : slots, t.n, t.pc, keys, keys + max_slots,
                                 reinterpret_cast<uint32_t*>(blob + oHI) + (size_t)i * kTileBuckets, t.out,
-                                b->dntiles + i, hs)) != CUTE_OK)
+                                b->dntiles + 2 * (size_t)i, hs)) != CUTE_OK)
             return s;
     }
     uint32_t over = 0;
@@ -415,7 +419,7 @@ static cute_status batch_stats(const cute_batch* b, int32_t item, const unsigned
         st->flips += sv[2];
         st->tiles += sv[3];
         for (int64_t k = 0; k < b->words[i]; k++) st->pairs_in_range += h[b->offset[i] + k];
-        complete = complete && sv[3] == ntiles[i];
+        complete = complete && sv[3] == ntiles[2 * (size_t)i];
     }
     if (!complete) return fail(CUTE_E_INTERNAL, "not every tile was processed");
     return CUTE_OK;
@@ -427,7 +431,7 @@ extern "C" cute_status cute_batch_stats(const cute_batch* b, int32_t item, cute_
     if (item < -1 || item >= b->n_items) return fail(CUTE_E_INVALID_ARG, "item out of range");
     hipStream_t hs = (hipStream_t)stream;
     std::vector<unsigned long long> h(b->work_words);
-    std::vector<uint32_t> nt((size_t)b->n_items);
+    std::vector<uint32_t> nt(2 * (size_t)b->n_items);
     CUTE_HIP(hipMemcpyAsync(h.data(), b->work, b->work_words * 8, hipMemcpyDeviceToHost, hs));
     CUTE_HIP(hipMemcpyAsync(nt.data(), b->dntiles, nt.size() * 4, hipMemcpyDeviceToHost, hs));
     CUTE_HIP(hipStreamSynchronize(hs));
@@ -457,7 +461,7 @@ extern "C" cute_status cute_count_pairs_batched(const cute_batch_item* items, in
                 if ((r = cute_batch_counts(b, i, counts[i], 1, stream)) != CUTE_OK) return r;
         // counts, statistics and tile counts in one wait, through pinned memory
         // unless they are large
-        const size_t wb = b->work_words * 8, bytes = wb + (size_t)n_items * 4;
+        const size_t wb = b->work_words * 8, bytes = wb + (size_t)n_items * 8;
         HostStage stage(hs);
         std::vector<unsigned char> pageable;
         unsigned char* hb = nullptr;
@@ -468,7 +472,7 @@ extern "C" cute_status cute_count_pairs_batched(const cute_batch_item* items, in
             return r;
         }
         CUTE_HIP(hipMemcpyAsync(hb, b->work, wb, hipMemcpyDeviceToHost, hs));
-        CUTE_HIP(hipMemcpyAsync(hb + wb, b->dntiles, (size_t)n_items * 4, hipMemcpyDeviceToHost, hs));
+        CUTE_HIP(hipMemcpyAsync(hb + wb, b->dntiles, (size_t)n_items * 8, hipMemcpyDeviceToHost, hs));
         CUTE_HIP(hipStreamSynchronize(hs));
         const unsigned long long* h = reinterpret_cast<const unsigned long long*>(hb);
         if (!counts_on_device)

@@ -50,7 +50,7 @@ __device__ __forceinline__ uint32_t next_item(const BatchArgs& BA, uint32_t pos,
         uint32_t e = 0, left = 0;
         if (o + (uint32_t)lane < n) {
             e = (uint32_t)(((uint64_t)pos + 1u + o + (uint32_t)lane) % n);
-            const uint32_t item = BA.list[e], all = BA.ntiles[item] << BA.plog;
+            const uint32_t item = BA.list[e], all = BA.ntiles[2u * item] << BA.ntiles[2u * item + 1u];
             const uint32_t head = (uint32_t)__hip_atomic_load(BA.heads + item, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             left = head < all ? all - head : 0u;
         }
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
     while (pos != kNoBin) {
         const uint32_t item = uni(list[pos]);
         const CountArgs& P = *(const CountArgs*)(cargp)(uintptr_t)(BA.items + item);
-        const uint32_t ntasks = uni(ntl[item]) << BA.plog;
+        const uint32_t plog = uni(ntl[2u * item + 1u]), ntasks = uni(ntl[2u * item]) << plog;
         uint32_t* head = reinterpret_cast<uint32_t*>(BA.heads + item);
         bool any = false;
         for (;;) {
@@ -114,14 +114,14 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count_batch(Bat
                 break;
             }
             any = true;
-            const cu32p tp = (cu32p)(const void*)P.tiles + 4 * (size_t)(t >> BA.plog);
+            const cu32p tp = (cu32p)(const void*)P.tiles + 4 * (size_t)(t >> plog);
             Tile tl;
             tl.start = uni(tp[0]);
             tl.end = uni(tp[1]);
             tl.row = uni(tp[2]);
             tl.c0c1 = uni(tp[3]);
             do_tile<MODE, PREC, EST, true, false>(P, W, S, B1, B2, T1, T2, lane, tl,
-                                                  t & ((1u << BA.plog) - 1u), BA.plog);
+                                                  t & ((1u << plog) - 1u), plog);
         }
         if (any) {
             // the re-test queue refers to this item's points: empty it now

@@ -334,11 +334,18 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     // bound on their number is far above the points' worth of tiles (very
     // sparse grids: memory and time would go into empty slots) or the tuner
     // wants to sample them on the host. The longest-first order compacts the
-    // slots and leaves the count on the device; when every task is some
-    // wave's first, no order is needed and the waves look at the slots as
-    // they are (an empty one costs its wave a read): with the one copy for
-    // tables and arguments, 116 -> 66 us for a kept grid of 2000 points. Two
-    // tasks per wave slot is where the order starts to pay for its kernels.
+    // slots, cuts them into parts by their costs (see part_rule) and leaves
+    // both on the device; when every task is some wave's first, no order is
+    // needed and the waves look at the slots as they are (an empty one costs
+    // its wave a read): with the one copy for tables and arguments, 116 -> 66 us
+    // for a kept grid of 2000 points. Two tasks per wave slot is where the order
+    // starts to pay for its kernels. Unordered tiles are cut by a host estimate
+    // of their neighbours, which holds for periodic boxes; the points of another
+    // grid may fill a small part of its box, and a count with many possible
+    // pairs is ordered (three launches, 40 us: data-random counts of light cones
+    // with 6e4 and 1.2e5 points 1.75 -> 0.75 ms, an r-mu count of an open box of
+    // 6e4 0.33 -> 0.38 ms where it was ordered too; the limit, in evaluations of
+    // the kernel, lies at 4.2e9 pairs for the fastest).
     Tile *slots = nullptr, *owned = nullptr;
     const Tile* tiles = nullptr;
     uint32_t ntiles = 0;   // tiles, or slots (slotted)
@@ -352,6 +359,9 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     const uint64_t bound = A.n > 0 && B.n > 0 ? tile_count_bound(A, geo.max_w) : 0;
     int ncu = 0;
     CUTE_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    int wgs = 1;   // workgroups that run at a time
+    if ((s = launch_count(a, pl.mode, kprec, pl.est, kWgWaves, pl.lds, hs, &wgs)) != CUTE_OK) return s;
+    const PartCost pc = part_cost(pl, kprec, (uint32_t)(wgs * kWgWaves));
     if (bound > 0 && (fixed || (max_tiles == 0 && bound <= std::max<uint64_t>(65536, 4 * min_tiles)))) {
         if (bound >= (uint64_t(1) << 31)) return fail(CUTE_E_INTERNAL, "tile bound too large");
         slotted = true;
@@ -359,7 +369,9 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
         // the tiles lie between the two bounds: their geometric mean stands
         // for their number
         a.plog = part_log(std::sqrt((double)min_tiles * (double)bound), geo.near, ncu);
-        ordered = (bound << a.plog) > 32 * (uint64_t)ncu;
+        const double most = 7.0 * (double)pc.wait * (double)pc.wait;
+        ordered = (bound << a.plog) > 32 * (uint64_t)ncu ||
+                  (A.geom != CUTE_GEOM_BOX_PERIODIC && (double)A.n * (double)B.n > most);
         if ((s = tmp.get(&slots, (size_t)bound)) != CUTE_OK) return s;
         tiles = slots;
         uint32_t *key = nullptr, *rank = nullptr;
@@ -370,6 +382,7 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
             if ((s = tmp.get(&out, (size_t)bound)) != CUTE_OK) return s;
             tiles = out;
             a.ntiles_dev = ntiles_dev;
+            a.plog = kMaxPartLog;
         }
         a.tiles = tiles;
         a.ntiles = ntiles;
@@ -378,7 +391,7 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
         if ((s = tiles_to_slots(A, geo.max_w, ntiles, slots, slot_overflow, ordered ? nullptr : ntiles_dev, hs)) !=
             CUTE_OK)
             return s;
-        if (ordered && (s = order_tiles_to(a, slots, ntiles, key, rank, reinterpret_cast<uint32_t*>(blob + oBK),
+        if (ordered && (s = order_tiles_to(a, slots, ntiles, pc, key, rank, reinterpret_cast<uint32_t*>(blob + oBK),
                                            out, ntiles_dev, hs)) != CUTE_OK)
             return s;
     } else {
@@ -386,9 +399,12 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
         CUTE_HIP(hipMemcpyAsync(blob, hb, total, hipMemcpyHostToDevice, hs));
         if (bound > 0) {
             if ((s = build_tiles(A, geo.max_w, hs, &owned, &ntiles)) != CUTE_OK) return s;
-            if (max_tiles == 0) a.plog = part_log((double)ntiles, geo.near, ncu);
+            if (max_tiles == 0) {
+                a.ntiles_dev = ntiles_dev;
+                a.plog = kMaxPartLog;
+            }
         }
-        if ((s = order_tiles(a, &owned, ntiles, hs)) != CUTE_OK) {
+        if ((s = order_tiles(a, &owned, ntiles, pc, ntiles_dev, hs)) != CUTE_OK) {
             drop_tiles();
             return s;
         }
@@ -467,7 +483,7 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
         st->pairs_in_range = tot;
     }
     if (slotted && hst[6] != 0) return fail(CUTE_E_INTERNAL, "tile slots overflowed");
-    const uint64_t want_tiles = slotted ? (uint64_t)hst[5] : (uint64_t)ntiles;
+    const uint64_t want_tiles = slotted ? (uint64_t)(uint32_t)hst[5] : (uint64_t)ntiles;
     if (hst[3] != want_tiles) return fail(CUTE_E_INTERNAL, "not every tile was processed");
     return CUTE_OK;
 }

@@ -66,8 +66,8 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count(CountArgs
     // tasks: the parts of the tiles. Every wave starts with the task of its
     // own number, so that a launch of no more tasks than waves pops none; an
     // empty tile slot is no tile.
-    const uint32_t plog = (uint32_t)P.plog;
-    const uint32_t ntasks = (P.ntiles_dev ? uni(*P.ntiles_dev) : P.ntiles) << plog;
+    const uint32_t plog = P.ntiles_dev ? uni(P.ntiles_dev[1]) : (uint32_t)P.plog;
+    const uint32_t ntasks = (P.ntiles_dev ? uni(P.ntiles_dev[0]) : P.ntiles) << plog;
     const uint32_t nw = gridDim.x * (uint32_t)nwaves;
     for (uint32_t t = blockIdx.x * (uint32_t)nwaves + (uint32_t)unii(wave); t < ntasks;) {
         const cu32p tp = (cu32p)(const void*)P.tiles + 4 * (size_t)(t >> plog);
@@ -147,6 +147,10 @@ cute_status launch_one(const CountArgs& a, int wg_waves, size_t lds, hipStream_t
         cache[std::make_tuple(dev, wg_waves, lds, WT)] = std::make_pair(ncu, per_cu);
     }
     int64_t want = (int64_t)per_cu * ncu;
+    if (a.tiles == nullptr) {   // only asked how many workgroups run at a time
+        if (grid_used) *grid_used = (int)want;
+        return CUTE_OK;
+    }
     int64_t need = (((int64_t)a.ntiles << a.plog) + wg_waves - 1) / wg_waves;
     int grid = (int)(want < need ? want : need);
     if (grid < 1) grid = 1;
@@ -477,30 +481,119 @@ __global__ __launch_bounds__(256) void k_tile_rank(const uint32_t* __restrict__ 
     if (live) rank[t] = lbase[b] + lr;
 }
 
+// Parts per home tile (log2), from the tiles' costs (one bucket per thread: v
+// tiles of cost c, upto of them up to this bucket; all threads of one block).
+// pc.slots waves take the tasks longest first. A task of a full chip takes its
+// pairs and its set-up, at least the set-up's waits beside which pairs of other
+// waves are issued (own); one that starts when the tasks before it are shared
+// out ends at (theirs and its own) / slots + own. The tasks that are their
+// waves' first run on while others have ended, faster; when all of them are,
+// some CUs have more of them than others (a chip half full takes twice the time
+// of an even share). The count ends at the latest of these, and the rule takes
+// the cut that ends first.
+// Costs are the device's because a host estimate sees the bounding box only:
+// with one, a light-cone FP64 count of 2e5 points, mostly empty box, was left
+// uncut and took 3.9 ms (1.9 in four parts), and an r-mu count of 3e5 with 15
+// points a tile was cut into four parts and took 1.06 ms (0.50 uncut).
+__device__ __forceinline__ uint32_t part_rule(uint32_t v, float c, uint32_t upto, uint32_t ntiles,
+                                              const PartCost& pc) {
+    constexpr int P = kMaxPartLog + 1, W = kCostBuckets / 64;
+    __shared__ float wsum[W][P], wend[W][P];
+    const int lane = (int)(threadIdx.x & 63u);
+    const uint32_t wave = threadIdx.x >> 6;
+    const float slots = (float)pc.slots, is = 1.0f / slots;
+    float own[P], sum[P];
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        const float n = (float)(1u << p);
+        own[p] = fmaxf(c / n + pc.issue, 0.3f * (c / n) + pc.wait);
+        sum[p] = (float)v * n * own[p];
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1)
+#pragma unroll
+        for (int p = 0; p < P; p++) {
+            const float u = __shfl_up(sum[p], o);
+            sum[p] += lane >= o ? u : 0.f;
+        }
+    if (lane == 63)
+#pragma unroll
+        for (int p = 0; p < P; p++) wsum[wave][p] = sum[p];
+    __syncthreads();
+    float end[P];
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        const float n = (float)(1u << p);
+        float all = 0.f;
+        for (uint32_t w = 0; w < W; w++) {
+            sum[p] += w < wave ? wsum[w][p] : 0.f;
+            all += wsum[w][p];
+        }
+        end[p] = v == 0u ? 0.f : (float)upto * n > slots ? own[p] + sum[p] * is : pc.first * (c / n) + pc.wait;
+        end[p] = fmaxf(end[p], (float)ntiles * n <= slots ? all * (0.6f * is + 0.75f / ((float)ntiles * n)) : 0.f);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int p = 0; p < P; p++) end[p] = fmaxf(end[p], __shfl_xor(end[p], o));
+    if (lane == 0)
+#pragma unroll
+        for (int p = 0; p < P; p++) wend[wave][p] = end[p];
+    __syncthreads();
+    uint32_t best = 0;
+    float least = 0.f;
+    for (int p = 0; p < P; p++) {
+        // (past some dozens of tasks per wave no cut is worth its parts)
+        if (p > 0 && (float)ntiles * (float)(1u << p) > 64.0f * slots) break;
+        float e = 0.f;
+        for (uint32_t w = 0; w < W; w++) e = fmaxf(e, wend[w][p]);
+        if (p == 0 || e < 0.98f * least) {
+            best = (uint32_t)p;
+            least = e;
+        }
+    }
+    return best;
+}
+
+// The offsets of the buckets in the ordered list (a block of one thread per
+// bucket, which holds v tiles); total, when set, receives the number of tiles
+// and the log2 of their parts.
+__device__ __forceinline__ void bucket_offsets(uint32_t v, uint32_t* off, uint32_t* total, const PartCost& pc) {
+    static_assert(kCostBuckets == 256, "one bucket per thread");
+    __shared__ uint32_t wsum[kCostBuckets / 64];
+    const int lane = (int)(threadIdx.x & 63u);
+    const uint32_t wave = threadIdx.x >> 6;
+    const uint32_t incl = wave_incl_scan(v, lane);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t base = 0, n = 0;
+    for (uint32_t w = 0; w < kCostBuckets / 64; w++) {
+        base += w < wave ? wsum[w] : 0u;
+        n += wsum[w];
+    }
+    off[threadIdx.x] = base + incl - v;
+    if (total != nullptr) {
+        const float c = __builtin_amdgcn_exp2f(11.0f + ((float)(kCostBuckets - 1 - threadIdx.x) + 0.5f) * 0.125f);
+        const uint32_t p = part_rule(v, c, base + incl, n, pc);
+        if (threadIdx.x == 0) {
+            total[0] = n;
+            total[1] = p;
+        }
+    }
+}
+
 // Scatter the tiles into bucket order: every block scans the bucket counts in
 // LDS (kCostBuckets of them), then each tile goes to its bucket's offset plus
-// its rank within the bucket.
+// its rank within the bucket. total: the number of tiles and the log2 of their
+// parts.
 __global__ __launch_bounds__(256) void k_tile_scatter(const Tile* __restrict__ tiles, uint32_t ntiles,
                                                       const uint32_t* __restrict__ key,
                                                       const uint32_t* __restrict__ rank,
                                                       const uint32_t* __restrict__ hist,
                                                       Tile* __restrict__ out,
-                                                      uint32_t* __restrict__ total) {
+                                                      uint32_t* __restrict__ total, PartCost pc) {
     __shared__ uint32_t off[kCostBuckets];
-    __shared__ uint32_t wsum[kCostBuckets / 64];
-    {
-        // one bucket per thread: the waves scan 64 buckets each
-        static_assert(kCostBuckets == 256, "one bucket per thread");
-        const int lane = (int)(threadIdx.x & 63u);
-        const uint32_t v = hist[threadIdx.x];
-        const uint32_t incl = wave_incl_scan(v, lane);
-        if (lane == 63) wsum[threadIdx.x >> 6] = incl;
-        __syncthreads();
-        uint32_t base = 0;
-        for (uint32_t w = 0; w < (threadIdx.x >> 6); w++) base += wsum[w];
-        off[threadIdx.x] = base + incl - v;
-        if (blockIdx.x == 0 && threadIdx.x == 255 && total != nullptr) *total = base + incl;
-    }
+    bucket_offsets(hist[threadIdx.x], off, blockIdx.x == 0 ? total : nullptr, pc);
     __syncthreads();
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= ntiles) return;
@@ -512,10 +605,9 @@ __global__ __launch_bounds__(256) void k_tile_scatter(const Tile* __restrict__ t
 }  // namespace
 
 // Reorder tiles longest first (estimated cost, descending): the persistent
-// waves take the heavy tiles early and the light ones fill the tail. With
-// total set, empty slots are dropped.
-cute_status order_tiles_to(const CountArgs& a, const Tile* in, uint32_t ntiles, uint32_t* key, uint32_t* rank,
-                           uint32_t* hist, Tile* out, uint32_t* total, hipStream_t s) {
+// waves take the heavy tiles early and the light ones fill the tail.
+cute_status order_tiles_to(const CountArgs& a, const Tile* in, uint32_t ntiles, const PartCost& pc, uint32_t* key,
+                           uint32_t* rank, uint32_t* hist, Tile* out, uint32_t* total, hipStream_t s) {
     static_assert(kCostBuckets == kTileBuckets, "one count per bucket");
     const unsigned nb = (ntiles + 255u) / 256u;
     auto cost = a.geom == CUTE_GEOM_SPHERE ? k_tile_cost<true> : k_tile_cost<false>;
@@ -523,13 +615,14 @@ cute_status order_tiles_to(const CountArgs& a, const Tile* in, uint32_t ntiles, 
     CUTE_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_tile_rank, dim3(nb), dim3(256), 0, s, key, ntiles, rank, hist);
     CUTE_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_tile_scatter, dim3(nb), dim3(256), 0, s, in, ntiles, key, rank, hist, out, total);
+    hipLaunchKernelGGL(k_tile_scatter, dim3(nb), dim3(256), 0, s, in, ntiles, key, rank, hist, out, total, pc);
     CUTE_HIP(hipGetLastError());
     return CUTE_OK;
 }
 
-cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, hipStream_t s) {
-    if (ntiles < 2) return CUTE_OK;
+cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, const PartCost& pc, uint32_t* total,
+                        hipStream_t s) {
+    if (ntiles == 0) return CUTE_OK;
     TempList tmp(s);
     uint32_t* w = nullptr;   // keys | ranks | bucket counts
     Tile* t1 = nullptr;
@@ -538,7 +631,7 @@ cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, hipSt
     uint32_t* hist = w + 2 * (size_t)ntiles;
     if ((st = zero_u32(hist, kTileBuckets, s)) != CUTE_OK) return st;
     if ((st = dalloc(&t1, ntiles, s)) != CUTE_OK) return st;
-    if ((st = order_tiles_to(a, *tiles, ntiles, w, w + ntiles, hist, t1, nullptr, s)) != CUTE_OK) {
+    if ((st = order_tiles_to(a, *tiles, ntiles, pc, w, w + ntiles, hist, t1, total, s)) != CUTE_OK) {
         dfree(t1, s);
         return st;
     }

@@ -102,8 +102,8 @@ struct CountArgs {
     GridView A, B;
     const Tile* tiles;
     uint32_t ntiles;
-    const uint32_t* ntiles_dev;     // when set, the tile count in device memory (ntiles is
-                                    // then only the capacity of tiles)
+    const uint32_t* ntiles_dev;     // when set, [0] the tile count and [1] plog in device memory
+                                    // (ntiles and plog are then only the most they can be)
     int plog;                       // every tile is counted in 2^plog parts (see do_tile)
     uint32_t* work_head;            // tasks (tile parts) popped beyond the first of every wave
     unsigned long long* counts;     // nbins global uint64 counts
@@ -230,8 +230,7 @@ struct BatchArgs {
     const uint32_t* list;           // items of the launch
     uint32_t nlist;
     const uint32_t* first;          // per workgroup: the entry of list it starts with
-    const uint32_t* ntiles;         // home tiles of each item (indexed by item)
-    uint32_t plog;                  // every tile is counted in 2^plog parts
+    const uint32_t* ntiles;         // [2 i] the home tiles of item i, [2 i + 1] the log2 of their parts
     unsigned long long* heads;      // per item: its next task (a tile's part)
     unsigned long long* done;       // entries of the list whose tasks are all taken
     int n1, n2, nbins, copies, hist_words;
@@ -310,12 +309,21 @@ constexpr int kDecisionConsts = 17;
 
 struct Plan {
     int mode = 0, est = 0;
+    bool uneven = false;             // edges that neither a linear nor a log estimate finds
     bool muf = false;                // RMU: linear mu edges covering [0, 1], r edges that allow E_MUF
     double rmax = 0.0;               // largest countable separation
     std::vector<double> T1, T2;      // canonical thresholds
     std::vector<float2> band1, band2;
     CountArgs a;
     size_t lds = 0;                  // dynamic LDS bytes per workgroup
+};
+
+// What the cut of home tiles into parts goes by (see part_rule).
+struct PartCost {
+    uint32_t slots;      // waves that share the tiles
+    float issue, wait;   // a part's set-up (spans, staging) in pair evaluations: the instructions
+                         // it takes from the other waves, and how long its own wave waits
+    float first;         // time per pair of a wave whose CU has other waves ended
 };
 
 // whether the FP32_EDGE count of a plan runs a kMfma kernel
@@ -334,6 +342,7 @@ int served_prec(int prec, const ItemGeom& g, const GridHost& A, const GridHost& 
 // parts per home tile (log2) of a count with about ntiles tiles, each against
 // that many neighbours
 int part_log(double ntiles, double neighbours, int ncu);
+PartCost part_cost(const Plan& pl, int prec, uint32_t slots);
 std::vector<uint32_t> batch_first(const std::vector<double>& cost, int grid);
 int radial_prec(const double* edges, int n);
 void plan_radial(const double* edges, int n, Plan& pl, int* prec);
@@ -374,13 +383,15 @@ uint64_t tile_count_bound(const GridHost& g, int max_w);
 
 // out: the tiles of in (ntiles slots) longest first by estimated cost (a: the
 // count's arguments: grids, stencil and symmetry; its tile list is not read);
-// empty slots are dropped, and the number kept is written to *total when set.
+// empty slots are dropped; total[0] receives the number kept, total[1] the log2
+// of the parts that they are counted in, chosen for pc.slots waves.
 // key, rank: ntiles words each; hist: kTileBuckets words, zero.
 constexpr uint32_t kTileBuckets = 256;
-cute_status order_tiles_to(const CountArgs& a, const Tile* in, uint32_t ntiles, uint32_t* key, uint32_t* rank,
-                           uint32_t* hist, Tile* out, uint32_t* total, hipStream_t s);
+cute_status order_tiles_to(const CountArgs& a, const Tile* in, uint32_t ntiles, const PartCost& pc, uint32_t* key,
+                           uint32_t* rank, uint32_t* hist, Tile* out, uint32_t* total, hipStream_t s);
 // The same in place: *tiles, a stream-ordered allocation, is replaced.
-cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, hipStream_t s);
+cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, const PartCost& pc, uint32_t* total,
+                        hipStream_t s);
 
 // persistent count launch; *grid_used receives the number of workgroups
 // out[i] = in[input index of sorted point i] for the n points of g (in:

@@ -211,17 +211,18 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
     const int plog = part_log(0.5 * (double)ntiles, geo.near, ncu);
     const int gsz = (int)std::min<uint64_t>((uint64_t)per_cu * ncu,
                                             (((uint64_t)ntiles << plog) + kWgWaves - 1) / kWgWaves);
-    std::vector<uint32_t> nt((size_t)K), lst, first;
+    std::vector<uint32_t> nt(2 * (size_t)K), lst, first;
     std::vector<double> share;
     for (int k = 0; k < K; k++) {
-        nt[k] = off[k + 1] - off[k];
-        if (nt[k] == 0) continue;
+        nt[2 * (size_t)k] = off[k + 1] - off[k];
+        nt[2 * (size_t)k + 1] = (uint32_t)plog;
+        if (nt[2 * (size_t)k] == 0) continue;
         lst.push_back((uint32_t)k);
-        share.push_back((double)nt[k]);
+        share.push_back((double)nt[2 * (size_t)k]);
     }
     if (!lst.empty()) first = batch_first(share, gsz);
     // device block of the launch, filled by one copy:
-    // [T1 | T2 | B1 | B2 | stencil | ntiles per region | list | first | args]
+    // [T1 | T2 | B1 | B2 | stencil | tiles and parts per region | list | first | args]
     std::vector<unsigned char> img;
     auto put = [&](const void* p, size_t bytes) {
         const size_t o = img.size();
@@ -254,7 +255,7 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
         a.stencil = geo.stencil.empty() ? nullptr : reinterpret_cast<const int4*>(blob + oST);
         a.nst = (int)geo.stencil.size();
         a.tiles = dtiles + off[k];
-        a.ntiles = nt[k];
+        a.ntiles = nt[2 * (size_t)k];
         a.counts = work + (size_t)k * nbins;
         a.counts_hi = h2 ? work + nh + (size_t)k * nbins : nullptr;
         a.stats = work + hists + 4 * (size_t)k;
@@ -273,7 +274,6 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
     ba.nlist = (uint32_t)lst.size();
     ba.first = reinterpret_cast<const uint32_t*>(blob + oFI);
     ba.ntiles = reinterpret_cast<const uint32_t*>(blob + oNT);
-    ba.plog = (uint32_t)plog;
     ba.heads = work + hists + 4 * (size_t)K;
     ba.done = ba.heads + K;
     ba.n1 = pl.a.n1;

@@ -186,6 +186,7 @@ void plan_binning(const cute_binning* b, Plan& pl) {
     const double* e1 = b->edges1;
     const bool lin1 = is_linear(e1, n1), log1 = !lin1 && is_log(e1, n1);
     pl.est = log1 ? E_LOG : E_LIN;
+    pl.uneven = !lin1 && !log1;
     if (b->kind == CUTE_BIN_SIGMAPI) pl.est = E_LIN;  // sigma estimated linearly
     {
         const double lo = e1[0], hi = e1[n1];
@@ -228,6 +229,7 @@ void plan_binning(const cute_binning* b, Plan& pl) {
         a.e2a = (float)(1.0 / sp);
         a.e2b = (float)(-lo / sp);
         a.d2_generic = is_linear(b->edges2, n2) ? 0 : 1;
+        pl.uneven = pl.uneven || a.d2_generic != 0;
         a.s2 = (float)(((double)a.e2b - 0.5) / (double)a.e2a);
         pl.band2.resize(n2);
         for (int k = 0; k < n2; k++) {
@@ -483,6 +485,27 @@ int part_log(double ntiles, double neighbours, int ncu) {
         p++;
     }
     return p;
+}
+
+// What a part costs beside its pairs (see part_rule), in pair evaluations of the
+// kernel that counts them: fitted to forced cuts of 1, 2, 4 and 8 parts (an r-mu
+// count of 3e5 points in FP32_EDGE took 0.50, 0.64, 1.05 and 1.96 ms, a midpoint
+// one of 2e5 in FP64 3.9, 2.7, 1.9 and 1.9). weight: an evaluation of the kernel
+// against one of the one-variable FP32_EDGE kernels; where bins are mostly
+// searched (FP64) or re-tested, a pair costs as much as there against the
+// midpoint.
+PartCost part_cost(const Plan& pl, int prec, uint32_t slots) {
+    const bool mid = h32_mode(pl.mode);
+    float weight = 1.0f;
+    if (pl.uneven)
+        weight = 4.0f;
+    else if (prec == P_FP64)
+        weight = mid || pl.mode == M_RADIAL ? 4.0f : 1.6f;
+    else if (mid)
+        weight = 2.5f;
+    else if (!mfma_plan(pl, prec))
+        weight = 1.5f;
+    return PartCost{std::max(slots, 1u), 4096.0f / weight, 24576.0f / weight, pl.uneven ? 1.0f : 0.5f};
 }
 
 // The item each workgroup of a batched launch starts with: the workgroups are
