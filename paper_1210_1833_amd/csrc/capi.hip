@@ -399,10 +399,8 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
         CUTE_HIP(hipMemcpyAsync(blob, hb, total, hipMemcpyHostToDevice, hs));
         if (bound > 0) {
             if ((s = build_tiles(A, geo.max_w, hs, &owned, &ntiles)) != CUTE_OK) return s;
-            if (max_tiles == 0) {
-                a.ntiles_dev = ntiles_dev;
-                a.plog = kMaxPartLog;
-            }
+            a.ntiles_dev = ntiles_dev;
+            a.plog = kMaxPartLog;
         }
         if ((s = order_tiles(a, &owned, ntiles, pc, ntiles_dev, hs)) != CUTE_OK) {
             drop_tiles();
@@ -411,9 +409,14 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
         const uint32_t tile_stride = max_tiles > 0 ? (ntiles + max_tiles - 1) / max_tiles : 1;
         if (tile_stride > 1 && ntiles > 0) {
             // keep every tile_stride-th tile (in place: a stream-ordered round trip)
+            // and, of the whole count, the parts
             std::vector<Tile> h(ntiles);
+            uint32_t np[2] = {0u, 0u};
             hipError_t e = hipMemcpyAsync(h.data(), owned, ntiles * sizeof(Tile), hipMemcpyDeviceToHost, hs);
+            if (e == hipSuccess) e = hipMemcpyAsync(np, ntiles_dev, sizeof(np), hipMemcpyDeviceToHost, hs);
             if (e == hipSuccess) e = hipStreamSynchronize(hs);
+            a.ntiles_dev = nullptr;
+            a.plog = (int)np[1];
             if (e != hipSuccess) {
                 drop_tiles();
                 return hip_status(e, "tile sample");

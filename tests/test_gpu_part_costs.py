@@ -1,7 +1,7 @@
 """How home tiles are cut into parts: by the tiles' costs on the device. The
 statistics of a cut count are those of the uncut walk, exactly; a mostly empty
 bounding box and short tiles get the cut that they need (kernel times against
-each other, with wide margins)."""
+each other, with wide margins); and the tuner times counts cut as a user's are."""
 import math
 
 import numpy as np
@@ -82,3 +82,16 @@ def test_short_tiles():
     print("rates %.3g, %.3g evaluations a ms" % (small, large), flush=True)
     assert small > 0.45 * large
 
+
+def test_tuner_counts_as_users_do():
+    rng = np.random.default_rng(7)
+    p = rng.uniform(0.0, 500.0, (20000, 3))
+    bn = cute.Binning(cute.BIN_MONO, np.linspace(0.0, 100.0, 11))
+    cells = [250.0, 100.0]
+    _, _, ms = cute.tune_grid(p, cute.GEOM_BOX_OPEN, bn, r_max=100.0, cells=cells, tiles=[64])
+    for cell in cells:
+        t = ms[(cell, 64)]
+        g = cute.build_grid(p, cute.GEOM_BOX_OPEN, r_max=100.0, cell_size=cell, tile_points=64)
+        own = min(cute.count_pairs(g, None, bn, with_stats=True)[1]["ms_count"] for _ in range(6))
+        print("cell %g: tuner %.3f ms, count %.3f ms" % (cell, t, own), flush=True)
+        assert t < 1.6 * own
