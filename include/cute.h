@@ -476,6 +476,32 @@ cute_status cute_fp32_decision_tables(const cute_binning* bins, const double* er
  * error bounds), CUTE_E_UNSUPPORTED (other binnings or lines of sight). */
 cute_status cute_fp32_zlos_constants(const cute_binning* bins, const double* err, float* consts);
 
+/* Host-only diagnostic: what the FP32_EDGE autocorrelation of n points with the
+ * bounding box [lo, hi] and largest norm max_norm, in a grid of parameters p
+ * (as cute_build_grid takes them, device_ptrs ignored), decides pairs by:
+ * its cells, its FP32 error model and the constants of its kernel, built as the
+ * count builds them. With n_radial > 0 it is the radial count over the edges
+ * radial (n_radial + 1 of them), and bins the THETA binning {0, aperture}.
+ * No device work; it exists so that the rounding analysis can be checked
+ * against exact arithmetic without a GPU.
+ * band1: 2 (n + 1) floats with n = n1 (or n_radial), band2: 2 (n2 + 1); entries
+ * that the count does not use are 0.
+ * consts: 49 doubles: the path (0: FP64, 1: separations as differences of
+ * components, 2: separations from the matrix cores, with home points and
+ * neighbours in the frame of the home tile), the estimate flags, the error
+ * bounds ec, ec64, el, el64 of the components of p - q and p + q and the reach ta
+ * of a tile, the cells per axis (3), the lower corner (3), the cell sides (3),
+ * the centre (3), the home tile's width limit in cells; then skip32, out_lo,
+ * e1a, s1, e2a, s2, rB0, muB2, muB1, muB0, dA1, dA0p, llg, K1, K0, the midpoint's
+ * M, TR, 2R, Tmin, fe and N, the radial count's bins per unit, largest certain
+ * chord^2 and low-edge flag, the clamps of the two estimates, w of sigma_0 and
+ * of pi_0 and the low-side flag of sigma-pi.
+ * Errors: CUTE_E_INVALID_ARG (bad binning, NULL, n < 1), and those of a count of
+ * such a grid. */
+cute_status cute_fp32_count_constants(const cute_grid_params* p, int64_t n, const double* lo, const double* hi,
+                                      double max_norm, const cute_binning* bins, int32_t n_radial,
+                                      const double* radial, float* band1, float* band2, double* consts);
+
 const char* cute_status_string(cute_status s);
 
 /* Message of the last failed call on this thread ("" if none). */

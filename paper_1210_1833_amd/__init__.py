@@ -33,7 +33,7 @@ EXPORTED = ["cute_build_grid", "cute_free_grid", "cute_get_grid_info", "cute_cou
             "cute_count_jackknife_cross",
             "cute_build_pixel_map", "cute_pixel_map_read", "cute_count_radial",
             "cute_xi_estimate", "cute_xi_multipoles", "cute_fp32_decision_tables",
-            "cute_fp32_zlos_constants",
+            "cute_fp32_zlos_constants", "cute_fp32_count_constants",
             "cute_status_string", "cute_last_error"]
 
 
@@ -155,6 +155,9 @@ def load():
     lib.cute_fp32_decision_tables.argtypes = [ctypes.POINTER(CBinning), dp, vp, vp, vp]
     lib.cute_fp32_zlos_constants.restype = ctypes.c_int
     lib.cute_fp32_zlos_constants.argtypes = [ctypes.POINTER(CBinning), dp, vp]
+    lib.cute_fp32_count_constants.restype = ctypes.c_int
+    lib.cute_fp32_count_constants.argtypes = [ctypes.POINTER(GridParams), ctypes.c_int64, dp, dp, ctypes.c_double,
+                                              ctypes.POINTER(CBinning), ctypes.c_int32, vp, vp, vp, vp]
     lib.cute_status_string.restype = ctypes.c_char_p
     lib.cute_status_string.argtypes = [ctypes.c_int]
     lib.cute_last_error.restype = ctypes.c_char_p
@@ -710,3 +713,32 @@ def fp32_zlos_constants(binning: Binning, ec: float, ec64: float):
                                         err.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
                                         c.ctypes.data))
     return dict(zip(ZLOS_CONSTS, c.tolist()))
+
+
+COUNT_CONSTS = ("path", "est", "ec", "ec64", "el", "el64", "ta", "nx", "ny", "nz", "ox", "oy", "oz", "ax", "ay", "az",
+                "cx", "cy", "cz", "max_w", "skip32", "out_lo", "e1a", "s1", "e2a", "s2", "rB0", "muB2", "muB1", "muB0",
+                "dA1", "dA0p", "llg", "K1", "K0", "M", "TR", "2R", "Tmin", "fe", "N", "rdA", "rdIn", "rdLow", "top1",
+                "top2", "wsbot", "wpbot", "low")
+
+
+def fp32_count_constants(geom: int, n: int, lo, hi, max_norm: float, binning: Binning, box_size: float = 0.0,
+                         r_max: float = 0.0, cell_size: float = 0.0, radial=None):
+    """cute_fp32_count_constants (host only): what the FP32_EDGE autocorrelation
+    of n points in the box [lo, hi] decides pairs by, as (dict of constants,
+    band1 [n1 + 1, 2], band2 [n2 + 1, 2]); radial: the redshift-difference
+    edges of a radial count whose aperture is the THETA binning."""
+    lib = load()
+    cb = binning.c()
+    p = GridParams(int(geom), float(box_size), float(r_max), float(cell_size), 0, 0)
+    dp = ctypes.POINTER(ctypes.c_double)
+    lo, hi = (np.ascontiguousarray(v, dtype=np.float64) for v in (lo, hi))
+    rad = None if radial is None else np.ascontiguousarray(radial, dtype=np.float64)
+    n1 = binning.shape[0] if rad is None else len(rad) - 1
+    n2 = binning.shape[1] if len(binning.shape) > 1 else 0
+    b1, b2 = np.zeros((n1 + 1, 2), dtype=np.float32), np.zeros((n2 + 1, 2), dtype=np.float32)
+    c = np.zeros(len(COUNT_CONSTS))
+    _check(lib.cute_fp32_count_constants(ctypes.byref(p), int(n), lo.ctypes.data_as(dp), hi.ctypes.data_as(dp),
+                                         float(max_norm), ctypes.byref(cb), 0 if rad is None else n1,
+                                         None if rad is None else rad.ctypes.data, b1.ctypes.data, b2.ctypes.data,
+                                         c.ctypes.data))
+    return dict(zip(COUNT_CONSTS, c.tolist())), b1, b2

@@ -688,6 +688,53 @@ extern "C" cute_status cute_fp32_zlos_constants(const cute_binning* bins, const 
     return CUTE_OK;
 }
 
+extern "C" cute_status cute_fp32_count_constants(const cute_grid_params* p, int64_t n, const double* lo,
+                                                 const double* hi, double max_norm, const cute_binning* bins,
+                                                 int32_t n_radial, const double* radial, float* band1,
+                                                 float* band2, double* consts) {
+    cute_status s;
+    if ((s = validate_binning(bins)) != CUTE_OK) return s;
+    if (!p || !lo || !hi || !band1 || !band2 || !consts || n < 1 || (n_radial > 0 && !radial))
+        return fail(CUTE_E_INVALID_ARG, "NULL argument");
+    if (n_radial > 0 && bins->kind != CUTE_BIN_THETA)
+        return fail(CUTE_E_INVALID_ARG, "radial edges need a THETA aperture");
+    GridHost g;
+    if ((s = plan_box(p, n, lo, hi, max_norm, &g)) != CUTE_OK) return s;
+    Plan pl;
+    plan_binning(bins, pl);
+    ItemGeom geo;
+    int prec = P_FP32E;
+    if (n_radial > 0) prec = radial_prec(radial, n_radial);
+    if ((s = plan_item(g, g, true, bins, pl, prec, &geo)) != CUTE_OK) return s;
+    plan_bands(bins, geo.em, pl);
+    prec = served_prec(prec, geo, g, g, pl);
+    if (n_radial > 0) plan_radial(radial, n_radial, pl, &prec);
+    const CountArgs& a = pl.a;
+    const int form = prec == P_FP64 ? 0 : mfma_plan(pl, prec) && (pl.mode != M_RMU_MID || est_muf(pl.est)) ? 2 : 1;
+    const ErrModel& em = geo.em;
+    const double c[kCountConsts] = {
+        (double)form, (double)pl.est, em.ec, em.ec64, em.el, em.el64, em.ta,
+        (double)g.nx, (double)g.ny, (double)g.nz, g.ox, g.oy, g.oz, g.ax, g.ay, g.az, g.cx, g.cy, g.cz,
+        (double)geo.max_w, a.skip32, a.out_lo, a.e1a, a.s1, a.e2a, a.s2, a.rB0, a.muB2, a.muB1, a.muB0,
+        a.dA1, a.dA0p, a.llg, a.spK1, a.spK0, a.mdM, a.mdTR, a.md2R, a.mdTmin, a.mdFe, a.mdN, a.rdA, a.rdIn,
+        (double)a.rdLow, (double)(a.top1 - 0x4B000000u), (double)(a.top2 - 0x4B000000u), a.sp_wsbot, a.sp_wpbot,
+        (double)a.sp_low};
+    for (int k = 0; k < kCountConsts; k++) consts[k] = c[k];
+    // (matrix cores: sigma-pi tables hold one entry past the last bin)
+    const size_t more = pl.mode == M_SIGMAPI && form == 2 ? 1 : 0;
+    for (size_t k = 0; k < (size_t)a.n1 + 1; k++) {
+        const bool in = k < (size_t)a.n1 + more;
+        band1[2 * k] = in ? pl.band1[k].x : 0.0f;
+        band1[2 * k + 1] = in ? pl.band1[k].y : 0.0f;
+    }
+    for (size_t k = 0; k < (size_t)a.n2 + 1; k++) {
+        const bool in = a.n2 > 0 && k < (size_t)a.n2 + more;
+        band2[2 * k] = in ? pl.band2[k].x : 0.0f;
+        band2[2 * k + 1] = in ? pl.band2[k].y : 0.0f;
+    }
+    return CUTE_OK;
+}
+
 extern "C" cute_status cute_xi_estimate(cute_estimator e, const uint64_t* dd, const uint64_t* dr,
                                         const uint64_t* rr, int64_t nd, int64_t nr,
                                         const cute_binning* bins, double box_size, double* xi) {

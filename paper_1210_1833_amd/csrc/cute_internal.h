@@ -304,8 +304,15 @@ struct ItemGeom {
 };
 
 // A count launch: thresholds, band tables and the binning's kernel constants.
+// cells and frame of a grid over n points of this bounding box (host only; the
+// grid holds no points)
+cute_status plan_box(const cute_grid_params* p, int64_t n, const double* lo, const double* hi, double max_norm,
+                     GridHost* g);
+
 // number of floats cute_fp32_decision_tables writes to consts
 constexpr int kDecisionConsts = 17;
+// number of doubles cute_fp32_count_constants writes to consts
+constexpr int kCountConsts = 49;
 
 struct Plan {
     int mode = 0, est = 0;

@@ -455,6 +455,22 @@ static cute_status plan_cells(GridHost& g, const cute_grid_params* p, const InSt
     return CUTE_OK;
 }
 
+cute_status plan_box(const cute_grid_params* p, int64_t n, const double* lo, const double* hi, double max_norm,
+                     GridHost* g) {
+    InStats s;
+    memset(&s, 0, sizeof(s));
+    for (int d = 0; d < 3; d++) {
+        s.lo[d] = lo[d];
+        s.hi[d] = hi[d];
+    }
+    s.maxnorm2 = max_norm * max_norm;
+    memset(g, 0, sizeof(*g));
+    g->geom = p->geom;
+    g->n = n;
+    g->tile_max = p->tile_points > 0 ? p->tile_points : 64;
+    return plan_cells(*g, p, s);
+}
+
 }  // namespace cute
 
 using namespace cute;
