@@ -713,7 +713,7 @@ extern "C" cute_status cute_fp32_count_constants(const cute_grid_params* p, int6
     const int form = prec == P_FP64 ? 0 : mfma_plan(pl, prec) && (pl.mode != M_RMU_MID || est_muf(pl.est)) ? 2 : 1;
     const ErrModel& em = geo.em;
     const double c[kCountConsts] = {
-        (double)form, (double)pl.est, em.ec, em.ec64, em.el, em.el64, em.ta,
+        (double)form, (double)pl.est, em.ec, em.ec64, form == 2 ? em.elm : em.el, em.el64, em.ta,
         (double)g.nx, (double)g.ny, (double)g.nz, g.ox, g.oy, g.oz, g.ax, g.ay, g.az, g.cx, g.cy, g.cz,
         (double)geo.max_w, a.skip32, a.out_lo, a.e1a, a.s1, a.e2a, a.s2, a.rB0, a.muB2, a.muB1, a.muB0,
         a.dA1, a.dA0p, a.llg, a.spK1, a.spK0, a.mdM, a.mdTR, a.md2R, a.mdTmin, a.mdFe, a.mdN, a.rdA, a.rdIn,

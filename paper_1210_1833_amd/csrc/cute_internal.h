@@ -280,7 +280,8 @@ cute_status grid_wait(const cute_grid* g, hipStream_t s);
 struct ErrModel {
     double ec = 0.0;     // FP32 separation components
     double ec64 = 0.0;   // canonical FP64 separation components
-    double el = 0.0;     // FP32 line-of-sight components (midpoint)
+    double el = 0.0;     // FP32 line-of-sight components (midpoint), component-wise form
+    double elm = 0.0;    // and of the matrix-core kernels
     double el64 = 0.0;   // FP64 line-of-sight components, before the sqrt(3) factor
     double ta = 0.0;     // matrix-core separations: largest distance of a home point from its
                          // tile's origin (0: differences formed component by component)

@@ -341,10 +341,12 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
                    (A.ext + B.ext + extra + 2 * ca + (B.ext + offmax + 2 * ca) + (A.lmax + B.lmax));
         // matrix cores: l = L0 + a + b with L0 = FP32(2 (cA + o)) as such: the
         // roundings of both copies, of the neighbour's move, of a and b, and
-        // of L0 (at most 2 max|p| and 2 ta in any component)
+        // of L0 (at most 2 max|p| and 2 ta in any component). (Both bounds are
+        // kept: whether an r-mu count takes the matrix cores is decided with
+        // its bands.)
         if (g->em.ta > 0.0)
-            g->em.el = 1.0001 * kU32 * (A.ext + B.ext + extra + (2.0 * g->em.ta + Re) +
-                                        2.0 * (A.rawmax + g->em.ta));
+            g->em.elm = 1.0001 * kU32 * (A.ext + B.ext + extra + (2.0 * g->em.ta + Re) +
+                                         2.0 * (A.rawmax + g->em.ta));
         g->em.el64 = 2.0 * kU64 * (A.lmax + B.lmax);
         g->lcx = (float)(2.0 * A.cx);
         g->lcy = (float)(2.0 * A.cy);
@@ -449,6 +451,7 @@ ErrModel max_err(const ErrModel& x, const ErrModel& y) {
     m.ec = std::max(x.ec, y.ec);
     m.ec64 = std::max(x.ec64, y.ec64);
     m.el = std::max(x.el, y.el);
+    m.elm = std::max(x.elm, y.elm);
     m.el64 = std::max(x.el64, y.el64);
     m.ta = std::max(x.ta, y.ta);
     return m;
@@ -546,7 +549,8 @@ static void midpoint_bands(const cute_binning* b, const ErrModel& em, Plan& pl) 
     const int n1 = b->n1, n2 = b->n2;
     const double s3 = std::sqrt(3.0), u = kU32;
     const double es = s3 * em.ec;            // |s32 - s|
-    const double fe = s3 * em.el;            // |l32 - l|
+    // |l32 - l|; the r-mu tables are those of the component-wise form
+    const double fe = s3 * (pl.mode == M_SIGMAPI && em.ta > 0.0 ? em.elm : em.el);
     const double kg = 16.0;                  // guard: |l32| >= kg fe
     const double ig = 1.0 / (1.0 - 1.0 / kg);
     const double lrel = 1.0 + 2.0 * kRsqRel; // |l32| <= fl(ll rsq(ll)) (1 + 2^-20)
@@ -729,7 +733,7 @@ static void midpoint_mu_band(const cute_binning* b, const ErrModel& em, Plan& pl
     const int n2 = b->n2;
     const double u = kU32, s3 = std::sqrt(3.0);
     const double A = (double)a.e2a, B = (double)a.e2b, S2 = (double)a.s2;
-    const double es = s3 * em.ec, fe = s3 * em.el;
+    const double es = s3 * em.ec, fe = s3 * em.elm;
     double dev = 0.0;
     for (int j = 0; j <= n2; j++) dev = std::max(dev, std::fabs(b->edges2[j] * A + B - (double)j));
     dev = dev * (1.0 + 1e-9) + 1e-12;

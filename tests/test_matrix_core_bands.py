@@ -448,3 +448,22 @@ def test_decisions_on_adversarial_pairs(name):
     assert far_decided == far, (far, far_decided)
     # (most pairs lie within a few bands of an edge by construction)
     assert decided > 100
+
+
+@pytest.mark.parametrize("lo,hi", [([1600.0] * 3, [2600.0] * 3), ([3000.0, -200.0, 2500.0], [4000.0, 800.0, 3500.0])])
+def test_midpoint_line_of_sight_of_the_component_form(lo, hi):
+    # r bins so fine in a tile so large that r-mu is counted with component-wise
+    # separations: its line of sight l = h + ((q - c) + 2 c) has roundings of
+    # its own, which the planned bound of l covers
+    c = case("mid", np.linspace(0.0, 120.0, 1001), np.linspace(0.0, 1.0, 5), mid=True, n=200000, cell=60.0, lo=lo, hi=hi)
+    cn = Count(c)
+    assert cn.k["path"] == 1.0, cn.k
+    rng = np.random.default_rng(5)
+    pts = rng.uniform(lo, hi, (200000, 3))
+    q = pts + rng.uniform(-60.0, 60.0, pts.shape)
+    hp, hq = (pts - cn.c).astype(np.float32), (q - cn.c).astype(np.float32)
+    l32 = hp + (hq + (2.0 * cn.c).astype(np.float32))
+    # (the exact sum of two doubles: l32 - p is exact to far below the bound)
+    err = np.abs((l32.astype(np.float64) - pts) - q).max()
+    print("worst |l32 - l|", err, "bound", cn.k["el"])
+    assert err <= cn.k["el"]
