@@ -84,7 +84,11 @@ typedef enum {
     CUTE_PREC_FP64 = 0,      /* every pair classified in FP64                 */
     CUTE_PREC_FP32_EDGE = 1, /* FP32 separations; pairs inside the rounding
                                 band of an edge are re-tested in FP64. Same
-                                counts as CUTE_PREC_FP64.                     */
+                                counts as CUTE_PREC_FP64. Counts whose
+                                lengths FP32 cannot square (catalogs past
+                                about 1e16 units, r_max below 1e-12; against
+                                the midpoint r_max times twice the distance
+                                past 1e18, r_max below 1e-6) run in FP64.     */
     CUTE_PREC_FP32_ONLY = 2  /* FP32 decisions only, no re-test (not exact;
                                 for measuring the FP32 miscount rate)         */
 } cute_precision;
@@ -432,8 +436,9 @@ cute_status cute_xi_multipoles(const double* xi_rmu, const cute_binning* bins, i
 
 /* Host-only diagnostic: the FP32 decision constants of the midpoint line of
  * sight (SIGMAPI, or RMU with CUTE_LOS_MIDPOINT; mu, pi = r mu and
- * sigma = sqrt(r^2 - pi^2) of Sec. 2.1 measured against l = p + q), built
- * exactly as a count builds them, for a given FP32 error model. No device
+ * sigma = sqrt(r^2 - pi^2) of Sec. 2.1 measured against l = p + q), built as
+ * a count whose separations are differences of components builds them (path 1
+ * of cute_fp32_count_constants), for a given FP32 error model. No device
  * work. It exists so that the rounding analysis behind the exact FP32 path can
  * be checked against exact arithmetic without a GPU.
  * err[4]: bounds per component on |FP32 s - s| (s = p - q), on |FP64 s - s|,
@@ -457,8 +462,9 @@ cute_status cute_fp32_decision_tables(const cute_binning* bins, const double* er
                                       float* band1, float* band2, float* consts);
 
 /* Host-only diagnostic: the FP32 decision constants of an RMU count with the
- * z line of sight (r and mu = |dz| / r of Sec. 2.1), built exactly as a
- * count builds them for a given FP32 error model. No device work; it exists
+ * z line of sight (r and mu = |dz| / r of Sec. 2.1), built as a count whose
+ * separations are differences of components builds them (path 1 of
+ * cute_fp32_count_constants) for a given FP32 error model. No device work; it exists
  * so that the rounding analysis can be checked against exact arithmetic
  * without a GPU.
  * err[2]: bounds per component on |FP32 s - s| and on |FP64 s - s|

@@ -18,7 +18,7 @@ namespace {
 // Items of one binning, counted by one persistent launch.
 struct Group {
     Plan pl;
-    int prec = 0;                    // precision path of the launch (served_prec)
+    int prec = 0;                    // precision path of the launch (plan_form)
     int grid = 0;                    // workgroups
     BatchArgs ba;                    // device pointers filled at creation
     std::vector<int> items;          // item indices, largest estimated cost first
@@ -110,7 +110,7 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
             plan_binning(it.bins, b->groups[g].pl);
         }
         Group& G = b->groups[g];
-        if ((s = plan_item(it.a->h, gb->h, is_auto, it.bins, G.pl, b->prec, &geo[i])) != CUTE_OK) {
+        if ((s = plan_item(it.a->h, gb->h, is_auto, it.bins, G.pl, &geo[i])) != CUTE_OK) {
             set_error("item " + std::to_string(i) + ": " + std::string(cute_last_error()));
             return s;
         }
@@ -134,15 +134,9 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
     b->device = dev;
     CUTE_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     for (Group& G : b->groups) {
-        ErrModel em = geo[G.items[0]].em;
-        G.prec = b->prec;
-        for (int i : G.items) {
-            const cute_batch_item& it = items[i];
-            em = max_err(em, geo[i].em);
-            if (served_prec(b->prec, geo[i], it.a->h, it.b ? it.b->h : it.a->h, G.pl) == P_FP64)
-                G.prec = P_FP64;
-        }
-        plan_bands(items[G.items[0]].bins, em, G.pl);
+        FormErr em = geo[G.items[0]].em;
+        for (int i : G.items) em = max_err(em, geo[i].em);
+        G.prec = plan_form(items[G.items[0]].bins, em, b->prec, G.pl);
         if ((s = plan_lds(G.pl, 16, &G.prec)) != CUTE_OK) return s;
         int per_cu = 1;
         if ((s = batch_prepare(G.pl.mode, G.prec, G.pl.est, G.pl.lds, &per_cu)) != CUTE_OK) return s;

@@ -205,13 +205,25 @@ cute_status launch_b(const BatchArgs& ba, int grid, size_t lds, hipStream_t s) {
 #define CUTE_DISPATCH(FN, mode, prec, est, ...)                                              \
     do {                                                                                      \
         const int m_ = (mode), p_ = (prec), e_ = (est) & E_LOG;                               \
-        if (m_ == M_RMU_Z && p_ == P_FP32E && est_muf(est)) {                                 \
-            if (e_) return FN<1, 1, E_LOG | E_MUF>(__VA_ARGS__);                                \
-            return FN<1, 1, E_MUF>(__VA_ARGS__);                                               \
-        }                                                                                     \
-        if (m_ == M_RMU_MID && p_ == P_FP32E && est_muf(est)) {                               \
-            if (e_) return FN<2, 1, E_LOG | E_MUF>(__VA_ARGS__);                                \
-            return FN<2, 1, E_MUF>(__VA_ARGS__);                                               \
+        if (p_ == P_FP32E && ((est) & (E_DIF | E_MUF)) != 0) {                                \
+            switch (m_ * 8 + (est)) {                                                         \
+                case 4: return FN<0, 1, 4>(__VA_ARGS__);                                      \
+                case 5: return FN<0, 1, 5>(__VA_ARGS__);                                      \
+                case 14: return FN<1, 1, 6>(__VA_ARGS__);                                     \
+                case 15: return FN<1, 1, 7>(__VA_ARGS__);                                     \
+                case 12: return FN<1, 1, 4>(__VA_ARGS__);                                     \
+                case 13: return FN<1, 1, 5>(__VA_ARGS__);                                     \
+                case 10: return FN<1, 1, 2>(__VA_ARGS__);                                     \
+                case 11: return FN<1, 1, 3>(__VA_ARGS__);                                     \
+                case 20: return FN<2, 1, 4>(__VA_ARGS__);                                     \
+                case 21: return FN<2, 1, 5>(__VA_ARGS__);                                     \
+                case 18: return FN<2, 1, 2>(__VA_ARGS__);                                     \
+                case 19: return FN<2, 1, 3>(__VA_ARGS__);                                     \
+                case 28: return FN<3, 1, 4>(__VA_ARGS__);                                     \
+                case 36: return FN<4, 1, 4>(__VA_ARGS__);                                     \
+                case 37: return FN<4, 1, 5>(__VA_ARGS__);                                     \
+                default: return fail(CUTE_E_INTERNAL, "unknown kernel variant");              \
+            }                                                                                 \
         }                                                                                     \
         switch (m_ * 6 + p_ * 2 + e_) {                                                       \
             case 0: return FN<0, 0, 0>(__VA_ARGS__);                                          \
@@ -222,22 +234,15 @@ cute_status launch_b(const BatchArgs& ba, int grid, size_t lds, hipStream_t s) {
             case 5: return FN<0, 2, 1>(__VA_ARGS__);                                          \
             case 6: return FN<1, 0, 0>(__VA_ARGS__);                                          \
             case 7: return FN<1, 0, 1>(__VA_ARGS__);                                          \
-            case 8: return FN<1, 1, 0>(__VA_ARGS__);                                          \
-            case 9: return FN<1, 1, 1>(__VA_ARGS__);                                          \
             case 10: return FN<1, 2, 0>(__VA_ARGS__);                                         \
             case 11: return FN<1, 2, 1>(__VA_ARGS__);                                         \
             case 12: return FN<2, 0, 0>(__VA_ARGS__);                                         \
             case 13: return FN<2, 0, 1>(__VA_ARGS__);                                         \
-            case 14: return FN<2, 1, 0>(__VA_ARGS__);                                         \
-            case 15: return FN<2, 1, 1>(__VA_ARGS__);                                         \
             case 16: return FN<2, 2, 0>(__VA_ARGS__);                                         \
             case 17: return FN<2, 2, 1>(__VA_ARGS__);                                         \
             case 18: return FN<3, 0, 0>(__VA_ARGS__);                                         \
-            case 19: return FN<3, 0, 1>(__VA_ARGS__);                                         \
             case 20: return FN<3, 1, 0>(__VA_ARGS__);                                         \
-            case 21: return FN<3, 1, 1>(__VA_ARGS__);                                         \
             case 22: return FN<3, 2, 0>(__VA_ARGS__);                                         \
-            case 23: return FN<3, 2, 1>(__VA_ARGS__);                                         \
             case 24: return FN<4, 0, 0>(__VA_ARGS__);                                         \
             case 25: return FN<4, 0, 1>(__VA_ARGS__);                                         \
             case 26: return FN<4, 1, 0>(__VA_ARGS__);                                         \

@@ -223,9 +223,8 @@ cute_status count_impl(const cute_grid* ga, const cute_grid* gb, const cute_binn
     Plan pl;
     plan_binning(bins, pl);
     ItemGeom geo;
-    if ((s = plan_item(A, B, is_auto, bins, pl, (int)prec, &geo)) != CUTE_OK) return s;
-    plan_bands(bins, geo.em, pl);
-    int kprec = served_prec((int)prec, geo, A, B, pl);
+    if ((s = plan_item(A, B, is_auto, bins, pl, &geo)) != CUTE_OK) return s;
+    int kprec = plan_form(bins, geo.em, (int)prec, pl, rad != nullptr);
     if (rad) {
         // the aperture binning gave the geometry; the histogram is over the
         // redshift difference, compared with the unsquared edges
@@ -705,15 +704,14 @@ extern "C" cute_status cute_fp32_count_constants(const cute_grid_params* p, int6
     ItemGeom geo;
     int prec = P_FP32E;
     if (n_radial > 0) prec = radial_prec(radial, n_radial);
-    if ((s = plan_item(g, g, true, bins, pl, prec, &geo)) != CUTE_OK) return s;
-    plan_bands(bins, geo.em, pl);
-    prec = served_prec(prec, geo, g, g, pl);
+    if ((s = plan_item(g, g, true, bins, pl, &geo)) != CUTE_OK) return s;
+    prec = plan_form(bins, geo.em, prec, pl, n_radial > 0);
     if (n_radial > 0) plan_radial(radial, n_radial, pl, &prec);
     const CountArgs& a = pl.a;
-    const int form = prec == P_FP64 ? 0 : mfma_plan(pl, prec) && (pl.mode != M_RMU_MID || est_muf(pl.est)) ? 2 : 1;
-    const ErrModel& em = geo.em;
+    const int form = prec == P_FP64 ? 0 : pl.mc ? 2 : 1;
+    const ErrModel& em = pl.mc ? geo.em.mc : geo.em.dif;
     const double c[kCountConsts] = {
-        (double)form, (double)pl.est, em.ec, em.ec64, form == 2 ? em.elm : em.el, em.el64, em.ta,
+        (double)form, (double)pl.est, em.ec, em.ec64, em.el, em.el64, em.ta,
         (double)g.nx, (double)g.ny, (double)g.nz, g.ox, g.oy, g.oz, g.ax, g.ay, g.az, g.cx, g.cy, g.cz,
         (double)geo.max_w, a.skip32, a.out_lo, a.e1a, a.s1, a.e2a, a.s2, a.rB0, a.muB2, a.muB1, a.muB0,
         a.dA1, a.dA0p, a.llg, a.spK1, a.spK0, a.mdM, a.mdTR, a.md2R, a.mdTmin, a.mdFe, a.mdN, a.rdA, a.rdIn,

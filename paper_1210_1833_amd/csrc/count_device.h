@@ -788,18 +788,6 @@ __device__ __forceinline__ void home_valid(const CountArgs& P, uint32_t h, bool*
     }
 }
 
-// Every mode has a separation past which no pair is counted: the top edge of
-// r or of the chord of theta, the aperture of radial pairs, and for sigma-pi
-// sqrt(sigma_max^2 + pi_max^2), since sigma^2 + pi^2 = r^2 for any line of
-// sight. A step whose every pair lies past it (skip32 in FP32, on the
-// clean-out side of the rounding band; top64 in FP64) is skipped after the
-// separations alone. Points are sorted by cell and home tiles are compact, so
-// on clustered catalogs whole steps (four home points against a chunk of
-// nearby neighbours) often fall beyond r_max together; the separations are
-// still formed for every pair.
-template <int MODE>
-constexpr bool kTopSkip = true;
-
 // Weights of home points h .. h+U-1 (wave-uniform, scalar loads).
 template <bool WT, uint32_t U>
 __device__ __forceinline__ void home_weights(const CountArgs& P, uint32_t h, uint32_t* hw) {
@@ -825,9 +813,15 @@ __device__ __forceinline__ void step32(const CountArgs& P, WaveState& W, const T
     home_valid<PM, U>(P, h, hv);
     uint32_t hw[U];
     home_weights<WT, U>(P, h, hw);
-    if constexpr (kTopSkip<MODE>) {
-        // every pair of the step on the clean-out side of the top edge:
-        // nothing to count or re-test (see kTopSkip)
+    {
+        // Every mode has a separation past which no pair is counted: the top edge of r or of the
+        // chord of theta, the aperture of radial pairs, and for sigma-pi sqrt(sigma_max^2 +
+        // pi_max^2), since sigma^2 + pi^2 = r^2 for any line of sight. A step whose every pair
+        // lies past it (skip32 in FP32, on the clean-out side of the rounding band; top64 in
+        // FP64) is skipped after the separations alone. Points are sorted by cell and home tiles
+        // are compact, so on clustered catalogs whole steps (four home points against a chunk of
+        // nearby neighbours) often fall beyond r_max together; the separations are still formed
+        // for every pair.
         float vmin = 0.f;
 #pragma unroll
         for (uint32_t u = 0; u < U; u++) {
@@ -1032,7 +1026,7 @@ struct Column {
 // their arguments through a pointer, and the compiler took these up again from
 // memory in every step (six loads, each a wait): PIN keeps it from doing so.
 struct Hot {
-    float s1, e1a, s2, e2a, skip32, muB2, rB0, dA1, out_lo, rdIn;
+    float s1, e1a, s2, e2a, skip32, muB2, rB0, out_lo, rdIn;
     uint32_t top1, top2, hs1, hs2, rdLow;
 };
 template <bool PIN>
@@ -1053,7 +1047,6 @@ __device__ __forceinline__ Hot hot_args(const CountArgs& P) {
     h.skip32 = f(P.skip32);
     h.muB2 = f(P.muB2);
     h.rB0 = f(P.rB0);
-    h.dA1 = f(P.dA1);
     h.out_lo = f(P.out_lo);
     h.rdIn = P.rdIn;
     h.top1 = u(P.top1);
@@ -1137,31 +1130,21 @@ __device__ __forceinline__ uint64_t decide(const Hot& P, const Tab32& T, float v
         const float rinv = __builtin_amdgcn_rsqf(v);
         const float ts = est_log(EST) ? __builtin_amdgcn_logf(v) + P.s1 : fmaf(v, rinv, P.s1);
         const float ts2 = fmaf(fabsf(dz), rinv, P.s2);
-        if constexpr (est_muf(EST)) {
-            const float bias1 = __uint_as_float(T.vbias1);
-            const float em = fmaf(ts2, P.e2a, bias1);
-            const float half = fmaf(fmaf(P.muB2, rinv, T.d1), rinv, T.d0);
-            const uint64_t min_ = __builtin_amdgcn_ballot_w64(fabsf(fmaf(ts2, P.e2a, bias1 - em)) <= half);
-            const uint32_t om = __umul24(__float_as_uint(em), (uint32_t)P.hs2) + lb;
-            if constexpr (!est_log(EST)) {
-                const float er = fmaf(ts, P.e1a, bias1);
-                *off = __umul24(__float_as_uint(er), (uint32_t)P.hs1) + om;
-                return __builtin_amdgcn_ballot_w64(fabsf(fmaf(ts, P.e1a, bias1 - er)) <= P.rB0) & min_ & lt;
-            } else {
-                const uint32_t kr = est_bits(ts, P.e1a, T, P.top1);
-                *off = __umul24(kr, (uint32_t)P.hs1) + om;
-                return __builtin_amdgcn_ballot_w64(in_band(v, band_at(T.tb1, kr))) & min_ & lt;
-            }
+        static_assert(MODE == M_SIGMAPI || MODE == M_RADIAL || est_muf(EST),
+                      "r-mu with band tables forms its separations component by component");
+        const float bias1 = __uint_as_float(T.vbias1);
+        const float em = fmaf(ts2, P.e2a, bias1);
+        const float half = fmaf(fmaf(P.muB2, rinv, T.d1), rinv, T.d0);
+        const uint64_t min_ = __builtin_amdgcn_ballot_w64(fabsf(fmaf(ts2, P.e2a, bias1 - em)) <= half);
+        const uint32_t om = __umul24(__float_as_uint(em), (uint32_t)P.hs2) + lb;
+        if constexpr (!est_log(EST)) {
+            const float er = fmaf(ts, P.e1a, bias1);
+            *off = __umul24(__float_as_uint(er), (uint32_t)P.hs1) + om;
+            return __builtin_amdgcn_ballot_w64(fabsf(fmaf(ts, P.e1a, bias1 - er)) <= P.rB0) & min_ & lt;
         } else {
             const uint32_t kr = est_bits(ts, P.e1a, T, P.top1);
-            const uint32_t km = est_bits(ts2, P.e2a, T, P.top2);
-            *off = __umul24(kr, (uint32_t)P.hs1) + (__umul24(km, (uint32_t)P.hs2) + lb);
-            const float2 m = band_at(T.tb2, km);
-            const float dz2 = dz * dz;
-            const float delta = est_log(EST) ? fmaf(P.dA1, v * rinv, T.d0) : fmaf(P.dA1, ts, T.d0);
-            return __builtin_amdgcn_ballot_w64(fmaf(m.x, v, dz2) >= delta) &
-                   __builtin_amdgcn_ballot_w64(fmaf(m.y, v, dz2) <= -delta) &
-                   __builtin_amdgcn_ballot_w64(in_band(v, band_at(T.tb1, kr)));
+            *off = __umul24(kr, (uint32_t)P.hs1) + om;
+            return __builtin_amdgcn_ballot_w64(in_band(v, band_at(T.tb1, kr))) & min_ & lt;
         }
     }
 }
@@ -1346,7 +1329,7 @@ __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const d
     home_valid<PM, U>(P, h, hv);
     uint32_t hw[U];
     home_weights<WT, U>(P, h, hw);
-    if constexpr (kTopSkip<MODE>) {
+    {
         // every pair of the step at or past the top threshold (exact FP64)
         double dmin = 0.0;
 #pragma unroll

@@ -166,19 +166,36 @@ cute_status launch_est(const CountArgs& a, int est, int wg_waves, size_t lds, hi
     if (a.wA != nullptr) {
         // weighted pairs: the angular kernels only (pixel maps)
         if constexpr (MODE == M_THETA) {
+            if constexpr (PREC == P_FP32E) {
+                if (est == (E_DIF | E_LOG)) return launch_one<MODE, PREC, E_DIF | E_LOG, true>(a, wg_waves, lds, s, g);
+                if (est == E_DIF) return launch_one<MODE, PREC, E_DIF, true>(a, wg_waves, lds, s, g);
+            }
             if (est_log(est)) return launch_one<MODE, PREC, E_LOG, true>(a, wg_waves, lds, s, g);
             return launch_one<MODE, PREC, E_LIN, true>(a, wg_waves, lds, s, g);
         } else {
             return fail(CUTE_E_UNSUPPORTED, "weighted pairs need a THETA binning");
         }
     }
-    if constexpr ((MODE == M_RMU_Z || MODE == M_RMU_MID) && PREC == P_FP32E) {
-        // the mu decision in mu space (FP32_EDGE only)
-        if (est == (E_LOG | E_MUF)) return launch_one<MODE, PREC, E_LOG | E_MUF, false>(a, wg_waves, lds, s, g);
-        if (est == E_MUF) return launch_one<MODE, PREC, E_MUF, false>(a, wg_waves, lds, s, g);
+    if constexpr (PREC == P_FP32E) {
+        // component-wise separations, and the mu decision in mu space
+        if constexpr (MODE == M_RMU_Z) {
+            if (est == (E_DIF | E_LOG | E_MUF))
+                return launch_one<MODE, PREC, E_DIF | E_LOG | E_MUF, false>(a, wg_waves, lds, s, g);
+            if (est == (E_DIF | E_MUF)) return launch_one<MODE, PREC, E_DIF | E_MUF, false>(a, wg_waves, lds, s, g);
+        }
+        if constexpr (MODE != M_SIGMAPI)
+            if (est == (E_DIF | E_LOG)) return launch_one<MODE, PREC, E_DIF | E_LOG, false>(a, wg_waves, lds, s, g);
+        if (est == E_DIF) return launch_one<MODE, PREC, E_DIF, false>(a, wg_waves, lds, s, g);
+        if constexpr (MODE == M_RMU_Z || MODE == M_RMU_MID) {
+            if (est == (E_LOG | E_MUF)) return launch_one<MODE, PREC, E_LOG | E_MUF, false>(a, wg_waves, lds, s, g);
+            if (est == E_MUF) return launch_one<MODE, PREC, E_MUF, false>(a, wg_waves, lds, s, g);
+        }
+        if constexpr (MODE == M_RMU_Z || MODE == M_RMU_MID) return fail(CUTE_E_INTERNAL, "unknown kernel variant");
     }
-    if (est_log(est)) return launch_one<MODE, PREC, E_LOG, false>(a, wg_waves, lds, s, g);
-    return launch_one<MODE, PREC, E_LIN, false>(a, wg_waves, lds, s, g);
+    constexpr bool general = PREC != P_FP32E || (MODE != M_RMU_Z && MODE != M_RMU_MID);
+    if constexpr (general && MODE != M_SIGMAPI)   // (sigma is estimated linearly)
+        if (est_log(est)) return launch_one<MODE, PREC, E_LOG, false>(a, wg_waves, lds, s, g);
+    if constexpr (general) return launch_one<MODE, PREC, E_LIN, false>(a, wg_waves, lds, s, g);
 }
 
 template <int MODE>

@@ -48,7 +48,7 @@ constexpr bool kSphere = MODE == M_THETA || MODE == M_RADIAL;
 // estimated from log(d2) (log-spaced edges) rather than linearly; bit 1, the
 // mu decision of the z line of sight is taken in mu space (linear mu edges
 // covering [0, 1]), FP32_EDGE only.
-enum Est : int { E_LIN = 0, E_LOG = 1, E_MUF = 2 };
+enum Est : int { E_LIN = 0, E_LOG = 1, E_MUF = 2, E_DIF = 4 };
 constexpr bool est_log(int e) { return (e & E_LOG) != 0; }
 constexpr bool est_muf(int e) { return (e & E_MUF) != 0; }
 // Precision path.
@@ -71,10 +71,10 @@ constexpr bool h32_mode(int mode) { return mode == M_SIGMAPI || mode == M_RMU_MI
 constexpr bool alpha_mode(int mode) { return h32_mode(mode) || mode == M_RADIAL; }
 
 // Count kernels whose separations come from the matrix cores (see step_mfma):
-// every FP32_EDGE kernel, r-mu against the midpoint with the mu decision in mu
-// space only.
+// the FP32_EDGE kernels, except those that form them component by component
+// (E_DIF, see plan_form).
 template <int MODE, int PREC, int EST>
-constexpr bool kMfma = PREC == P_FP32E && (MODE != M_RMU_MID || est_muf(EST));
+constexpr bool kMfma = PREC == P_FP32E && (EST & E_DIF) == 0;
 
 // A home tile: a run of sorted points inside one row of cells.
 struct Tile {
@@ -280,11 +280,18 @@ cute_status grid_wait(const cute_grid* g, hipStream_t s);
 struct ErrModel {
     double ec = 0.0;     // FP32 separation components
     double ec64 = 0.0;   // canonical FP64 separation components
-    double el = 0.0;     // FP32 line-of-sight components (midpoint), component-wise form
-    double elm = 0.0;    // and of the matrix-core kernels
+    double el = 0.0;     // FP32 line-of-sight components (midpoint)
     double el64 = 0.0;   // FP64 line-of-sight components, before the sqrt(3) factor
     double ta = 0.0;     // matrix-core separations: largest distance of a home point from its
                          // tile's origin (0: differences formed component by component)
+};
+
+// The error model of a count in each form of its separations (see plan_form).
+struct FormErr {
+    ErrModel dif, mc;
+    bool fp32 = true;    // lengths inside the range of FP32 squares, component by component
+    bool mfma = true;    // and of the matrix-core kernels
+    double in = 1.0;     // share of the candidate pairs that are in range (uniform catalogs)
 };
 
 // What one pair of grids contributes to a launch.
@@ -294,7 +301,7 @@ struct ItemGeom {
     double L = 0.0, Rs = 0.0, th_s = 0.0, sin_th_s = 0.0;
     float offx = 0.f, offy = 0.f, offz = 0.f, lcx = 0.f, lcy = 0.f, lcz = 0.f;
     int max_w = 1;       // home-tile width limit in cells
-    ErrModel em;
+    FormErr em;
     double cost = 0.0;   // estimated candidate pairs
     double near = 0.0;   // estimated neighbours of a home tile
     // rows of neighbour cells as offsets from the home row (3-D grids of one
@@ -319,6 +326,7 @@ struct Plan {
     int mode = 0, est = 0;
     bool uneven = false;             // edges that neither a linear nor a log estimate finds
     bool muf = false;                // RMU: linear mu edges covering [0, 1], r edges that allow E_MUF
+    bool mc = false;                 // FP32_EDGE: separations from the matrix cores
     double rmax = 0.0;               // largest countable separation
     std::vector<double> T1, T2;      // canonical thresholds
     std::vector<float2> band1, band2;
@@ -334,17 +342,15 @@ struct PartCost {
     float first;         // time per pair of a wave whose CU has other waves ended
 };
 
-// whether the FP32_EDGE count of a plan runs a kMfma kernel
-inline bool mfma_plan(const Plan& pl, int prec) { return prec == P_FP32E && (pl.mode != M_RMU_MID || pl.muf); }
-
 cute_status validate_binning(const cute_binning* b);
 bool same_binning(const cute_binning* a, const cute_binning* b);
 void plan_binning(const cute_binning* b, Plan& pl);
 cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const cute_binning* b,
-                      const Plan& pl, int prec, ItemGeom* g);
-// the precision path that serves a request: FP32_EDGE counts whose lengths
-// leave the range of the FP32 path run the FP64 classifier (same counts)
-int served_prec(int prec, const ItemGeom& g, const GridHost& A, const GridHost& B, const Plan& pl);
+                      const Plan& pl, ItemGeom* g);
+// bands of a plan in the form that serves it (pl.mc), and the precision path:
+// FP32_EDGE counts whose lengths leave the range of FP32 run the FP64 classifier
+// (same counts)
+int plan_form(const cute_binning* b, const FormErr& em, int prec, Plan& pl, bool radial = false);
 // the precision path of a radial count over these edges, and the plan of its
 // aperture (a THETA binning) made into the radial one
 // parts per home tile (log2) of a count with about ntiles tiles, each against
@@ -354,7 +360,7 @@ PartCost part_cost(const Plan& pl, int prec, uint32_t slots);
 std::vector<uint32_t> batch_first(const std::vector<double>& cost, int grid);
 int radial_prec(const double* edges, int n);
 void plan_radial(const double* edges, int n, Plan& pl, int* prec);
-ErrModel max_err(const ErrModel& x, const ErrModel& y);
+FormErr max_err(const FormErr& x, const FormErr& y);
 void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl);
 cute_status plan_lds(Plan& pl, size_t extra, int* prec);
 void apply_item(const ItemGeom& g, CountArgs* a);

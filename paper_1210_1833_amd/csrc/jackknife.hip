@@ -174,11 +174,10 @@ cute_status region_pass(const RegionCopy& home, const GridHost& nb, const uint16
     Plan pl;
     plan_binning(bins, pl);
     ItemGeom geo;
-    if ((s = plan_item(R, nb, false, bins, pl, (int)prec, &geo)) != CUTE_OK) return s;
+    if ((s = plan_item(R, nb, false, bins, pl, &geo)) != CUTE_OK) return s;
     if (selfx && geo.stencil.empty() && R.n > 0)
         return fail(CUTE_E_UNSUPPORTED, "stencil too large for the region pass");
-    plan_bands(bins, geo.em, pl);
-    int kprec = served_prec((int)prec, geo, R, nb, pl);
+    int kprec = plan_form(bins, geo.em, (int)prec, pl);
     if ((s = plan_lds(pl, 16, &kprec)) != CUTE_OK) return s;
     const size_t nbins = (size_t)pl.a.nbins, nh = (size_t)K * nbins;
     h->assign(nh, 0);

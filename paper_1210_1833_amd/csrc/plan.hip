@@ -254,7 +254,7 @@ void plan_binning(const cute_binning* b, Plan& pl) {
 // stencil radius, the home-tile width limit, the FP32 frame offsets and the
 // inputs of the rounding-error model.
 cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const cute_binning* b,
-                      const Plan& pl, int prec, ItemGeom* g) {
+                      const Plan& pl, ItemGeom* g) {
     if (A.geom != B.geom) return fail(CUTE_E_INVALID_ARG, "grids have different geometries");
     const bool sphere = A.geom == CUTE_GEOM_SPHERE;
     const bool periodic = A.geom == CUTE_GEOM_BOX_PERIODIC;
@@ -326,32 +326,38 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
     g->offz = no_off ? 0.f : (float)(A.cz - B.cz);
     const double Re = rmax * 1.01 + 1e-30;
     const double extra = offmax > 0.0 ? kU32 * offmax + kU32 * (B.ext + offmax) : 0.0;
-    g->em.ec = 1.0001 * (kU32 * A.ext + kU32 * B.ext + extra + kU32 * Re);
-    g->em.ec64 = 2.0 * kU64 * (A.rawmax + B.rawmax + (periodic ? A.L : 0.0)) * 1.0001;
-    if (mfma_plan(pl, prec)) {
-        // both points moved into the tile's frame: u (|a| + |b|) more
-        g->em.ta = tile_reach(A, g->max_w);
-        g->em.ec += 1.01 * kU32 * (2.0 * g->em.ta + Re);
-    }
+    ErrModel &dif = g->em.dif, &mc = g->em.mc;
+    dif.ec = 1.0001 * (kU32 * A.ext + kU32 * B.ext + extra + kU32 * Re);
+    dif.ec64 = mc.ec64 = 2.0 * kU64 * (A.rawmax + B.rawmax + (periodic ? A.L : 0.0)) * 1.0001;
+    // matrix cores: both points moved into the tile's frame: u (|a| + |b|) more
+    mc.ta = tile_reach(A, g->max_w);
+    mc.ec = dif.ec + 1.01 * kU32 * (2.0 * mc.ta + Re);
     if (mid) {
         // l = h + ((q - off) + FP32(2 cA)): the roundings of both copies, of the
         // frame shift, of 2 cA, of the two additions (|l| <= max|p| + max|q|)
         const double ca = std::max({std::fabs(A.cx), std::fabs(A.cy), std::fabs(A.cz)});
-        g->em.el = 1.0001 * kU32 *
-                   (A.ext + B.ext + extra + 2 * ca + (B.ext + offmax + 2 * ca) + (A.lmax + B.lmax));
+        dif.el = 1.0001 * kU32 *
+                 (A.ext + B.ext + extra + 2 * ca + (B.ext + offmax + 2 * ca) + (A.lmax + B.lmax));
         // matrix cores: l = L0 + a + b with L0 = FP32(2 (cA + o)) as such: the
         // roundings of both copies, of the neighbour's move, of a and b, and
-        // of L0 (at most 2 max|p| and 2 ta in any component). (Both bounds are
-        // kept: whether an r-mu count takes the matrix cores is decided with
-        // its bands.)
-        if (g->em.ta > 0.0)
-            g->em.elm = 1.0001 * kU32 * (A.ext + B.ext + extra + (2.0 * g->em.ta + Re) +
-                                         2.0 * (A.rawmax + g->em.ta));
-        g->em.el64 = 2.0 * kU64 * (A.lmax + B.lmax);
+        // of L0 (at most 2 max|p| and 2 ta in any component)
+        mc.el = 1.0001 * kU32 * (A.ext + B.ext + extra + (2.0 * mc.ta + Re) + 2.0 * (A.rawmax + mc.ta));
+        dif.el64 = mc.el64 = 2.0 * kU64 * (A.lmax + B.lmax);
         g->lcx = (float)(2.0 * A.cx);
         g->lcy = (float)(2.0 * A.cy);
         g->lcz = (float)(2.0 * A.cz);
     }
+
+    // Both forms square lengths in FP32, and the midpoint's predicates multiply
+    // |s|^2 and |l|^2 of the pairs in range; the matrix cores also mark the
+    // points that are not there with a huge square. Lengths past these limits
+    // are counted in FP64 (r-mu counts of 2e5 points against the midpoint: 1.7 ms
+    // component by component, 2.1 in FP64).
+    const double big = 4.0 * (A.ext + B.ext + std::fabs((double)g->offx) + std::fabs((double)g->offy) +
+                              std::fabs((double)g->offz) + g->L + g->Rs + (mid ? A.lmax + B.lmax : 0.0));
+    const bool small = rmax < (mid ? 1e-6 : 1e-12);
+    g->em.fp32 = !small && big <= 1e17 && (!mid || g->Rs * (A.lmax + B.lmax) <= 1e18);
+    g->em.mfma = !small && big + 4.0 * mc.ta <= (mid ? 1e8 : 1e15);
 
     // Neighbour rows as offsets, when both grids have one geometry (always
     // for an autocorrelation): the gap between the home row and the row at
@@ -429,44 +435,45 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
     }
     // neighbours of a tile of one cell: the cells of its stencil rows, or the
     // tile's box grown by the reach (whose corners hold no rows)
+    double near;   // their share of B's points, of the whole stencil
     if (!g->stencil.empty() && !sphere) {
         double cells = 0.0;
         for (const int4& e : g->stencil) cells += std::min<double>(e.z + e.w + 1, B.nx);
-        g->near = (double)B.n * cells / ((double)B.nx * B.ny * B.nz);
+        near = cells / ((double)B.nx * B.ny * B.nz);
+        g->near = (double)B.n * near;
+        if (is_auto) near *= 2.0;   // (half of the stencil is tabulated)
     } else if (sphere) {
-        g->near = (double)B.n * std::min(1.0, (A.ay + 2.0 * g->th_s) * (A.ax + 2.0 * g->th_s) / vol_b);
+        near = std::min(1.0, (A.ay + 2.0 * g->th_s) * (A.ax + 2.0 * g->th_s) / vol_b);
+        g->near = (double)B.n * near;
     } else {
-        g->near = (double)B.n * std::min(1.0, 0.7 * (A.ax + 2.0 * g->Rs) * (A.ay + 2.0 * g->Rs) *
-                                                  (A.az + 2.0 * g->Rs) / vol_b);
+        near = std::min(1.0, 0.7 * (A.ax + 2.0 * g->Rs) * (A.ay + 2.0 * g->Rs) * (A.az + 2.0 * g->Rs) / vol_b);
+        g->near = (double)B.n * near * (is_auto ? 0.5 : 1.0);
     }
-    if (is_auto && g->stencil.empty()) g->near *= 0.5;
+    g->em.in = std::min(1.0, std::min(1.0, vol_s / vol_b) / std::max(std::min(1.0, near), 1e-300));
     g->cost = (double)A.n * (double)B.n * std::min(1.0, 1.5 * vol_s / vol_b) * (is_auto ? 0.5 : 1.0);
     return CUTE_OK;
 }
 
 // The error model of several items: every term of the bounds grows with each
 // input, so the component-wise maximum bounds every item.
-ErrModel max_err(const ErrModel& x, const ErrModel& y) {
+static ErrModel max_err(const ErrModel& x, const ErrModel& y) {
     ErrModel m;
     m.ec = std::max(x.ec, y.ec);
     m.ec64 = std::max(x.ec64, y.ec64);
     m.el = std::max(x.el, y.el);
-    m.elm = std::max(x.elm, y.elm);
     m.el64 = std::max(x.el64, y.el64);
     m.ta = std::max(x.ta, y.ta);
     return m;
 }
 
-// The matrix-core path forms squares of lengths in FP32 and marks the points
-// that are not there with a huge one: lengths must stay inside [1e-12, 1e15],
-// and for the midpoint, whose predicates multiply squares, inside [1e-6, 1e8].
-int served_prec(int prec, const ItemGeom& g, const GridHost& A, const GridHost& B, const Plan& pl) {
-    if (!mfma_plan(pl, prec)) return prec;
-    const bool mid = pl.mode == M_RMU_MID || pl.mode == M_SIGMAPI;
-    const double big = 4.0 * (A.ext + B.ext + std::fabs((double)g.offx) + std::fabs((double)g.offy) +
-                              std::fabs((double)g.offz) + g.L + g.em.ta + g.Rs +
-                              (mid ? A.lmax + B.lmax : 0.0));
-    return pl.rmax >= (mid ? 1e-6 : 1e-12) && big <= (mid ? 1e8 : 1e15) ? prec : P_FP64;
+FormErr max_err(const FormErr& x, const FormErr& y) {
+    FormErr m;
+    m.dif = max_err(x.dif, y.dif);
+    m.mc = max_err(x.mc, y.mc);
+    m.fp32 = x.fp32 && y.fp32;
+    m.mfma = x.mfma && y.mfma;
+    m.in = std::max(x.in, y.in);
+    return m;
 }
 
 // Parts per home tile (log2). A wave counts one task (a part of a tile) at a
@@ -506,7 +513,7 @@ PartCost part_cost(const Plan& pl, int prec, uint32_t slots) {
         weight = mid || pl.mode == M_RADIAL ? 4.0f : 1.6f;
     else if (mid)
         weight = 2.5f;
-    else if (!mfma_plan(pl, prec))
+    else if (!pl.mc)
         weight = 1.5f;
     return PartCost{std::max(slots, 1u), 4096.0f / weight, 24576.0f / weight, pl.uneven ? 1.0f : 0.5f};
 }
@@ -549,8 +556,7 @@ static void midpoint_bands(const cute_binning* b, const ErrModel& em, Plan& pl) 
     const int n1 = b->n1, n2 = b->n2;
     const double s3 = std::sqrt(3.0), u = kU32;
     const double es = s3 * em.ec;            // |s32 - s|
-    // |l32 - l|; the r-mu tables are those of the component-wise form
-    const double fe = s3 * (pl.mode == M_SIGMAPI && em.ta > 0.0 ? em.elm : em.el);
+    const double fe = s3 * em.el;            // |l32 - l|
     const double kg = 16.0;                  // guard: |l32| >= kg fe
     const double ig = 1.0 / (1.0 - 1.0 / kg);
     const double lrel = 1.0 + 2.0 * kRsqRel; // |l32| <= fl(ll rsq(ll)) (1 + 2^-20)
@@ -733,7 +739,7 @@ static void midpoint_mu_band(const cute_binning* b, const ErrModel& em, Plan& pl
     const int n2 = b->n2;
     const double u = kU32, s3 = std::sqrt(3.0);
     const double A = (double)a.e2a, B = (double)a.e2b, S2 = (double)a.s2;
-    const double es = s3 * em.ec, fe = s3 * em.elm;
+    const double es = s3 * em.ec, fe = s3 * em.el;
     double dev = 0.0;
     for (int j = 0; j <= n2; j++) dev = std::max(dev, std::fabs(b->edges2[j] * A + B - (double)j));
     dev = dev * (1.0 + 1e-9) + 1e-12;
@@ -844,12 +850,9 @@ void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl) {
         const double k1 = 2 * std::sqrt(2.0) * ec + (2 + 2 * s3) * ec64;
         // the kernel uses delta = dA0 + dA1 r with the v term folded in:
         // A2 v <= A2 Re r for every pair whose mu decision counts (r < Re)
-        // (matrix-core separations: M2 E <= 5.1 u (r^2 + 4 ta r + 4 ta^2) more)
-        const double em2 = em.ta > 0.0 ? kMfmaEval : 0.0;
-        const double a2 = 1.5 * (8.1 * kU32 + 16 * kU64 + em2) * 1.0001;
-        const double A1 = (1.5 * (k1 * (1 + 8 * kU32) + 4.0 * em2 * em.ta) + a2 * Re) * 1.0001;
-        const double A0 = 1.5 * (k1 * s3 * ec + 3 * ec * ec + 4 * ec64 * ec64 +
-                                 4.0 * em2 * em.ta * em.ta) * 1.0001;
+        const double a2 = 1.5 * (8.1 * kU32 + 16 * kU64) * 1.0001;
+        const double A1 = (1.5 * k1 * (1 + 8 * kU32) + a2 * Re) * 1.0001;
+        const double A0 = 1.5 * (k1 * s3 * ec + 3 * ec * ec + 4 * ec64 * ec64) * 1.0001;
         a.dA1 = (float)A1;
         a.dA0 = (float)A0;
         a.dA2 = 0.0f;
@@ -870,6 +873,73 @@ void plan_bands(const cute_binning* b, const ErrModel& em, Plan& pl) {
         if (pl.mode == M_RMU_MID && pl.muf && em.ta > 0.0 && (pl.est != E_LIN || r_space_band(b, em, pl)))
             midpoint_mu_band(b, em, pl);
     }
+}
+
+// The share of the pairs in range that the matrix-core form of a plan re-tests
+// beyond the component-wise one (dif): the width of the additional bands times
+// the density of a uniform catalog's pairs there (3 r^2 / R^3 in r, 1 / R^2 in
+// the squared chord and in sigma^2; mu uniform). em: the matrix-core error model.
+static double mc_share(const cute_binning* b, const FormErr& em, const Plan& mc, const Plan& dif) {
+    const double R = mc.rmax, R2 = R * R;
+    const int n1 = b->n1;
+    double share = 0.0;
+    if (mc.mode == M_SIGMAPI) {
+        const double w = 1.25 * kMfmaEval * (2.0 * em.mc.ta + R) * (2.0 * em.mc.ta + R);
+        return 2.0 * w * n1 / mc.T1[n1];
+    }
+    const bool bins = est_muf(mc.est) && !est_log(mc.est);   // r in bin units
+    if (bins) {
+        const double had = est_muf(dif.est) ? (double)dif.a.rB0 : 0.5;
+        share += 2.0 * std::max(0.0, had - (double)mc.a.rB0);
+    } else {
+        for (int k = 0; k <= n1; k++) {
+            if (mc.T1[k] == 0.0) continue;
+            const double r = std::sqrt(mc.T1[k]);
+            const double m = 1.5 * (d2_bound(r, em.mc) - d2_bound(r, em.dif));
+            share += 2.0 * m * (mc.mode == M_THETA ? 1.0 / R2 : 1.5 * r / (R * R2));
+        }
+    }
+    if (est_muf(mc.est)) {
+        const double had = est_muf(dif.est) ? -(double)dif.a.muB1 : 0.0;
+        share += 2.0 * (1.5 * std::max(0.0, -(double)mc.a.muB1 - had) / R - 3.0 * (double)mc.a.muB2 / R2);
+    }
+    return share;
+}
+
+// The form of a FP32_EDGE count's separations. The error of the matrix-core form
+// grows with the square of the home tile's extent, and every pair within it of
+// an edge is re-tested: w(theta) of 3e5 against 3e5 points in one cell, 256 bins,
+// re-tests 3.5 % of its pairs and takes 88.6 ms, component by component 51.3. Over
+// 130 counts of five kinds (cells of 1/6 to 60 times the reach, 10 to 256 bins)
+// the matrix cores are ahead, by 0 to 47 %, where the expected re-tests stay
+// below 0.002 of the candidate pairs (angular counts: 0.92 of the time at 0.0007,
+// 1.03 at 0.002, 1.21 at 0.006), and r-mu ones along z only where few of the pairs
+// in range are re-tested as well (0.98 of the time at 0.0015 of them, 1.02 at
+// 0.009, 1.43 at 0.011). With the band tables of general r or mu edges r-mu has no
+// gain from them (0.98 to 1.4 times). Radial counts have FP64 for the other form,
+// four times slower.
+int plan_form(const cute_binning* b, const FormErr& em, int prec, Plan& pl, bool radial) {
+    pl.mc = false;
+    if (prec == P_FP32E && !em.fp32) prec = P_FP64;
+    if (prec != P_FP32E) {
+        plan_bands(b, em.dif, pl);
+        return prec;
+    }
+    Plan mc = pl;
+    plan_bands(b, em.dif, pl);
+    const bool rmu = b->kind == CUTE_BIN_RMU;
+    if (em.mfma && (!rmu || pl.muf)) {
+        plan_bands(b, em.mc, mc);
+        const double share = mc_share(b, em, mc, pl);
+        if ((!rmu || est_muf(mc.est)) && (pl.mode != M_RMU_Z || share <= 0.01) &&
+            share * em.in <= (radial ? 0.04 : 0.002)) {
+            mc.mc = true;
+            pl = mc;
+            return prec;
+        }
+    }
+    pl.est |= E_DIF;
+    return prec;
 }
 
 // Radial pairs by matrix-core separations, for linear redshift-difference
@@ -910,6 +980,10 @@ void plan_radial(const double* edges, int n, Plan& pl, int* prec) {
     a.nbins = n;
     a.n2p1 = 1;
     if (*prec != P_FP32E) return;
+    if (!pl.mc) {
+        *prec = P_FP64;   // (no other FP32 kernel)
+        return;
+    }
     const double u = kU32, A = n / (edges[n] - edges[0]), B = -edges[0] * A, s = B - 0.5;
     double dev = 0.0;
     for (int k = 0; k <= n; k++) dev = std::max(dev, std::fabs(edges[k] * A + B - (double)k));
@@ -945,8 +1019,8 @@ cute_status plan_lds(Plan& pl, size_t extra, int* prec) {
     if (tables + (size_t)kWgWaves * kWaveLds + ctl + pad + es * (size_t)nbins > lds_max)
         return fail(CUTE_E_UNSUPPORTED, "histogram does not fit in LDS");
     // (kMfma kernels: the band tables have room for one entry more)
-    size_t fixed = tables + (size_t)kWgWaves * wave_lds(mfma_plan(pl, *prec), alpha_mode(pl.mode)) + ctl +
-                   (mfma_plan(pl, *prec) ? 16 : 0);
+    const bool mc = pl.mc && *prec == P_FP32E;
+    size_t fixed = tables + (size_t)kWgWaves * wave_lds(mc, alpha_mode(pl.mode)) + ctl + (mc ? 16 : 0);
     if (fixed + pad + es * (size_t)nbins > lds_max) {
         *prec = P_FP64;
         fixed = tables + (size_t)kWgWaves * wave_lds(false, false) + ctl;
@@ -954,7 +1028,7 @@ cute_status plan_lds(Plan& pl, size_t extra, int* prec) {
     int C = 0;
     // (the kernels of five workgroups per CU: 32000 bytes each; 1500 bins run
     // 4 % faster with one copy and five than with two copies and four)
-    const size_t best = mfma_plan(pl, *prec) && !h32 ? 32000 : 40 * 1024;
+    const size_t best = *prec == P_FP32E && !h32 ? 32000 : 40 * 1024;
     for (size_t budget : {best, (size_t)40 * 1024, (size_t)80 * 1024, lds_max}) {
         if (fixed + pad + es * (size_t)nbins > budget) continue;
         size_t cmax = (budget - fixed - pad) / (es * (size_t)nbins);

@@ -209,12 +209,7 @@ def decide(cn, v, a, b, a2, b2, org, pert, zz):
             kr = int(float(er) - float(B231))
         cert = kr * n2 + km if inr and inm and lt else None
         return cert, not lt or low, dict(ts=ts, ts2=ts2, half=half)
-    kr, km = clamped(ts, e1a, k["top1"]), clamped(ts2, e2a, k["top2"])
-    dz2 = dz * dz
-    delta = fma32(F32(k["dA1"]), v * rinv if int(k["est"]) & 1 else ts, F32(k["dA0p"]))
-    m = cn.b2[km]
-    ok = fma32(m[0], v, dz2) >= delta and fma32(m[1], v, dz2) <= -delta and in_band(v, cn.b1[kr])
-    return (kr * n2 + km if ok and lt else None), not lt or low, {}
+    raise AssertionError("r-mu with band tables has no matrix-core kernel")
 
 
 LIN, MU = np.linspace(0.0, 200.0, 41), np.arange(51) / 50.0
@@ -238,13 +233,11 @@ CASES = {
     "rmu_far": case("rmu", LIN[:31], MU[::2], n=100000, lo=[2e4, -3e4, 1e4], hi=[2.3e4, -2.7e4, 1.3e4]),
     "rmu_coarse": case("rmu", LIN[:13], MU[::5], n=300000, cell=180.0, **BOX),
     "rmu_log": case("rmu", np.geomspace(0.1, 150.0, 25), MU, n=500000, **BOX),
-    "rmu_tables": case("rmu", LIN[4:], np.array([0.1, 0.3, 0.8, 0.95]), n=500000, **BOX),
     "rmu_kpc": case("rmu", LIN * 1e3, MU, n=1000000, lo=[0.0] * 3, hi=[2e6] * 3),
     "mono": case("mono", LIN, n=1000000, **BOX),
     "mono_up_coarse": case("mono", LIN[3:20], n=300000, cell=150.0, **BOX),
     "mono_log_kpc": case("mono", np.geomspace(1e-2, 1.5e5, 30), n=200000, lo=[0.0] * 3, hi=[2e6] * 3),
     "mono_periodic": case("mono", LIN[:31], n=100000, geom="BOX_PERIODIC", L=1000.0, lo=[0.0] * 3, hi=[999.99] * 3),
-    "mono_slab": case("mono", LIN[:13], n=100000, lo=[0.0] * 3, hi=[2000.0, 2000.0, 20.0]),
     "sp": case("sp", np.linspace(0.0, 150.0, 31), np.linspace(0.0, 150.0, 31), mid=True, n=3000000, **SURVEY),
     "sp_up": case("sp", np.linspace(3.0, 80.0, 21), np.linspace(3.0, 60.0, 21), mid=True, n=300000, **SURVEY),
     "mid": case("mid", LIN, MU, mid=True, n=1000000, **SURVEY),
@@ -467,3 +460,34 @@ def test_midpoint_line_of_sight_of_the_component_form(lo, hi):
     err = np.abs((l32.astype(np.float64) - pts) - q).max()
     print("worst |l32 - l|", err, "bound", cn.k["el"])
     assert err <= cn.k["el"]
+
+
+@pytest.mark.parametrize("path,c", [
+    # a tile's frame as large as the separations, and bins as fine as its error
+    (1, case("theta", np.deg2rad(np.linspace(0.0, 30.0, 257)), n=300000, geom="SPHERE", lo=[0.9, 0.0, 0.0],
+             hi=[1.0, 0.31, 0.31], norm=1.0, cell=6.0)),
+    (2, case("theta", np.deg2rad(np.linspace(0.0, 30.0, 257)), n=300000, geom="SPHERE", lo=[0.9, 0.0, 0.0],
+             hi=[1.0, 0.31, 0.31], norm=1.0)),
+    (1, case("rmu", np.linspace(0.0, 60.0, 101), MU[::5], n=100000, cell=300.0, lo=[0.0] * 3, hi=[500.0] * 3)),
+    (2, case("rmu", np.linspace(0.0, 60.0, 101), MU[::5], n=100000, lo=[0.0] * 3, hi=[500.0] * 3)),
+    # general r or mu edges
+    (1, case("rmu", LIN[4:], MU, n=500000, **BOX)),
+    (1, case("rmu", LIN, MU ** 2, n=500000, **BOX)),
+    # lengths past the range of the matrix cores, and of FP32 squares
+    (2, case("mid", LIN, MU, mid=True, n=1000000, **SURVEY)),
+    (1, case("mid", LIN * 2e4, MU, mid=True, n=1000000, lo=[x * 2e4 for x in SURVEY["lo"]],
+             hi=[x * 2e4 for x in SURVEY["hi"]])),
+    (1, case("mid", LIN * 1e6, MU, mid=True, n=1000000, lo=[x * 1e6 for x in SURVEY["lo"]],
+             hi=[x * 1e6 for x in SURVEY["hi"]])),
+    (0, case("mid", LIN * 1e9, MU, mid=True, n=1000000, lo=[x * 1e9 for x in SURVEY["lo"]],
+             hi=[x * 1e9 for x in SURVEY["hi"]])),
+    (1, case("mono", LIN * 1e12, n=1000000, lo=[0.0] * 3, hi=[2e15] * 3)),
+    (0, case("mono", LIN * 1e15, n=1000000, lo=[0.0] * 3, hi=[2e18] * 3)),
+    # radial counts: the matrix cores unless most pairs in the aperture are near it
+    (2, case("radial", [0.0, math.radians(1.0)], n=100000, geom="SPHERE", lo=[0.9, 0.0, 0.0], hi=[1.0, 0.31, 0.31],
+             norm=1.0, radial=np.linspace(0.0, 0.1, 101), cell=6.0)),
+    (0, case("radial", [0.0, math.radians(0.5)], n=100000, geom="SPHERE", lo=[0.999, 0.0, 0.0], hi=[1.0, 0.0175, 0.0175],
+             norm=1.0, radial=np.linspace(0.0, 0.1, 101), cell=6.0)),
+])
+def test_form_of_the_separations(path, c):
+    assert Count(c).k["path"] == path
