@@ -83,8 +83,8 @@ double d2_bound(double r, const ErrModel& em) {
 
 // Largest distance between a home point and its tile's origin, in the FP32
 // frame (see tile_origin): half the diagonal of the tile's box of cells for
-// 3-D grids (an axis of one cell takes the grid's centre: at most the half
-// extent); the extent of a block of pixels for the sphere, whose origin is one
+// 3-D grids (an axis of one cell takes the grid's centre, and its points span no
+// more than the cell or the largest extent); the extent of a block of pixels for the sphere, whose origin is one
 // of the tile's points.
 double tile_reach(const GridHost& A, int max_w) {
     const double slack = 1e-6 * A.ext + 1e-300;
@@ -97,7 +97,7 @@ double tile_reach(const GridHost& A, int max_w) {
         return std::min(2.0, std::sqrt(dz * dz + ds * ds + dp * dp)) * (1.0 + 1e-6) + 1e-5;
     }
     auto half = [&](int cells, int n, double a) {
-        return n == 1 ? A.ext : 0.5 * (double)std::min(cells, n) * a;
+        return n == 1 ? std::min(A.ext, 0.5 * a) : 0.5 * (double)std::min(cells, n) * a;
     };
     const double hx = half(max_w, A.nx, A.ax), hy = half(1, A.ny, A.ay), hz = half(1, A.nz, A.az);
     return std::sqrt(hx * hx + hy * hy + hz * hz) * (1.0 + 1e-6) + slack;

@@ -238,6 +238,9 @@ CASES = {
     "mono_up_coarse": case("mono", LIN[3:20], n=300000, cell=150.0, **BOX),
     "mono_log_kpc": case("mono", np.geomspace(1e-2, 1.5e5, 30), n=200000, lo=[0.0] * 3, hi=[2e6] * 3),
     "mono_periodic": case("mono", LIN[:31], n=100000, geom="BOX_PERIODIC", L=1000.0, lo=[0.0] * 3, hi=[999.99] * 3),
+    # a thin slab: one cell along z, whose points span far less than the others
+    "mono_slab": case("mono", LIN[:13], n=100000, lo=[0.0] * 3, hi=[2000.0, 2000.0, 20.0]),
+    "rmu_slab": case("rmu", LIN[:13], MU[::5], n=100000, lo=[0.0] * 3, hi=[2000.0, 2000.0, 20.0]),
     "sp": case("sp", np.linspace(0.0, 150.0, 31), np.linspace(0.0, 150.0, 31), mid=True, n=3000000, **SURVEY),
     "sp_up": case("sp", np.linspace(3.0, 80.0, 21), np.linspace(3.0, 60.0, 21), mid=True, n=300000, **SURVEY),
     "mid": case("mid", LIN, MU, mid=True, n=1000000, **SURVEY),
@@ -491,3 +494,12 @@ def test_midpoint_line_of_sight_of_the_component_form(lo, hi):
 ])
 def test_form_of_the_separations(path, c):
     assert Count(c).k["path"] == path
+
+
+def test_reach_of_a_slabs_tiles():
+    # the reach is that of the tile's own box: with the largest half extent in
+    # place of the slab's, 1000 here, r-mu counts lost the matrix cores
+    for name in ("mono_slab", "rmu_slab"):
+        k = Count(CASES[name]).k
+        assert k["nz"] == 1.0 and k["path"] == 2.0
+        assert k["ta"] <= 0.51 * math.sqrt((k["max_w"] * k["ax"]) ** 2 + k["ay"] ** 2 + k["az"] ** 2)
