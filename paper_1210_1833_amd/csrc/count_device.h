@@ -509,6 +509,7 @@ struct WaveState {
     // evaluations not reported to it yet
     uint32_t* budget;
     uint32_t pend;
+    uint32_t all64;      // radial: counting in FP64 for now (see do_tile)
 };
 
 // LDS of a count workgroup: [staged home points | tables | histogram |
@@ -579,6 +580,7 @@ __device__ __forceinline__ WaveState wave_state(const WgLds& l, int wave) {
     W.hist = l.hist;
     W.budget = nullptr;
     W.pend = 0;
+    W.all64 = 0;
     W.qi = l.queue + (size_t)wave * 2 * kQCap;
     W.qj = W.qi + kQCap;
     W.qc = l.qcodes + (size_t)wave * kQCap;
@@ -2111,7 +2113,21 @@ __device__ void do_tile(const CountArgs& P, WaveState& W, SpanBuf& S, const floa
             next_chunk<kSphere<MODE>>(P, W, S, N, tl, lane, part, plog);
             if ((uint32_t)lane < N.filled) load_near<MODE, PM, WT>(P, pn, N.lj);
             if (C.filled == 0u) continue;
-            if (MODE == M_RMU_MID && W.mt < 0.f)
+            // Radial: redshifts rounded to the bin width leave most pairs on an
+            // edge, where re-tests take longer than FP64 throughout: a wave
+            // that re-tested more than 1/24 of its pairs so far (pend, in units
+            // of 64; looked at every 512 of them) counts so. Data and randoms
+            // of 3e5 rounded to the width: 8.1 ms without, 5.5 with this as in
+            // FP64 throughout; rounded to a tenth of it, 2 % re-tested: 2.6.
+            bool all64 = MODE == M_RMU_MID && W.mt < 0.f;
+            if constexpr (MODE == M_RADIAL) {
+                const uint32_t seen = W.pend + ((C.filled * (tl.end - tl.start) + 63u) >> 6);
+                if (((seen ^ W.pend) & ~511u) != 0u)
+                    W.all64 = uni(W.rstat[0] * 24ull > (unsigned long long)seen * 64ull ? 1u : 0u);
+                W.pend = seen;
+                all64 = W.all64 != 0u;
+            }
+            if ((MODE == M_RMU_MID || MODE == M_RADIAL) && all64)
                 run_chunk<MODE, P_FP64, EST & E_LOG, PM, WT>(P, W, B1, B2, T1, T2, lane, C, tl.start, tl.end);
             else
                 run_chunk_mfma<MODE, EST, PM, WT>(P, hot, W, tab, B1, B2, T1, T2, lane, C, p, tl.start, tl.end);
