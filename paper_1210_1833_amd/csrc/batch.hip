@@ -166,7 +166,10 @@ cute_status create(const cute_batch_item* items, int32_t n_items, cute_precision
         if (A.n > 0 && B.n > 0) {
             const uint64_t min_tiles = ((uint64_t)A.n + A.tile_max - 1) / A.tile_max;
             const uint64_t bound = tile_count_bound(A, geo[i].max_w);
-            if (bound <= std::max<uint64_t>(65536, 4 * min_tiles)) {
+            // (the ordered list keeps a slot per possible tile for the batch's
+            // life: at most eight times what the points need and 32 KB, where a
+            // single count accepts 1 MB for its own duration)
+            if (bound <= 8 * min_tiles + 2048 && bound < (uint64_t(1) << 31)) {
                 t.n = (uint32_t)bound;
                 t.est = std::sqrt((double)min_tiles * (double)bound);
                 max_slots = std::max<size_t>(max_slots, t.n);
