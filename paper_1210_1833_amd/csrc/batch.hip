@@ -27,7 +27,7 @@ struct Group {
 }  // namespace
 
 struct cute_batch {
-    int device = 0;
+    int device = -1;                 // where its memory lies (-1: none yet)
     int prec = 0;
     int n_items = 0;
     std::vector<Group> groups;
@@ -55,11 +55,17 @@ cute_status owned_alloc(cute_batch* b, T** p, size_t count, hipStream_t s) {
 
 void release(cute_batch* b) {
     if (!b) return;
+    // the batch's device, whatever device is current: its work ends, and its
+    // memory goes back to that device's pool
+    int cur = -1;
+    const bool other = b->device >= 0 && hipGetDevice(&cur) == hipSuccess && cur != b->device;
+    if (other) (void)hipSetDevice(b->device);
     (void)hipDeviceSynchronize();
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->cap) (void)hipStreamDestroy(b->cap);
     for (void* p : b->owned) dfree(p, nullptr);
+    if (other) (void)hipSetDevice(cur);
     delete b;
 }
 
