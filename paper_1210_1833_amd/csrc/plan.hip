@@ -565,7 +565,11 @@ static void midpoint_bands(const cute_binning* b, const ErrModel& em, Plan& pl) 
     if (pl.mode == M_SIGMAPI) {
         // |s| of any pair with v32 < skip32 (skip32 covers the FP32 and FP64
         // errors of d2 up to there)
-        const double Rv = std::sqrt((double)a.skip32 * (1.0 + 3.02 * u)) + es;
+        // (component-wise the three-term sum errs by 3.02 u of itself, and es
+        // covers its components; the expanded form's v by the d2 bound)
+        const double rt = std::sqrt((double)a.skip32) * (1.0 + 1e-3);
+        const double Rv = em.ta > 0.0 ? std::sqrt((double)a.skip32 + 1.01 * d2_bound(rt, em)) + es
+                                      : std::sqrt((double)a.skip32 * (1.0 + 3.02 * u)) + es;
         const double Tmax = std::max(pl.T1[n1], pl.T2[n2]);
         const double E64 = 64.0 * kU64 * (Rv * Rv + Tmax);
         const double xmax = std::sqrt(Tmax + E64) * (1.0 + 1e-9);

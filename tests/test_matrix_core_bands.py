@@ -503,3 +503,14 @@ def test_reach_of_a_slabs_tiles():
         k = Count(CASES[name]).k
         assert k["nz"] == 1.0 and k["path"] == 2.0
         assert k["ta"] <= 0.51 * math.sqrt((k["max_w"] * k["ax"]) ** 2 + k["ay"] ** 2 + k["az"] ** 2)
+
+
+@pytest.mark.parametrize("cell", [0.0, 300.0])
+def test_largest_separation_of_a_decided_sigma_pi_pair(cell):
+    # a pair is decided when v < skip32, and v may be below |s|^2 by its error
+    c = case("sp", np.linspace(0.0, 20.0, 5), np.linspace(0.0, 20.0, 5), mid=True, n=300000, cell=cell, **SURVEY)
+    k = Count(c).k
+    assert k["path"] == 2.0
+    R = 0.5 * k["2R"]
+    err = 5.1 * U32 * (2 * k["ta"] + R) ** 2 + 2 * math.sqrt(3.0) * R * k["ec"]
+    assert R * R >= k["skip32"] + err
