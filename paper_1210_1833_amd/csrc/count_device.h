@@ -20,7 +20,6 @@ constexpr double kPi = 3.14159265358979323846264338327950288;
 typedef const __attribute__((address_space(4))) float* cfp;
 typedef const __attribute__((address_space(4))) double* cdp;
 typedef const __attribute__((address_space(4))) uint32_t* cu32p;
-typedef const __attribute__((address_space(4))) double* cf64p;
 typedef const __attribute__((address_space(4))) CountArgs* cargp;
 
 // x, y, z of the U consecutive points h .. h+U-1 from one base address with
@@ -677,7 +676,7 @@ __device__ __forceinline__ uint32_t classify_radial(const CountArgs& P, const do
 }
 
 // Re-test up to 64 queued pairs per pass, one per lane, through the canonical
-// FP64 predicates; count the pairs whose FP32-only decision differs (flips).
+// FP64 predicates; count the pairs for which FP32_ONLY decides otherwise (flips).
 // Returns the new queue length.
 template <int MODE, int EST>
 __device__ __forceinline__ uint32_t drain_queue(
@@ -703,7 +702,7 @@ __device__ __forceinline__ uint32_t drain_queue(
             }
             if (k != kNoBin) hist_add<kH32<MODE>>(hist, k, P.copies, lane, pair_weight2(P, i, j));
             if constexpr (MODE != M_RADIAL) {
-                // the FP32-only decision of the same pair, as the main loop made it
+                // the decision that FP32_ONLY makes for the same pair
                 const float4 a = P.A.p32[i];
                 const float4 b = P.B.p32[j];
                 const float Lf = (float)P.L;
@@ -771,9 +770,11 @@ __device__ __forceinline__ uint32_t enqueue_chunk(
 
 // ---------------------------------------------------------------------------
 // The hot loop. A chunk holds up to 64 neighbour points, one per lane, in
-// VGPRs; the home points of the tile are wave-uniform and arrive through
-// scalar loads, U at a time, so that U independent pair evaluations per lane
-// interleave. Every lane evaluates the pair (home h, its neighbour).
+// VGPRs; the home points of the tile are taken U at a time, so that U
+// independent pair evaluations per lane interleave. Every lane evaluates the
+// pair (home h, its neighbour). In the matrix-core kernels the home points are
+// rows of a product, staged in LDS (see step_mfma); in the others they are
+// wave-uniform and arrive through scalar loads.
 // ---------------------------------------------------------------------------
 // Home points h .. h+U-1 not excluded by the point mask (wave-uniform).
 template <bool PM, uint32_t U>
@@ -1405,7 +1406,7 @@ __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const d
     }
     double hr[U];
     if constexpr (MODE == M_RADIAL) {
-        const cf64p ra = (cf64p)(const void*)P.rA;
+        const cdp ra = (cdp)(const void*)P.rA;
 #pragma unroll
         for (uint32_t u = 0; u < U; u++) hr[u] = ra[h + u];
     }

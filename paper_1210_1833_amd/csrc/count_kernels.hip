@@ -5,10 +5,13 @@
 // contiguous spans of the other catalog. The spans are cut into chunks of 64
 // neighbour points, one per lane in VGPRs. A step evaluates four home points
 // against them, four independent pairs per lane: in FP32_EDGE the separations
-// are matrix products whose rows are home points staged in LDS, in the other
-// paths the home points are wave-uniform and arrive through scalar loads. Counts go to one 64-bit LDS histogram per
+// are matrix products whose rows are home points staged in LDS (or, where that
+// form would re-test too many pairs, differences of components, see
+// plan_form); there and in the other paths the home points are wave-uniform
+// and arrive through scalar loads. Counts go to one LDS histogram per
 // workgroup (several interleaved copies, so that lanes hitting the same bin
-// use different banks), summed into uint64 global counts at the end.
+// use different banks; 64-bit counters, 32-bit ones for the midpoint kinds),
+// summed into uint64 global counts at the end.
 //
 // Precision paths
 //  - FP64: every pair is classified by the canonical FP64 predicates.
@@ -63,7 +66,7 @@ __global__ __launch_bounds__(256, (kWgPerCu<MODE, PREC>)) void k_count(CountArgs
     W.budget = L.ctl;   // 32-bit histograms only
     SpanBuf S = span_buf(L, wave);
 
-    // tasks: the parts of the tiles. Every wave starts with the task of its
+    // tasks: the parts of the tiles (see part_rule). Every wave starts with the task of its
     // own number, so that a launch of no more tasks than waves pops none; an
     // empty tile slot is no tile.
     const uint32_t plog = P.ntiles_dev ? uni(P.ntiles_dev[1]) : (uint32_t)P.plog;

@@ -43,11 +43,11 @@ enum Mode : int { M_MONO = 0, M_RMU_Z = 1, M_RMU_MID = 2, M_SIGMAPI = 3, M_THETA
 // Kinds counted on spherical grids; the others take 3-D boxes.
 template <int MODE>
 constexpr bool kSphere = MODE == M_THETA || MODE == M_RADIAL;
-// How a bin index is estimated from the squared separation.
-// Estimate flags of a count kernel: bit 0, dimension 1 (r or theta) is
+// How a count kernel finds a pair's bin. Bit 0: dimension 1 (r or theta) is
 // estimated from log(d2) (log-spaced edges) rather than linearly; bit 1, the
 // mu decision of the z line of sight is taken in mu space (linear mu edges
-// covering [0, 1]), FP32_EDGE only.
+// covering [0, 1]), FP32_EDGE only; bit 2, FP32_EDGE forms the separations
+// component by component and not on the matrix cores (see plan_form).
 enum Est : int { E_LIN = 0, E_LOG = 1, E_MUF = 2, E_DIF = 4 };
 constexpr bool est_log(int e) { return (e & E_LOG) != 0; }
 constexpr bool est_muf(int e) { return (e & E_MUF) != 0; }
@@ -311,7 +311,6 @@ struct ItemGeom {
     std::vector<int4> stencil;
 };
 
-// A count launch: thresholds, band tables and the binning's kernel constants.
 // cells and frame of a grid over n points of this bounding box (host only; the
 // grid holds no points)
 cute_status plan_box(const cute_grid_params* p, int64_t n, const double* lo, const double* hi, double max_norm,
@@ -322,6 +321,7 @@ constexpr int kDecisionConsts = 17;
 // number of doubles cute_fp32_count_constants writes to consts
 constexpr int kCountConsts = 49;
 
+// A count launch: thresholds, band tables and the binning's kernel constants.
 struct Plan {
     int mode = 0, est = 0;
     bool uneven = false;             // edges that neither a linear nor a log estimate finds
@@ -351,13 +351,14 @@ cute_status plan_item(const GridHost& A, const GridHost& B, bool is_auto, const 
 // FP32_EDGE counts whose lengths leave the range of FP32 run the FP64 classifier
 // (same counts)
 int plan_form(const cute_binning* b, const FormErr& em, int prec, Plan& pl, bool radial = false);
-// the precision path of a radial count over these edges, and the plan of its
-// aperture (a THETA binning) made into the radial one
 // parts per home tile (log2) of a count with about ntiles tiles, each against
 // that many neighbours
 int part_log(double ntiles, double neighbours, int ncu);
 PartCost part_cost(const Plan& pl, int prec, uint32_t slots);
+// first item of each workgroup of a batched launch, by the items' costs
 std::vector<uint32_t> batch_first(const std::vector<double>& cost, int grid);
+// the precision path of a radial count over these edges, and the plan of its
+// aperture (a THETA binning) made into the radial one
 int radial_prec(const double* edges, int n);
 void plan_radial(const double* edges, int n, Plan& pl, int* prec);
 FormErr max_err(const FormErr& x, const FormErr& y);
@@ -407,7 +408,6 @@ cute_status order_tiles_to(const CountArgs& a, const Tile* in, uint32_t ntiles, 
 cute_status order_tiles(const CountArgs& a, Tile** tiles, uint32_t ntiles, const PartCost& pc, uint32_t* total,
                         hipStream_t s);
 
-// persistent count launch; *grid_used receives the number of workgroups
 // out[i] = in[input index of sorted point i] for the n points of g (in:
 // host or device memory); waits for the stream; rejects non-finite values.
 cute_status gather_values(const GridHost& g, const double* in, bool on_device, double* out,
@@ -430,6 +430,8 @@ cute_status count_pairs_fixed(const cute_grid* a, const cute_grid* b, const cute
                               cute_precision prec, uint64_t* counts, int32_t counts_on_device,
                               cute_count_stats* st, void* stream, const FixedArea* fixed);
 
+// persistent count launch; *grid_used receives the number of workgroups (all
+// that it does when args.tiles is nullptr)
 cute_status launch_count(const CountArgs& args, int mode, int prec, int est, int wg_waves,
                          size_t lds_bytes, hipStream_t stream, int* grid_used);
 

@@ -67,7 +67,6 @@ class DevArena {
     explicit DevArena(hipStream_t s) : s_(s) {}
     DevArena(hipStream_t s, unsigned char* base, size_t cap) : s_(s), base_(base), cap_(cap) {}
     bool fixed() const { return base_ != nullptr; }
-    size_t capacity() const { return cap_; }
     // bytes a fixed area spends on `count` elements of T (with alignment)
     template <typename T>
     static size_t cost(size_t count) {
@@ -155,10 +154,6 @@ struct EventTimer {
         float ms = 0.f;
         (void)hipEventElapsedTime(&ms, a, b);
         return ms;
-    }
-    double stop_ms() {
-        stop();
-        return elapsed_ms();
     }
     ~EventTimer() {
         if (!own) return;
