@@ -1371,36 +1371,57 @@ __device__ __forceinline__ void step64(const CountArgs& P, WaveState& W, const d
         for (uint32_t u = 0; u < U; u++)
             if (cnt[u]) lds_add<kH32<MODE>>(off[u] + lb, WT ? lw * hw[u] : lw);
         if (__builtin_amdgcn_ballot_w64(any) == 0ull) return;
-#pragma unroll 1
-        for (uint32_t u = 0; u < U; u++) {
-            bool a = false;
-            double x = 0.0, y = 0.0, z = 0.0;
-            uint32_t w = 1u;
+        // The misses. Edges that no guess fits miss in nearly every step, so the
+        // one-variable kinds search unrolled (the loop below selects a pair's
+        // home point among four: uneven angular bins 9.40 ms so, 8.24 unrolled;
+        // the r-mu kernel, with twice the search, gains nothing from it).
+        if constexpr (MODE != M_RMU_Z) {
 #pragma unroll
-            for (uint32_t t = 0; t < U; t++)
-                if (t == u) {
-                    a = amb[t];
-                    x = hx[t];
-                    y = hy[t];
-                    z = hz[t];
-                    w = hw[t];
+            for (uint32_t u = 0; u < U; u++) {
+                if (!amb[u]) continue;
+                double dx = hx[u] - qx, dy = hy[u] - qy, dz = hz[u] - qz;
+                if (SHIFTED) {
+                    dx = dx - sx;
+                    dy = dy - sy;
+                    dz = dz - sz;
                 }
-            if (!a) continue;
-            double dx = x - qx, dy = y - qy, dz = z - qz;
-            if (SHIFTED) {
-                dx = dx - sx;
-                dy = dy - sy;
-                dz = dz - sz;
+                const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
+                const int k1 = guess1<MODE == M_THETA ? M_THETA : M_MONO, EST>(P, (float)d2);
+                const uint32_t bin = classify64<MODE>(P, T1, T2, dx, dy, dz, 0.0, 0.0, 0.0, k1, 0);
+                if (bin != kNoBin)
+                    hist_add<kH32<MODE>>(W.hist, bin, P.copies, lane, WT ? lw * hw[u] : lw);
             }
-            const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
-            const float v = (float)d2;
-            const int k1 = guess1<MODE == M_THETA ? M_THETA : M_MONO, EST>(P, v);
-            int k2 = 0;
-            if constexpr (MODE == M_RMU_Z)
-                k2 = guess_lin(fabsf((float)dz) * __builtin_amdgcn_rsqf(v), P.e2a, P.e2b, P.n2m1);
-            const uint32_t bin = classify64<MODE>(P, T1, T2, dx, dy, dz, 0.0, 0.0, 0.0, k1, k2);
-            if (bin != kNoBin)
-                hist_add<kH32<MODE>>(W.hist, bin, P.copies, lane, WT ? lw * w : lw);
+        } else {
+#pragma unroll 1
+            for (uint32_t u = 0; u < U; u++) {
+                bool a = false;
+                double x = 0.0, y = 0.0, z = 0.0;
+                uint32_t w = 1u;
+#pragma unroll
+                for (uint32_t t = 0; t < U; t++)
+                    if (t == u) {
+                        a = amb[t];
+                        x = hx[t];
+                        y = hy[t];
+                        z = hz[t];
+                        w = hw[t];
+                    }
+                if (!a) continue;
+                double dx = x - qx, dy = y - qy, dz = z - qz;
+                if (SHIFTED) {
+                    dx = dx - sx;
+                    dy = dy - sy;
+                    dz = dz - sz;
+                }
+                const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
+                const float v = (float)d2;
+                const int k1 = guess1<M_MONO, EST>(P, v);
+                const int k2 =
+                    guess_lin(fabsf((float)dz) * __builtin_amdgcn_rsqf(v), P.e2a, P.e2b, P.n2m1);
+                const uint32_t bin = classify64<MODE>(P, T1, T2, dx, dy, dz, 0.0, 0.0, 0.0, k1, k2);
+                if (bin != kNoBin)
+                    hist_add<kH32<MODE>>(W.hist, bin, P.copies, lane, WT ? lw * w : lw);
+            }
         }
         return;
     }
