@@ -507,9 +507,10 @@ __global__ __launch_bounds__(256) void k_tile_rank(const uint32_t* __restrict__ 
 // pairs and its set-up, at least the set-up's waits beside which pairs of other
 // waves are issued (own); one that starts when the tasks before it are shared
 // out ends at (theirs and its own) / slots + own. The tasks that are their
-// waves' first run on while others have ended, faster; when all of them are,
-// some CUs have more of them than others (a chip half full takes twice the time
-// of an even share). The count ends at the latest of these, and the rule takes
+// waves' first run on while others have ended, faster; when all of them are, or
+// nearly all, some CUs have more of them than others (a chip half full takes
+// twice the time of an even share; a radial count of 5126 tiles on 5120 waves
+// took 1.78 ms uncut and 1.58 in eight parts). The count ends at the latest of these, and the rule takes
 // the cut that ends first.
 // Costs are the device's because a host estimate sees the bounding box only:
 // with one, a light-cone FP64 count of 2e5 points, mostly empty box, was left
@@ -550,7 +551,7 @@ __device__ __forceinline__ uint32_t part_rule(uint32_t v, float c, uint32_t upto
             all += wsum[w][p];
         }
         end[p] = v == 0u ? 0.f : (float)upto * n > slots ? own[p] + sum[p] * is : pc.first * (c / n) + pc.wait;
-        end[p] = fmaxf(end[p], (float)ntiles * n <= slots ? all * (0.6f * is + 0.75f / ((float)ntiles * n)) : 0.f);
+        end[p] = fmaxf(end[p], all * (0.6f * is + 0.75f / ((float)ntiles * n)));
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)

@@ -476,7 +476,9 @@ FormErr max_err(const FormErr& x, const FormErr& y) {
     return m;
 }
 
-// Parts per home tile (log2). A wave counts one task (a part of a tile) at a
+// Parts per home tile (log2), estimated on the host: what unordered tiles and
+// region passes are cut in and a batch's launch is sized by (ordered tiles are
+// cut by their costs, see part_rule). A wave counts one task (a part of a tile) at a
 // time, so a count whose tiles hardly outnumber the wave slots ends with most
 // of the chip waiting for the last tiles: at 2 tiles per slot the r-mu count
 // of 250 000 points ran at 1200 Gpair/s, at 6 at 1550. The tiles are cut until
