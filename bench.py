@@ -27,7 +27,20 @@ sys.path.insert(0, ROOT)
 
 PEAK_LANE_OPS = 256 * 64 * 2.4e9     # unpacked VALU lane-instructions/s (256 CUs, 2.4 GHz)
 PEAK_FP32_FLOPS = 157.3e12            # FP32 vector peak (packed FMA counted as 4 flops per lane)
-I_ALG_RMU_Z = 21                      # algorithmic FP32 lane-ops per r-mu pair evaluation
+
+# FP32-pipe operations per candidate pair that a count cannot do without, in
+# vector lane-ops: a pair of a decided step takes its vector operations and its
+# matrix products (four per separation of four pairs and one more per dz, s.l or
+# |l|^2; at the published rates one takes the pipe as long as two vector
+# instructions), a pair of a step that is dropped after its separations
+# (wholly past the top edge) one compare and the four products. The shares of
+# dropped steps were counted with an instrumented copy of the kernels on these
+# workloads.
+def i_alg(vector, products, dropped):
+    return (1.0 - dropped) * (vector + 2.0 * products / 4.0) + dropped * (1.0 + 2.0)
+
+
+I_ALG_RMU_Z = i_alg(16, 5, 0.33)      # r and mu in bin units, line of sight z
 
 
 def log(*a):
@@ -523,7 +536,7 @@ def main():
                      "traffic_source": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this kernel "
                                        "source (profiles/k_count_rmu_clustered_1e6_dd.json), "
                                        "not measured in this run; null when the source changed",
-                     "kernel_ms": round(kern_ms, 4), "i_alg": I_ALG_RMU_Z,
+                     "kernel_ms": round(kern_ms, 4), "i_alg": round(I_ALG_RMU_Z, 2),
                      "flop_convention_frac": round(evals * I_ALG_RMU_Z / (kern_ms * 1e-3)
                                                    / PEAK_FP32_FLOPS, 4),
                      "flop_convention_peak_tflops": PEAK_FP32_FLOPS / 1e12},
@@ -549,8 +562,8 @@ def main():
     print(json.dumps(out), flush=True)
 
 
-I_ALG_SIGMAPI = 40                    # algorithmic FP32 lane-ops per sigma-pi (midpoint) pair evaluation
-I_ALG_THETA = 16                      # algorithmic FP32 lane-ops per theta pair evaluation
+I_ALG_SIGMAPI = i_alg(24, 6, 0.26)    # sigma and pi against the pair midpoint
+I_ALG_THETA = i_alg(10, 4, 0.46)       # log theta bins
 
 
 def mode_leg(cute, torch, dev, kind, reps=2):
@@ -567,7 +580,7 @@ def mode_leg(cute, torch, dev, kind, reps=2):
         cat, _ = catalogs.lightcone_3e6()
         e = np.arange(76) * 2.0
         bn = cute.Binning(cute.BIN_SIGMAPI, e, e, los=cute.LOS_MIDPOINT)
-        geom, reach, i_alg = cute.GEOM_BOX_OPEN, float(np.hypot(e[-1], e[-1])) * (1 + 1e-12), I_ALG_SIGMAPI
+        geom, reach, ops = cute.GEOM_BOX_OPEN, float(np.hypot(e[-1], e[-1])) * (1 + 1e-12), I_ALG_SIGMAPI
         golden, workload = "lightcone_3e6_dd_sigmapi.json", (
             "sigma-pi DD of the light cone: 3e6 points, RA 0-60 deg, Dec 0-30 deg, Gaussian n(z), "
             "sigma and pi in [0, 150) Mpc/h, 75 x 75 bins, midpoint line of sight")
@@ -575,7 +588,7 @@ def mode_leg(cute, torch, dev, kind, reps=2):
         cat, _ = catalogs.angular_cap_1e7()
         e = np.deg2rad(0.001 * 10.0 ** (np.arange(31) * 4.0 / 30.0))
         bn = cute.Binning(cute.BIN_THETA, e)
-        geom, reach, i_alg = cute.GEOM_SPHERE, float(e[-1]), I_ALG_THETA
+        geom, reach, ops = cute.GEOM_SPHERE, float(e[-1]), I_ALG_THETA
         golden, workload = None, ("theta DD of the angular cap: 1e7 clustered unit vectors in "
                                   "5000 sq-deg, 30 log bins of theta in [0.001, 10] deg")
     xyz = [torch.from_numpy(np.ascontiguousarray(v)).to(dev) for v in (cat.x, cat.y, cat.z)]
@@ -611,12 +624,11 @@ def mode_leg(cute, torch, dev, kind, reps=2):
             "fp32_only_hist_l1": l1, "flips": int(st["flips"]),
             "gpair_evals_per_s": round(st["pair_evals"] / (ms * 1e-3) / 1e9, 1),
             "speedup_fp32edge_vs_fp64": round(res["fp64"][1]["ms_count"] / ms, 3),
-            "lane_op_frac_at_i_alg": round(st["pair_evals"] * i_alg / (ms * 1e-3) / PEAK_LANE_OPS, 4),
-            "i_alg": i_alg,
-            "lane_op_note": "i_alg lane-ops counted for every candidate pair, also those of steps "
-                            "dropped after the top-edge vote (a few operations each), so the "
-                            "fraction can pass 1; the VALU instructions actually issued per pair "
-                            "and the issue share are in the rocprofv3 counter summaries",
+            "lane_op_frac_at_i_alg": round(st["pair_evals"] * ops / (ms * 1e-3) / PEAK_LANE_OPS, 4),
+            "i_alg": round(ops, 2),
+            "lane_op_note": "i_alg: vector lane-ops and matrix products (as two) per candidate pair, "
+                            "with the pairs of dropped steps at theirs; the instructions actually "
+                            "issued per pair are in the rocprofv3 counter summaries",
             "host_s": round(t_gen, 1)}
 
 

@@ -235,13 +235,13 @@ cute_status cute_count_pairs(const cute_grid* a, const cute_grid* b, const cute_
  * per GPU, which the library holds from the first call on that GPU until the
  * process ends. The call allocates no device or pinned host memory: its few
  * host copies go through pageable memory. The home tiles are always built
- * without a host wait and never cut shorter for small counts.
+ * without a host wait.
  * Every call on one GPU uses the same array and leaves the last call's
  * contents there; each call clears the counters it needs before its kernels
  * run. Calls that overlap on one GPU (two host threads or two streams) race
  * on the array: the caller must serialise them.
  * Errors: those of cute_count_pairs; CUTE_E_INVALID_ARG, before any work is
- * enqueued, when the count's temporaries exceed the array (about 64 bytes
+ * enqueued, when the count's temporaries exceed the array (about 40 bytes
  * per home-tile slot of grid a plus the tables: a 2e7-point grid of 64-point
  * tiles fits). */
 #define CUTE_NOALLOC_SCRATCH_BYTES (32u << 20)
