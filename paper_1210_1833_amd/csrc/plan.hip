@@ -84,8 +84,8 @@ double d2_bound(double r, const ErrModel& em) {
 // Largest distance between a home point and its tile's origin, in the FP32
 // frame (see tile_origin): half the diagonal of the tile's box of cells for
 // 3-D grids (an axis of one cell takes the grid's centre, and its points span no
-// more than the cell or the largest extent); the extent of a block of pixels for the sphere, whose origin is one
-// of the tile's points.
+// more than the cell or the largest extent); the extent of a block of pixels for
+// the sphere, whose origin is one of the tile's points.
 double tile_reach(const GridHost& A, int max_w) {
     const double slack = 1e-6 * A.ext + 1e-300;
     if (A.geom == CUTE_GEOM_SPHERE) {
@@ -504,12 +504,16 @@ int part_log(double ntiles, double neighbours, int ncu) {
 // count of 3e5 points in FP32_EDGE took 0.50, 0.64, 1.05 and 1.96 ms, a midpoint
 // one of 2e5 in FP64 3.9, 2.7, 1.9 and 1.9). weight: an evaluation of the kernel
 // against one of the one-variable FP32_EDGE kernels; where bins are mostly
-// searched (FP64) or re-tested, a pair costs as much as there against the
-// midpoint.
+// searched (FP64: uneven edges, pairs past a partial mu range) or re-tested, a
+// pair costs as much as there against the midpoint, and tiles differ by more
+// than their pairs (first): an r-mu count of 3e5 points with uneven edges takes
+// 3.67, 3.01, 2.14 and 2.72 ms in 1, 2, 4 and 8 parts in FP32_EDGE and 2.63, 1.94,
+// 2.07 and 2.66 in FP64, one of mu in [0.2, 0.7] there 1.65, 1.33, 1.53 and 2.29.
 PartCost part_cost(const Plan& pl, int prec, uint32_t slots) {
     const bool mid = h32_mode(pl.mode);
+    const bool slow = pl.uneven || (prec == P_FP64 && pl.a.d2_partial != 0);
     float weight = 1.0f;
-    if (pl.uneven)
+    if (slow)
         weight = 4.0f;
     else if (prec == P_FP64)
         weight = mid || pl.mode == M_RADIAL ? 4.0f : 1.6f;
@@ -517,7 +521,7 @@ PartCost part_cost(const Plan& pl, int prec, uint32_t slots) {
         weight = 2.5f;
     else if (!pl.mc)
         weight = 1.5f;
-    return PartCost{std::max(slots, 1u), 4096.0f / weight, 24576.0f / weight, pl.uneven ? 1.0f : 0.5f};
+    return PartCost{std::max(slots, 1u), 4096.0f / weight, 24576.0f / weight, !slow ? 0.5f : prec == P_FP32E ? 2.0f : 1.0f};
 }
 
 // The item each workgroup of a batched launch starts with: the workgroups are
